@@ -4,9 +4,9 @@
 // of that side and every occupied cube is replaced by the mean position of its points.  The grid of an object is
 // small (a few hundred to a few thousand cubes for N_target ~ 150), so it is held densely:
 //   k_vox_zero    clears the cubes' sums and counts
-//   k_vox_bin     one thread per point: cube index (fp32 decision chain), coordinates as 64-bit fixed point; spatially
-//                 sorted points fall into the same cube in runs, a run is added up inside the wave and its last lane
-//                 issues the atomics (integer sums: the result does not depend on the order in which they land)
+//   k_vox_bin     cube index of every point (fp32 decision chain), coordinates as 64-bit fixed point, added up per cube
+//                 in a workgroup's LDS table and from there in memory (integer sums: the result does not depend on the
+//                 order in which they land)
 //   k_vox_count   occupied cubes per block of 2048 cubes
 //   k_vox_scan    exclusive scan of the block counts (one workgroup); object offsets
 //   k_vox_emit    per block: position of every occupied cube in the output list, mean position, count
@@ -78,40 +78,82 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_zero(VoxArgs a) {
     z[i] = vox_u32x4{0u, 0u, 0u, 0u};
 }
 
-__global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab) {
+// Points per thread and trip, and entries of a workgroup's table.
+constexpr int kVoxRun = 8;
+constexpr int kVoxTrip = kVoxBlock * kVoxRun;   // 2048 points per workgroup and trip
+constexpr int kVoxSlots = 1024;                  // 32 KiB of LDS: four workgroups per compute unit
+
+// A workgroup adds `trips` * 2048 consecutive points of one object up in an LDS table before anything goes to memory.
+// Bound by the atomics: the cubes are few (a few hundred per object), so every atomic in memory meets others at its
+// address.  One set of them per run of equal cubes in a wave, found with a 64-lane scan, took 240 us for 64 objects of
+// 100 000 points; with the table a workgroup issues one set per cube that its points touch (the whole call 253 -> 72 us).
+// A thread takes 8 consecutive points, which in a spatially sorted cloud mostly share a cube, and goes to the table when
+// the cube changes.  An entry belongs to the first cube that claims it (index modulo 1024: objects of up to 1024 cubes
+// never collide); a cube that finds its entry taken adds to memory directly, so any number of cubes and any order of the
+// points is served.  Integer sums: the result does not depend on the order in which they land.
+__global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab, int trips) {
+  __shared__ unsigned long long s_sum[3][kVoxSlots];
+  __shared__ unsigned s_cnt[kVoxSlots];
+  __shared__ int s_key[kVoxSlots];                // cube within the object, -1: free
   const VoxObjDev ob = tab.o[blockIdx.y];
-  const int l0 = blockIdx.x * kVoxBlock;
-  if (l0 >= ob.n_pts) return;                       // uniform: whole workgroups leave
-  const int lane = threadIdx.x % kWave;
-  const int li = l0 + threadIdx.x;
-  const bool used = li < ob.n_pts;
-  const long long i = ob.pt_begin + (used ? li : ob.n_pts - 1);
-  const float* __restrict__ p = a.xyz + 3 * i;
-  int cell = -1 - lane;                             // unused lanes: an id no neighbour shares
-  long long q[3] = {0, 0, 0};
-  if (used) {
-    cell = vox_cell(ob, p);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) q[c] = __double2ll_rn(ldexp((double)p[c], a.shift));
+  const long long first = (long long)blockIdx.x * trips * kVoxTrip;
+  if (first >= ob.n_pts) return;                  // uniform: whole workgroups leave
+  for (int t = threadIdx.x; t < kVoxSlots; t += kVoxBlock) {
+    s_sum[0][t] = s_sum[1][t] = s_sum[2][t] = 0ull;
+    s_cnt[t] = 0u;
+    s_key[t] = -1;
   }
-  const int prev = __shfl_up(cell, 1, kWave), next = __shfl_down(cell, 1, kWave);
-  const bool head = lane == 0 || prev != cell, tail = lane == kWave - 1 || next != cell;
-  int start = head ? lane : 0;                      // lane of the run's first member
+  __syncthreads();
+  VoxCell* __restrict__ cells = a.cells + ob.cell_begin;
+  auto add = [&](int cube, const long long (&q)[3], int n) {
+    const int slot = cube & (kVoxSlots - 1);
+    int key = s_key[slot];
+    if (key < 0) key = atomicCAS(&s_key[slot], -1, cube);
+    if (key < 0 || key == cube) {
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) start = max(start, __shfl_up(start, o, kWave));
+      for (int c = 0; c < 3; ++c) atomicAdd(&s_sum[c][slot], (unsigned long long)q[c]);
+      atomicAdd(&s_cnt[slot], (unsigned)n);
+    } else {
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const long long up = __shfl_up(q[c], o, kWave);
-      if (lane - o >= start) q[c] += up;
+      for (int c = 0; c < 3; ++c) atomicAdd(reinterpret_cast<unsigned long long*>(&cells[cube].sum[c]), (unsigned long long)q[c]);
+      atomicAdd(reinterpret_cast<unsigned long long*>(&cells[cube].cnt), (unsigned long long)n);
     }
-  }
-  if (used && tail) {
-    VoxCell* cc = a.cells + cell;
+  };
+  for (int trip = 0; trip < trips; ++trip) {
+    const long long l0 = first + (long long)trip * kVoxTrip + threadIdx.x * kVoxRun;
+    if (l0 >= ob.n_pts) break;
+    const int n = (int)min((long long)kVoxRun, ob.n_pts - l0);
+    const float* __restrict__ p = a.xyz + 3 * (ob.pt_begin + l0);
+    float x[kVoxRun][3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) atomicAdd(reinterpret_cast<unsigned long long*>(&cc->sum[c]), (unsigned long long)q[c]);
-    atomicAdd(reinterpret_cast<unsigned long long*>(&cc->cnt), (unsigned long long)(lane - start + 1));
+    for (int e = 0; e < kVoxRun; ++e)   // all reads before the first use; past the end: the thread's first point again, unused
+#pragma unroll
+      for (int c = 0; c < 3; ++c) x[e][c] = p[3 * (e < n ? e : 0) + c];
+    long long q[3] = {0, 0, 0};
+    int cube = -1, run = 0;
+#pragma unroll
+    for (int e = 0; e < kVoxRun; ++e) {
+      if (e >= n) break;
+      const int now = vox_cell(ob, x[e]) - ob.cell_begin;
+      if (now != cube) {
+        if (run > 0) add(cube, q, run);
+        cube = now;
+        run = 0;
+        q[0] = q[1] = q[2] = 0;
+      }
+      ++run;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[c] += __double2ll_rn(ldexp((double)x[e][c], a.shift));
+    }
+    add(cube, q, run);
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < kVoxSlots; t += kVoxBlock) {
+    if (s_key[t] < 0) continue;
+    VoxCell* cc = cells + s_key[t];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) atomicAdd(reinterpret_cast<unsigned long long*>(&cc->sum[c]), s_sum[c][t]);
+    atomicAdd(reinterpret_cast<unsigned long long*>(&cc->cnt), (unsigned long long)s_cnt[t]);
   }
 }
 
@@ -276,7 +318,13 @@ hipError_t launch_voxel_downsample(const float* xyz, const VoxObj* objs, int B, 
   const dim3 block(kVoxBlock);
   const int zero_groups = a.n_blocks * 4 < 2048 ? a.n_blocks * 4 : 2048;
   hipLaunchKernelGGL(k_vox_zero, dim3(zero_groups), block, 0, stream, a);
-  if (max_pts > 0) hipLaunchKernelGGL(k_vox_bin, dim3((max_pts + kVoxBlock - 1) / kVoxBlock, B), block, 0, stream, a, tab);
+  if (max_pts > 0) {
+    // longer workgroups issue fewer atomics per point, as long as about a thousand of them (four per compute unit) remain
+    const long long want = n_points / (1024ll * kVoxTrip);
+    const int trips = (int)(want < 1 ? 1 : (want > 8 ? 8 : want));
+    const long long span = (long long)trips * kVoxTrip;
+    hipLaunchKernelGGL(k_vox_bin, dim3((unsigned)((max_pts + span - 1) / span), B), block, 0, stream, a, tab, trips);
+  }
   hipLaunchKernelGGL(k_vox_count, dim3(a.n_blocks), block, 0, stream, a);
   hipLaunchKernelGGL(k_vox_scan, dim3(1), block, 0, stream, a, tab);
   hipLaunchKernelGGL(k_vox_emit, dim3(a.n_blocks), block, 0, stream, a);

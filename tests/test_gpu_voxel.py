@@ -113,3 +113,20 @@ def test_full_size_c2(orc):
     ref = orc.voxel_downsample(s.xyz, 150, box_lo=lo, box_hi=hi)
     _compare(g, ref, s.N, np.abs(s.xyz).max())
     assert 40 <= ref["offsets"][-1] <= 400
+
+
+# The binning kernel's table has 1024 entries, a thread takes eight points and a workgroup 2048 per trip: one point, full
+# and just exceeded runs and trips, several trips (above 4 M points), and more cubes than entries with the points in order
+# and in none (entries that are taken, a cube per point).
+@pytest.mark.parametrize("n,n_target,in_order", [(1, 10, True), (7, 3, True), (9, 3, True), (2047, 50, True),
+                                                 (2049, 50, False), (40_000, 30_000, False), (40_000, 30_000, True),
+                                                 (5_000_001, 3_000, True)])
+def test_binning_table(orc, n, n_target, in_order):
+    rng = np.random.default_rng(n + n_target)
+    xyz = rng.uniform(-1.0, 1.0, (n, 3)).astype(np.float32)
+    if in_order:
+        xyz = xyz[np.lexsort(np.floor(xyz / 0.125).T)]
+    po = np.array([0, n], np.int64)
+    lo, hi = _boxes(xyz, po)
+    g = _run_gpu(xyz, po, lo, hi, n_target)
+    _compare(g, orc.voxel_downsample(xyz, n_target, box_lo=lo, box_hi=hi, pt_offsets=po), n, 2.0)
