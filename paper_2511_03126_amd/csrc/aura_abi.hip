@@ -473,10 +473,8 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
       // the kernels index rows by absolute point number: row c0 is the chunk's first
       float* rows = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(chunk) - (uintptr_t)c0 * (uintptr_t)views->D * sizeof(float));
       s = for_each_table(part, [&](const aura::ObjTable& tab, int n, int max_pts, int) {
-        hipError_t e = hipSuccess;
-        if (vis) e = aura::launch_project_visibility(va, xyz, vis, vis_pitch, nullptr, nullptr, tab, n, max_pts, st);
-        if (e != hipSuccess) return e;
-        return aura::launch_fuse_features(va, fa, xyz, rows, count, params->norm_eps, mean_only, nullptr, tab, n, max_pts, st);
+        return aura::launch_fuse_features(va, fa, xyz, rows, count, params->norm_eps, mean_only, nullptr, tab, n, max_pts, st,
+                                          nullptr, vis, vis_pitch);
       });
       if (s != AURA_OK) return s;
       s = hip_status(aura::launch_material_scores(chunk, c1 - c0, views->D, t32, K, y, P, params->temperature,
@@ -497,14 +495,10 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
   }
   s = for_each_table(objs, [&](const aura::ObjTable& tab, int n, int max_pts, int obj_base) {
     tws.obj_base = obj_base;
-    hipError_t e = hipSuccess;
-    if (vis && !lay.tile)   // the gather kernel does not write the mask: the visibility kernel does
-      e = aura::launch_project_visibility(va, xyz, vis, vis_pitch, nullptr, nullptr, tab, n, max_pts, st);
-    if (e != hipSuccess) return e;
     const aura::TileScoring want{sws.G, sws.Kpad, K, P, t32, y, 1.0f / params->temperature, unseen_zero, scores, prop, label};
     bool scored = false;   // the one-kernel form of the fusion scores its tiles itself where it can
-    e = aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only,
-                                   lay.tile ? &tws : nullptr, tab, n, max_pts, st, lay.by_cells ? sws.factor : nullptr,
+    hipError_t e = aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only,
+                                              lay.tile ? &tws : nullptr, tab, n, max_pts, st, lay.by_cells ? sws.factor : nullptr,
                                    vis, vis_pitch, nullptr, 0, (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0,
                                    lay.by_cells ? &want : nullptr, &scored);
     if (e != hipSuccess || !lay.by_cells || scored) return e;

@@ -31,7 +31,7 @@ struct FuseArgs {
   float norm_eps;
   int mean_only;
   float* out_factor;   // tile path only, may be nullptr: [N] factor applied to each point's raw tile product
-  uint8_t* out_vis;    // tile path only, may be nullptr: [N][vis_pitch] visibility mask (Eq. 1), as aura_project_visibility
+  uint8_t* out_vis;    // may be nullptr: [N][vis_pitch] visibility mask (Eq. 1), as aura_project_visibility
   int vis_pitch;
   const uint8_t* in_mask;   // may be nullptr: [N][in_mask_pitch], the views kept for each point (Sec. 3.2.2); given, it
   int in_mask_pitch;        // takes the place of the depth test (the caller passes no depth maps then)

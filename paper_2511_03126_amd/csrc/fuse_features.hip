@@ -11,6 +11,9 @@
 // HBM traffic is the compulsory output row (4 D bytes per point) plus each feature cell once;
 // the repeated cell reads are served by the caches, which is why points should arrive spatially
 // sorted and why workgroup ids are mapped so that each XCD walks a contiguous range of points.
+#include <algorithm>
+#include <type_traits>
+
 #include "aura_device.hpp"
 #include "fuse_args.hpp"
 #include "launch.hpp"
@@ -25,8 +28,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kFuseWaves = 4;
-constexpr int kFusePtsPerWave = 8;
-constexpr int kFusePtsPerBlock = kFuseWaves * kFusePtsPerWave;
+constexpr int kFusePtsPerWave = 8;   // at most: see launch_one
 
 __device__ __forceinline__ void widen_pair(uint32_t w, int dtype_is_bf16, float& lo, float& hi) {
   if (dtype_is_bf16) {
@@ -92,14 +94,26 @@ __device__ __forceinline__ void store_stream(float* __restrict__ p, const float 
   }
 }
 
+// The bilinear blend of one visible view: weights of the four cells and the start of their rows.
+struct ViewTaps {
+  const char* row[4];
+  float w[4];
+};
+
 // DT element type, VEC elements per lane per load, PASSES loads per cell row.
-// GENERIC == false: D == 64 * VEC * PASSES, the whole row lives in registers.
+// GENERIC == false: D <= 64 * VEC * PASSES and D a multiple of VEC: the whole row lives in registers, lanes beyond D
+//                   repeat the row's last VEC channels and drop out of the sums and the stores.
 // GENERIC == true : any D; channels are processed 64 * VEC * PASSES at a time (outer loop), the
 //                   unnormalised mean is stored first and rescaled in a second sweep.
+// A wave takes pts_per_wave consecutive points, one after the other.  What bounds a call of a few thousand points is that
+// chain (point -> projections -> depth texels -> cell rows -> norm): with 8 points per wave and one channel per lane and
+// load, 2001 points of 5 views and 384 channels took 97 us on 63 workgroups; one point per wave, 16-byte loads and the
+// rows of two views in flight together take 12 us.
 template <int DT, int VEC, int PASSES, bool GENERIC>
-__global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, ObjTable tab) {
+__global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, int pts_per_wave, ObjTable tab) {
   const ObjRange ob = tab.o[blockIdx.y];
-  const int nblk = (ob.n_pts + kFusePtsPerBlock - 1) / kFusePtsPerBlock;
+  const int pts_per_block = kFuseWaves * pts_per_wave;
+  const int nblk = (ob.n_pts + pts_per_block - 1) / pts_per_block;
   if ((int)blockIdx.x >= nblk) return;
   const int blk = xcd_contiguous(blockIdx.x, nblk);
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -108,8 +122,8 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, O
   const long long view_elems = (long long)Hf * Wf * D;
   const long long elt = DT == 0 ? 4 : 2;
 
-  for (int k = 0; k < kFusePtsPerWave; ++k) {
-    const int li = blk * kFusePtsPerBlock + wave * kFusePtsPerWave + k;
+  for (int k = 0; k < pts_per_wave; ++k) {
+    const int li = blk * pts_per_block + wave * pts_per_wave + k;
     if (li >= ob.n_pts) break;
     const long long i = ob.pt_begin + li;
     const float x = a.xyz[3 * i], y = a.xyz[3 * i + 1], z = a.xyz[3 * i + 2];
@@ -141,53 +155,72 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, O
             y0 = ty.i0; ay = ty.a;
           }
         }
+        if (a.out_vis && vb + lane < a.vis_pitch && cb == 0) a.out_vis[i * a.vis_pitch + vb + lane] = seen ? 1 : 0;
         unsigned long long m = __ballot(seen);
         cnt += __popcll(m);
-        // phase 2: wave-uniform loop over the visible views
-        while (m) {
-          const int src = __builtin_ctzll(m);
-          m &= m - 1;
+        // phase 2: wave-uniform loop over the visible views, two at a time so that the rows of both are in flight
+        auto taps_of = [&](int src) {
           const int sx0 = __builtin_amdgcn_readlane(x0, src), sy0 = __builtin_amdgcn_readlane(y0, src);
           const float sax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ax), src));
           const float say = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ay), src));
           const int sx1 = sx0 + 1 < Wf ? sx0 + 1 : Wf - 1, sy1 = sy0 + 1 < Hf ? sy0 + 1 : Hf - 1;
-          const float w00 = (1.0f - sax) * (1.0f - say), w01 = sax * (1.0f - say);
-          const float w10 = (1.0f - sax) * say, w11 = sax * say;
           const char* vbase = static_cast<const char*>(a.feat.feat) +
                               (long long)(ob.view_begin + vb + src) * view_elems * elt;
-          const long long o00 = (long long)(sy0 * Wf + sx0) * D, o01 = (long long)(sy0 * Wf + sx1) * D;
-          const long long o10 = (long long)(sy1 * Wf + sx0) * D, o11 = (long long)(sy1 * Wf + sx1) * D;
+          const long long row_bytes = (long long)D * elt;
+          ViewTaps t;
+          t.w[0] = (1.0f - sax) * (1.0f - say); t.w[1] = sax * (1.0f - say);
+          t.w[2] = (1.0f - sax) * say;          t.w[3] = sax * say;
+          t.row[0] = vbase + (sy0 * Wf + sx0) * row_bytes; t.row[1] = vbase + (sy0 * Wf + sx1) * row_bytes;
+          t.row[2] = vbase + (sy1 * Wf + sx0) * row_bytes; t.row[3] = vbase + (sy1 * Wf + sx1) * row_bytes;
+          return t;
+        };
+        auto channel = [&](int p) {
+          const int ch = cb + p * kWave * VEC + lane * VEC;
+          return GENERIC ? ch : min(ch, D - VEC);
+        };
+        auto blend = [&](auto n_views_c) {
+          constexpr int NV = decltype(n_views_c)::value;
+          ViewTaps t[NV];
+#pragma unroll
+          for (int q = 0; q < NV; ++q) {
+            t[q] = taps_of(__builtin_ctzll(m));
+            m &= m - 1;
+          }
 #pragma unroll
           for (int p = 0; p < PASSES; ++p) {
-            const int ch = cb + p * kWave * VEC + lane * VEC;
+            const int ch = channel(p);
             if (GENERIC && ch >= D) continue;
-            float t00[VEC], t01[VEC], t10[VEC], t11[VEC];
-            load_widen<DT, VEC>(vbase, o00 + ch, t00);
-            load_widen<DT, VEC>(vbase, o01 + ch, t01);
-            load_widen<DT, VEC>(vbase, o10 + ch, t10);
-            load_widen<DT, VEC>(vbase, o11 + ch, t11);
+            float v[NV][4][VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-              float s = acc[p][e];
-              s = __builtin_fmaf(w00, t00[e], s);
-              s = __builtin_fmaf(w01, t01[e], s);
-              s = __builtin_fmaf(w10, t10[e], s);
-              s = __builtin_fmaf(w11, t11[e], s);
-              acc[p][e] = s;
-            }
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) load_widen<DT, VEC>(t[q].row[c], ch, v[q][c]);
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                float s = acc[p][e];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) s = __builtin_fmaf(t[q].w[c], v[q][c][e], s);
+                acc[p][e] = s;
+              }
           }
-        }
+        };
+        while (m & (m - 1)) blend(std::integral_constant<int, 2>{});
+        if (m) blend(std::integral_constant<int, 1>{});
       }
 
       // mean over the visible views (Eq. 2); a point nobody sees keeps zeros
       const float inv = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
 #pragma unroll
-      for (int p = 0; p < PASSES; ++p)
+      for (int p = 0; p < PASSES; ++p) {
+        const bool mine = GENERIC || p * kWave * VEC + lane * VEC < D;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          acc[p][e] *= inv;
+          acc[p][e] = mine ? acc[p][e] * inv : 0.0f;
           ss = __builtin_fmaf(acc[p][e], acc[p][e], ss);
         }
+      }
       if constexpr (!GENERIC) {
         float scale = 1.0f;
         if (!a.mean_only) {
@@ -198,7 +231,8 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, O
         for (int p = 0; p < PASSES; ++p) {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) acc[p][e] *= scale;
-          store_stream<VEC>(out_row + p * kWave * VEC + lane * VEC, acc[p]);
+          const int ch = p * kWave * VEC + lane * VEC;
+          if (ch < D) store_stream<VEC>(out_row + ch, acc[p]);
         }
       } else {
 #pragma unroll
@@ -220,30 +254,58 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, O
         for (int ch = lane; ch < D; ch += kWave) out_row[ch] *= scale;
       }
     }
+    for (int j = (ob.n_views + kWave - 1) / kWave * kWave + lane; a.out_vis && j < a.vis_pitch; j += kWave)
+      a.out_vis[i * a.vis_pitch + j] = 0;   // mask columns beyond the views' last 64
     if (a.out_count && lane == 0) a.out_count[i] = cnt;
   }
 }
 
 template <int DT, int VEC, int PASSES, bool GENERIC>
 static hipError_t launch_one(const FuseArgs& a, const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream) {
-  dim3 grid((max_pts + kFusePtsPerBlock - 1) / kFusePtsPerBlock, n_obj), block(kFuseWaves * kWave);
+  // points per wave: one until the launch has 32 waves per compute unit, up to eight beyond
+  long long pts = 0;
+  for (int t = 0; t < n_obj; ++t) pts += tab.o[t].n_pts;
+  const int pts_per_wave = (int)std::min<long long>(kFusePtsPerWave, std::max<long long>(1, pts / 8192));
+  const int pts_per_block = kFuseWaves * pts_per_wave;
+  dim3 grid((unsigned)(((long long)max_pts + pts_per_block - 1) / pts_per_block), n_obj), block(kFuseWaves * kWave);
   const TimingRequest timed = take_timing_request();
   if (timed.start) (void)hipEventRecord(timed.start, stream);
-  hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, GENERIC>), grid, block, 0, stream, a, tab);
+  hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, GENERIC>), grid, block, 0, stream, a, pts_per_wave, tab);
   const hipError_t e = hipGetLastError();
   if (timed.stop) (void)hipEventRecord(timed.stop, stream);
   return e;
 }
 
+// The row in registers for every D that is a whole number of 16-byte pieces (8 bytes for 16-bit rows of up to 256
+// channels, so that all lanes have work) and fits: up to 2048 16-bit or 1536 fp32 channels.
 template <int DT>
 static hipError_t dispatch_d(const FuseArgs& a, const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream) {
-  constexpr int V = DT == 0 ? 4 : 8;   // widest load: 16 bytes per lane
-  switch (a.feat.D) {
-    case 512:  return launch_one<DT, V, 512 / (kWave * V), false>(a, tab, n_obj, max_pts, stream);
-    case 768:  return launch_one<DT, 4, 3, false>(a, tab, n_obj, max_pts, stream);
-    case 1024: return launch_one<DT, V, 1024 / (kWave * V), false>(a, tab, n_obj, max_pts, stream);
-    default:   return launch_one<DT, 1, 1, true>(a, tab, n_obj, max_pts, stream);
+  const int D = a.feat.D;
+  if constexpr (DT == 0) {
+    if (D % 4 == 0) {
+      switch ((D + 255) / 256) {
+        case 1: return launch_one<DT, 4, 1, false>(a, tab, n_obj, max_pts, stream);
+        case 2: return launch_one<DT, 4, 2, false>(a, tab, n_obj, max_pts, stream);
+        case 3: return launch_one<DT, 4, 3, false>(a, tab, n_obj, max_pts, stream);
+        case 4: return launch_one<DT, 4, 4, false>(a, tab, n_obj, max_pts, stream);
+        case 5: case 6: return launch_one<DT, 4, 6, false>(a, tab, n_obj, max_pts, stream);
+        default: break;
+      }
+    }
+  } else {
+    if (D % 4 == 0 && D <= 256) return launch_one<DT, 4, 1, false>(a, tab, n_obj, max_pts, stream);
+    if (D == 768) return launch_one<DT, 4, 3, false>(a, tab, n_obj, max_pts, stream);
+    if (D % 8 == 0) {
+      switch ((D + 511) / 512) {
+        case 1: return launch_one<DT, 8, 1, false>(a, tab, n_obj, max_pts, stream);
+        case 2: return launch_one<DT, 8, 2, false>(a, tab, n_obj, max_pts, stream);
+        case 3: return launch_one<DT, 8, 3, false>(a, tab, n_obj, max_pts, stream);
+        case 4: return launch_one<DT, 8, 4, false>(a, tab, n_obj, max_pts, stream);
+        default: break;
+      }
+    }
   }
+  return launch_one<DT, 1, 1, true>(a, tab, n_obj, max_pts, stream);
 }
 
 hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const float* xyz, float* fused,
@@ -254,7 +316,7 @@ hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const 
   if (scored) *scored = false;
   if (n_obj == 0 || max_pts == 0) return hipSuccess;
   FuseArgs a{vis, feat, xyz, fused, out_count, norm_eps, mean_only, tile_ws ? out_factor : nullptr,
-             tile_ws ? out_vis : nullptr, vis_pitch, in_mask, in_mask_pitch, two_kernels,
+             out_vis, vis_pitch, in_mask, in_mask_pitch, two_kernels,
              tile_ws && scoring ? *scoring : TileScoring{}};
   if (tile_ws) return launch_fuse_tile(a, *tile_ws, tab, n_obj, max_pts, stream, scored);
   switch (feat.dtype) {

@@ -230,6 +230,23 @@ def test_channel_counts_and_element_types(H, orc, D, dtype):
     H.compare_points(d.results(), H.oracle_points(orc, s), s)
 
 
+# The gather kernel's row widths at their edges: rows that end inside a wave's last load, the most passes, the channel
+# counts that go one at a time; an even and an odd number of visible views per point; several points per wave (from
+# 16 384 points on); the mask it writes, with more views than a wave has lanes.
+@pytest.mark.parametrize("D,dtype,N,V", [(4, "f32", 300, 3), (252, "f32", 300, 4), (260, "f32", 300, 5), (1284, "f32", 200, 4),
+                                         (1540, "f32", 200, 2), (252, "f16", 300, 4), (260, "bf16", 300, 3),
+                                         (264, "bf16", 300, 70), (384, "f16", 20_001, 3), (640, "bf16", 300, 4),
+                                         (1160, "f16", 200, 4), (2048, "bf16", 200, 3), (2056, "f16", 200, 3)])
+def test_gather_kernel_row_widths_and_mask(H, orc, D, dtype, N, V):
+    s = _custom_scene(N=N, V=V, D=D, K=min(12, D), dtype=dtype)
+    ref = H.oracle_points(orc, s)
+    d = H.DeviceScene(s)
+    for step in (d.step, d.step_combined, d.step_single_pass):
+        d.clear_outputs()
+        step()
+        H.compare_points(d.results(), ref, s, no_fused=step == d.step_single_pass)
+
+
 @pytest.mark.parametrize("K,P", [(1, 1), (2, 2), (12, 1), (31, 3), (33, 2), (64, 1), (100, 8), (128, 2)])
 def test_material_counts_and_property_columns(H, orc, K, P):
     s = _custom_scene(N=900, V=4, D=256, K=K, P=P, dtype="f32")
