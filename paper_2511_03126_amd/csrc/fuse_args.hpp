@@ -13,7 +13,6 @@ struct TileScoring {
   const uint32_t* G;    // [n_cells][Kpad]: hi | lo << 16
   int Kpad;             // K rounded up to the matrix-core tile
   int K, P;
-  const float* temb;    // [K][D] fp32, for tiles without k-steps
   const float* y;       // [K][P], may be nullptr with prop
   float inv_T;
   int unseen_zero;      // properties of a point with all-zero similarities: 0 instead of the mean of y
@@ -55,9 +54,9 @@ constexpr int kStepCells = 16;      // cells per k-step (K of the matrix-core pr
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 struct TileHdr {
-  int nsteps;               // k-steps written for the tile; -1: the prepare kernel fused this tile itself
+  int nsteps;               // k-steps written for the tile; -1: none, fused by a gather (push_tile in fuse_tile.hip)
   int pad_[3];
-  int cnt[kTilePts];        // views that see each point
+  int cnt[kTilePts];        // views that see each point (nsteps >= 0)
 };
 
 struct __attribute__((aligned(64))) TileStep {
@@ -69,7 +68,8 @@ struct __attribute__((aligned(64))) TileStep {
 struct TileWs {
   TileHdr* hdr;         // [n_tiles]
   unsigned* counters;   // [B][8]: tiles handed out so far, per object and XCD (zeroed by the prepare kernel)
-  unsigned* status;     // one word per call, zero unless a kernel had something to report (see aura_fuse_status_offset)
+  unsigned* status;     // 64 words: zero unless a kernel had something to report (see aura_fuse_status_offset), tiles fused
+                        // by a gather, and from word 32 the heads of the lists of such tiles
   TileStep* steps;      // [n_tiles][quota]: every tile owns a fixed run of k-steps
   int quota;
   int obj_base;         // index of the launch's first object within the call

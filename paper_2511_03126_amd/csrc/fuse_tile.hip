@@ -26,8 +26,8 @@
 //   C  per chunk of the list: the weights are scattered into a [32][cells] matrix in LDS, split
 //      into two 16-bit terms (hi + lo, about 16 mantissa bits), and copied out as k-steps of 16
 //      cells in the operand layout of the matrix-core instruction.  Every tile owns a fixed number
-//      of k-steps of storage; a tile that needs more (points far apart) is fused on the spot by a
-//      plain gather, so which way a tile goes depends on the tile alone and results are
+//      of k-steps of storage; a tile that needs more (points far apart) is fused by a plain
+//      gather after the others, so which way a tile goes depends on the tile alone and results are
 //      reproducible bit for bit.
 //
 // k_tile_product (one workgroup per tile, wave s owns channels [256 s, 256 s + 256)): per k-step
@@ -141,164 +141,260 @@ struct PairRec {
   float ax, ay;  // weights of the second cell per axis
 };
 
-// The slow way out when a tile needs more k-steps than it owns: the workgroup fuses its 32 points by a
-// per-point gather (wave per point, lanes over channels, 512 channels per sweep, the whole row in registers).
-// The row is stored when the call has a place for it (FuseArgs::fused); when the call wants scores as well
-// (FuseArgs::scoring), they are taken here from the row in registers, so that no later kernel needs the row:
-// omega_k by a wave-wide sum per material, then Eq. 4 and the label with lanes over the materials.
+// The slow way out when a tile needs more k-steps than it owns (points far apart): one wave fuses a point by a gather
+// (lanes over channels, 512 channels per sweep, the whole row in registers; the rows of two views in flight together).
+// The row is stored when the call has a place for it (FuseArgs::fused).  When the call wants scores as well
+// (FuseArgs::scoring), they come from the same walk over the views, lanes over the materials:
+// omega_k = s_i * sum_c w[i][c] G[c][k], as for the tiles; then Eq. 4 and the label.  (A dot product of the row with
+// every text embedding instead, a wave-wide sum per material, took longer than the gather itself.)
 constexpr int kGatherSweeps = 3;   // 512 channels each: D <= 1536 on this path
 
 template <int DT>
-__device__ __forceinline__ void gather_tile(const FuseArgs& a, const ObjRange& ob, int li0, int wave, int n_waves, int lane) {
+__device__ __forceinline__ void widen_16(uint32_t w, float& lo, float& hi) {
+  if constexpr (DT == 1) {
+    lo = __uint_as_float(w << 16);
+    hi = __uint_as_float(w & 0xffff0000u);
+  } else {
+    lo = (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));
+    hi = (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
+  }
+}
+
+template <int DT>
+__device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& ob, int li, int lane) {
+  const TileScoring& sc = a.scoring;
   const int D = a.feat.D, Hf = a.feat.Hf, Wf = a.feat.Wf;
-  const long long view_bytes = (long long)Hf * Wf * D * 2;
-  for (int k = 0; k < kTilePts / n_waves; ++k) {
-    const int li = li0 + wave * (kTilePts / n_waves) + k;
-    if (li >= ob.n_pts) break;
-    const long long i = ob.pt_begin + li;
-    const float x = a.xyz[3 * i], y = a.xyz[3 * i + 1], z = a.xyz[3 * i + 2];
-    float acc[kGatherSweeps][8];
+  const long long i = ob.pt_begin + li;
+  const float x = a.xyz[3 * i], y = a.xyz[3 * i + 1], z = a.xyz[3 * i + 2];
+  float acc[kGatherSweeps][8];
 #pragma unroll
-    for (int s = 0; s < kGatherSweeps; ++s)
+  for (int s = 0; s < kGatherSweeps; ++s)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[s][e] = 0.0f;
-    int cnt = 0;
-    for (int vb = 0; vb < ob.n_views; vb += kWave) {
-      bool seen = false;
-      int x0 = 0, y0 = 0;
-      float ax = 0.0f, ay = 0.0f;
-      if (vb + lane < ob.n_views) {
-        const int v = ob.view_begin + vb + lane;
-        const Proj p = project(a.vis.cam + (long long)v * 16, x, y, z);
-        const float* dv = a.vis.depth ? a.vis.depth + (long long)v * a.vis.H * a.vis.W : nullptr;
-        seen = visible(a.vis, dv, p) && view_kept(a, i, vb + lane);
-        if (a.out_vis) a.out_vis[i * a.vis_pitch + vb + lane] = seen ? 1 : 0;
-        if (seen) {
-          const Tap tx = tap_axis(p.u, a.feat.pitch_x, Wf), ty = tap_axis(p.v, a.feat.pitch_y, Hf);
-          x0 = tx.i0; ax = tx.a;
-          y0 = ty.i0; ay = ty.a;
-        }
+    for (int e = 0; e < 8; ++e) acc[s][e] = 0.0f;
+  float mine[2] = {0.0f, 0.0f};   // similarities of materials `lane` and `lane + 64`, before the point's factor
+  const int g0 = sc.G ? min(lane, sc.Kpad - 1) : 0, g1 = sc.G ? min(lane + kWave, sc.Kpad - 1) : 0;
+  int cnt = 0;
+  for (int vb = 0; vb < ob.n_views; vb += kWave) {
+    bool seen = false;
+    int x0 = 0, y0 = 0;
+    float ax = 0.0f, ay = 0.0f;
+    if (vb + lane < ob.n_views) {
+      const int v = ob.view_begin + vb + lane;
+      const Proj p = project(a.vis.cam + (long long)v * 16, x, y, z);
+      const float* dv = a.vis.depth ? a.vis.depth + (long long)v * a.vis.H * a.vis.W : nullptr;
+      seen = visible(a.vis, dv, p) && view_kept(a, i, vb + lane);
+      if (a.out_vis) a.out_vis[i * a.vis_pitch + vb + lane] = seen ? 1 : 0;
+      if (seen) {
+        const Tap tx = tap_axis(p.u, a.feat.pitch_x, Wf), ty = tap_axis(p.v, a.feat.pitch_y, Hf);
+        x0 = tx.i0; ax = tx.a;
+        y0 = ty.i0; ay = ty.a;
       }
-      unsigned long long m = __ballot(seen);
-      cnt += __popcll(m);
-      while (m) {
-        const int src = __builtin_ctzll(m);
-        m &= m - 1;
+    }
+    unsigned long long m = __ballot(seen);
+    cnt += __popcll(m);
+    while (m) {
+      // two views; of a single one left the second is the first again, its weights zero and its rows not added
+      const int src0 = __builtin_ctzll(m);
+      m &= m - 1;
+      const bool two = m != 0;
+      const int src1 = two ? __builtin_ctzll(m) : src0;
+      m &= m - 1;
+      float wgt[2][4];
+      long long cell[2][4];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int src = q ? src1 : src0;
         const int sx0 = __builtin_amdgcn_readlane(x0, src), sy0 = __builtin_amdgcn_readlane(y0, src);
         const float sax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ax), src));
         const float say = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ay), src));
         const int sx1 = sx0 + 1 < Wf ? sx0 + 1 : Wf - 1, sy1 = sy0 + 1 < Hf ? sy0 + 1 : Hf - 1;
-        const float wgt[4] = {(1.0f - sax) * (1.0f - say), sax * (1.0f - say), (1.0f - sax) * say, sax * say};
-        const int cell[4] = {sy0 * Wf + sx0, sy0 * Wf + sx1, sy1 * Wf + sx0, sy1 * Wf + sx1};
-        const char* vbase = static_cast<const char*>(a.feat.feat) + (long long)(ob.view_begin + vb + src) * view_bytes;
+        wgt[q][0] = (1.0f - sax) * (1.0f - say); wgt[q][1] = sax * (1.0f - say);
+        wgt[q][2] = (1.0f - sax) * say;          wgt[q][3] = sax * say;
+        const long long first = (long long)(ob.view_begin + vb + src) * Hf * Wf;
+        cell[q][0] = first + sy0 * Wf + sx0; cell[q][1] = first + sy0 * Wf + sx1;
+        cell[q][2] = first + sy1 * Wf + sx0; cell[q][3] = first + sy1 * Wf + sx1;
+      }
+      uint32_t gv[2][4][2];
+      if (sc.G) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            gv[q][c][0] = sc.G[cell[q][c] * sc.Kpad + g0];
+            gv[q][c][1] = sc.G[cell[q][c] * sc.Kpad + g1];
+          }
+      }
+      u32x4 raw[kGatherSweeps][2][4];
+#pragma unroll
+      for (int s = 0; s < kGatherSweeps; ++s) {
+        if (s * 8 * kWave >= D) break;   // uniform
+        const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            raw[s][q][c] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.feat.feat) + (cell[q][c] * D + ch) * 2);
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (q == 1 && !two) break;   // uniform
+        if (sc.G) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              float hi, lo;   // stored as hi | lo << 16
+              widen_16<DT>(gv[q][c][h], hi, lo);
+              mine[h] = __builtin_fmaf(wgt[q][c], hi + lo, mine[h]);
+            }
+        }
 #pragma unroll
         for (int s = 0; s < kGatherSweeps; ++s) {
-          const int ch = s * 8 * kWave + 8 * lane;
-          if (ch < D) {
+          if (s * 8 * kWave >= D) break;   // uniform
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const u32x4 raw = *reinterpret_cast<const u32x4*>(vbase + ((long long)cell[c] * D + ch) * 2);
+          for (int c = 0; c < 4; ++c)
 #pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                float lo, hi;
-                if constexpr (DT == 1) {
-                  lo = __uint_as_float(raw[j] << 16);
-                  hi = __uint_as_float(raw[j] & 0xffff0000u);
-                } else {
-                  lo = (float)__builtin_bit_cast(_Float16, (uint16_t)(raw[j] & 0xffffu));
-                  hi = (float)__builtin_bit_cast(_Float16, (uint16_t)(raw[j] >> 16));
-                }
-                acc[s][2 * j] = __builtin_fmaf(wgt[c], lo, acc[s][2 * j]);
-                acc[s][2 * j + 1] = __builtin_fmaf(wgt[c], hi, acc[s][2 * j + 1]);
-              }
+            for (int j = 0; j < 4; ++j) {
+              float lo, hi;
+              widen_16<DT>(raw[s][q][c][j], lo, hi);
+              acc[s][2 * j] = __builtin_fmaf(wgt[q][c], lo, acc[s][2 * j]);
+              acc[s][2 * j + 1] = __builtin_fmaf(wgt[q][c], hi, acc[s][2 * j + 1]);
             }
-          }
         }
       }
     }
-    // mean over the visible views (Eq. 2), then the L2 normalisation
-    const float inv = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
-    float ss = 0.0f;
+  }
+  // mean over the visible views (Eq. 2), then the L2 normalisation
+  float factor = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
+  float ss = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kGatherSweeps; ++s) {
+    const bool own = s * 8 * kWave + 8 * lane < D;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      acc[s][e] = own ? acc[s][e] * factor : 0.0f;
+      ss = __builtin_fmaf(acc[s][e], acc[s][e], ss);
+    }
+  }
+  if (!a.mean_only) {
+    const float scale = 1.0f / fmaxf(sqrtf(wave_sum(ss)), a.norm_eps);
 #pragma unroll
     for (int s = 0; s < kGatherSweeps; ++s)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        acc[s][e] *= inv;
-        ss = __builtin_fmaf(acc[s][e], acc[s][e], ss);
-      }
-    if (!a.mean_only) {
-      const float scale = 1.0f / fmaxf(sqrtf(wave_sum(ss)), a.norm_eps);
+      for (int e = 0; e < 8; ++e) acc[s][e] *= scale;
+    factor *= scale;
+  }
+  if (a.fused) {
+    float* __restrict__ out_row = a.fused + i * D;
 #pragma unroll
-      for (int s = 0; s < kGatherSweeps; ++s)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[s][e] *= scale;
-    }
-    if (a.fused) {
-      float* __restrict__ out_row = a.fused + i * D;
-#pragma unroll
-      for (int s = 0; s < kGatherSweeps; ++s) {
-        const int ch = s * 8 * kWave + 8 * lane;
-        if (ch < D) {
-          *reinterpret_cast<f32x4*>(out_row + ch) = f32x4{acc[s][0], acc[s][1], acc[s][2], acc[s][3]};
-          *reinterpret_cast<f32x4*>(out_row + ch + 4) = f32x4{acc[s][4], acc[s][5], acc[s][6], acc[s][7]};
-        }
+    for (int s = 0; s < kGatherSweeps; ++s) {
+      const int ch = s * 8 * kWave + 8 * lane;
+      if (ch < D) {
+        *reinterpret_cast<f32x4*>(out_row + ch) = f32x4{acc[s][0], acc[s][1], acc[s][2], acc[s][3]};
+        *reinterpret_cast<f32x4*>(out_row + ch + 4) = f32x4{acc[s][4], acc[s][5], acc[s][6], acc[s][7]};
       }
     }
-    if (a.out_count && lane == 0) a.out_count[i] = cnt;
+  }
+  if (a.out_count && lane == 0) a.out_count[i] = cnt;
 
-    if (a.scoring.G) {
-      // Sec. 3.4.1 for this point: lane l keeps the similarities of materials l and l + 64
-      const TileScoring& sc = a.scoring;
-      float mine[2] = {-INFINITY, -INFINITY};
-      for (int m = 0; m < sc.K; ++m) {
-        const float* __restrict__ t = sc.temb + (long long)m * D;
-        float dot = 0.0f;
+  if (sc.G) {   // Sec. 3.4.1 for this point
 #pragma unroll
-        for (int s = 0; s < kGatherSweeps; ++s) {
-          const int ch = s * 8 * kWave + 8 * lane;
-          if (ch < D) {
-            const f32x4 t0 = *reinterpret_cast<const f32x4*>(t + ch), t1 = *reinterpret_cast<const f32x4*>(t + ch + 4);
+    for (int h = 0; h < 2; ++h) mine[h] = lane + kWave * h < sc.K ? mine[h] * factor : -INFINITY;
+    float best = fmaxf(mine[0], mine[1]);
+    int bidx = mine[1] > mine[0] ? lane + 64 : lane;   // a lane without a material holds -inf
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              dot = __builtin_fmaf(acc[s][e], t0[e], dot);
-              dot = __builtin_fmaf(acc[s][4 + e], t1[e], dot);
-            }
-          }
-        }
-        dot = wave_sum(dot);
-        if ((m & 63) == lane) mine[m >> 6] = dot;
-      }
-      float best = fmaxf(mine[0], mine[1]);
-      int bidx = mine[1] > mine[0] ? lane + 64 : lane;   // a lane without a material holds -inf
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      const float ob_ = __shfl_xor(best, o, kWave);
+      const int oi = __shfl_xor(bidx, o, kWave);
+      if (ob_ > best || (ob_ == best && oi < bidx)) { best = ob_; bidx = oi; }   // lowest index wins ties
+    }
 #pragma unroll
-      for (int o = kWave / 2; o > 0; o >>= 1) {
-        const float ob_ = __shfl_xor(best, o, kWave);
-        const int oi = __shfl_xor(bidx, o, kWave);
-        if (ob_ > best || (ob_ == best && oi < bidx)) { best = ob_; bidx = oi; }   // lowest index wins ties
-      }
+    for (int h = 0; h < 2; ++h) {
+      const int m = lane + 64 * h;
+      if (m < sc.K) sc.scores[i * sc.K + m] = mine[h];
+    }
+    if (sc.label && lane == 0) sc.label[i] = bidx;
+    if (sc.prop) {
+      float e[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int m = lane + 64 * h;
-        if (m < sc.K) sc.scores[i * sc.K + m] = mine[h];
-      }
-      if (sc.label && lane == 0) sc.label[i] = bidx;
-      if (sc.prop) {
-        float e[2];
+      for (int h = 0; h < 2; ++h) e[h] = lane + 64 * h < sc.K ? weight_exp((mine[h] - best) * sc.inv_T) : 0.0f;
+      const float den = wave_sum(e[0] + e[1]);
+      // all similarities exactly zero (nobody sees the point): zero properties where the caller asks for that
+      const bool zero_row = sc.unseen_zero && __ballot((lane < sc.K && mine[0] != 0.0f) || (lane + 64 < sc.K && mine[1] != 0.0f)) == 0;
+      for (int p = 0; p < sc.P; ++p) {
+        float num = 0.0f;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) e[h] = lane + 64 * h < sc.K ? weight_exp((mine[h] - best) * sc.inv_T) : 0.0f;
-        const float den = wave_sum(e[0] + e[1]);
-        // all similarities exactly zero (nobody sees the point): zero properties where the caller asks for that
-        const bool zero_row = sc.unseen_zero && __ballot((lane < sc.K && mine[0] != 0.0f) || (lane + 64 < sc.K && mine[1] != 0.0f)) == 0;
-        for (int p = 0; p < sc.P; ++p) {
-          float num = 0.0f;
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            if (lane + 64 * h < sc.K) num = __builtin_fmaf(e[h], sc.y[(lane + 64 * h) * sc.P + p], num);
-          num = wave_sum(num);
-          if (lane == 0) sc.prop[i * sc.P + p] = zero_row ? 0.0f : num / den;
-        }
+        for (int h = 0; h < 2; ++h)
+          if (lane + 64 * h < sc.K) num = __builtin_fmaf(e[h], sc.y[(lane + 64 * h) * sc.P + p], num);
+        num = wave_sum(num);
+        if (lane == 0) sc.prop[i * sc.P + p] = zero_row ? 0.0f : num / den;
       }
     }
+  }
+}
+
+// Tiles without k-steps go to lists that the waves of the launch empty together when their workgroups have run out of
+// tiles.  Fused on the spot by the waves that found out, a single such tile held its workgroup up for hundreds of
+// microseconds (32 points one after the other), and with it the end of the kernel (8 tiles of 8000 points, 20 views, 768
+// channels: 671 us for the step, 169 us now).
+// kLists stacks (one would be a single address that every wave of the chip fights for): word kListWord + l of
+// TileWs::status holds the last entry pushed to list l (0: empty).  An entry is an eighth of a tile, tile * kParts +
+// part + 1; word `part` of TileHdr::cnt, which such a tile does not use, holds the entry below it, word kParts the tile's
+// object.  A tile is pushed once per launch, so an entry that was popped never comes back and the exchange in pop_part
+// cannot be fooled by a reused one.  Nobody waits: a wave that finds the lists empty leaves, and the waves of a workgroup
+// that pushed look at the lists after their last push.
+// Everything the waves share goes through agent-scope atomics, which act on memory that all XCDs see, so no cache has to
+// be written back or dropped: the words of an entry are complete (s_waitcnt) before the exchange that publishes it, and
+// their readers take their address from what the exchange left.
+constexpr int kParts = 8, kPartPts = kTilePts / kParts;
+constexpr int kLists = 32, kListWord = 32;
+
+__device__ __forceinline__ void push_tile(const TileWs& ws, int tile, int obj, int lane) {   // lanes 0 .. kParts - 1 of a wave
+  if (lane < kParts) {
+    int* words = ws.hdr[tile].cnt;
+    const unsigned entry = (unsigned)tile * kParts + (unsigned)lane + 1u;
+    unsigned* head = ws.status + kListWord + entry % kLists;
+    __hip_atomic_store(&words[kParts], obj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned top = __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool done = false;
+    while (!done) {
+      __hip_atomic_store(&words[lane], (int)top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      done = __hip_atomic_compare_exchange_strong(head, &top, entry, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane == 0) atomicAdd(ws.status + 1, 1u);   // second status word: tiles fused by the gather
+  }
+}
+
+// Called by whole waves, each on its own, at the end of a workgroup's life; `turn`: where a wave starts to look.
+template <int DT>
+__device__ __forceinline__ void drain_tiles(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, unsigned turn, int lane) {
+  static_assert(kLists == 32, "lanes 0 .. 31 look at one list each");
+  while (true) {
+    unsigned top = 0u;
+    if (lane < kLists) top = __hip_atomic_load(ws.status + kListWord + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t full = (uint32_t)__ballot(top != 0u);
+    if (full == 0u) return;
+    const int rot = (int)(turn % kLists);
+    const uint32_t rotated = rot ? (full >> rot) | (full << (kLists - rot)) : full;
+    const int list = (rot + __builtin_ctz(rotated)) % kLists;   // the first list at or after `turn` that holds something
+    unsigned taken = 0u;
+    int obj = 0;
+    if (lane == list) {
+      int* words = ws.hdr[(top - 1u) / kParts].cnt;
+      const unsigned below = (unsigned)__hip_atomic_load(&words[(top - 1u) % kParts], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      obj = __hip_atomic_load(&words[kParts], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__hip_atomic_compare_exchange_strong(ws.status + kListWord + list, &top, below, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT))
+        taken = top;
+    }
+    taken = (unsigned)__builtin_amdgcn_readlane((int)taken, list);
+    obj = __builtin_amdgcn_readlane(obj, list);
+    ++turn;
+    if (taken == 0u) continue;   // another wave was faster
+    const ObjRange ob = tab.o[obj];
+    const int li0 = (int)((taken - 1u) / kParts - (unsigned)ob.tile_begin) * kTilePts + (int)((taken - 1u) % kParts) * kPartPts;
+    for (int li = li0; li < min(li0 + kPartPts, ob.n_pts); ++li) gather_point<DT>(a, ob, li, lane);
   }
 }
 
@@ -545,11 +641,8 @@ void k_tile_prepare(FuseArgs a, TileWs ws, ObjTable tab) {
   }
   __syncthreads();
   if (exhausted) {
-    if (tid == 0) {
-      hdr->nsteps = -1;
-      atomicAdd(ws.status + 1, 1u);   // second status word: tiles fused by the gather
-    }
-    gather_tile<DT>(a, ob, li0, tid / kWave, kPrepThreads / kWave, lane);
+    if (tid == 0) hdr->nsteps = -1;
+    if (tid < kWave) push_tile(ws, ob.tile_begin + blk, blockIdx.y, lane);   // the product kernel fuses it by a gather
     return;
   }
   if (tid == 0) hdr->nsteps = used;
@@ -607,6 +700,15 @@ __device__ __forceinline__ int load_nsteps(const TileHdr* h) {
 // hardware counter larger than the compiler assumes; reads complete in order, so its waits remain
 // sufficient.  The workgroup waits for the copies explicitly (wait_copies) before the barrier that
 // publishes a buffer.
+// The one-kernel form's stage: what fits LDS beside the rest with as many workgroups per compute unit as the registers
+// allow (eight waves in all, see k_tile_fused), so that few tiles outgrow it (with 4, 8 and 16 k-steps for 256, 512 and
+// more channels, 123 457 points of 11 views took 469 us, 200 000 of 8 views and 256 channels 1080 us; 197 and 187 us now).
+template <int S, int NP, bool SC>
+constexpr int fused_stage_steps() {
+  constexpr int waves = S + NP + (SC ? 1 : 0);
+  return waves > 4 ? 32 : (S == 1 ? 8 : (S == 2 ? (SC ? 12 : 16) : 16));
+}
+
 template <int S>
 constexpr int stage_steps_for() { return S == 1 ? 4 : (S == 2 ? 8 : 16); }   // S: units of 256 channels   // keeps 8 waves per compute unit in LDS
 
@@ -707,7 +809,7 @@ struct ProdArgs {
 // a counter (tiles differ in length, a fixed split leaves a tail), so that at any time the tiles in
 // flight on an XCD are neighbours and share cell rows in its L2.
 constexpr int kXcd = 8;
-constexpr int kFusedGroupsMax = 512;  // one-kernel form: two workgroups per compute unit
+constexpr int kFusedGroupsMax = 512;  // one-kernel form: two workgroups per compute unit (four with one product wave)
 constexpr int kProdGroupsMax = 768;   // two workgroups fit a compute unit at a time; the rest take over as the first run out of tiles
 
 // The opening reads of a tile whose k-steps are staged at `sb` (n of them, possibly none): the rows of its
@@ -757,7 +859,7 @@ struct XcdTiles {
 
 template <int DT, int S, int H, int PF>
 __global__ __launch_bounds__(kWave* S) __attribute__((amdgpu_waves_per_eu(H == 1 ? 3 : 2, H == 1 ? 3 : 2)))
-void k_tile_product(ProdArgs a, ObjTable tab) {
+void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
   constexpr int kSpan = kHalf * H;   // channels per wave
   constexpr int kStage = stage_steps_for<S * H / 2>();
   __shared__ __attribute__((aligned(16))) char s_steps[2][kStage * sizeof(TileStep)];
@@ -792,15 +894,14 @@ void k_tile_product(ProdArgs a, ObjTable tab) {
   if (tid == 0) s_take[0] = (int)atomicAdd(ctr, 3u);
   __syncthreads();
   const int t0 = s_take[0];
-  if (t0 >= len) return;
-  int blk = tile_at(t0);
+  int blk = t0 < len ? tile_at(t0) : -1;
   int nxt = t0 + 1 < len ? tile_at(t0 + 1) : -1;    // -1: no further tile
   int nxt2 = t0 + 2 < len ? tile_at(t0 + 2) : -1;
   int buf = 0;
-  int n = load_nsteps(hdrs + blk);
+  int n = blk >= 0 ? load_nsteps(hdrs + blk) : 0;
   int n_next = nxt >= 0 ? load_nsteps(hdrs + nxt) : 0;
   int pend_n = hdrs[max(nxt2, 0)].nsteps;   // list length of the tile after the next, picked up one tile later
-  stage_steps<S>(s_steps[0], a.steps + (long long)(ob.tile_begin + blk) * a.quota, min(max(n, 0), kStage), span, lane);
+  stage_steps<S>(s_steps[0], a.steps + (long long)(ob.tile_begin + max(blk, 0)) * a.quota, min(max(n, 0), kStage), span, lane);
   wait_copies();
   __syncthreads();
   open_tile<H, PF>(s_steps[0], min(max(n, 0), kStage), a.feat, lane_off, lane, g, wa, rq);
@@ -938,6 +1039,7 @@ void k_tile_product(ProdArgs a, ObjTable tab) {
     n_next = n_next2;
     buf ^= 1;
   }
+  drain_tiles<DT>(fa, ws, tab, (blockIdx.y * gridDim.x + blockIdx.x) * S + (unsigned)span, lane);
 }
 
 // ------------------------------------------------------------------------------------ one kernel
@@ -949,8 +1051,7 @@ void k_tile_product(ProdArgs a, ObjTable tab) {
 // tile before it.  The tile's one barrier is shared: after it the buffer the products came from belongs to the producer
 // and the buffer it filled belongs to the product waves.  The producer has no barrier of its own: it is one wave, and
 // orders its LDS traffic with wave-level fences.  Tiles go to workgroups through the per-XCD counters as before; the
-// producer asks for a ticket one tile ahead.  A tile whose list does not fit the buffer is fused by the producer itself
-// (per-point gather): the launch code only takes this kernel where that is rare.
+// producer asks for a ticket one tile ahead.  A tile whose list does not fit the buffer goes to the list of push_tile.
 
 constexpr int kPBatch = 16;   // views per pass of the producer waves: two per trip, one per half wave
 constexpr int kMaxProducers = 4;
@@ -970,7 +1071,7 @@ struct ProducerScratch {
 
 struct TileSlot {    // what the product waves need to know about a staged tile
   int tile;          // index within the object; -1: no further tile
-  int nsteps;        // -1: fused by the producers
+  int nsteps;        // -1: no k-steps, see push_tile
   int pad_[2];
   int cnt[kMaxProducers][kTilePts];   // views that see each point, per producer wave
   uint32_t vmask[kCamRows];           // per view of the object: which of the tile's 32 points it sees (Eq. 1)
@@ -1073,7 +1174,8 @@ template <int DT, bool SEL, int NP>
 __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& ob, int blk,
                                              float3 pt, ProjectedBatch<NP>& pre, char* stage, int k_stage, int& dirty,
                                              TileSlot* slot, ProducerScratch* sc, lds_floats cam_lds, lds_flags flags,
-                                             unsigned* status, int w, int& seq, int lane) {
+                                             const TileWs& ws, int obj, int* pushed, int w, int& seq, int lane) {
+  unsigned* status = ws.status;
   constexpr int kTrips = kPBatch / 2 / NP;   // trips of one wave per batch of views
   const int p = lane & 31, h = lane >> 5;
   const int Hf = a.feat.Hf, Wf = a.feat.Wf;
@@ -1085,8 +1187,7 @@ __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& 
   bool exhausted = false;
 
   // zero weights, shared by the waves: complete for everybody at the first meeting, before any weight lands.  Only
-  // the k-steps that the buffer's last tile wrote (`dirty` of them; all of the buffer the first time) can hold
-  // anything but zeros.
+  // the k-steps that the buffer's last tile wrote (`dirty` of them) can hold anything but zeros.
   for (int q = w * kWave + lane; q < dirty * 128; q += NP * kWave)
     reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&st[q >> 7]) + 64)[q & 127] = u32x4{0u, 0u, 0u, 0u};
 
@@ -1286,11 +1387,13 @@ __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& 
   if (w == 0 && lane == 0) {
     slot->tile = blk;
     slot->nsteps = exhausted ? -1 : used;
-    if (exhausted) atomicAdd(status + 1, 1u);   // second status word: tiles fused by the gather
+  }
+  if (exhausted && w == 0) {
+    push_tile(ws, ob.tile_begin + blk, obj, lane);
+    if (lane == 0) *pushed = 1;
   }
   if (lane < kTilePts) slot->cnt[w][lane] = mine;
   dirty = used;   // the same in every producer wave
-  if (exhausted) gather_tile<DT>(a, ob, li0, w, NP, lane);   // writes the rows, the counts and the mask of the tile itself
 }
 
 // The scoring wave's part of a tile (Sec. 3.4.1): omega^T = G^T . W^T over the k-steps staged at `sb`, whose weight
@@ -1368,7 +1471,7 @@ template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC>
 __global__ __launch_bounds__(kWave* (S + NP + (SC ? 1 : 0))) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   constexpr int kSpan = kHalf * H;
-  constexpr int kStage = stage_steps_for<S * H / 2>();
+  constexpr int kStage = fused_stage_steps<S, NP, SC>();
   __shared__ __attribute__((aligned(16))) char s_steps[2][kStage * sizeof(TileStep)];
   __shared__ TileSlot s_slot[2];
   __shared__ __attribute__((aligned(16))) ProducerScratch s_sc;
@@ -1376,6 +1479,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ __attribute__((aligned(16))) float s_cam[kCamRows][16];   // the object's camera rows, for the producers
   __shared__ int s_plan[4];      // tickets of the workgroup's tiles, k-th tile in slot k & 3
   __shared__ __attribute__((aligned(16))) int s_flags[kMaxProducers];   // meeting numbers of the producer waves
+  __shared__ int s_pushed;       // whether this workgroup put a tile on the lists of push_tile
   __shared__ float s_ys[SC ? kScoreTileM * kScoreMaxP : 1];   // the property table y[K][P]
   __shared__ ScoreOut s_out[SC ? 2 : 1];                        // scores of the tile before the last, on their way to memory
 
@@ -1399,6 +1503,12 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   const int m = lane & 31, g = lane >> 5;
   const int D = a.D;
   const uint32_t lane_off = (uint32_t)(span * kSpan + 4 * m) * 2u;
+  if (tid == 0) s_pushed = 0;
+  const int room = min(kStage, ws.quota);   // k-steps a tile may have: the same bound as where they go to memory
+  // zero weights everywhere, by all waves (the barrier that follows in every branch publishes them); from then on the
+  // producers clear what a buffer's last tile wrote
+  for (int q = tid; q < 2 * room * (int)(sizeof(TileStep) / 16); q += blockDim.x)
+    reinterpret_cast<u32x4*>(s_steps[q >= room * (int)(sizeof(TileStep) / 16)])[q % (room * (int)(sizeof(TileStep) / 16))] = u32x4{0u, 0u, 0u, 0u};
 
   if (producer) {
     // With eight waves in the workgroup every producer shares its SIMD with a product wave, and the tile waits for the
@@ -1433,7 +1543,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     // a plan past the end reads (and projects) a tile that exists; it is never built
     auto tile_of = [&](int t) { return min(tile_at(t), last_tile); };
     ProjectedBatch<NP> pre;
-    int dirty0 = kStage, dirty1 = kStage;   // k-steps of each stage buffer that may hold non-zero weights
+    int dirty0 = 0, dirty1 = 0;   // k-steps of each stage buffer that hold weights of an earlier tile
     float3 pt;   // the lane's point of the tile that the next trip builds
     {
       const int t0 = s_plan[0], t1 = s_plan[1];
@@ -1441,8 +1551,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       const float3 pt1 = tile_point(fa, ob, tile_of(t1), lane);
       project_batch<SEL, NP>(fa, ob, tile_of(t0), pt0, 0, cam_lds, w, lane, pre);
       if (t0 < len) {
-        produce_tile<DT, SEL, NP>(fa, ob, tile_at(t0), pt0, pre, s_steps[0], kStage, dirty0, &s_slot[0], &s_sc, cam_lds,
-                                  (lds_flags)&s_flags[0], ws.status, w, seq, lane);
+        produce_tile<DT, SEL, NP>(fa, ob, tile_at(t0), pt0, pre, s_steps[0], room, dirty0, &s_slot[0], &s_sc, cam_lds,
+                                  (lds_flags)&s_flags[0], ws, blockIdx.y, &s_pushed, w, seq, lane);
       } else if (w == 0 && lane == 0) {
         s_slot[0].tile = -1;
         s_slot[0].nsteps = 0;
@@ -1459,8 +1569,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       const int t = s_plan[k & 3], tn = s_plan[(k + 1) & 3];
       const float3 pt_next = tile_point(fa, ob, tile_of(tn), lane);   // requested now, looked at after this tile is built
       if (t < len) {
-        produce_tile<DT, SEL, NP>(fa, ob, tile_at(t), pt, pre, s_steps[buf ^ 1], kStage, buf ? dirty0 : dirty1, &s_slot[buf ^ 1], &s_sc, cam_lds,
-                                  (lds_flags)&s_flags[0], ws.status, w, seq, lane);
+        produce_tile<DT, SEL, NP>(fa, ob, tile_at(t), pt, pre, s_steps[buf ^ 1], room, buf ? dirty0 : dirty1, &s_slot[buf ^ 1], &s_sc, cam_lds,
+                                  (lds_flags)&s_flags[0], ws, blockIdx.y, &s_pushed, w, seq, lane);
       } else if (w == 0 && lane == 0) {
         s_slot[buf ^ 1].tile = -1;
         s_slot[buf ^ 1].nsteps = 0;
@@ -1476,10 +1586,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       buf ^= 1;
       ++k;
     }
-    return;
-  }
-  if constexpr (SC) {
-    if (span == S) {
+  } else if (SC && span == S) {
+    if constexpr (SC) {
       // The scoring wave follows the product waves through the tiles, one barrier behind.  During a tile it multiplies
       // the staged weights with G.  After the tile's barrier the product waves' sums of squares are in LDS: the factor
       // of every point follows as in the product waves, and the scores, labels and properties of the tile go to LDS
@@ -1507,7 +1615,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
           const int li = blk_prev * kTilePts + m;
           const bool valid = li < ob.n_pts;
           const long long ip = ob.pt_begin + (valid ? li : ob.n_pts - 1);
-          // (a tile that the producers fused themselves, n_prev < 0, has its scores already: gather_tile)
+          // (a tile without k-steps, n_prev < 0, gets its scores in gather_point)
           const float inv = cnt_prev > 0 ? 1.0f / (float)cnt_prev : 0.0f;
           float tot = 0.0f;
 #pragma unroll
@@ -1540,174 +1648,177 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
         cnt_prev = my_cnt;
         buf ^= 1;
       }
-      return;
     }
-  }
-  __syncthreads();
-  __syncthreads();
+  } else {
+    __syncthreads();
+    __syncthreads();
 
-  StepA wa[2];
-  StepC wc;
-  StepQ<H> rq[PF];
-  int buf = 0;
-  if (s_slot[0].tile >= 0)
-    open_tile<H, PF>(s_steps[0], min(max(s_slot[0].nsteps, 0), kStage), a.feat, lane_off, lane, g, wa, rq);
+    StepA wa[2];
+    StepC wc;
+    StepQ<H> rq[PF];
+    int buf = 0;
+    if (s_slot[0].tile >= 0)
+      open_tile<H, PF>(s_steps[0], min(max(s_slot[0].nsteps, 0), kStage), a.feat, lane_off, lane, g, wa, rq);
 
-  while (true) {
-    const int blk = s_slot[buf].tile;   // uniform over the workgroup: written before the last barrier
-    if (blk < 0) break;
-    const int n = s_slot[buf].nsteps;
-    int my_cnt = 0;                      // views that see point (lane % 32) of this tile
-#pragma unroll
-    for (int o = 0; o < NP; ++o) my_cnt += s_slot[buf].cnt[o][m];
-    f32x16 acc[4 * H];
-#pragma unroll
-    for (int t = 0; t < 4 * H; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+    while (true) {
+      const int blk = s_slot[buf].tile;   // uniform over the workgroup: written before the last barrier
+      if (blk < 0) break;
+      const int n = s_slot[buf].nsteps;
+      int my_cnt = 0;                      // views that see point (lane % 32) of this tile
+  #pragma unroll
+      for (int o = 0; o < NP; ++o) my_cnt += s_slot[buf].cnt[o][m];
+      f32x16 acc[4 * H];
+  #pragma unroll
+      for (int t = 0; t < 4 * H; ++t)
+  #pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
 
-    const char* sb = s_steps[buf];
-    {
-      const int cnt = max(n, 0), l0 = cnt - 1;
-      int s = 0;
-      for (; s + PF <= cnt; s += PF) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j) {
-          lds_c(sb, min(s + j + PF, l0), g, wc);
-          lds_a(sb, min(s + j + 1, l0), lane, wa[(j + 1) & 1]);
-          mma_step<DT, H>(wa[j & 1], rq[j], acc);
-          __builtin_amdgcn_sched_barrier(0);
-          load_q(a.feat, wc, lane_off, rq[j]);
-          __builtin_amdgcn_sched_barrier(0);
+      const char* sb = s_steps[buf];
+      {
+        const int cnt = max(n, 0), l0 = cnt - 1;
+        int s = 0;
+        for (; s + PF <= cnt; s += PF) {
+  #pragma unroll
+          for (int j = 0; j < PF; ++j) {
+            lds_c(sb, min(s + j + PF, l0), g, wc);
+            lds_a(sb, min(s + j + 1, l0), lane, wa[(j + 1) & 1]);
+            mma_step<DT, H>(wa[j & 1], rq[j], acc);
+            __builtin_amdgcn_sched_barrier(0);
+            load_q(a.feat, wc, lane_off, rq[j]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+  #pragma unroll
+        for (int j = 0; j < PF - 1; ++j) {
+          if (s + j < cnt) {
+            lds_a(sb, min(s + j + 1, l0), lane, wa[(j + 1) & 1]);
+            mma_step<DT, H>(wa[j & 1], rq[j], acc);
+          }
         }
       }
-#pragma unroll
-      for (int j = 0; j < PF - 1; ++j) {
-        if (s + j < cnt) {
-          lds_a(sb, min(s + j + 1, l0), lane, wa[(j + 1) & 1]);
-          mma_step<DT, H>(wa[j & 1], rq[j], acc);
-        }
-      }
-    }
 
-    // What goes to memory besides the fused rows.  After the products, not before: the memory counter is in order
-    // and covers stores as well, so a store issued ahead of the first product (behind a condition, which makes the
-    // compiler count it as possibly absent) would have to be acknowledged before the cell rows requested earlier count
-    // as arrived - one store round trip per tile on the critical path.
-    if (n >= 0 && span == 0 && tid < kTilePts && fa.out_count && blk * kTilePts + tid < ob.n_pts)
-      fa.out_count[ob.pt_begin + blk * kTilePts + tid] = my_cnt;
-    if constexpr (SC) {   // what the scoring wave finished during the last tile (the tile before that one)
-      if (span == (S > 1 ? 1 : 0)) store_scores(s_out[buf], fa.scoring, ob, lane);
-    }
-    if (keep && tid == 0) ws.hdr[ob.tile_begin + blk].nsteps = n;   // the scoring kernel reads the header from memory
-    if (fa.out_vis && lane < kTilePts && blk * kTilePts + lane < ob.n_pts) {
-      // The visibility mask (Eq. 1) of the tile, as aura_project_visibility writes it: lane = point, and the product
-      // waves share the views, eight at a time (eight bytes of the point's row).  A tile that the producers fused
-      // themselves has its mask already, up to the columns beyond the object's views.
-      uint8_t* __restrict__ vrow = fa.out_vis + (ob.pt_begin + blk * kTilePts + lane) * fa.vis_pitch;
-      const uint32_t* vm = s_slot[buf].vmask;
-      if (n >= 0) {
-        const bool pairs = (fa.vis_pitch & 7) == 0 && (reinterpret_cast<uintptr_t>(fa.out_vis) & 7) == 0;
-        const bool words = (fa.vis_pitch & 3) == 0 && (reinterpret_cast<uintptr_t>(fa.out_vis) & 3) == 0;
-        // who takes the first eight views, the next eight, ...: the last wave, the first, then the others, with the
-        // second wave (which stores the scores where the workgroup has a scoring wave) at the end
-        const int turn = S <= 2 ? span : (span == S - 1 ? 0 : (span == 0 ? 1 : (span == 1 ? S - 1 : span)));
-        for (int v0 = 8 * turn; v0 < ob.n_views; v0 += 8 * S) {
-          uint32_t wd[2] = {0u, 0u};
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (v0 + e < ob.n_views) wd[e >> 2] |= ((vm[v0 + e] >> lane) & 1u) << (8 * (e & 3));
-          if (pairs && v0 + 8 <= ob.n_views) {
-            *reinterpret_cast<u32x2*>(vrow + v0) = u32x2{wd[0], wd[1]};
-          } else {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              if (words && v0 + 4 * q + 4 <= ob.n_views) {
-                *reinterpret_cast<uint32_t*>(vrow + v0 + 4 * q) = wd[q];
-              } else {
-                for (int e = 0; e < 4 && v0 + 4 * q + e < ob.n_views; ++e) vrow[v0 + 4 * q + e] = (uint8_t)((wd[q] >> (8 * e)) & 1u);
+      // What goes to memory besides the fused rows.  After the products, not before: the memory counter is in order
+      // and covers stores as well, so a store issued ahead of the first product (behind a condition, which makes the
+      // compiler count it as possibly absent) would have to be acknowledged before the cell rows requested earlier count
+      // as arrived - one store round trip per tile on the critical path.
+      if (n >= 0 && span == 0 && tid < kTilePts && fa.out_count && blk * kTilePts + tid < ob.n_pts)
+        fa.out_count[ob.pt_begin + blk * kTilePts + tid] = my_cnt;
+      if constexpr (SC) {   // what the scoring wave finished during the last tile (the tile before that one)
+        if (span == (S > 1 ? 1 : 0)) store_scores(s_out[buf], fa.scoring, ob, lane);
+      }
+      if (keep && tid == 0) ws.hdr[ob.tile_begin + blk].nsteps = n;   // the scoring kernel reads the header from memory
+      if (fa.out_vis && lane < kTilePts && blk * kTilePts + lane < ob.n_pts) {
+        // The visibility mask (Eq. 1) of the tile, as aura_project_visibility writes it: lane = point, and the product
+        // waves share the views, eight at a time (eight bytes of the point's row).  A tile without
+        // k-steps has its mask from gather_point, up to the columns beyond the object's views.
+        uint8_t* __restrict__ vrow = fa.out_vis + (ob.pt_begin + blk * kTilePts + lane) * fa.vis_pitch;
+        const uint32_t* vm = s_slot[buf].vmask;
+        if (n >= 0) {
+          const bool pairs = (fa.vis_pitch & 7) == 0 && (reinterpret_cast<uintptr_t>(fa.out_vis) & 7) == 0;
+          const bool words = (fa.vis_pitch & 3) == 0 && (reinterpret_cast<uintptr_t>(fa.out_vis) & 3) == 0;
+          // who takes the first eight views, the next eight, ...: the last wave, the first, then the others, with the
+          // second wave (which stores the scores where the workgroup has a scoring wave) at the end
+          const int turn = S <= 2 ? span : (span == S - 1 ? 0 : (span == 0 ? 1 : (span == 1 ? S - 1 : span)));
+          for (int v0 = 8 * turn; v0 < ob.n_views; v0 += 8 * S) {
+            uint32_t wd[2] = {0u, 0u};
+  #pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (v0 + e < ob.n_views) wd[e >> 2] |= ((vm[v0 + e] >> lane) & 1u) << (8 * (e & 3));
+            if (pairs && v0 + 8 <= ob.n_views) {
+              *reinterpret_cast<u32x2*>(vrow + v0) = u32x2{wd[0], wd[1]};
+            } else {
+  #pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                if (words && v0 + 4 * q + 4 <= ob.n_views) {
+                  *reinterpret_cast<uint32_t*>(vrow + v0 + 4 * q) = wd[q];
+                } else {
+                  for (int e = 0; e < 4 && v0 + 4 * q + e < ob.n_views; ++e) vrow[v0 + 4 * q + e] = (uint8_t)((wd[q] >> (8 * e)) & 1u);
+                }
               }
             }
           }
         }
+        if (span == S - 1)
+          for (int j = ob.n_views; j < fa.vis_pitch; ++j) vrow[j] = 0;
       }
-      if (span == S - 1)
-        for (int j = ob.n_views; j < fa.vis_pitch; ++j) vrow[j] = 0;
-    }
-    if (keep && n > 0) {
-      // The scoring kernel wants the k-steps in memory: the product waves, which have issue slots to spare, copy the
-      // staged tile out (the producers do not: their vector ALU work is what the tile waits for).
-      u32x4* __restrict__ dst = reinterpret_cast<u32x4*>(ws.steps + (long long)(ob.tile_begin + blk) * ws.quota);
-      const u32x4* src = reinterpret_cast<const u32x4*>(sb);
-      for (int q = span * kWave + lane; q < n * (int)(sizeof(TileStep) / 16); q += S * kWave) dst[q] = src[q];
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 8 * (r >> 2) + 4 * g + (r & 3);
-      float ss = 0.0f;
-#pragma unroll
-      for (int t = 0; t < 4 * H; ++t) ss = __builtin_fmaf(acc[t][r], acc[t][r], ss);
-      ss = half_wave_sum(ss);
-      if (m == 31) s_ss[buf][span][row] = ss;
-    }
-    __syncthreads();   // the one barrier of a tile: the sums are in LDS, the producers have staged the next tile, and
-                       // every product wave is done with this tile's buffer
-
-    float factor;
-    {
-      const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
-      float tot = 0.0f;
-#pragma unroll
-      for (int wv = 0; wv < S; ++wv) tot += s_ss[buf][wv][m];
-      const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
-      factor = a.mean_only ? inv : normed;
-    }
-    {
-      const int rows_f = a.factor ? min(kTilePts, ob.n_pts - blk * kTilePts) : 0;
-      const __amdgpu_buffer_rsrc_t fout = __builtin_amdgcn_make_buffer_rsrc(a.factor + (a.factor ? ob.pt_begin + blk * kTilePts : 0), 0,
-                                                                            rows_f * 4, 0x00020000);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(factor), fout, tid < kTilePts ? 4 * tid : 0x7ffffff0, 0, 0);
-    }
-    {
-      const int li0 = blk * kTilePts;
-      float* obase = a.fused ? a.fused + (ob.pt_begin + li0) * D + span * kSpan : nullptr;
-      uint32_t row_bytes = (uint32_t)D * 4u;
-      asm volatile("" : "+s"(row_bytes));
-      const int rows = (n >= 0 && a.fused) ? min(kTilePts, ob.n_pts - li0) : 0;
-      const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(obase, 0, (int)(rows * row_bytes), 0x00020000);
-      const uint32_t lane_out = (uint32_t)(4 * g) * row_bytes + (uint32_t)(4 * m) * 4u;
-#pragma unroll
+      if (keep && n > 0) {
+        // The scoring kernel wants the k-steps in memory: the product waves, which have issue slots to spare, copy the
+        // staged tile out (the producers do not: their vector ALU work is what the tile waits for).
+        u32x4* __restrict__ dst = reinterpret_cast<u32x4*>(ws.steps + (long long)(ob.tile_begin + blk) * ws.quota);
+        const u32x4* src = reinterpret_cast<const u32x4*>(sb);
+        for (int q = span * kWave + lane; q < n * (int)(sizeof(TileStep) / 16); q += S * kWave) dst[q] = src[q];
+      }
+  #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row0 = 8 * (r >> 2) + (r & 3);
-        const float scale = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (row0 + 4 * g), __float_as_int(factor)));
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-          const f32x4 v = {acc[4 * h][r] * scale, acc[4 * h + 1][r] * scale, acc[4 * h + 2][r] * scale, acc[4 * h + 3][r] * scale};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out,
-                                                 (int)(lane_out + (uint32_t)row0 * row_bytes) + h * kHalf * 4, 0, /*streaming*/ 2);
+        const int row = 8 * (r >> 2) + 4 * g + (r & 3);
+        float ss = 0.0f;
+  #pragma unroll
+        for (int t = 0; t < 4 * H; ++t) ss = __builtin_fmaf(acc[t][r], acc[t][r], ss);
+        ss = half_wave_sum(ss);
+        if (m == 31) s_ss[buf][span][row] = ss;
+      }
+      __syncthreads();   // the one barrier of a tile: the sums are in LDS, the producers have staged the next tile, and
+                         // every product wave is done with this tile's buffer
+
+      float factor;
+      {
+        const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
+        float tot = 0.0f;
+  #pragma unroll
+        for (int wv = 0; wv < S; ++wv) tot += s_ss[buf][wv][m];
+        const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
+        factor = a.mean_only ? inv : normed;
+      }
+      {
+        const int rows_f = a.factor ? min(kTilePts, ob.n_pts - blk * kTilePts) : 0;
+        const __amdgpu_buffer_rsrc_t fout = __builtin_amdgcn_make_buffer_rsrc(a.factor + (a.factor ? ob.pt_begin + blk * kTilePts : 0), 0,
+                                                                              rows_f * 4, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(factor), fout, tid < kTilePts ? 4 * tid : 0x7ffffff0, 0, 0);
+      }
+      {
+        const int li0 = blk * kTilePts;
+        float* obase = a.fused ? a.fused + (ob.pt_begin + li0) * D + span * kSpan : nullptr;
+        uint32_t row_bytes = (uint32_t)D * 4u;
+        asm volatile("" : "+s"(row_bytes));
+        const int rows = (n >= 0 && a.fused) ? min(kTilePts, ob.n_pts - li0) : 0;
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(obase, 0, (int)(rows * row_bytes), 0x00020000);
+        const uint32_t lane_out = (uint32_t)(4 * g) * row_bytes + (uint32_t)(4 * m) * 4u;
+  #pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row0 = 8 * (r >> 2) + (r & 3);
+          const float scale = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (row0 + 4 * g), __float_as_int(factor)));
+  #pragma unroll
+          for (int h = 0; h < H; ++h) {
+            const f32x4 v = {acc[4 * h][r] * scale, acc[4 * h + 1][r] * scale, acc[4 * h + 2][r] * scale, acc[4 * h + 3][r] * scale};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out,
+                                                   (int)(lane_out + (uint32_t)row0 * row_bytes) + h * kHalf * 4, 0, /*streaming*/ 2);
+          }
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+      buf ^= 1;
+      {
+        const int nn = s_slot[buf].tile >= 0 ? min(max(s_slot[buf].nsteps, 0), kStage) : 0;
+        open_tile<H, PF>(s_steps[buf], nn, a.feat, lane_off, lane, g, wa, rq);
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    buf ^= 1;
-    {
-      const int nn = s_slot[buf].tile >= 0 ? min(max(s_slot[buf].nsteps, 0), kStage) : 0;
-      open_tile<H, PF>(s_steps[buf], nn, a.feat, lane_off, lane, g, wa, rq);
+    if constexpr (SC) {   // the tile before the workgroup's last one (the scoring wave stores the last one itself)
+      if (span == (S > 1 ? 1 : 0)) store_scores(s_out[buf], fa.scoring, ob, lane);
     }
   }
-  if constexpr (SC) {   // the tile before the workgroup's last one (the scoring wave stores the last one itself)
-    if (span == (S > 1 ? 1 : 0)) store_scores(s_out[buf], fa.scoring, ob, lane);
-  }
+  // The lists are looked at by the workgroups that may have pushed last and by the launch's last workgroups, which have
+  // nobody to make room for (a look costs a round trip to memory, and a workgroup in a launch of many thousands that ends
+  // early is replaced by the next one).
+  const unsigned group = blockIdx.y * gridDim.x + blockIdx.x;
+  if (s_pushed != 0 || group + kFusedGroupsMax >= gridDim.x * gridDim.y)
+    drain_tiles<DT>(fa, ws, tab, group * (unsigned)(blockDim.x / kWave) + (unsigned)span, lane);
 }
 
 // Clears the ticket counters of a launch's objects (the prepare kernel does it on the two-kernel path).
 __global__ void k_clear_counters(unsigned* counters, int n, unsigned* status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) counters[i] = 0u;
-  if (i == 0 && status) {
-    status[0] = 0u;
-    status[1] = 0u;
-  }
+  if (i < 64 && status) status[i] = 0u;   // the status words and the lists of push_tile (which every launch leaves empty)
 }
 
 // ------------------------------------------------------------------------------------ host
@@ -1754,17 +1865,21 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
          D / 256 != 5 && feat_bytes <= 0xffffffffll;
 }
 
-// How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  The lists of (nearly) all
-// tiles must fit the LDS buffer of kStage k-steps, and when the scoring kernel wants the k-steps in memory, the
-// tile's share of the workspace as well.  Measured need on spatially sorted points: 0.3 to 0.4 k-steps per view for
-// coarse grids, up to 1 for pixel-sized cells.  One producer wave keeps up with the product waves for a few views per
-// object; beyond that four share the views of a tile and a compute unit holds one workgroup of at most eight waves
-// (two per SIMD: a product wave needs about 250 registers).
-static int one_kernel_producers(const FuseArgs& a, int k_stage, int quota, int views_per_obj, int product_waves) {
-  const float per_view = (a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f) ? 0.5f : 1.0f;
-  if (a.two_kernels || k_stage > quota || views_per_obj > kCamRows || (float)views_per_obj * per_view > (float)k_stage) return 0;
-  if (views_per_obj <= kOneKernelViews) return 1;
-  if (product_waves + 4 > 8) return 0;
+// How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  One producer wave keeps up with
+// the product waves for a few views per object; beyond that four share the views of a tile and a compute unit holds one
+// workgroup of at most eight waves (two per SIMD: a product wave needs about 250 registers).
+// Cells of at least 4 x 4 pixels: a tile needs 0.3 to 0.4 k-steps per view on spatially sorted points, so the producers
+// keep up for every number of views they take.  Smaller cells need up to one k-step per view, and many views of them
+// make the producers the longer side (32 views of pixel-sized cells, 512 channels: 1.17 ms against 1.12 ms for the two
+// kernels): those go to the two kernels above 4 (256 channels), 8 (512) and 16 views.
+static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int product_waves) {
+  const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
+  if (a.two_kernels || views_per_obj > kCamRows || (!coarse && views_per_obj > (product_waves >= 3 ? 16 : 4 * product_waves))) return 0;
+  // Few views: where two workgroups fit a compute unit.  (Five waves leave three idle: 63 objects of 2 views and 1024
+  // channels 708 us as two kernels, 1015 us as one; 300 000 points of 8 views 390 and 426 us.)  With three views of 512
+  // channels per object the other way round: 811 against 1002 us, two views 1062 against 1509 us.
+  if (views_per_obj <= kOneKernelViews) return product_waves + 1 <= 4 ? 1 : 0;
+  if (product_waves == 1 || product_waves + 4 > 8) return 0;   // (one product wave leaves four producers idle: 32 views of 256 channels 413 us, 383 us as two kernels)
   // (where the scoring kernel wants the k-steps in memory the product waves copy them out: measured 3 to 7 % faster than
   // the two kernels on 768 channels with 16 views and on 1024 channels with 24 views)
   return 4;
@@ -1789,15 +1904,15 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
               ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only};
   int max_views = 0;
   for (int t = 0; t < n_obj; ++t) max_views = std::max(max_views, tab.o[t].n_views);
-  const int np = one_kernel_producers(a, stage_steps_for<S * H / 2>(), ws.quota, max_views, S);
+  const int np = one_kernel_producers(a, max_views, S);
   if (np > 0) {
     // (the status word of the call is cleared along with the counters of its first launch)
     hipLaunchKernelGGL(k_clear_counters, dim3((n_obj * kXcd + 63) / 64), dim3(64), 0, stream, pa.counters, n_obj * kXcd,
                        ws.obj_base == 0 ? ws.status : nullptr);
-    // with one producer wave two workgroups fit a compute unit, with four one; several objects in one launch share
-    // the machine
-    const int groups_max = np == 1 ? kFusedGroupsMax : kFusedGroupsMax / 2;
+    // with one producer wave two workgroups fit a compute unit (four where the workgroup has just the two waves), with
+    // four one; several objects in one launch share the machine
     const bool scoring = scoring_wave_fits(a, np, S);
+    const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring ? 2 * kFusedGroupsMax : kFusedGroupsMax);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time.  The workgroups of
     // an object share its tiles through the per-XCD tickets and are dispatched object after object, so the machine
@@ -1845,7 +1960,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   if (e != hipSuccess) return e;
   // several objects in one launch share the machine: fewer workgroups per object
   const int groups = std::max(kXcd, std::min(max_tiles, (kProdGroupsMax / n_obj + kXcd - 1) / kXcd * kXcd));
-  hipLaunchKernelGGL((k_tile_product<DT, S, H, PF>), dim3(std::min(groups, max_tiles), n_obj), dim3(kWave * S), 0, stream, pa, tab);
+  hipLaunchKernelGGL((k_tile_product<DT, S, H, PF>), dim3(std::min(groups, max_tiles), n_obj), dim3(kWave * S), 0, stream, a, pa, ws, tab);
   e = hipGetLastError();
   if (timed.stop) (void)hipEventRecord(timed.stop, stream);
   return e;

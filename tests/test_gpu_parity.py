@@ -380,6 +380,30 @@ def test_unsorted_points_on_the_matrix_core_path(H, orc, name, kw):
         assert ds.status_words(word=1)["fuse_features"] <= max(2, ntile // 50)
 
 
+# Tiles without k-steps (points in no order): every fusion kernel that pushes and empties the lists - one to four product
+# waves, one and four producers, with the scoring wave, with the scoring kernel behind it, as two kernels - with a ragged
+# last tile, and several objects in one launch, most of whose workgroups look at the lists only if they pushed.
+@pytest.mark.parametrize("N,B,V,D,K,dtype", [(1_601, 1, 5, 256, 12, "f16"), (1_601, 1, 12, 512, 12, "bf16"),
+                                             (1_601, 1, 7, 512, 40, "f16"), (1_633, 1, 14, 768, 32, "f16"),
+                                             (1_601, 1, 14, 1024, 70, "bf16"), (901, 1, 3, 1024, 128, "f16"),
+                                             (33, 1, 6, 512, 5, "f16"), (3_301, 1, 12, 512, 32, "f16"),
+                                             (3_301, 1, 12, 512, 40, "bf16"), (2_101, 1, 7, 256, 128, "f16"),
+                                             (3_000, 20, 4, 512, 24, "f16")])
+def test_tiles_without_k_steps(H, orc, N, B, V, D, K, dtype):
+    kw = dict(overrides=dict(V=V, D=D, K=K, dtype=dtype, grid=16 if N > 2_000 else 32), order="random")
+    s = make_scene("c1", n_points=N, **kw) if B == 1 else make_scene("c5", n_points=N, n_objects=B, **kw)
+    ref = H.oracle_points(orc, s, flags=1)
+    d = H.DeviceScene(s, flags=1)       # no depth test: every pair in an image counts, so the lists are long
+    for step in (d.step_combined, d.step, d.step_single_pass, d.step_two_kernels):
+        d.clear_outputs()
+        step()
+        H.compare_points(d.results(), ref, s, no_fused=step == d.step_single_pass)
+    tiles = int(np.sum((np.diff(s.pt_offsets) + 31) // 32))
+    words = d.status_words(word=1)
+    print("tiles", tiles, words, flush=True)
+    assert all(0 < w <= tiles for w in words.values())
+
+
 def test_flags_and_degenerate_inputs(H, orc):
     import paper_2511_03126_amd as aura
     from paper_2511_03126_amd import binding
