@@ -138,6 +138,19 @@ static bool tile_path(int32_t dtype, int32_t D, int32_t Hf, int32_t Wf, int32_t 
   return aura::fuse_tile_supported(dtype, D, Hf, Wf, feat_bytes);
 }
 
+// Whether a call that the matrix-core kernels could take has too few points for them: below 64 M (point, view, channel)
+// triples the gather kernel, one wave per point, is done before their pipeline of tiles has filled (points and the k-steps of
+// a tile, then its products, one tile ahead), and sparse points give a tile long lists.  Measured, one call per stage,
+// matrix cores / gather: 5 views and 512 channels, 2000 points 67 / 42 us, 16 000 (41 M) 97 / 54 us; 16 views and 768 channels,
+// 4000 points (49 M) 120 / 74 us, 8000 (98 M) 98 / 87 us, 16 000 105 / 110 us; 10 views and 256 channels, 16 000 points
+// (41 M) 76 / 53 us.  Only for cells of at least 4 x 4 pixels, where neighbouring points share them in the caches.
+static bool few_points(const aura_views_t* v, const aura_params_t* p, int64_t N, int32_t B) {
+  if (p->flags & AURA_FUSE_TWO_KERNELS) return false;
+  if (v->W < 4 * (int64_t)v->Wf || v->H < 4 * (int64_t)v->Hf) return false;
+  const int64_t views = ((int64_t)v->n_views + B - 1) / B;
+  return (double)N * (double)views * (double)v->D <= 64e6;
+}
+
 static bool known_dtype(int32_t t) { return t == AURA_F32 || t == AURA_BF16 || t == AURA_F16; }
 
 // Workspace of aura_fuse_scores: the fusion workspace, then (where the scores come from per-cell
@@ -334,26 +347,26 @@ static aura_status_t fuse_features_impl(const aura_views_t* views, const aura_pa
   const hipStream_t st = static_cast<hipStream_t>(stream);
   // matrix-core tile path: 16-bit maps, D a multiple of 256, a workspace, and not switched off
   aura::TileWs tws{};
-  const bool tile = workspace && !(params->flags & AURA_FUSE_GATHER) &&
-                    tile_path(views->feat_dtype, views->D, views->Hf, views->Wf, views->n_views);
+  bool tile = workspace && !(params->flags & AURA_FUSE_GATHER) &&
+              tile_path(views->feat_dtype, views->D, views->Hf, views->Wf, views->n_views);
   if (tile) {
     if (!aligned(workspace, 256) || workspace_bytes < aura::fuse_tile_workspace_bytes(N, B, views->n_views))
       return AURA_ERR_WORKSPACE;
     tws = aura::fuse_tile_workspace(workspace, N, B, views->n_views);
+    if (few_points(views, params, N, B)) tile = false;
   }
+  unsigned* clear_status = nullptr;
   if (!tile && workspace && aligned(workspace, 256) &&
       tile_path(views->feat_dtype, views->D, views->Hf, views->Wf, views->n_views) &&
       workspace_bytes >= aura::fuse_tile_workspace_bytes(N, B, views->n_views)) {
-    // AURA_FUSE_GATHER with the workspace of the matrix-core kernels: its status word still says "nothing to report"
-    const aura_status_t sc = hip_status(aura::launch_calibration_fill(
-        static_cast<char*>(workspace) + aura::fuse_tile_status_offset(N, B), 16, 0u, st));
-    if (sc != AURA_OK) return sc;
+    // the gather kernel with the workspace of the matrix-core kernels: its status word still says "nothing to report"
+    clear_status = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + aura::fuse_tile_status_offset(N, B));
   }
   return for_each_table(objs, [&](const aura::ObjTable& tab, int n, int max_pts, int obj_base) {
     tws.obj_base = obj_base;
     return aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only, tile ? &tws : nullptr,
                                       tab, n, max_pts, st, nullptr, nullptr, 0, sel_mask, mask_pitch,
-                                      (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0);
+                                      (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0, nullptr, nullptr, clear_status);
   });
 }
 
@@ -432,11 +445,10 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
                                      const float* y, int32_t P, float* fused, int32_t* count, uint8_t* vis,
                                      int32_t vis_pitch, float* scores, float* prop, int32_t* label, FuseScoresLayout lay,
                                      char* wbase, hipStream_t st) {
-  if ((params->flags & AURA_FUSE_GATHER) && lay.tile) {
+  unsigned* clear_status = nullptr;
+  if (lay.tile && ((params->flags & AURA_FUSE_GATHER) || (few_points(views, params, N, B) && (fused || N <= lay.chunk_pts)))) {
     // the matrix-core kernels stay out: the status word in their part of the workspace still says "nothing to report"
-    const aura_status_t sc = hip_status(aura::launch_calibration_fill(
-        wbase + lay.fuse_off + aura::fuse_tile_status_offset(N, B), 16, 0u, st));
-    if (sc != AURA_OK) return sc;
+    clear_status = reinterpret_cast<unsigned*>(wbase + lay.fuse_off + aura::fuse_tile_status_offset(N, B));
     lay.tile = lay.by_cells = false;
   }
   const aura::VisArgs va = vis_args(views, params);
@@ -474,7 +486,7 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
       float* rows = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(chunk) - (uintptr_t)c0 * (uintptr_t)views->D * sizeof(float));
       s = for_each_table(part, [&](const aura::ObjTable& tab, int n, int max_pts, int) {
         return aura::launch_fuse_features(va, fa, xyz, rows, count, params->norm_eps, mean_only, nullptr, tab, n, max_pts, st,
-                                          nullptr, vis, vis_pitch);
+                                          nullptr, vis, vis_pitch, nullptr, 0, 0, nullptr, nullptr, clear_status);
       });
       if (s != AURA_OK) return s;
       s = hip_status(aura::launch_material_scores(chunk, c1 - c0, views->D, t32, K, y, P, params->temperature,
@@ -499,8 +511,8 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
     bool scored = false;   // the one-kernel form of the fusion scores its tiles itself where it can
     hipError_t e = aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only,
                                               lay.tile ? &tws : nullptr, tab, n, max_pts, st, lay.by_cells ? sws.factor : nullptr,
-                                   vis, vis_pitch, nullptr, 0, (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0,
-                                   lay.by_cells ? &want : nullptr, &scored);
+                                              vis, vis_pitch, nullptr, 0, (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0,
+                                              lay.by_cells ? &want : nullptr, &scored, clear_status);
     if (e != hipSuccess || !lay.by_cells || scored) return e;
     return aura::launch_tile_scores(fa, tws, sws, K, y, P, params->temperature, unseen_zero, scores, prop, label, tab, n,
                                     max_pts, st);

@@ -35,6 +35,8 @@ struct FuseArgs {
   const uint8_t* in_mask;   // may be nullptr: [N][in_mask_pitch], the views kept for each point (Sec. 3.2.2); given, it
   int in_mask_pitch;        // takes the place of the depth test (the caller passes no depth maps then)
   int two_kernels;          // tile path: keep the prepare and the product kernel apart (AURA_FUSE_TWO_KERNELS)
+  unsigned* clear_status;   // gather kernel, may be nullptr: four words to clear (the status words of a workspace it does
+                            // not use otherwise)
   TileScoring scoring;      // tile path: scores, labels and properties wanted along with the fused rows (G == nullptr: no)
 };
 

@@ -111,6 +111,7 @@ struct ViewTaps {
 // rows of two views in flight together take 12 us.
 template <int DT, int VEC, int PASSES, bool GENERIC>
 __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, int pts_per_wave, ObjTable tab) {
+  if (a.clear_status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 4) a.clear_status[threadIdx.x] = 0u;
   const ObjRange ob = tab.o[blockIdx.y];
   const int pts_per_block = kFuseWaves * pts_per_wave;
   const int nblk = (ob.n_pts + pts_per_block - 1) / pts_per_block;
@@ -312,11 +313,11 @@ hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const 
                                 int* out_count, float norm_eps, int mean_only, const TileWs* tile_ws,
                                 const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream, float* out_factor,
                                 uint8_t* out_vis, int vis_pitch, const uint8_t* in_mask, int in_mask_pitch, int two_kernels,
-                                const TileScoring* scoring, bool* scored) {
+                                const TileScoring* scoring, bool* scored, unsigned* clear_status) {
   if (scored) *scored = false;
   if (n_obj == 0 || max_pts == 0) return hipSuccess;
   FuseArgs a{vis, feat, xyz, fused, out_count, norm_eps, mean_only, tile_ws ? out_factor : nullptr,
-             out_vis, vis_pitch, in_mask, in_mask_pitch, two_kernels,
+             out_vis, vis_pitch, in_mask, in_mask_pitch, two_kernels, clear_status,
              tile_ws && scoring ? *scoring : TileScoring{}};
   if (tile_ws) return launch_fuse_tile(a, *tile_ws, tab, n_obj, max_pts, stream, scored);
   switch (feat.dtype) {

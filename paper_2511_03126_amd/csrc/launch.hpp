@@ -33,7 +33,8 @@ hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const 
                                 const uint8_t* in_mask = nullptr, int in_mask_pitch = 0,     // see FuseArgs::in_mask
                                 int two_kernels = 0,                                        // see FuseArgs::two_kernels
                                 const TileScoring* scoring = nullptr,    // tile path only: see FuseArgs::scoring
-                                bool* scored = nullptr);                 // whether the launch did what `scoring` asks for
+                                bool* scored = nullptr,                  // whether the launch did what `scoring` asks for
+                                unsigned* clear_status = nullptr);       // gather kernel only: see FuseArgs::clear_status
 
 // Sec. 3.2.2, view importance-based filtering (select_views.hip).
 constexpr int kSelectMaxK = 8;

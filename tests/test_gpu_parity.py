@@ -382,15 +382,15 @@ def test_unsorted_points_on_the_matrix_core_path(H, orc, name, kw):
 
 # Tiles without k-steps (points in no order): every fusion kernel that pushes and empties the lists - one to four product
 # waves, one and four producers, with the scoring wave, with the scoring kernel behind it, as two kernels - with a ragged
-# last tile, and several objects in one launch, most of whose workgroups look at the lists only if they pushed.
-@pytest.mark.parametrize("N,B,V,D,K,dtype", [(1_601, 1, 5, 256, 12, "f16"), (1_601, 1, 12, 512, 12, "bf16"),
-                                             (1_601, 1, 7, 512, 40, "f16"), (1_633, 1, 14, 768, 32, "f16"),
-                                             (1_601, 1, 14, 1024, 70, "bf16"), (901, 1, 3, 1024, 128, "f16"),
-                                             (33, 1, 6, 512, 5, "f16"), (3_301, 1, 12, 512, 32, "f16"),
-                                             (3_301, 1, 12, 512, 40, "bf16"), (2_101, 1, 7, 256, 128, "f16"),
-                                             (3_000, 20, 4, 512, 24, "f16")])
-def test_tiles_without_k_steps(H, orc, N, B, V, D, K, dtype):
-    kw = dict(overrides=dict(V=V, D=D, K=K, dtype=dtype, grid=16 if N > 2_000 else 32), order="random")
+# last tile, and several objects in one launch, most of whose workgroups look at the lists only if they pushed.  The sizes
+# are above those that take the gather kernel (64 M point-view-channels), or the cells are too small for that (64 x 64).
+@pytest.mark.parametrize("N,B,V,D,K,dtype,grid", [(1_601, 1, 4, 256, 12, "f16", 64), (16_501, 1, 4, 256, 128, "f16", 64),
+                                                  (10_601, 1, 12, 512, 32, "f16", 16), (10_601, 1, 12, 512, 40, "bf16", 24),
+                                                  (18_501, 1, 7, 512, 40, "f16", 16), (6_201, 1, 14, 768, 32, "f16", 16),
+                                                  (4_701, 1, 14, 1024, 70, "bf16", 16), (1_601, 1, 3, 1024, 128, "f16", 64),
+                                                  (33, 1, 4, 512, 5, "f16", 64), (3_000, 20, 4, 512, 24, "f16", 16)])
+def test_tiles_without_k_steps(H, orc, N, B, V, D, K, dtype, grid):
+    kw = dict(overrides=dict(V=V, D=D, K=K, dtype=dtype, grid=grid), order="random")
     s = make_scene("c1", n_points=N, **kw) if B == 1 else make_scene("c5", n_points=N, n_objects=B, **kw)
     ref = H.oracle_points(orc, s, flags=1)
     d = H.DeviceScene(s, flags=1)       # no depth test: every pair in an image counts, so the lists are long
@@ -402,6 +402,31 @@ def test_tiles_without_k_steps(H, orc, N, B, V, D, K, dtype):
     words = d.status_words(word=1)
     print("tiles", tiles, words, flush=True)
     assert all(0 < w <= tiles for w in words.values())
+
+
+@pytest.mark.parametrize("N,V,D,K,dtype,B", [(1, 1, 256, 3, "f16", 1), (2_001, 5, 512, 24, "bf16", 1), (8_300, 10, 768, 33, "f16", 1),
+                                             (700, 4, 1024, 100, "bf16", 5)])
+def test_few_points_take_the_gather_kernel(H, orc, N, V, D, K, dtype, B):
+    """Calls of up to 64 M point-view-channels: the bits of AURA_FUSE_GATHER in every output, the oracle's results (as the
+    matrix-core kernels give them too, asked for as two kernels), and status words that say nothing to report although
+    the workspace held something else."""
+    from paper_2511_03126_amd import binding
+    kw = dict(overrides=dict(V=V, D=D, K=K, dtype=dtype))
+    s = make_scene("c1", n_points=N, **kw) if B == 1 else make_scene("c5", n_points=N, n_objects=B, **kw)
+    ref = H.oracle_points(orc, s)
+    out = []
+    for flags in (0, binding.FUSE_GATHER, binding.FUSE_TWO_KERNELS):
+        d = H.DeviceScene(s, flags=flags)
+        for ws in (d.ws_fuse, d.ws_fuse_scores):
+            ws.fill_(0xA5)
+        for step in (d.step, d.step_combined, d.step_single_pass):
+            d.clear_outputs()
+            step()
+            out.append(d.results())
+            H.compare_points(out[-1], ref, s, no_fused=step == d.step_single_pass)
+        assert not any(d.status_words(word=1).values()) or flags == binding.FUSE_TWO_KERNELS
+    for here, gather in zip(out[:3], out[3:6]):
+        _same_bits(here, gather, ("vis", "count", "fused", "scores", "prop", "label", "mass", "n_used"))
 
 
 def test_flags_and_degenerate_inputs(H, orc):
