@@ -96,13 +96,13 @@ __global__ __launch_bounds__(256) void k_material_scores(ScoreArgs a) {
 }
 
 // The same contraction for whole macro steps and 16-byte aligned rows, software-pipelined: what step s + 1 needs - the
-// lane's 64 bytes of each of its RT rows and, with PRE_A, the split embeddings of the step (MT * 4 KiB, L2 hits) - is
+// lane's 64 bytes of each of its RT rows and the split embeddings of the step (MT * 4 KiB, L2 hits) - is
 // requested before the products of step s and kept in a second set of registers (the loop is unrolled by two, so
 // that nothing that is still on its way has to be copied).  The memory counter returns reads in order: the requests
 // for the next step are always the youngest, so waiting for this step's operands never waits for them.  Without the
 // pipeline a wave asked for a step only when it needed it, and the kernel reached 4.0 of the 5.3 TB/s that the same
 // read pattern reaches without arithmetic.  RT tiles of 32 points per wave share the embeddings of a step.
-template <int MT, int RT, bool PRE_A>
+template <int MT, int RT>
 __global__ __launch_bounds__(256) void k_material_scores_rt(ScoreArgs a) {
   __shared__ float ys[kMaxK * kMaxP];
   __shared__ __attribute__((aligned(16))) float s_stage[4][score_stage_floats<16>()];
@@ -175,16 +175,16 @@ __global__ __launch_bounds__(256) void k_material_scores_rt(ScoreArgs a) {
   Rows r0, r1;
   Emb e0, e1;
   load_rows(0, r0);
-  if constexpr (PRE_A) load_emb(0, e0);
+  load_emb(0, e0);
   for (int s = 0; s < a.steps; s += 2) {
     // step s from set 0 while step s + 1 arrives in set 1 (past the end: the last step again, read and not used)
-    if constexpr (PRE_A) load_emb(min(s + 1, last), e1); else load_emb(s, e0);
+    load_emb(min(s + 1, last), e1);
     load_rows(min(s + 1, last), r1);
     __builtin_amdgcn_sched_barrier(0);
     products(r0, e0);
     __builtin_amdgcn_sched_barrier(0);
     if (s + 1 < a.steps) {   // uniform
-      if constexpr (PRE_A) load_emb(min(s + 2, last), e0); else load_emb(s + 1, e1);
+      load_emb(min(s + 2, last), e0);
       load_rows(min(s + 2, last), r0);
       __builtin_amdgcn_sched_barrier(0);
       products(r1, e1);
@@ -294,6 +294,101 @@ __global__ __launch_bounds__(kLdsWaves* kWave) void k_material_scores_lds(ScoreA
   }
 }
 
+// The same with the split embeddings of a step (MT * 4 KiB) passed through LDS, double buffered, once per workgroup of four
+// waves and 128 points (whole macro steps, 16-byte aligned rows).  Read from L2 by every wave they are as many bytes as the
+// rows with 32 materials and four times as many with 128, and set the time (300 007 rows of 1024 channels, 100 materials:
+// 501 us, 393 us here; 1 677 001 rows, 128 materials: 2553 and 1966 us = 3.9 TB/s; 1 M rows of 768 channels, 64 materials:
+// 876 and 752 us).  Bound by the row stream from HBM; the products
+// of a step (24 matrix-core instructions of 32 cycles per wave) run beside it.  A step: the next block, requested a step ago,
+// goes to LDS, the block after it and the rows of the step after next are requested, then the products; one barrier.
+template <int MT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_material_scores_wide(ScoreArgs a) {
+  constexpr int kBlock = MT * 2 * 2 * kWave;   // 16-byte operand slots of a step
+  constexpr int kCopies = kBlock / 256;        // per thread
+  __shared__ float ys[kMaxK * kMaxP];
+  __shared__ __attribute__((aligned(16))) bf16x8 s_a[2][kBlock];
+  __shared__ __attribute__((aligned(16))) float s_stage[4][score_stage_floats<16>()];
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 32;
+  if (a.prop) {
+    for (int t = tid; t < a.K * a.P; t += 256) ys[t] = a.y[t];
+  }
+  const long long n0 = ((long long)blockIdx.x * 4 + wave) * kTileN;   // a wave beyond the last row takes part in the copies
+  const long long n = min(n0 + (lane & 31), a.N - 1);
+  const float* __restrict__ row = a.fused + n * a.D + g * 16;
+  const int last = a.steps - 1;                // requests past the end repeat the last step (read, not used)
+
+  f32x16 acc[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
+  struct Rows { f32x4 v[4]; };
+  bf16x8 copy[kCopies];
+  auto load_rows = [&](int s, Rows& r) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r.v[q] = *reinterpret_cast<const f32x4*>(row + min(s, last) * kStepK + 4 * q);
+  };
+  auto load_block = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) copy[u] = a.a_split[(long long)min(s, last) * kBlock + u * 256 + tid];
+  };
+  auto step = [&](int s, Rows& r) {
+    bf16x8* next = s_a[(s + 1) & 1];
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) next[u * 256 + tid] = copy[u];
+    load_block(s + 2);
+    bf16x8 bh[2], bl[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float x = r.v[2 * j + (c >> 2)][c & 3];
+        const __bf16 h = (__bf16)x;
+        bh[j][c] = h;
+        bl[j][c] = (__bf16)(x - (float)h);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    load_rows(s + 2, r);
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16x8* cur = s_a[s & 1] + lane;
+    // two tiles at a time: their accumulators take turns, so that no product waits for the one before it
+    constexpr int kPair = MT > 1 ? 2 : 1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int m0 = 0; m0 < MT; m0 += kPair) {
+        bf16x8 ah[kPair], al[kPair];
+#pragma unroll
+        for (int i = 0; i < kPair; ++i) {
+          ah[i] = cur[((m0 + i) * 2 + j) * 2 * kWave];
+          al[i] = cur[(((m0 + i) * 2 + j) * 2 + 1) * kWave];
+        }
+#pragma unroll
+        for (int i = 0; i < kPair; ++i) acc[m0 + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc[m0 + i], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kPair; ++i) acc[m0 + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc[m0 + i], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kPair; ++i) acc[m0 + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bh[j], acc[m0 + i], 0, 0, 0);
+      }
+    __syncthreads();   // the next step's block is in place, and nobody reads this step's any more
+  };
+  Rows r0, r1;
+  load_block(0);
+#pragma unroll
+  for (int u = 0; u < kCopies; ++u) s_a[0][u * 256 + tid] = copy[u];
+  load_block(1);
+  load_rows(0, r0);
+  load_rows(1, r1);
+  __syncthreads();
+  for (int s = 0; s < a.steps; s += 2) {   // uniform over the workgroup
+    step(s, r0);
+    if (s + 1 < a.steps) step(s + 1, r1);
+  }
+  if (n0 >= a.N) return;
+  finish_scores_staged<MT, 16>(acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
+                               a.prop, a.label, a.unseen_zero != 0, s_stage[wave]);
+}
+
 size_t split_embeddings_bytes(int D, int MT) {
   return (size_t)((D + kStepK - 1) / kStepK) * MT * 2 * 2 * kWave * 8 * sizeof(__bf16);
 }
@@ -336,15 +431,8 @@ hipError_t launch_widen_embeddings(const void* src, int dtype, long long n, floa
   return hipGetLastError();
 }
 
-#ifndef AURA_SCORES_RT
-#define AURA_SCORES_RT 1
-#endif
-
 template <int MT>
 static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream) {
-  // embeddings of the next step in registers where they are few (up to 64 materials)
-  constexpr int RT = MT == 1 ? AURA_SCORES_RT : 1;
-  constexpr bool PRE_A = MT <= 2;
   if constexpr (MT <= 2) {
     if (aligned && a.D % kStepK == 0 && a.steps * MT <= kLdsSlots) {
       constexpr int kWaves = MT == 1 ? 16 : 8;
@@ -359,11 +447,22 @@ static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream
       }
     }
   }
-  if (aligned && a.D % kStepK == 0) {
-    const long long per_group = 4ll * kTileN * RT;
-    hipLaunchKernelGGL((k_material_scores_rt<MT, RT, PRE_A>), dim3((unsigned)((a.N + per_group - 1) / per_group)), dim3(256),
-                       0, stream, a);
-    return hipGetLastError();
+  // Embeddings through LDS (times in us, through L2 / through LDS): 128 materials always (100 000 rows of 768 channels 169 / 141,
+  // 2001 rows of 384 31 / 29); up to 64 from 65 536 rows on (100 000 x 512, 64 materials 65 / 58; 200 000 x 768, 32 materials
+  // 156 / 144), below that the copies and barriers of a call of one workgroup per compute unit or less are not hidden by
+  // others (20 000 x 512, 12 materials 18.0 / 20.3).
+  if (MT == 4 || a.N >= 65536) {
+    if (aligned && a.D % kStepK == 0) {
+      hipLaunchKernelGGL((k_material_scores_wide<MT>), dim3((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), dim3(256), 0, stream, a);
+      return hipGetLastError();
+    }
+  }
+  // few rows of up to 64 materials: the embeddings of the next step in registers
+  if constexpr (MT <= 2) {
+    if (aligned && a.D % kStepK == 0) {
+      hipLaunchKernelGGL((k_material_scores_rt<MT, 1>), dim3((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), dim3(256), 0, stream, a);
+      return hipGetLastError();
+    }
   }
   dim3 grid((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), block(256);
   if (aligned)

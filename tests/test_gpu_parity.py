@@ -340,6 +340,30 @@ def test_scores_kernel_alone_on_random_unit_rows(H, orc):
         assert es <= 1e-5 and ep <= 1e-4 and not bad.any()
 
 
+# The kernel that passes the embeddings through LDS: waves and workgroups without rows, one step and odd numbers of steps,
+# material counts that do and do not fill the last tile, and up to 64 materials from 65 536 rows on.  The bound on a score:
+# three of the four partial products of two-term operands, 2^-16 relative per channel, unit rows and embeddings.
+@pytest.mark.parametrize("N,D,K", [(1, 32, 65), (127, 64, 100), (129, 96, 128), (4_097, 384, 97), (65_536, 32, 5),
+                                   (65_537, 544, 33), (66_001, 160, 64)])
+def test_scores_with_embeddings_in_lds(H, orc, N, D, K):
+    import paper_2511_03126_amd as aura
+    from paper_2511_03126_amd import binding
+    rng = np.random.default_rng(N + D + K)
+    f, t = rng.standard_normal((N, D)).astype(np.float32), rng.standard_normal((K, D)).astype(np.float32)
+    f /= np.linalg.norm(f, axis=1, keepdims=True)
+    t /= np.linalg.norm(t, axis=1, keepdims=True)
+    y = rng.uniform(100, 8000, (K, 2)).astype(np.float32)
+    scores, prop = torch.full((N, K), np.nan, device="cuda:0"), torch.full((N, 2), np.nan, device="cuda:0")
+    label = torch.full((N,), -7, dtype=torch.int32, device="cuda:0")
+    ws = torch.empty(aura.workspace_bytes(binding.CALL_MATERIAL_SCORES, D=D, K=K), dtype=torch.uint8, device="cuda:0")
+    aura.material_scores(*(torch.from_numpy(x).to("cuda:0") for x in (f, t, y)), aura.Params(temperature=0.1), scores, prop,
+                         label, ws)
+    ref = orc.material_scores(f.astype(np.float64), t, y, T=0.1)
+    assert np.abs(scores.cpu().numpy() - ref["scores"]).max() <= 2.0 ** -16
+    assert (np.abs(prop.cpu().numpy() - ref["prop"]) / np.abs(y).max(0)).max() <= 1e-4
+    assert not ((label.cpu().numpy() != ref["label"]) & (ref["margin"] > 2.0 ** -15)).any()
+
+
 @pytest.mark.parametrize("name,kw", [("c2", dict(n_points=6000)),
                                      ("c3", dict(n_points=6000, overrides=dict(V=5, HW=112, grid=112))),
                                      ("c5", dict(n_points=3000, n_objects=3))])
