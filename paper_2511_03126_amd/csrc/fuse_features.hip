@@ -41,12 +41,13 @@ __device__ __forceinline__ void widen_pair(uint32_t w, int dtype_is_bf16, float&
   }
 }
 
-// Reads VEC consecutive elements starting at element index e of `base` and widens them to fp32.
+// Reads VEC consecutive elements `off` bytes behind `base` (wave-uniform; an unsigned 32-bit offset per lane keeps the
+// 64-bit part of the address on the scalar unit) and widens them to fp32.
 // DT: 0 fp32, 1 bf16, 2 fp16.  The address is VEC * sizeof(element) aligned by construction.
 template <int DT, int VEC>
-__device__ __forceinline__ void load_widen(const void* __restrict__ base, long long e, float (&out)[VEC]) {
+__device__ __forceinline__ void load_widen(const char* __restrict__ base, uint32_t off, float (&out)[VEC]) {
   if constexpr (DT == 0) {
-    const float* p = static_cast<const float*>(base) + e;
+    const float* p = reinterpret_cast<const float*>(base + off);
     if constexpr (VEC == 4) {
       f32x4 v = *reinterpret_cast<const f32x4*>(p);
       out[0] = v[0]; out[1] = v[1]; out[2] = v[2]; out[3] = v[3];
@@ -58,7 +59,7 @@ __device__ __forceinline__ void load_widen(const void* __restrict__ base, long l
       out[0] = *p;
     }
   } else {
-    const uint16_t* p = static_cast<const uint16_t*>(base) + e;
+    const uint16_t* p = reinterpret_cast<const uint16_t*>(base + off);
     if constexpr (VEC == 8) {
       u32x4 v = *reinterpret_cast<const u32x4*>(p);
 #pragma unroll
@@ -101,15 +102,20 @@ struct ViewTaps {
 };
 
 // DT element type, VEC elements per lane per load, PASSES loads per cell row.
-// GENERIC == false: D <= 64 * VEC * PASSES and D a multiple of VEC: the whole row lives in registers, lanes beyond D
-//                   repeat the row's last VEC channels and drop out of the sums and the stores.
-// GENERIC == true : any D; channels are processed 64 * VEC * PASSES at a time (outer loop), the
-//                   unnormalised mean is stored first and rescaled in a second sweep.
+// EXACT:   D == 64 * VEC * PASSES, the whole row lives in registers.
+// MASKED:  D below that and a multiple of VEC: lanes beyond D repeat the row's last VEC channels and drop out of the sums
+//          and the stores.
+// GENERIC: any D; channels are processed 64 * VEC * PASSES at a time (outer loop), the unnormalised mean is stored first
+//          and rescaled in a second sweep.
+enum class RowWidth { EXACT, MASKED, GENERIC };
+
 // A wave takes pts_per_wave consecutive points, one after the other.  What bounds a call of a few thousand points is that
 // chain (point -> projections -> depth texels -> cell rows -> norm): with 8 points per wave and one channel per lane and
 // load, 2001 points of 5 views and 384 channels took 97 us on 63 workgroups; one point per wave, 16-byte loads and the
-// rows of two views in flight together take 12 us.
-template <int DT, int VEC, int PASSES, bool GENERIC>
+// rows of two views in flight together bring the call's other stages and it from 122 to 43 us.
+// PAIRS: two views at a time.  For calls that fill the chip many times over it is one: the second view's rows cost registers
+// and with them waves (317 202 points, 6 views of 512 fp32 channels: 434 us staged with pairs, 415 without).
+template <int DT, int VEC, int PASSES, RowWidth WIDTH, bool PAIRS>
 __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, int pts_per_wave, ObjTable tab) {
   if (a.clear_status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 4) a.clear_status[threadIdx.x] = 0u;
   const ObjRange ob = tab.o[blockIdx.y];
@@ -119,9 +125,15 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
   const int blk = xcd_contiguous(blockIdx.x, nblk);
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   constexpr int CH = kWave * VEC * PASSES;
-  const int D = a.feat.D, Hf = a.feat.Hf, Wf = a.feat.Wf;
+  constexpr bool GENERIC = WIDTH == RowWidth::GENERIC, EXACT = WIDTH == RowWidth::EXACT;
+  static_assert(!GENERIC || (VEC == 1 && PASSES == 1), "one channel per lane and sweep");
+  const int D = EXACT ? CH : a.feat.D, Hf = a.feat.Hf, Wf = a.feat.Wf;
   const long long view_elems = (long long)Hf * Wf * D;
-  const long long elt = DT == 0 ? 4 : 2;
+  constexpr long long elt = DT == 0 ? 4 : 2;
+  uint32_t off[PASSES];   // byte offset of the lane's channels within a row
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p)
+    off[p] = (uint32_t)(GENERIC ? lane : (EXACT ? p * kWave * VEC + lane * VEC : min(p * kWave * VEC + lane * VEC, D - VEC))) * (uint32_t)elt;
 
   for (int k = 0; k < pts_per_wave; ++k) {
     const int li = blk * pts_per_block + wave * pts_per_wave + k;
@@ -159,7 +171,7 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
         if (a.out_vis && vb + lane < a.vis_pitch && cb == 0) a.out_vis[i * a.vis_pitch + vb + lane] = seen ? 1 : 0;
         unsigned long long m = __ballot(seen);
         cnt += __popcll(m);
-        // phase 2: wave-uniform loop over the visible views, two at a time so that the rows of both are in flight
+        // phase 2: wave-uniform loop over the visible views, with PAIRS two at a time so that the rows of both are in flight
         auto taps_of = [&](int src) {
           const int sx0 = __builtin_amdgcn_readlane(x0, src), sy0 = __builtin_amdgcn_readlane(y0, src);
           const float sax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ax), src));
@@ -167,17 +179,14 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
           const int sx1 = sx0 + 1 < Wf ? sx0 + 1 : Wf - 1, sy1 = sy0 + 1 < Hf ? sy0 + 1 : Hf - 1;
           const char* vbase = static_cast<const char*>(a.feat.feat) +
                               (long long)(ob.view_begin + vb + src) * view_elems * elt;
-          const long long row_bytes = (long long)D * elt;
+          // (32 x 32 bit products: a 64-bit one would leave the scalar unit, and the row addresses with it)
+          auto row_of = [&](int y, int x) { return vbase + (long long)(y * Wf + x) * D * (DT == 0 ? 4 : 2); };
           ViewTaps t;
           t.w[0] = (1.0f - sax) * (1.0f - say); t.w[1] = sax * (1.0f - say);
           t.w[2] = (1.0f - sax) * say;          t.w[3] = sax * say;
-          t.row[0] = vbase + (sy0 * Wf + sx0) * row_bytes; t.row[1] = vbase + (sy0 * Wf + sx1) * row_bytes;
-          t.row[2] = vbase + (sy1 * Wf + sx0) * row_bytes; t.row[3] = vbase + (sy1 * Wf + sx1) * row_bytes;
+          t.row[0] = row_of(sy0, sx0); t.row[1] = row_of(sy0, sx1);
+          t.row[2] = row_of(sy1, sx0); t.row[3] = row_of(sy1, sx1);
           return t;
-        };
-        auto channel = [&](int p) {
-          const int ch = cb + p * kWave * VEC + lane * VEC;
-          return GENERIC ? ch : min(ch, D - VEC);
         };
         auto blend = [&](auto n_views_c) {
           constexpr int NV = decltype(n_views_c)::value;
@@ -189,13 +198,14 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
           }
 #pragma unroll
           for (int p = 0; p < PASSES; ++p) {
-            const int ch = channel(p);
-            if (GENERIC && ch >= D) continue;
+            if (GENERIC && cb + lane >= D) continue;
+            uint32_t o = EXACT ? off[0] : off[p] + (GENERIC ? (uint32_t)cb * (uint32_t)elt : 0u);
+            asm("" : "+v"(o));   // stays a 32-bit offset to a scalar base (widened outside the loop it becomes 64-bit vector adds)
             float v[NV][4][VEC];
 #pragma unroll
             for (int q = 0; q < NV; ++q)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) load_widen<DT, VEC>(t[q].row[c], ch, v[q][c]);
+              for (int c = 0; c < 4; ++c) load_widen<DT, VEC>(t[q].row[c] + (EXACT ? p * kWave * VEC * (int)elt : 0), o, v[q][c]);
 #pragma unroll
             for (int q = 0; q < NV; ++q)
 #pragma unroll
@@ -207,15 +217,17 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
               }
           }
         };
-        while (m & (m - 1)) blend(std::integral_constant<int, 2>{});
-        if (m) blend(std::integral_constant<int, 1>{});
+        if constexpr (PAIRS) {
+          while (m & (m - 1)) blend(std::integral_constant<int, 2>{});
+        }
+        while (m) blend(std::integral_constant<int, 1>{});
       }
 
       // mean over the visible views (Eq. 2); a point nobody sees keeps zeros
       const float inv = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
 #pragma unroll
       for (int p = 0; p < PASSES; ++p) {
-        const bool mine = GENERIC || p * kWave * VEC + lane * VEC < D;
+        const bool mine = GENERIC || EXACT || p * kWave * VEC + lane * VEC < D;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           acc[p][e] = mine ? acc[p][e] * inv : 0.0f;
@@ -233,7 +245,7 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
 #pragma unroll
           for (int e = 0; e < VEC; ++e) acc[p][e] *= scale;
           const int ch = p * kWave * VEC + lane * VEC;
-          if (ch < D) store_stream<VEC>(out_row + ch, acc[p]);
+          if (EXACT || ch < D) store_stream<VEC>(out_row + ch, acc[p]);
         }
       } else {
 #pragma unroll
@@ -261,8 +273,8 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
   }
 }
 
-template <int DT, int VEC, int PASSES, bool GENERIC>
-static hipError_t launch_one(const FuseArgs& a, const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream) {
+template <int DT, int VEC, int PASSES, RowWidth WIDTH>
+static hipError_t launch_width(const FuseArgs& a, const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream) {
   // points per wave: one until the launch has 32 waves per compute unit, up to eight beyond
   long long pts = 0;
   for (int t = 0; t < n_obj; ++t) pts += tab.o[t].n_pts;
@@ -271,10 +283,19 @@ static hipError_t launch_one(const FuseArgs& a, const ObjTable& tab, int n_obj, 
   dim3 grid((unsigned)(((long long)max_pts + pts_per_block - 1) / pts_per_block), n_obj), block(kFuseWaves * kWave);
   const TimingRequest timed = take_timing_request();
   if (timed.start) (void)hipEventRecord(timed.start, stream);
-  hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, GENERIC>), grid, block, 0, stream, a, pts_per_wave, tab);
+  if (pts_per_wave < kFusePtsPerWave)
+    hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, WIDTH, true>), grid, block, 0, stream, a, pts_per_wave, tab);
+  else
+    hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, WIDTH, false>), grid, block, 0, stream, a, pts_per_wave, tab);
   const hipError_t e = hipGetLastError();
   if (timed.stop) (void)hipEventRecord(timed.stop, stream);
   return e;
+}
+
+template <int DT, int VEC, int PASSES>
+static hipError_t launch_one(const FuseArgs& a, const ObjTable& tab, int n_obj, int max_pts, hipStream_t stream) {
+  return a.feat.D == kWave * VEC * PASSES ? launch_width<DT, VEC, PASSES, RowWidth::EXACT>(a, tab, n_obj, max_pts, stream)
+                                          : launch_width<DT, VEC, PASSES, RowWidth::MASKED>(a, tab, n_obj, max_pts, stream);
 }
 
 // The row in registers for every D that is a whole number of 16-byte pieces (8 bytes for 16-bit rows of up to 256
@@ -285,28 +306,28 @@ static hipError_t dispatch_d(const FuseArgs& a, const ObjTable& tab, int n_obj, 
   if constexpr (DT == 0) {
     if (D % 4 == 0) {
       switch ((D + 255) / 256) {
-        case 1: return launch_one<DT, 4, 1, false>(a, tab, n_obj, max_pts, stream);
-        case 2: return launch_one<DT, 4, 2, false>(a, tab, n_obj, max_pts, stream);
-        case 3: return launch_one<DT, 4, 3, false>(a, tab, n_obj, max_pts, stream);
-        case 4: return launch_one<DT, 4, 4, false>(a, tab, n_obj, max_pts, stream);
-        case 5: case 6: return launch_one<DT, 4, 6, false>(a, tab, n_obj, max_pts, stream);
+        case 1: return launch_one<DT, 4, 1>(a, tab, n_obj, max_pts, stream);
+        case 2: return launch_one<DT, 4, 2>(a, tab, n_obj, max_pts, stream);
+        case 3: return launch_one<DT, 4, 3>(a, tab, n_obj, max_pts, stream);
+        case 4: return launch_one<DT, 4, 4>(a, tab, n_obj, max_pts, stream);
+        case 5: case 6: return launch_one<DT, 4, 6>(a, tab, n_obj, max_pts, stream);
         default: break;
       }
     }
   } else {
-    if (D % 4 == 0 && D <= 256) return launch_one<DT, 4, 1, false>(a, tab, n_obj, max_pts, stream);
-    if (D == 768) return launch_one<DT, 4, 3, false>(a, tab, n_obj, max_pts, stream);
+    if (D % 4 == 0 && D <= 256) return launch_one<DT, 4, 1>(a, tab, n_obj, max_pts, stream);
+    if (D == 768) return launch_one<DT, 4, 3>(a, tab, n_obj, max_pts, stream);
     if (D % 8 == 0) {
       switch ((D + 511) / 512) {
-        case 1: return launch_one<DT, 8, 1, false>(a, tab, n_obj, max_pts, stream);
-        case 2: return launch_one<DT, 8, 2, false>(a, tab, n_obj, max_pts, stream);
-        case 3: return launch_one<DT, 8, 3, false>(a, tab, n_obj, max_pts, stream);
-        case 4: return launch_one<DT, 8, 4, false>(a, tab, n_obj, max_pts, stream);
+        case 1: return launch_one<DT, 8, 1>(a, tab, n_obj, max_pts, stream);
+        case 2: return launch_one<DT, 8, 2>(a, tab, n_obj, max_pts, stream);
+        case 3: return launch_one<DT, 8, 3>(a, tab, n_obj, max_pts, stream);
+        case 4: return launch_one<DT, 8, 4>(a, tab, n_obj, max_pts, stream);
         default: break;
       }
     }
   }
-  return launch_one<DT, 1, 1, true>(a, tab, n_obj, max_pts, stream);
+  return launch_width<DT, 1, 1, RowWidth::GENERIC>(a, tab, n_obj, max_pts, stream);
 }
 
 hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const float* xyz, float* fused,
