@@ -502,7 +502,7 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
   if (lay.tile) tws = aura::fuse_tile_workspace(wbase + lay.fuse_off, N, B, views->n_views);
   if (lay.by_cells) {
     sws = aura::tile_scores_workspace(wbase + lay.cells_off, N, n_cells, K);
-    s = hip_status(aura::launch_cell_scores(fa, n_cells, t32, K, sws, st));
+    s = hip_status(aura::launch_cell_scores(fa, n_cells, t32, K, sws, &tws, B, st));
     if (s != AURA_OK) return s;
   }
   s = for_each_table(objs, [&](const aura::ObjTable& tab, int n, int max_pts, int obj_base) {

@@ -75,6 +75,7 @@ struct TileWs {
   TileStep* steps;      // [n_tiles][quota]: every tile owns a fixed run of k-steps
   int quota;
   int obj_base;         // index of the launch's first object within the call
+  bool cleared;         // an earlier kernel of the call has cleared all counters and status words
 };
 
 // Byte offset of a cell row as stored in a k-step (a multiple of 512 * units, units = D / 256 in 1..6) -> cell index.
@@ -91,6 +92,7 @@ __device__ __forceinline__ uint32_t cell_index(uint32_t off, uint32_t units) {
 
 bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes);
 size_t fuse_tile_workspace_bytes(long long N, int B, int n_views);
+int fuse_tile_clear_words(int B);   // from TileWs::counters on: the counters and the status words of a call of B objects
 size_t fuse_tile_status_offset(long long N, int B);   // byte offset of the status word within that workspace
 // Splits a workspace of fuse_tile_workspace_bytes(N, B, n_views) bytes into its parts.
 TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views);

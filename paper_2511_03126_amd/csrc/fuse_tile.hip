@@ -1852,8 +1852,11 @@ TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views) {
   ws.steps = reinterpret_cast<TileStep*>(base);
   ws.quota = steps_quota(B, n_views);
   ws.obj_base = 0;
+  ws.cleared = false;
   return ws;
 }
+
+int fuse_tile_clear_words(int B) { return (int)((round256((size_t)B * 8 * sizeof(unsigned)) + 256) / sizeof(unsigned)); }
 
 size_t fuse_tile_status_offset(long long N, int B) {
   return round256((size_t)tile_count_bound(N, B) * sizeof(TileHdr)) + round256((size_t)B * 8 * sizeof(unsigned));
@@ -1907,8 +1910,9 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   const int np = one_kernel_producers(a, max_views, S);
   if (np > 0) {
     // (the status word of the call is cleared along with the counters of its first launch)
-    hipLaunchKernelGGL(k_clear_counters, dim3((n_obj * kXcd + 63) / 64), dim3(64), 0, stream, pa.counters, n_obj * kXcd,
-                       ws.obj_base == 0 ? ws.status : nullptr);
+    if (!ws.cleared)
+      hipLaunchKernelGGL(k_clear_counters, dim3((n_obj * kXcd + 63) / 64), dim3(64), 0, stream, pa.counters, n_obj * kXcd,
+                         ws.obj_base == 0 ? ws.status : nullptr);
     // with one producer wave two workgroups fit a compute unit (four where the workgroup has just the two waves), with
     // four one; several objects in one launch share the machine
     const bool scoring = scoring_wave_fits(a, np, S);
@@ -1921,7 +1925,9 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // while others have run out (64 objects of 100 000 points and 4 views: the workgroups' end times were spread over
     // the last quarter of the kernel; fusion call 2.79 -> 2.33 ms with 256 workgroups per object, the combined call,
     // whose workgroups also write the k-steps for the scoring kernel, 3.10 -> 2.94 ms with 64 and slower beyond).
-    const int per_object = n_obj > 1 ? ((keep || scoring) ? 64 : 256) : 0;
+    // At least eight tiles per workgroup beyond the resident ones (22 objects of 153 tiles, 2 views: 249 us with a workgroup
+    // per tile, 214 with 24 per object).
+    const int per_object = n_obj > 1 ? std::min((keep || scoring) ? 64 : 256, max_tiles / 8 / kXcd * kXcd) : 0;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * (S + np + (scoring ? 1 : 0)));
     const TimingRequest timed = take_timing_request();
@@ -1945,7 +1951,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     if (timed.stop) (void)hipEventRecord(timed.stop, stream);
     return e;
   }
-  if (ws.obj_base == 0) {   // the status words of the call (the prepare kernel clears its objects' ticket counters itself)
+  if (ws.obj_base == 0 && !ws.cleared) {   // the status words of the call (the prepare kernel clears its objects' ticket counters itself)
     hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(64), 0, stream, pa.counters, 0, ws.status);
     const hipError_t ec = hipGetLastError();
     if (ec != hipSuccess) return ec;

@@ -60,13 +60,20 @@ struct CellArgs {
   const float* temb;    // [K][D] fp32
   uint32_t* G;          // [n_cells][Kpad]: hi | lo << 16
   ts_u32x4* t_split;    // the text embeddings as matrix-core operands: [D / 16][Kpad / 32][hi, lo][64 lanes] x 16 bytes
+  uint32_t* clear;      // n_clear words that the first kernel of the call clears for the fusion kernel behind it: a launch
+  int n_clear;          // of its own costs about 4 us
 };
+
+__device__ __forceinline__ void clear_words(const CellArgs& a) {
+  for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < a.n_clear; w += gridDim.x * blockDim.x) a.clear[w] = 0u;
+}
 
 // The text embeddings split into two terms of the maps' 16-bit type, once per call, in the order in which the lanes of
 // k_cell_scores take them: lane (material n = l % 32, kg = l / 32) of slot (step s, tile mt) holds channels
 // 16 s + 8 kg .. + 7 of material 32 mt + n (zeros beyond K).
 template <int DT>
 __global__ __launch_bounds__(256) void k_split_for_cells(CellArgs a) {
+  clear_words(a);
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;   // one thread per (step, tile, lane)
   const int MT = a.Kpad / 32;
   if (t >= (long long)(a.D / 16) * MT * kWave) return;
@@ -164,6 +171,7 @@ __global__ __launch_bounds__(256) void k_cell_scores(CellArgs a) {
 // (16 384 cells: 12 us for this kernel alone, while the launch that builds the table costs 5 us by itself).
 template <int DT, int MT>
 __global__ __launch_bounds__(256) void k_cell_scores_small(CellArgs a) {
+  clear_words(a);
   __shared__ float s_part[3][MT][16][kWave];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const long long c0 = (long long)blockIdx.x * 32;
@@ -376,8 +384,10 @@ static hipError_t launch_cells(const CellArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_cell_scores(const FeatArgs& feat, long long n_cells, const float* temb, int K, const TileScoreWs& ws,
-                              hipStream_t stream) {
-  CellArgs a{static_cast<const char*>(feat.feat), n_cells, feat.D, K, ws.Kpad, temb, ws.G, static_cast<ts_u32x4*>(ws.t_split)};
+                              TileWs* tws, int B, hipStream_t stream) {
+  CellArgs a{static_cast<const char*>(feat.feat), n_cells, feat.D, K, ws.Kpad, temb, ws.G, static_cast<ts_u32x4*>(ws.t_split),
+             tws->counters, fuse_tile_clear_words(B)};
+  tws->cleared = true;
   return feat.dtype == 1 ? launch_cells<1>(a, stream) : launch_cells<2>(a, stream);
 }
 

@@ -17,9 +17,10 @@ struct TileScoreWs {
 size_t tile_scores_workspace_bytes(long long N, long long n_cells, int K);
 TileScoreWs tile_scores_workspace(void* workspace, long long N, long long n_cells, int K);
 
-// G = F . T^T over all n_cells cells (16-bit maps, D a multiple of 256).
+// G = F . T^T over all n_cells cells (16-bit maps, D a multiple of 256).  Also clears the counters and status words of `tws`
+// (a call of B objects) and says so in it.
 hipError_t launch_cell_scores(const FeatArgs& feat, long long n_cells, const float* temb, int K, const TileScoreWs& ws,
-                              hipStream_t stream);
+                              TileWs* tws, int B, hipStream_t stream);
 // Scores, labels and properties of the objects of one launch table from the k-steps in `tws` (after the
 // product kernel of the same table has run with ws.factor as its factor output).
 hipError_t launch_tile_scores(const FeatArgs& feat, const TileWs& tws, const TileScoreWs& ws,
