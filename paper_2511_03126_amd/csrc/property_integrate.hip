@@ -22,6 +22,7 @@ namespace aura {
 constexpr int kMassBlock = 256;
 constexpr int kMassPtsPerBlock = 512;    // slice of points summed by one workgroup
 constexpr int kVoxPerBlock = 2048;       // slice of voxels summed by one workgroup
+constexpr int kSmallSlices = 8;          // point mode: objects of up to this many slices in one launch
 constexpr int kAbsmaxPerGroup = 1024;    // up to this many slices of points every workgroup takes their maximum itself
 
 struct MassObjDev {
@@ -101,6 +102,66 @@ __global__ __launch_bounds__(kMassBlock) void k_mass_points(MassArgs a, MassTabl
   if (threadIdx.x == 0) {
     a.part_sum[ob.slice_begin + blockIdx.x] = s;
     a.part_used[ob.slice_begin + blockIdx.x] = used;
+  }
+}
+
+// Objects of up to kSmallSlices slices: one workgroup per object takes them all, with every read in flight at once, and
+// adds them up in the order of k_mass_points and k_mass_final, in one launch instead of two (2001 points, one call per
+// stage: 43.7 -> 39 us; a launch costs about 4 us whatever it does).
+__global__ __launch_bounds__(kMassBlock) void k_mass_points_small(MassArgs a, MassTable tab, float* mass, long long* n_used) {
+  constexpr int kPer = kMassPtsPerBlock / kMassBlock;
+  __shared__ double shd[kSmallSlices][kMassBlock / kWave];
+  __shared__ long long shl[kSmallSlices][kMassBlock / kWave];
+  const MassObjDev ob = tab.o[blockIdx.x];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  double s[kSmallSlices];
+  long long used[kSmallSlices];
+#pragma unroll
+  for (int j = 0; j < kSmallSlices; ++j) {
+    s[j] = 0.0;
+    used[j] = 0;
+    if (j >= ob.n_slices) continue;   // uniform
+    int cnt[kPer];
+    float pr[kPer], v[kPer];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const long long i = ob.pt_begin + min(j * kMassPtsPerBlock + e * kMassBlock + (int)threadIdx.x, ob.n_pts - 1);
+      cnt[e] = a.count ? a.count[i] : 1;
+      v[e] = a.vol ? a.vol[i] : a.vol_uniform;
+      pr[e] = a.prop[i * a.P + a.p_index];
+    }
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (j * kMassPtsPerBlock + e * kMassBlock + (int)threadIdx.x >= ob.n_pts || cnt[e] <= 0) continue;
+      s[j] += (double)(pr[e] * v[e]);
+      ++used[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallSlices; ++j) {
+    if (j >= ob.n_slices) break;   // uniform
+    s[j] = wave_sum(s[j]);
+    used[j] = wave_sum(used[j]);
+    if (lane == 0) {
+      shd[j][wave] = s[j];
+      shl[j][wave] = used[j];
+    }
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  double total = 0.0;
+  long long n = 0;
+  if (lane < ob.n_slices) {
+    for (int w = 0; w < kMassBlock / kWave; ++w) {
+      total += shd[lane][w];
+      n += shl[lane][w];
+    }
+  }
+  total = wave_sum(total);
+  n = wave_sum(n);
+  if (lane == 0) {
+    mass[a.obj_base + blockIdx.x] = (float)total;
+    if (n_used) n_used[a.obj_base + blockIdx.x] = n;
   }
 }
 
@@ -358,7 +419,9 @@ hipError_t launch_property_integrate(const float* prop, int P, int p_index, cons
   // objects go to the device in tables of kMaxObjPerLaunch; grid mode needs every object's maxima
   // and bins finished before any voxel is read, so the passes run over all tables one after another
   const int n_chunks = (B + kMaxObjPerLaunch - 1) / kMaxObjPerLaunch;
-  const int n_passes = G > 0 ? 4 : 2;
+  bool small = G == 0;
+  for (int b = 0; b < B; ++b) small = small && objs[b].n_pts <= kSmallSlices * kMassPtsPerBlock;
+  const int n_passes = G > 0 ? 4 : (small ? 1 : 2);
   for (int pass = 0; pass < n_passes; ++pass) {
     int pt_cursor = 0, vox_cursor = 0;
     if (G > 0 && pass == 1 && a.n_absmax > kAbsmaxPerGroup) {   // the slot behind the last per-slice maximum
@@ -389,7 +452,9 @@ hipError_t launch_property_integrate(const float* prop, int P, int p_index, cons
       a.obj_base = obj_base;
       dim3 block(kMassBlock);
       if (G == 0) {
-        if (pass == 0) {
+        if (small) {
+          hipLaunchKernelGGL(k_mass_points_small, dim3(n_obj), block, 0, stream, a, tab, mass, n_used);
+        } else if (pass == 0) {
           if (max_pt_slices > 0)
             hipLaunchKernelGGL(k_mass_points, dim3(max_pt_slices, n_obj), block, 0, stream, a, tab);
         } else {

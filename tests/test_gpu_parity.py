@@ -508,6 +508,28 @@ def test_point_volume_mode_with_per_point_volumes_and_objects(H, orc):
     assert np.allclose(mass.cpu().numpy(), ref["mass"], rtol=1e-5, atol=0)
 
 
+# Objects of up to eight slices of 512 points are summed in one launch, larger ones in two: both sides of that line, slices
+# that are just full, and a call that holds an object of each kind.  The sums of a slice and of an object are the same.
+@pytest.mark.parametrize("sizes", [(1,), (511, 512, 513, 0), (4_095,), (4_096, 1), (4_097,), (100, 9_000)])
+def test_point_volume_mode_of_small_objects(H, orc, sizes):
+    import paper_2511_03126_amd as aura
+    from paper_2511_03126_amd import binding
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    N, B = int(off[-1]), len(sizes)
+    rng = np.random.default_rng(N)
+    prop = rng.uniform(-5, 8000, (N, 3)).astype(np.float32)
+    vol = rng.uniform(1e-7, 3e-7, N).astype(np.float32)
+    count = rng.integers(0, 3, N).astype(np.int32)
+    dev = "cuda:0"
+    ws = torch.empty(aura.workspace_bytes(binding.CALL_PROPERTY_INTEGRATE, N=N, B=B, G=0), dtype=torch.uint8, device=dev)
+    mass = torch.full((B,), np.nan, device=dev); used = torch.full((B,), -7, dtype=torch.int64, device=dev)
+    aura.property_integrate(torch.from_numpy(prop).to(dev), mass, p_index=2, count=torch.from_numpy(count).to(dev),
+                            vol=torch.from_numpy(vol).to(dev), pt_offsets=off, n_used=used, workspace=ws)
+    ref = orc.property_integrate(prop.astype(np.float64), 2, count, vol=vol, pt_offsets=off)
+    assert np.array_equal(used.cpu().numpy(), ref["n_used"])
+    assert np.allclose(mass.cpu().numpy(), ref["mass"], rtol=1e-5, atol=0)
+
+
 @pytest.mark.parametrize("N", [300_000, 700_000])
 def test_grid_mode_with_few_and_with_many_slices_of_points(H, orc, N):
     """Grid mode of Sec. 3.4.2 on random points in three objects: the fixed-point scale comes from the largest |prop|
