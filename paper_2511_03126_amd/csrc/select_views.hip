@@ -26,6 +26,10 @@ struct SelArgs {
   int* n_sel;          // [N] or nullptr
 };
 
+// Views whose depth texels are requested together.  A sampled set is a few hundred points - one or two workgroups - so the
+// call is bound by each thread's chain of projection -> depth read per view (150 points, 16 views: 18.8 -> 16.9 us).
+constexpr int kSelectAhead = 8;
+
 __global__ __launch_bounds__(256) void k_select_views(SelArgs a, ObjTable tab) {
   const ObjRange ob = tab.o[blockIdx.y];
   const int li = blockIdx.x * blockDim.x + threadIdx.x;
@@ -41,36 +45,50 @@ __global__ __launch_bounds__(256) void k_select_views(SelArgs a, ObjTable tab) {
     best_v[t] = -1;
   }
   int seen = 0;
-  for (int j = 0; j < ob.n_views; ++j) {
-    const int v = ob.view_begin + j;
-    const float* __restrict__ c = a.vis.cam + (long long)v * 16;
-    const Proj p = project(c, x, y, z);
-    const float* dv = a.vis.depth ? a.vis.depth + (long long)v * a.vis.H * a.vis.W : nullptr;
-    if (!visible(a.vis, dv, p)) continue;
-    ++seen;
-    const float xc = __builtin_fmaf(c[2], z, __builtin_fmaf(c[1], y, __builtin_fmaf(c[0], x, c[9])));
-    const float yc = __builtin_fmaf(c[5], z, __builtin_fmaf(c[4], y, __builtin_fmaf(c[3], x, c[10])));
-    const float zc = p.z;
-    const float rnx = c[0] * nx + c[1] * ny + c[2] * nz;   // the normal in the camera frame
-    const float rny = c[3] * nx + c[4] * ny + c[5] * nz;
-    const float rnz = c[6] * nx + c[7] * ny + c[8] * nz;
-    const float len = sqrtf(xc * xc + yc * yc + zc * zc);
-    const float s_angle = fmaxf(0.0f, -(xc * rnx + yc * rny + zc * rnz) / len);
-    float s = s_angle / (1.0f + zc);
-    int sv = j;
-    // insert into the sorted list: a later view only moves ahead of an entry with a strictly smaller score; from
-    // there on every entry moves down one place
-    bool moving = false;
+  for (int j0 = 0; j0 < ob.n_views; j0 += kSelectAhead) {
+    Proj ps[kSelectAhead];
+    bool frs[kSelectAhead];
+    float deps[kSelectAhead];
 #pragma unroll
-    for (int t = 0; t < kSelectMaxK; ++t) {
-      moving = moving || s > best_s[t];
-      if (t < a.k && moving) {
-        const float ts = best_s[t];
-        const int tv = best_v[t];
-        best_s[t] = s;
-        best_v[t] = sv;
-        s = ts;
-        sv = tv;
+    for (int e = 0; e < kSelectAhead; ++e) {
+      const int v = ob.view_begin + min(j0 + e, ob.n_views - 1);   // (past the end: the last view again, unused)
+      ps[e] = project(a.vis.cam + (long long)v * 16, x, y, z);
+      frs[e] = in_frustum(a.vis, ps[e]);
+      deps[e] = 1.0f;
+      if (a.vis.depth) deps[e] = a.vis.depth[(long long)v * a.vis.H * a.vis.W + (frs[e] ? depth_texel(a.vis, ps[e]) : 0)];
+    }
+#pragma unroll
+    for (int e = 0; e < kSelectAhead; ++e) {
+      const int j = j0 + e;
+      if (j >= ob.n_views) break;   // uniform
+      const float* __restrict__ c = a.vis.cam + (long long)(ob.view_begin + j) * 16;
+      const Proj p = ps[e];
+      if (!(frs[e] && (a.vis.frustum_only || passes_depth(a.vis, p, deps[e])))) continue;
+      ++seen;
+      const float xc = __builtin_fmaf(c[2], z, __builtin_fmaf(c[1], y, __builtin_fmaf(c[0], x, c[9])));
+      const float yc = __builtin_fmaf(c[5], z, __builtin_fmaf(c[4], y, __builtin_fmaf(c[3], x, c[10])));
+      const float zc = p.z;
+      const float rnx = c[0] * nx + c[1] * ny + c[2] * nz;   // the normal in the camera frame
+      const float rny = c[3] * nx + c[4] * ny + c[5] * nz;
+      const float rnz = c[6] * nx + c[7] * ny + c[8] * nz;
+      const float len = sqrtf(xc * xc + yc * yc + zc * zc);
+      const float s_angle = fmaxf(0.0f, -(xc * rnx + yc * rny + zc * rnz) / len);
+      float s = s_angle / (1.0f + zc);
+      int sv = j;
+      // insert into the sorted list: a later view only moves ahead of an entry with a strictly smaller score; from
+      // there on every entry moves down one place
+      bool moving = false;
+#pragma unroll
+      for (int t = 0; t < kSelectMaxK; ++t) {
+        moving = moving || s > best_s[t];
+        if (t < a.k && moving) {
+          const float ts = best_s[t];
+          const int tv = best_v[t];
+          best_s[t] = s;
+          best_v[t] = sv;
+          s = ts;
+          sv = tv;
+        }
       }
     }
   }

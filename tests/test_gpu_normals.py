@@ -146,3 +146,28 @@ def test_neighbourhood_sizes_around_the_limit_of_the_one_sweep_path(orc, k):
         g_n, g_w = _gpu(shell, np.zeros((1, 3), np.float32), [[0, 0, -1]], 200)
         ref = orc.estimate_normals(shell, np.zeros((1, 3), np.float32), [[0, 0, -1]], 200)
         assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
+
+
+# The candidate list holds 8192 points: shells of points at one distance just inside and beyond it; and clouds on both sides
+# of the sizes at which the strided subset halves (8192 points, and k times the stride above 1500).
+@pytest.mark.parametrize("n,k", [(8_191, 200), (8_192, 200), (9_001, 200)])
+def test_candidate_list_full_and_overflowing(orc, n, k):
+    rng = np.random.default_rng(n)
+    d = rng.standard_normal((n - 1, 3))
+    far = (0.5 * np.sign(d) * (np.abs(d) == np.abs(d).max(1, keepdims=True))).astype(np.float32)   # exactly 0.5 away
+    shell = np.concatenate([np.zeros((1, 3), np.float32), far])
+    q = np.zeros((1, 3), np.float32)
+    _, g_w = _gpu(shell, q, [[0, 0, -1]], k)
+    ref = orc.estimate_normals(shell, q, [[0, 0, -1]], k)
+    assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
+
+
+@pytest.mark.parametrize("n,k", [(8_192, 30), (8_193, 30), (16_385, 256), (409_600, 30), (409_601, 30), (40_000, 256)])
+def test_subset_sizes(orc, n, k):
+    rng = np.random.default_rng(n + k)
+    cloud = rng.standard_normal((n, 3)).astype(np.float32) * np.array([1.0, 0.6, 0.3], np.float32)
+    q = cloud[:: n // 5][:5]
+    centre = cloud.mean(0, keepdims=True).astype(np.float32)
+    _, g_w = _gpu(cloud, q, centre, k)
+    ref = orc.estimate_normals(cloud, q, centre, k)
+    assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
