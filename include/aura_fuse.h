@@ -78,7 +78,8 @@ enum {
                                   its one-kernel form applies, and aura_fuse_scores scores with a kernel of its
                                   own; same results bit for bit wherever every tile's cell list fits the
                                   one-kernel form's on-chip buffer (a longer list is fused there by the gather
-                                  arithmetic, which can differ in the last bit)                 */,
+                                  arithmetic, which can differ in the last bit) and the call has more points than
+                                  those that take the gather kernel                             */,
   AURA_UNSEEN_PRIOR = 0u,      /* default.  A point that no view sees (Eq. 2 is 0 / 0 there: all-zero fused row, view
                                   count 0) has similarity 0 to every material, so Eq. 4 gives it the plain mean of y -
                                   the value before any observation.  It never enters an integral: aura_property_integrate
@@ -166,8 +167,8 @@ aura_status_t aura_workspace_bytes(int32_t call, const aura_sizes_t* sizes, size
  * the word when it starts.  The library never copies to the host: a caller who wants the guarantee reads the word
  * (workspace + *offset, device memory) after the stream has passed the call; zero means nothing to report.
  * The 32-bit word after it (workspace + *offset + 4) counts the tiles of 32 consecutive points whose list of touched
- * feature cells outgrew its storage and which were therefore fused point by point inside the kernel: correct, but many
- * times slower than either path at its best.  Spatially sorted points that are dense against the feature cells give
+ * feature cells outgrew its storage and which were therefore fused point by point at the end of the launch: correct, but
+ * several times slower than either path at its best.  Spatially sorted points that are dense against the feature cells give
  * 0 or a handful; a count near N / 32 says that the 32 points of a tile lie too far apart for this path (points not
  * sorted, or far sparser than the cells): sort them (Morton order), or pass AURA_FUSE_GATHER.
  *   call  AURA_CALL_FUSE_FEATURES (also for aura_fuse_selected), AURA_CALL_FUSE_SCORES or AURA_CALL_FUSE_SCORE_INTEGRATE
@@ -213,9 +214,11 @@ aura_status_t aura_project_visibility(const aura_views_t* views, const aura_para
  *          or NULL.  With a workspace, 16-bit maps whose D is a multiple of 256 (up to 1536, except
  *          1280; maps below 4 GiB) run on the matrix cores: the
  *          points are taken 32 at a time and should arrive spatially sorted (e.g. Morton order),
- *          and the maps must be finite everywhere.  Without one, or for other shapes, or with
- *          AURA_FUSE_GATHER, a per-point gather kernel is used.  Both give the same result up to
- *          fp32 rounding.
+ *          and the maps must be finite everywhere.  Without one, or for other shapes, for calls of few
+ *          points (N times the views per object times D up to 64 M, cells of at least 4 x 4 pixels, without
+ *          AURA_FUSE_TWO_KERNELS), or with AURA_FUSE_GATHER, a per-point gather kernel is used.  Both
+ *          give the same result up to fp32 rounding.  (aura_fuse_scores and aura_fuse_score_integrate
+ *          choose in the same way.)
  * Errors: AURA_ERR_NULL, AURA_ERR_SHAPE, AURA_ERR_DTYPE, AURA_ERR_ALIGN (feat or fused not
  * 16-byte aligned), AURA_ERR_WORKSPACE (given but misaligned or too small), AURA_ERR_HIP.
  */
