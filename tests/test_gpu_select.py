@@ -77,6 +77,32 @@ def test_selection_matches_oracle(orc, name, kw, k):
     assert np.array_equal(only["sel_view"], g["sel_view"])
 
 
+# Small calls give a wave to every point, large ones a thread: the same points in calls of every size must get the same
+# choice.  Scores are at most 1 and come from two sums of three products of unit vectors, a root and two divisions: where the
+# compiler contracts the sums differently in the two kernels they differ by at most 16 roundings.
+@pytest.mark.parametrize("name,kw,k", [("c1", dict(n_points=70_000), 3), ("c3", dict(n_points=70_000, overrides=dict(V=32, HW=112, grid=112)), 8)])
+def test_a_wave_per_point_chooses_as_a_thread_per_point(name, kw, k):
+    import paper_2511_03126_amd as aura
+    import gpu_harness as H
+    s, nrm = _scene(name, **kw)
+    d = H.DeviceScene(s)
+    whole = _gpu_select(d, s, nrm, k)
+    first = differ = 0
+    for n in (1, 3, 4, 5, 64, 1_001):
+        part = slice(first, first + n)
+        out = [torch.full((n, k), -7, dtype=torch.int32, device=d.dev), torch.full((n, k), float("nan"), device=d.dev),
+               torch.full((n, s.vis_pitch), 9, dtype=torch.uint8, device=d.dev), torch.full((n,), -7, dtype=torch.int32, device=d.dev)]
+        aura.select_views(d.views, d.params, d.xyz[part].contiguous(), torch.from_numpy(nrm[part]).to(d.dev), k, *out)
+        view, score, mask, n_sel = (t.cpu().numpy() for t in out)
+        assert np.array_equal(n_sel, whole["n_sel"][part])
+        assert np.abs(score - whole["sel_score"][part]).max() <= 16 * 2.0 ** -24
+        same = (view == whole["sel_view"][part]).all(axis=1)   # (views whose scores differ by less than that may change places)
+        differ += int((~same).sum())
+        assert np.array_equal(mask[same], whole["sel_mask"][part][same])
+        first += n
+    assert differ <= 2
+
+
 def test_hand_worked_rig_on_the_gpu():
     """Cameras on a line at known distances: S_total = 1 / (1 + distance), nearest first; equal distances by index; a
     camera behind the surface scores 0 and comes last."""
