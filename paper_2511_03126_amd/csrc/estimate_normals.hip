@@ -9,8 +9,9 @@
 //
 // Usual path (k up to 256), one sweep over the cloud:
 //   1. an upper bound of the k-th smallest distance that is exact by construction: the k-th smallest distance among
-//      every stride-th point (at most 16384 of them, kept in LDS; the k-th smallest of a subset can only be larger);
-//   2. one sweep over the whole cloud collects the points within that bound (about k * stride of them) in LDS;
+//      every stride-th quad of points (at most 16384 points, kept in LDS; the k-th smallest of a subset can only be larger);
+//   2. one sweep over the whole cloud collects the points within that bound (about k * stride of them) in LDS
+//      (a cloud that fits the list goes there whole, without a bound);
 //   3. among those, the k-th smallest distance by a radix select over the bit pattern of d (non-negative floats order
 //      like their bits: histograms of the next 11 / 11 / 10 bits among the candidates left) and, when more points share
 //      that distance than are still needed, the same select over their indices;
@@ -26,10 +27,11 @@ namespace aura {
 
 constexpr int kNrmBlock = 1024;   // a sweep over the cloud is shared by 16 waves
 constexpr int kNrmBins = 2048;
-// The strided subset that bounds the k-th distance: its points lie far apart in memory, so that a read of a wave touches a
-// cache line per lane; read once into LDS instead of once per pass of the select (and 16 points of the sweep in flight per
-// thread instead of 8), 150 queries against 200 000 points take 60 us instead of 80.  Half the size where the candidates
-// (about k * stride) stay few.
+// The strided subset that bounds the k-th distance lies far apart in memory: a read of a wave touches a cache line per
+// lane, 16384 single points three times that.  Quads of neighbouring points (48 bytes, three 16-byte loads) take a quarter of
+// the lines and a sixteenth of the loads; the sweep reads quads too (with the matrices of the last step in registers, 150 queries against 200 000 points 56 -> 46.6 us,
+// against 1 M points 174 -> 154, against 8000, all of them candidates, 26 -> 20).
+// Half the size where the candidates (about k * stride) stay few.
 constexpr int kNrmSubSmall = 8192, kNrmSub = 16384;
 constexpr int kNrmFewCand = 1500;
 constexpr int kNrmCand = 8192;    // candidates the LDS list holds (distance and index: as many words as the subset)
@@ -62,6 +64,19 @@ __device__ __forceinline__ uint32_t dist_bits(const float* __restrict__ p, float
   float t = dx * dx + dy * dy;
   t = t + dz * dz;
   return __float_as_uint(t);
+}
+
+// Four consecutive points.  The loads are 16 bytes wide at any 4-byte address, which global loads allow.
+struct __attribute__((packed, aligned(4))) PointQuad {
+  float v[12];
+};
+
+__device__ __forceinline__ void quad_dist(const PointQuad& q, float qx, float qy, float qz, uint32_t (&d)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float p[3] = {q.v[3 * e], q.v[3 * e + 1], q.v[3 * e + 2]};
+    d[e] = dist_bits(p, qx, qy, qz);
+  }
 }
 
 // Among the elements i of [0, n) with eligible(i), the `want`-th smallest key(i) (want >= 1, at most the number of
@@ -145,54 +160,68 @@ __device__ __forceinline__ double nrm_block_sum(double v, double* sh) {
   return t;
 }
 
+// One Jacobi rotation in the plane (p, q): app, aqq, apq the matrix there, arp and arq the third row's entries, vp and vq the
+// columns of the eigenvectors.  The rotation's tangent t = sign(theta) / (|theta| + sqrt(theta^2 + 1)), theta = d / b, is taken
+// without the division for theta.  (Entries are products of fp32 differences: their squares neither overflow nor vanish in
+// fp64.)
+__device__ __forceinline__ void rotate(double& app, double& aqq, double& apq, double& arp, double& arq, double (&vp)[3], double (&vq)[3]) {
+  if (apq == 0.0) return;
+  const double d = aqq - app, b = 2.0 * apq;
+  const double t = (d < 0.0 ? -b : b) / (fabs(d) + sqrt(d * d + b * b));
+  const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
+  app -= t * apq;
+  aqq += t * apq;
+  apq = 0.0;
+  const double rp = arp, rq = arq;
+  arp = cs * rp - sn * rq;
+  arq = sn * rp + cs * rq;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const double p = vp[r], q = vq[r];
+    vp[r] = cs * p - sn * q;
+    vq[r] = sn * p + cs * q;
+  }
+}
+
 // Eigenvalues (ascending in w) and the eigenvector of the smallest one of the symmetric matrix
-// [a00 a01 a02; a01 a11 a12; a02 a12 a22], by cyclic Jacobi rotations.
-__device__ void smallest_eigenvector(const double (&c)[6], double (&w)[3], double (&n)[3]) {
-  double a[3][3] = {{c[0], c[1], c[2]}, {c[1], c[3], c[4]}, {c[2], c[4], c[5]}};
-  double v[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+// [a00 a01 a02; a01 a11 a12; a02 a12 a22], by cyclic Jacobi rotations.  One thread's chain: everything has a register of its
+// own (as arrays indexed by loops the matrices were in scratch memory, a round trip per entry).
+__device__ __forceinline__ void smallest_eigenvector(const double (&c)[6], double (&w)[3], double (&n)[3]) {
+  double a00 = c[0], a01 = c[1], a02 = c[2], a11 = c[3], a12 = c[4], a22 = c[5];
+  double v0[3] = {1, 0, 0}, v1[3] = {0, 1, 0}, v2[3] = {0, 0, 1};
+#pragma unroll 1
   for (int sweep = 0; sweep < 24; ++sweep) {
-    const double off = fabs(a[0][1]) + fabs(a[0][2]) + fabs(a[1][2]);
-    const double diag = fabs(a[0][0]) + fabs(a[1][1]) + fabs(a[2][2]);
+    const double off = fabs(a01) + fabs(a02) + fabs(a12);
+    const double diag = fabs(a00) + fabs(a11) + fabs(a22);
     if (off <= 1e-300 || off <= 1e-17 * diag) break;
-    for (int p = 0; p < 2; ++p) {
-      for (int q = p + 1; q < 3; ++q) {
-        if (a[p][q] == 0.0) continue;
-        const double theta = (a[q][q] - a[p][p]) / (2.0 * a[p][q]);
-        const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
-        for (int r = 0; r < 3; ++r) {   // A <- A J
-          const double arp = a[r][p], arq = a[r][q];
-          a[r][p] = cs * arp - sn * arq;
-          a[r][q] = sn * arp + cs * arq;
-        }
-        for (int r = 0; r < 3; ++r) {   // A <- J^T A
-          const double apr = a[p][r], aqr = a[q][r];
-          a[p][r] = cs * apr - sn * aqr;
-          a[q][r] = sn * apr + cs * aqr;
-        }
-        for (int r = 0; r < 3; ++r) {   // V <- V J
-          const double vrp = v[r][p], vrq = v[r][q];
-          v[r][p] = cs * vrp - sn * vrq;
-          v[r][q] = sn * vrp + cs * vrq;
-        }
+    rotate(a00, a11, a01, a02, a12, v0, v1);
+    rotate(a00, a22, a02, a01, a12, v0, v2);
+    rotate(a11, a22, a12, a01, a02, v1, v2);
+  }
+  auto ascending = [](double& x, double& y, double (&vx)[3], double (&vy)[3]) {
+    if (x > y) {
+      const double t = x;
+      x = y;
+      y = t;
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double u = vx[r];
+        vx[r] = vy[r];
+        vy[r] = u;
       }
     }
-  }
-  int order[3] = {0, 1, 2};
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2 - i; ++j)
-      if (a[order[j]][order[j]] > a[order[j + 1]][order[j + 1]]) {
-        const int t = order[j];
-        order[j] = order[j + 1];
-        order[j + 1] = t;
-      }
-  for (int i = 0; i < 3; ++i) w[i] = a[order[i]][order[i]];
-  const double len = sqrt(v[0][order[0]] * v[0][order[0]] + v[1][order[0]] * v[1][order[0]] + v[2][order[0]] * v[2][order[0]]);
-  for (int r = 0; r < 3; ++r) n[r] = v[r][order[0]] / len;
+  };
+  ascending(a00, a11, v0, v1);
+  ascending(a11, a22, v1, v2);
+  ascending(a00, a11, v0, v1);
+  w[0] = a00; w[1] = a11; w[2] = a22;
+  const double len = sqrt(v0[0] * v0[0] + v0[1] * v0[1] + v0[2] * v0[2]);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) n[r] = v0[r] / len;
 }
 
 // From the sums of r and r r^T over the kk selected points to the stored normal (one thread).
-__device__ void finish_normal(const NrmArgs& a, const NrmObjDev& ob, long long m, float qx, float qy, float qz, int kk,
+__device__ __forceinline__ void finish_normal(const NrmArgs& a, const NrmObjDev& ob, long long m, float qx, float qy, float qz, int kk,
                               const double (&s1)[3], const double (&s2)[6]) {
   const double inv = 1.0 / (double)kk;
   const double mx = s1[0] * inv, my = s1[1] * inv, mz = s1[2] * inv;
@@ -228,40 +257,63 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
   }
   auto dist = [&](int i) { return dist_bits(pts + 3 * (long long)i, qx, qy, qz); };
   int n_equal, need;
+  double s1[3] = {0, 0, 0}, s2[6] = {0, 0, 0, 0, 0, 0};   // sums of r and r r^T (in the first thread)
+  bool summed = false;
   if (kk <= kNrmSel) {
-    __shared__ uint32_t s_list[2 * kNrmCand];                  // the subset's distances, later the candidates:
+    __shared__ __attribute__((aligned(16))) uint32_t s_list[2 * kNrmCand];                  // the subset's distances, later the candidates:
     uint32_t* const s_cd = s_list;                             // distance bits ...
     int* const s_ci = reinterpret_cast<int*>(s_list + kNrmCand);   // ... and point index
     __shared__ int s_cn, s_ns;
     __shared__ int s_sel[kNrmSel];        // the k selected points, unordered, then in index order
     __shared__ float s_pt[kNrmSel][3];
-    const int small = (n + kNrmSubSmall - 1) / kNrmSubSmall;
-    const int stride = kk * small <= kNrmFewCand ? small : (n + kNrmSub - 1) / kNrmSub;
-    const int m_sub = (n + stride - 1) / stride;   // >= kk: kk <= n, and kk <= 256 < 8192 where stride > 1
-    for (int j0 = threadIdx.x; j0 < m_sub; j0 += 8 * kNrmBlock) {
-      uint32_t d[8];
+    auto quad = [&](int first) { return *reinterpret_cast<const PointQuad*>(pts + 3 * (long long)first); };
+    constexpr int kTrip = 4;   // quads per thread and trip: reads in flight together
+    if (n <= kNrmCand) {       // (uniform)
+      for (int i = threadIdx.x; i < n; i += kNrmBlock) {
+        s_cd[i] = dist(i);
+        s_ci[i] = i;
+      }
+      if (threadIdx.x == 0) { s_cn = n; s_ns = 0; }
+    } else {
+      const int small = (n + kNrmSubSmall - 1) / kNrmSubSmall;
+      const int stride = kk * small <= kNrmFewCand ? small : (n + kNrmSub - 1) / kNrmSub;
+      const int n_sub = (n / 4 + stride - 1) / stride;   // quads: at least 1024, at most kNrmSub / 4, and kk <= 256
+      for (int j0 = threadIdx.x; j0 < n_sub; j0 += kTrip * kNrmBlock) {
+        PointQuad q[kTrip];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) d[e] = dist(min(j0 + e * kNrmBlock, m_sub - 1) * stride);
+        for (int e = 0; e < kTrip; ++e) q[e] = quad(4 * stride * min(j0 + e * kNrmBlock, n_sub - 1));
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (j0 + e * kNrmBlock < m_sub) s_list[j0 + e * kNrmBlock] = d[e];
-    }
-    __syncthreads();
-    const uint32_t bound = radix_select(m_sub, kk, [&](int j) { return s_list[j]; }, [](int) { return true; }, s_hist,
-                                        s_pick, &n_equal, &need);
-    if (threadIdx.x == 0) { s_cn = 0; s_ns = 0; }
-    __syncthreads();
-    constexpr int kTrip = 16;   // points per thread and trip: reads in flight together
-    for (int i0 = threadIdx.x; i0 < n; i0 += kTrip * kNrmBlock) {
-      uint32_t d[kTrip];
+        for (int e = 0; e < kTrip; ++e) {
+          uint32_t d[4];
+          quad_dist(q[e], qx, qy, qz, d);
+          if (j0 + e * kNrmBlock < n_sub) *reinterpret_cast<uint4*>(s_list + 4 * (j0 + e * kNrmBlock)) = uint4{d[0], d[1], d[2], d[3]};
+        }
+      }
+      __syncthreads();
+      const uint32_t bound = radix_select(4 * n_sub, kk, [&](int j) { return s_list[j]; }, [](int) { return true; }, s_hist,
+                                          s_pick, &n_equal, &need);
+      if (threadIdx.x == 0) { s_cn = 0; s_ns = 0; }
+      __syncthreads();
+      const int n_quads = (n + 3) / 4;
+      for (int g0 = threadIdx.x; g0 < n_quads; g0 += kTrip * kNrmBlock) {
+        PointQuad q[kTrip];
+        int first[kTrip];   // the last quad may begin before its place: points that the quad before it holds are left out
 #pragma unroll
-      for (int e = 0; e < kTrip; ++e) d[e] = dist(min(i0 + e * kNrmBlock, n - 1));
+        for (int e = 0; e < kTrip; ++e) {
+          first[e] = min(4 * (g0 + e * kNrmBlock), n - 4);
+          q[e] = quad(first[e]);
+        }
 #pragma unroll
-      for (int e = 0; e < kTrip; ++e) {
-        const int i = i0 + e * kNrmBlock;
-        if (i < n && d[e] <= bound) {
-          const int pos = atomicAdd(&s_cn, 1);
-          if (pos < kNrmCand) { s_cd[pos] = d[e]; s_ci[pos] = i; }
+        for (int e = 0; e < kTrip; ++e) {
+          uint32_t d[4];
+          quad_dist(q[e], qx, qy, qz, d);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            if (d[c] <= bound && first[e] + c >= 4 * (g0 + e * kNrmBlock)) {
+              const int pos = atomicAdd(&s_cn, 1);
+              if (pos < kNrmCand) { s_cd[pos] = d[c]; s_ci[pos] = first[e] + c; }
+            }
+          }
         }
       }
     }
@@ -292,53 +344,52 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
       }
       __syncthreads();
       if (threadIdx.x == 0) {
-        double s1[3] = {0, 0, 0}, s2[6] = {0, 0, 0, 0, 0, 0};
         for (int j = 0; j < kk; ++j) {
           const double rx = (double)s_pt[j][0] - (double)qx, ry = (double)s_pt[j][1] - (double)qy, rz = (double)s_pt[j][2] - (double)qz;
           s1[0] += rx; s1[1] += ry; s1[2] += rz;
           s2[0] += rx * rx; s2[1] += rx * ry; s2[2] += rx * rz;
           s2[3] += ry * ry; s2[4] += ry * rz; s2[5] += rz * rz;
         }
-        finish_normal(a, ob, m, qx, qy, qz, kk, s1, s2);
       }
-      return;
+      summed = true;
     }
   }
-  const uint32_t tau = radix_select(n, kk, dist, [](int) { return true; }, s_hist, s_pick, &n_equal, &need);
-  int last_idx = 0x7fffffff;   // points at distance tau are taken up to this index
-  if (need < n_equal) {
-    int e2, n2;
-    last_idx = (int)radix_select(n, need, [](int i) { return (uint32_t)i; }, [&](int i) { return dist(i) == tau; }, s_hist,
-                                 s_pick, &e2, &n2);
-  }
-  double s1[3] = {0, 0, 0}, s2[6] = {0, 0, 0, 0, 0, 0};
-  for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kNrmBlock) {
-    float px[4], py[4], pz[4];
-    bool in[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = min(i0 + e * kNrmBlock, n - 1);
-      const float* __restrict__ p = pts + 3 * (long long)i;
-      px[e] = p[0]; py[e] = p[1]; pz[e] = p[2];
-      in[e] = i0 + e * kNrmBlock < n;
+  if (!summed) {   // uniform
+    const uint32_t tau = radix_select(n, kk, dist, [](int) { return true; }, s_hist, s_pick, &n_equal, &need);
+    int last_idx = 0x7fffffff;   // points at distance tau are taken up to this index
+    if (need < n_equal) {
+      int e2, n2;
+      last_idx = (int)radix_select(n, need, [](int i) { return (uint32_t)i; }, [&](int i) { return dist(i) == tau; }, s_hist,
+                                   s_pick, &e2, &n2);
     }
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kNrmBlock) {
+      float px[4], py[4], pz[4];
+      bool in[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = i0 + e * kNrmBlock;
-      const float pe[3] = {px[e], py[e], pz[e]};
-      const uint32_t d = dist_bits(pe, qx, qy, qz);
-      if (in[e] && (d < tau || (d == tau && i <= last_idx))) {
-        const double rx = (double)px[e] - (double)qx, ry = (double)py[e] - (double)qy, rz = (double)pz[e] - (double)qz;
-        s1[0] += rx; s1[1] += ry; s1[2] += rz;
-        s2[0] += rx * rx; s2[1] += rx * ry; s2[2] += rx * rz;
-        s2[3] += ry * ry; s2[4] += ry * rz; s2[5] += rz * rz;
+      for (int e = 0; e < 4; ++e) {
+        const int i = min(i0 + e * kNrmBlock, n - 1);
+        const float* __restrict__ p = pts + 3 * (long long)i;
+        px[e] = p[0]; py[e] = p[1]; pz[e] = p[2];
+        in[e] = i0 + e * kNrmBlock < n;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e * kNrmBlock;
+        const float pe[3] = {px[e], py[e], pz[e]};
+        const uint32_t d = dist_bits(pe, qx, qy, qz);
+        if (in[e] && (d < tau || (d == tau && i <= last_idx))) {
+          const double rx = (double)px[e] - (double)qx, ry = (double)py[e] - (double)qy, rz = (double)pz[e] - (double)qz;
+          s1[0] += rx; s1[1] += ry; s1[2] += rz;
+          s2[0] += rx * rx; s2[1] += rx * ry; s2[2] += rx * rz;
+          s2[3] += ry * ry; s2[4] += ry * rz; s2[5] += rz * rz;
+        }
       }
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s1[c] = nrm_block_sum(s1[c], s_red);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) s2[c] = nrm_block_sum(s2[c], s_red);
   }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) s1[c] = nrm_block_sum(s1[c], s_red);
-#pragma unroll
-  for (int c = 0; c < 6; ++c) s2[c] = nrm_block_sum(s2[c], s_red);
   if (threadIdx.x == 0) finish_normal(a, ob, m, qx, qy, qz, kk, s1, s2);
 }
 
