@@ -223,6 +223,100 @@ __global__ __launch_bounds__(256) void k_material_scores_few(ScoreArgs a) {
                                a.prop, a.label, a.unseen_zero != 0, s_stage[wave]);
 }
 
+// Few rows: what such a call takes is launches and the chain of a wave's steps, not bytes.  A workgroup of four waves shares
+// 32 rows, every fourth macro step to a wave, and adds the four partial sums up through LDS; the embeddings are split where
+// they are used (a row of them is read like a row of points), so no kernel has to run before this one.  2001 rows of 384
+// channels against 10 materials 15.1 -> 8.9 us, 40 rows 12.1 -> 9.1 (the host's time for a call).
+template <int MT, typename T>
+__global__ __launch_bounds__(256) void k_material_scores_split(ScoreArgs a, const float* __restrict__ temb) {
+  constexpr int kWaves = 4;
+  __shared__ float ys[MT * kTileM * kMaxP];
+  __shared__ f32x4 s_part[kWaves - 1][4 * MT][kWave];
+  __shared__ __attribute__((aligned(16))) float s_stage[score_stage_floats<16>()];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const long long n0 = (long long)blockIdx.x * kTileN;
+  const float* __restrict__ row = a.fused + std::min<long long>(n0 + (lane & 31), a.N - 1) * a.D + (lane / 32) * 16;
+  const float* __restrict__ emb[MT];   // (a material beyond the last one: the last again, into sums that nobody reads)
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) emb[mt] = temb + (long long)min(mt * kTileM + (lane & 31), a.K - 1) * a.D + (lane / 32) * 16;
+  ScoreSums<MT, T> sum;
+
+  struct Piece { f32x4 v[4]; };   // a lane's 16 channels of a step
+  struct Step { Piece row, emb[MT]; };
+  const int last = a.steps - 1;
+  auto load = [&](int s, Step& b) {   // (past the end: the last step, read and not used)
+    const int at = min(s, last) * kStepK;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b.row.v[q] = *reinterpret_cast<const f32x4*>(row + at + 4 * q);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b.emb[mt].v[q] = *reinterpret_cast<const f32x4*>(emb[mt] + at + 4 * q);
+  };
+  auto split = [](const Piece& b, Term8<T> (&hi)[2], Term8<T> (&lo)[2]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        T h, l;
+        split_terms<T>(b.v[2 * j + (c >> 2)][c & 3], h, l);
+        hi[j][c] = h;
+        lo[j][c] = l;
+      }
+  };
+  auto products = [&](const Step& b) {
+    Term8<T> bh[2], bl[2];
+    split(b.row, bh, bl);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      Term8<T> eh[2], el[2];
+      split(b.emb[mt], eh, el);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        sum.acc[mt] = score_mma(eh[j], bh[j], sum.acc[mt]);
+        sum.low(mt) = score_mma(eh[j], bl[j], sum.low(mt));
+        sum.low(mt) = score_mma(el[j], bh[j], sum.low(mt));
+      }
+    }
+  };
+  Step b0, b1;
+  load(wave, b0);
+  load(wave + kWaves, b1);
+  if (a.prop) {
+    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
+  }
+  for (int s = wave; s < a.steps; s += 2 * kWaves) {   // uniform over the wave
+    products(b0);
+    load(s + 2 * kWaves, b0);
+    if (s + kWaves < a.steps) {
+      products(b1);
+      load(s + 3 * kWaves, b1);
+    }
+  }
+  sum.join();
+  if (wave > 0) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        s_part[wave - 1][4 * mt + q][lane] = f32x4{sum.acc[mt][4 * q], sum.acc[mt][4 * q + 1], sum.acc[mt][4 * q + 2], sum.acc[mt][4 * q + 3]};
+  }
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 part = s_part[w][4 * mt + q][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum.acc[mt][4 * q + e] += part[e];
+      }
+  finish_scores_staged<MT, 16>(sum.acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
+                               a.prop, a.label, a.unseen_zero != 0, s_stage);
+}
+
 // Where all the split embeddings of a call fit into LDS (steps * MT <= kLdsSlots blocks of 4 KiB: up to 1024 channels
 // for 32 materials, 512 for 64), one workgroup of 16 waves per compute unit copies them there once and then walks over
 // tiles of 32 points: the embeddings no longer come from L2 once per tile - reading them there costs the row stream 15 %
@@ -498,6 +592,13 @@ static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream
   return hipErrorInvalidValue;
 }
 
+// Which calls of up to 64 materials take k_material_scores_split: every workgroup of 32 rows reads the embeddings and splits
+// them, so the more of them there are, the fewer rows pay.  With both kernels, us per call, two launches / one: 384 channels,
+// 10 materials 2001 rows 15.1 / 8.9, 20 000 15.9 / 14.3, 40 000 23.4 / 21.2, 65 000 24.2 / 30.9; 512 channels, 32 materials
+// 5000 rows 19.0 / 11.1, 10 000 18.9 / 16.7, 20 000 19.7 / 22.0; 50 materials 5000 rows 23.6 / 15.5, 10 000 24.1 / 23.1, 20 000
+// 25.7 / 31.6; 1024 channels, 32 materials 10 000 rows 28.0 / 23.5, 20 000 28.2 / 32.7.
+static bool few_rows(long long N, int K) { return N <= 40000 && N * K <= 400000; }
+
 hipError_t launch_material_scores(const float* fused, long long N, int D, const float* temb, int K,
                                   const float* y, int P, float temperature, float* scores, float* prop,
                                   int* label, void* workspace, hipStream_t stream, int unseen_zero, bool f16_terms) {
@@ -505,6 +606,20 @@ hipError_t launch_material_scores(const float* fused, long long N, int D, const 
   int MT = tiles_m(K);
   if (MT == 3) MT = 4;
   const int S = steps_k(D);
+  ScoreArgs a{fused, N, D, K, P, y, 1.0f / temperature, unseen_zero, scores, prop, label,
+              static_cast<const bf16x8*>(workspace), S};
+  const bool aligned = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(fused) & 15) == 0;
+  if (MT <= 2 && few_rows(N, K) && aligned && D % kStepK == 0 && (reinterpret_cast<uintptr_t>(temb) & 15) == 0) {
+    const dim3 grid((unsigned)((N + kTileN - 1) / kTileN)), block(256);
+    if (f16_terms) {
+      if (MT == 1) hipLaunchKernelGGL((k_material_scores_split<1, TermH>), grid, block, 0, stream, a, temb);
+      else hipLaunchKernelGGL((k_material_scores_split<2, TermH>), grid, block, 0, stream, a, temb);
+    } else {
+      if (MT == 1) hipLaunchKernelGGL((k_material_scores_split<1, TermB>), grid, block, 0, stream, a, temb);
+      else hipLaunchKernelGGL((k_material_scores_split<2, TermB>), grid, block, 0, stream, a, temb);
+    }
+    return hipGetLastError();
+  }
   {
     long long total = (long long)S * MT * 2 * kWave;
     const dim3 grid((unsigned)((total + 255) / 256)), block(256);
@@ -515,9 +630,6 @@ hipError_t launch_material_scores(const float* fused, long long N, int D, const 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  ScoreArgs a{fused, N, D, K, P, y, 1.0f / temperature, unseen_zero, scores, prop, label,
-              static_cast<const bf16x8*>(workspace), S};
-  const bool aligned = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(fused) & 15) == 0;
   if (f16_terms) {
     if (!aligned || D % kStepK != 0) return hipErrorInvalidValue;
     switch (MT) {
