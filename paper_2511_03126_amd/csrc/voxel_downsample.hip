@@ -8,8 +8,8 @@
 //                 in a workgroup's LDS table and from there in memory (integer sums: the result does not depend on the
 //                 order in which they land)
 //   k_vox_count   occupied cubes per block of 2048 cubes
-//   k_vox_scan    exclusive scan of the block counts (one workgroup); object offsets
-//   k_vox_emit    per block: position of every occupied cube in the output list, mean position, count
+//   k_vox_emit    per block: the occupied cubes of the blocks before it, from there the position of every occupied cube in
+//                 the output list, mean position, count; object offsets
 //   k_vox_point   per point: the list position of its cube
 // Every object's cubes start at a multiple of 2048, so blocks never straddle objects.  All traffic is a few bytes per
 // point plus the grid: the call is bound by launch latency.
@@ -44,8 +44,7 @@ struct VoxArgs {
   const float* xyz;
   VoxCell* cells;      // [total cells]
   int* cell_slot;      // [total cells]: list position of an occupied cube
-  int* block_cnt;      // [blocks]
-  int* block_off;      // [blocks + 1]
+  int* block_cnt;      // [blocks]: occupied cubes
   int n_blocks;
   int shift;           // fixed-point scale 2^shift
   float* out_xyz;      // [capacity][3]
@@ -78,9 +77,18 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_zero(VoxArgs a) {
     z[i] = vox_u32x4{0u, 0u, 0u, 0u};
 }
 
+// Eight or four consecutive points.  The loads are 16 bytes wide at any 4-byte address, which global loads allow.
+template <int N>
+struct __attribute__((packed, aligned(4))) VoxRun {
+  float v[3 * N];
+};
+struct __attribute__((packed, aligned(4))) VoxIds {
+  int v[4];
+};
+
 // Points per thread and trip, and entries of a workgroup's table.
-constexpr int kVoxRun = 8;
-constexpr int kVoxTrip = kVoxBlock * kVoxRun;   // 2048 points per workgroup and trip
+constexpr int kVoxPts = 8;
+constexpr int kVoxTrip = kVoxBlock * kVoxPts;   // 2048 points per workgroup and trip
 constexpr int kVoxSlots = 1024;                  // 32 KiB of LDS: four workgroups per compute unit
 
 // A workgroup adds `trips` * 2048 consecutive points of one object up in an LDS table before anything goes to memory.
@@ -119,22 +127,30 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab, 
       atomicAdd(reinterpret_cast<unsigned long long*>(&cells[cube].cnt), (unsigned long long)n);
     }
   };
+  auto fixed = [&](float x) { return __double2ll_rn(ldexp((double)x, a.shift)); };
+  if (ob.n_pts < kVoxPts) {   // (uniform) a point per thread
+    if ((int)threadIdx.x < ob.n_pts) {
+      const float* __restrict__ p = a.xyz + 3 * (ob.pt_begin + threadIdx.x);
+      const long long q[3] = {fixed(p[0]), fixed(p[1]), fixed(p[2])};
+      add(vox_cell(ob, p) - ob.cell_begin, q, 1);
+    }
+    trips = 0;
+  }
   for (int trip = 0; trip < trips; ++trip) {
-    const long long l0 = first + (long long)trip * kVoxTrip + threadIdx.x * kVoxRun;
+    const long long l0 = first + (long long)trip * kVoxTrip + threadIdx.x * kVoxPts;
     if (l0 >= ob.n_pts) break;
-    const int n = (int)min((long long)kVoxRun, ob.n_pts - l0);
-    const float* __restrict__ p = a.xyz + 3 * (ob.pt_begin + l0);
-    float x[kVoxRun][3];
-#pragma unroll
-    for (int e = 0; e < kVoxRun; ++e)   // all reads before the first use; past the end: the thread's first point again, unused
-#pragma unroll
-      for (int c = 0; c < 3; ++c) x[e][c] = p[3 * (e < n ? e : 0) + c];
+    // Six loads of 16 bytes: lanes are 96 bytes apart, so that every load of a wave touches most of its cache lines again,
+    // and as 24 loads of 4 bytes that was what the kernel took its time for.  The last thread's run begins early enough to
+    // end with the object; the points before its own are left out.
+    const long long l = min(l0, (long long)ob.n_pts - kVoxPts);
+    const VoxRun<kVoxPts> r = *reinterpret_cast<const VoxRun<kVoxPts>*>(a.xyz + 3 * (ob.pt_begin + l));
     long long q[3] = {0, 0, 0};
     int cube = -1, run = 0;
 #pragma unroll
-    for (int e = 0; e < kVoxRun; ++e) {
-      if (e >= n) break;
-      const int now = vox_cell(ob, x[e]) - ob.cell_begin;
+    for (int e = 0; e < kVoxPts; ++e) {
+      if (l + e < l0) continue;
+      const float x[3] = {r.v[3 * e], r.v[3 * e + 1], r.v[3 * e + 2]};
+      const int now = vox_cell(ob, x) - ob.cell_begin;
       if (now != cube) {
         if (run > 0) add(cube, q, run);
         cube = now;
@@ -143,7 +159,7 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab, 
       }
       ++run;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) q[c] += __double2ll_rn(ldexp((double)x[e][c], a.shift));
+      for (int c = 0; c < 3; ++c) q[c] += fixed(x[c]);
     }
     add(cube, q, run);
   }
@@ -189,31 +205,21 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_count(VoxArgs a) {
   if (threadIdx.x == 0) a.block_cnt[blockIdx.x] = total;
 }
 
-// One workgroup: block_off = exclusive scan of block_cnt; out_offsets[b] = occupied cubes before object b.
-__global__ __launch_bounds__(kVoxBlock) void k_vox_scan(VoxArgs a, VoxTable tab) {
+// The blocks are few (one per object of up to 2048 cubes), so every workgroup adds the counts of the blocks before its own
+// up itself, and the first one of an object, and the last one of all, write the object offsets; a scan of the counts by a
+// workgroup of its own was one more launch.  (Counting a cube when the first points are added to it saves another launch, but
+// the atomics then have to answer: 64 objects of 100 000 points 72 -> 108 us.)
+__global__ __launch_bounds__(kVoxBlock) void k_vox_emit(VoxArgs a, VoxTable tab) {
   __shared__ int sh[kVoxBlock / kWave];
-  __shared__ int s_carry;
-  if (threadIdx.x == 0) s_carry = 0;
-  __syncthreads();
-  for (int base = 0; base < a.n_blocks; base += kVoxBlock) {
-    const int j = base + threadIdx.x;
-    const int mine = j < a.n_blocks ? a.block_cnt[j] : 0;
-    int total;
-    const int before = vox_block_prefix(mine, sh, &total);
-    const int carry = s_carry;
-    if (j < a.n_blocks) a.block_off[j] = carry + before;
-    __syncthreads();                 // everyone has read the carry and the wave totals
-    if (threadIdx.x == 0) s_carry = carry + total;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.block_off[a.n_blocks] = s_carry;
-  __syncthreads();
-  for (int b = threadIdx.x; b <= a.n_obj; b += kVoxBlock)
-    a.out_offsets[b] = b < a.n_obj ? a.block_off[tab.o[b].cell_begin / kVoxCellsPerBlock] : a.block_off[a.n_blocks];
-}
-
-__global__ __launch_bounds__(kVoxBlock) void k_vox_emit(VoxArgs a) {
-  __shared__ int sh[kVoxBlock / kWave];
+  int before = 0;
+  for (int j = threadIdx.x; j < (int)blockIdx.x; j += kVoxBlock) before += a.block_cnt[j];
+  int block_off;
+  vox_block_prefix(before, sh, &block_off);   // (its total)
+  const int first_cell = blockIdx.x * kVoxCellsPerBlock;
+  for (int b = threadIdx.x; b < a.n_obj; b += kVoxBlock)
+    if (tab.o[b].cell_begin == first_cell) a.out_offsets[b] = block_off;
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) a.out_offsets[a.n_obj] = block_off + a.block_cnt[blockIdx.x];
+  __syncthreads();   // sh is free again
   const long long c0 = (long long)blockIdx.x * kVoxCellsPerBlock + threadIdx.x * kVoxCellsPerThread;
   long long cnt[kVoxCellsPerThread];
   int mine = 0;
@@ -223,7 +229,7 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_emit(VoxArgs a) {
     mine += cnt[e] > 0 ? 1 : 0;
   }
   int total;
-  long long slot = a.block_off[blockIdx.x] + vox_block_prefix(mine, sh, &total);
+  long long slot = block_off + vox_block_prefix(mine, sh, &total);
 #pragma unroll
   for (int e = 0; e < kVoxCellsPerThread; ++e) {
     if (cnt[e] <= 0) {
@@ -241,12 +247,25 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_emit(VoxArgs a) {
   }
 }
 
+// Four points per thread: loads and stores of 16 bytes.
 __global__ __launch_bounds__(kVoxBlock) void k_vox_point(VoxArgs a, VoxTable tab) {
   const VoxObjDev ob = tab.o[blockIdx.y];
-  const int li = blockIdx.x * kVoxBlock + threadIdx.x;
+  const long long li = 4 * ((long long)blockIdx.x * kVoxBlock + threadIdx.x);
   if (li >= ob.n_pts) return;
-  const long long i = ob.pt_begin + li;
-  a.voxel_of_point[i] = a.cell_slot[vox_cell(ob, a.xyz + 3 * i)];
+  const float* __restrict__ p = a.xyz + 3 * (ob.pt_begin + li);
+  int* __restrict__ out = a.voxel_of_point + ob.pt_begin + li;
+  if (li + 4 <= ob.n_pts) {
+    const VoxRun<4> r = *reinterpret_cast<const VoxRun<4>*>(p);
+    VoxIds ids;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x[3] = {r.v[3 * e], r.v[3 * e + 1], r.v[3 * e + 2]};
+      ids.v[e] = a.cell_slot[vox_cell(ob, x)];
+    }
+    *reinterpret_cast<VoxIds*>(out) = ids;
+  } else {
+    for (int e = 0; li + e < ob.n_pts; ++e) out[e] = a.cell_slot[vox_cell(ob, p + 3 * e)];
+  }
 }
 
 // ---------------------------------------------------------------- host side
@@ -280,7 +299,8 @@ long long voxel_padded_cells(long long cells) { return vox_padded(cells); }
 size_t voxel_workspace_bytes(long long padded_cells) {
   const size_t blocks = (size_t)(padded_cells / kVoxCellsPerBlock);
   return vox_align256((size_t)padded_cells * sizeof(VoxCell)) + vox_align256((size_t)padded_cells * sizeof(int)) +
-         vox_align256(blocks * sizeof(int)) + vox_align256((blocks + 1) * sizeof(int));
+         vox_align256(blocks * sizeof(int)) +
+         vox_align256((blocks + 1) * sizeof(int));   // (the last part is not used: the size that the call asks for is kept)
 }
 
 hipError_t launch_voxel_downsample(const float* xyz, const VoxObj* objs, int B, float max_abs, long long n_points,
@@ -304,8 +324,7 @@ hipError_t launch_voxel_downsample(const float* xyz, const VoxObj* objs, int B, 
   size_t off = 0;
   a.cells = reinterpret_cast<VoxCell*>(ws + off);   off += vox_align256((size_t)cells * sizeof(VoxCell));
   a.cell_slot = reinterpret_cast<int*>(ws + off);   off += vox_align256((size_t)cells * sizeof(int));
-  a.block_cnt = reinterpret_cast<int*>(ws + off);   off += vox_align256((size_t)a.n_blocks * sizeof(int));
-  a.block_off = reinterpret_cast<int*>(ws + off);
+  a.block_cnt = reinterpret_cast<int*>(ws + off);
   // fixed point: |x| 2^shift n_points < 2^62 for every coordinate up to max_abs
   int e = 0, nbits = 1;
   frexpf(max_abs, &e);
@@ -326,10 +345,9 @@ hipError_t launch_voxel_downsample(const float* xyz, const VoxObj* objs, int B, 
     hipLaunchKernelGGL(k_vox_bin, dim3((unsigned)((max_pts + span - 1) / span), B), block, 0, stream, a, tab, trips);
   }
   hipLaunchKernelGGL(k_vox_count, dim3(a.n_blocks), block, 0, stream, a);
-  hipLaunchKernelGGL(k_vox_scan, dim3(1), block, 0, stream, a, tab);
-  hipLaunchKernelGGL(k_vox_emit, dim3(a.n_blocks), block, 0, stream, a);
+  hipLaunchKernelGGL(k_vox_emit, dim3(a.n_blocks), block, 0, stream, a, tab);
   if (voxel_of_point && max_pts > 0)
-    hipLaunchKernelGGL(k_vox_point, dim3((max_pts + kVoxBlock - 1) / kVoxBlock, B), block, 0, stream, a, tab);
+    hipLaunchKernelGGL(k_vox_point, dim3((max_pts + 4 * kVoxBlock - 1) / (4 * kVoxBlock), B), block, 0, stream, a, tab);
   return hipGetLastError();
 }
 
