@@ -187,7 +187,9 @@ def _hptr(a):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # The raw handle of torch's current stream on the current device, without a Stream object around it (made and taken apart
+    # for every call).
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(status, what):
