@@ -130,3 +130,22 @@ def test_binning_table(orc, n, n_target, in_order):
     lo, hi = _boxes(xyz, po)
     g = _run_gpu(xyz, po, lo, hi, n_target)
     _compare(g, orc.voxel_downsample(xyz, n_target, box_lo=lo, box_hi=hi, pt_offsets=po), n, 2.0)
+
+
+# Coordinates on the borders of cubes and a few fp32 steps beside them, where the product with 1 / s and the quotient by s can
+# fall on different sides; zeros, subnormals and tiny values among them, whose fixed point needs rounding.  Everything that
+# decides is a whole number and must be the same; runs of one, several and all lanes of a wave in one cube.
+@pytest.mark.parametrize("n,n_target", [(8, 5), (4_099, 30), (70_001, 150), (70_001, 20_000)])
+def test_cube_borders(orc, n, n_target):
+    import paper_2511_03126_amd as aura
+    rng = np.random.default_rng(n + n_target)
+    lo, hi = np.array([[-1.0, 0.0, -0.5]], np.float32), np.array([[0.9, 1.3, 0.7]], np.float32)
+    s, dims = aura.voxel_grid(lo[0], hi[0], n_target)
+    k = np.stack([rng.integers(0, int(d) + 1, n) for d in dims], axis=1)
+    k = k[np.lexsort(k.T)]
+    xyz = (lo.astype(np.float64) + k * np.float64(s)).astype(np.float32)
+    xyz = np.clip(xyz + rng.integers(-3, 4, (n, 3)).astype(np.float32) * np.spacing(np.abs(xyz)), lo, hi).astype(np.float32)
+    xyz[::7, 1] = rng.choice(np.array([0.0, 1e-42, 3e-20, 1e-9], np.float32), len(xyz[::7]))
+    po = np.array([0, n], np.int64)
+    g = _run_gpu(xyz, po, lo, hi, n_target)
+    _compare(g, orc.voxel_downsample(xyz, n_target, box_lo=lo, box_hi=hi, pt_offsets=po), n, 1.3)
