@@ -1602,6 +1602,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     // producers: they go first where both are ready (measured on 1024 channels with 24 views: 12 % faster; with seven
     // waves it does not pay).
     if constexpr (S + NP >= 8) __builtin_amdgcn_s_setprio(1);
+    // ... and so does a call without rows wait for its one producer (40 objects of two to four views 681 -> 669 us)
+    else if (NP == 1 && a.fused == nullptr) __builtin_amdgcn_s_setprio(1);
     const int w = span - kFirstProducer;
     int seq = 0;
     // The first producer wave takes the tickets (the counters are zeroed once per call, before its first launch) and
