@@ -596,8 +596,9 @@ static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream
 // them, so the more of them there are, the fewer rows pay.  With both kernels, us per call, two launches / one: 384 channels,
 // 10 materials 2001 rows 15.1 / 8.9, 20 000 15.9 / 14.3, 40 000 23.4 / 21.2, 65 000 24.2 / 30.9; 512 channels, 32 materials
 // 5000 rows 19.0 / 11.1, 10 000 18.9 / 16.7, 20 000 19.7 / 22.0; 50 materials 5000 rows 23.6 / 15.5, 10 000 24.1 / 23.1, 20 000
-// 25.7 / 31.6; 1024 channels, 32 materials 10 000 rows 28.0 / 23.5, 20 000 28.2 / 32.7.
-static bool few_rows(long long N, int K) { return N <= 40000 && N * K <= 400000; }
+// 25.7 / 31.6; 1024 channels, 10 materials 20 000 rows 26.6 / 25.1, 32 materials 10 000 rows 28.0 / 23.5, 20 000 28.2 / 32.7.
+// The line keeps clear of where the two meet.
+static bool few_rows(long long N, int K) { return N <= 40000 && N * K <= 250000; }
 
 hipError_t launch_material_scores(const float* fused, long long N, int D, const float* temb, int K,
                                   const float* y, int P, float temperature, float* scores, float* prop,
