@@ -2056,8 +2056,8 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // works on a few objects at a time - their depth and feature maps stay in L2, where with eight workgroups per object
     // all 64 objects of a launch were in progress at once - and no workgroup is left with a fixed share of one object
     // while others have run out (64 objects of 100 000 points and 4 views: the workgroups' end times were spread over
-    // the last quarter of the kernel; fusion call, with the producers as they are now, 2.44 ms with 64 workgroups per object, 2.41 with
-    // 128, 2.43 with 256 and 512; with slower producers it was 2.34 with 256: the stores alone set the time, the combined call,
+    // the last quarter of the kernel; fusion call 2.44 ms with 64 workgroups per object, 2.41 with 128, 2.43 with 256 and 384
+    // (2.34 with 256 while the producers were slower: the pace of the row stores sets the time); the combined call,
     // whose workgroups also write the k-steps for the scoring kernel, 3.10 -> 2.94 ms with 64 and slower beyond).
     // At least eight tiles per workgroup beyond the resident ones (22 objects of 153 tiles, 2 views: 249 us with a workgroup
     // per tile, 214 with 24 per object).
