@@ -223,97 +223,105 @@ __global__ __launch_bounds__(256) void k_material_scores_few(ScoreArgs a) {
                                a.prop, a.label, a.unseen_zero != 0, s_stage[wave]);
 }
 
-// Few rows: what such a call takes is launches and the chain of a wave's steps, not bytes.  A workgroup of four waves shares
-// 32 rows, every fourth macro step to a wave, and adds the four partial sums up through LDS; the embeddings are split where
-// they are used (a row of them is read like a row of points), so no kernel has to run before this one.  2001 rows of 384
-// channels against 10 materials 15.1 -> 8.9 us, 40 rows 12.1 -> 9.1 (the host's time for a call).
+// Few rows: what such a call takes is launches and the chain of a wave's steps, not bytes.  A workgroup has 32 rows.  Its first
+// waves read rows and embeddings, two macro steps at a time and three such pairs ahead, split them into two terms (no kernel
+// has to run before this one) and leave the operands in LDS; a wave per 32 materials multiplies them, the steps in their order:
+// the products of a score are added up as every other kernel here adds them, so a row's scores do not depend on how many
+// rows the call has (and it takes no longer than a quarter of the steps to each of four waves and a sum of four parts did: 2001 rows
+// of 384 channels and 10 materials 7.0 and 7.1 us, 10 000 of 512 and 32 materials 14.9 and 16.1; two launches 14.6 and 18.1).
 template <int MT, typename T>
-__global__ __launch_bounds__(256) void k_material_scores_split(ScoreArgs a, const float* __restrict__ temb) {
-  constexpr int kWaves = 4;
+__global__ __launch_bounds__((2 + 3 * MT) * kWave) void k_material_scores_split(ScoreArgs a, const float* __restrict__ temb) {
+  constexpr int kReaders = 2 * (1 + MT);   // wave w: operand w / 2 (the rows, then 32 materials each), step w % 2 of a pair
+  constexpr int kAhead = 3;
   __shared__ float ys[MT * kTileM * kMaxP];
-  __shared__ f32x4 s_part[kWaves - 1][4 * MT][kWave];
+  __shared__ __attribute__((aligned(16))) Term8<T> s_op[2][2][1 + MT][2][2][kWave];   // [pair][step][operand][j][hi, lo]
+  __shared__ f32x4 s_part[MT > 1 ? MT - 1 : 1][4][kWave];
   __shared__ __attribute__((aligned(16))) float s_stage[score_stage_floats<16>()];
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const long long n0 = (long long)blockIdx.x * kTileN;
-  const float* __restrict__ row = a.fused + std::min<long long>(n0 + (lane & 31), a.N - 1) * a.D + (lane / 32) * 16;
-  const float* __restrict__ emb[MT];   // (a material beyond the last one: the last again, into sums that nobody reads)
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) emb[mt] = temb + (long long)min(mt * kTileM + (lane & 31), a.K - 1) * a.D + (lane / 32) * 16;
-  ScoreSums<MT, T> sum;
-
-  struct Piece { f32x4 v[4]; };   // a lane's 16 channels of a step
-  struct Step { Piece row, emb[MT]; };
-  const int last = a.steps - 1;
-  auto load = [&](int s, Step& b) {   // (past the end: the last step, read and not used)
-    const int at = min(s, last) * kStepK;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) b.row.v[q] = *reinterpret_cast<const f32x4*>(row + at + 4 * q);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b.emb[mt].v[q] = *reinterpret_cast<const f32x4*>(emb[mt] + at + 4 * q);
-  };
-  auto split = [](const Piece& b, Term8<T> (&hi)[2], Term8<T> (&lo)[2]) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        T h, l;
-        split_terms<T>(b.v[2 * j + (c >> 2)][c & 3], h, l);
-        hi[j][c] = h;
-        lo[j][c] = l;
-      }
-  };
-  auto products = [&](const Step& b) {
-    Term8<T> bh[2], bl[2];
-    split(b.row, bh, bl);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      Term8<T> eh[2], el[2];
-      split(b.emb[mt], eh, el);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        sum.acc[mt] = score_mma(eh[j], bh[j], sum.acc[mt]);
-        sum.low(mt) = score_mma(eh[j], bl[j], sum.low(mt));
-        sum.low(mt) = score_mma(el[j], bh[j], sum.low(mt));
-      }
-    }
-  };
-  Step b0, b1;
-  load(wave, b0);
-  load(wave + kWaves, b1);
+  const int pairs = (a.steps + 1) / 2;
   if (a.prop) {
     for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
   }
-  for (int s = wave; s < a.steps; s += 2 * kWaves) {   // uniform over the wave
-    products(b0);
-    load(s + 2 * kWaves, b0);
-    if (s + kWaves < a.steps) {
-      products(b1);
-      load(s + 3 * kWaves, b1);
+  if (wave < kReaders) {
+    const int op = wave >> 1, half = wave & 1;
+    // (a row or material beyond the last one: the last again, into sums that nobody reads)
+    const float* __restrict__ src = (op == 0 ? a.fused + std::min<long long>(n0 + (lane & 31), a.N - 1) * a.D
+                                             : temb + (long long)min((op - 1) * kTileM + (lane & 31), a.K - 1) * a.D) + (lane / 32) * 16;
+    struct Piece { f32x4 v[4]; } p[kAhead];   // the lane's 16 channels of a step
+    auto load = [&](int pair, Piece& b) {     // (past the end: the last step, read and not used)
+      const int at = min(2 * pair + half, a.steps - 1) * kStepK;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b.v[q] = *reinterpret_cast<const f32x4*>(src + at + 4 * q);
+    };
+    auto hand_over = [&](int pair, Piece& b) {
+      Term8<T>(&out)[2][2][kWave] = s_op[pair & 1][half][op];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        Term8<T> hi, lo;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          T h, l;
+          split_terms<T>(b.v[2 * j + (c >> 2)][c & 3], h, l);
+          hi[c] = h;
+          lo[c] = l;
+        }
+        out[j][0][lane] = hi;
+        out[j][1][lane] = lo;
+      }
+      load(pair + kAhead, b);
+      __syncthreads();
+    };
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) load(e, p[e]);
+    for (int i = 0; i < pairs; i += kAhead) {   // uniform over the workgroup: one barrier per pair here and below
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e)
+        if (i + e < pairs) hand_over(i + e, p[e]);
     }
+    if constexpr (MT > 1) __syncthreads();
+    return;
+  }
+  const int mt = wave - kReaders;
+  ScoreSums<1, T> sum;
+  auto products = [&](int s) {
+    const Term8<T>(&row)[2][2][kWave] = s_op[(s >> 1) & 1][s & 1][0];
+    const Term8<T>(&emb)[2][2][kWave] = s_op[(s >> 1) & 1][s & 1][1 + mt];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const Term8<T> bh = row[j][0][lane], bl = row[j][1][lane], eh = emb[j][0][lane], el = emb[j][1][lane];
+      sum.acc[0] = score_mma(eh, bh, sum.acc[0]);
+      sum.low(0) = score_mma(eh, bl, sum.low(0));
+      sum.low(0) = score_mma(el, bh, sum.low(0));
+    }
+  };
+  __syncthreads();   // the first pair is in LDS
+  for (int i = 0; i < pairs; ++i) {
+    products(2 * i);
+    if (2 * i + 1 < a.steps) products(2 * i + 1);
+    if (i + 1 < pairs) __syncthreads();   // the next pair is there, and this one's place is free
   }
   sum.join();
-  if (wave > 0) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+  f32x16 acc[MT];
+  acc[0] = sum.acc[0];
+  if constexpr (MT > 1) {
+    if (mt > 0) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        s_part[wave - 1][4 * mt + q][lane] = f32x4{sum.acc[mt][4 * q], sum.acc[mt][4 * q + 1], sum.acc[mt][4 * q + 2], sum.acc[mt][4 * q + 3]};
-  }
-  __syncthreads();
-  if (wave > 0) return;
+        s_part[mt - 1][q][lane] = f32x4{acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
+    }
+    __syncthreads();
+    if (mt > 0) return;
 #pragma unroll
-  for (int w = 0; w < kWaves - 1; ++w)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int t = 1; t < MT; ++t)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4 part = s_part[w][4 * mt + q][lane];
+        const f32x4 part = s_part[t - 1][q][lane];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum.acc[mt][4 * q + e] += part[e];
+        for (int e = 0; e < 4; ++e) acc[t][4 * q + e] = part[e];
       }
-  finish_scores_staged<MT, 16>(sum.acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
+  }
+  finish_scores_staged<MT, 16>(acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
                                a.prop, a.label, a.unseen_zero != 0, s_stage);
 }
 
@@ -592,13 +600,18 @@ static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream
   return hipErrorInvalidValue;
 }
 
-// Which calls of up to 64 materials take k_material_scores_split: every workgroup of 32 rows reads the embeddings and splits
-// them, so the more of them there are, the fewer rows pay.  With both kernels, us per call, two launches / one: 384 channels,
-// 10 materials 2001 rows 15.1 / 8.9, 20 000 15.9 / 14.3, 40 000 23.4 / 21.2, 65 000 24.2 / 30.9; 512 channels, 32 materials
-// 5000 rows 19.0 / 11.1, 10 000 18.9 / 16.7, 20 000 19.7 / 22.0; 50 materials 5000 rows 23.6 / 15.5, 10 000 24.1 / 23.1, 20 000
-// 25.7 / 31.6; 1024 channels, 10 materials 20 000 rows 26.6 / 25.1, 32 materials 10 000 rows 28.0 / 23.5, 20 000 28.2 / 32.7.
-// The line keeps clear of where the two meet.
-static bool few_rows(long long N, int K) { return N <= 40000 && N * K <= 250000; }
+// Which calls of up to 64 materials take k_material_scores_split: those of up to two of its workgroups per compute unit (512
+// of 32 rows), of up to three with at most 16 materials and 1024 channels.  Every workgroup reads and splits the embeddings, and
+// each round of workgroups adds to the time; the two launches take as long for 500 rows as for 30 000.  us per call, two
+// launches / one (rows x channels, materials):
+//   2001 x 384, 10     14.6 / 7.0     5000 x 512, 50     22.4 / 13.1     10 000 x 1024, 64   34.6 / 32.9
+//   16 384 rows        x 32, 1   7.5 / 5.4     x 64, 64   13.8 / 13.6    x 512, 64   24.0 / 22.9    x 1024, 16   26.5 / 18.0
+//                      x 2048, 64   56.3 / 54.0      x 4096, 32   87.0 / 65.0
+//   16 385 rows        x 256, 32   13.9 / 12.9       x 64, 64   13.9 / 19.7          x 512, 64   24.0 / 32.3
+//   24 576 rows        x 32, 16   8.5 / 8.5    x 512, 16   17.9 / 16.3   x 512, 20   18.9 / 17.7   x 1024, 16   26.6 / 25.0
+//                      x 1024, 20   27.3 / 26.6      x 2048, 16   44.0 / 46.5
+//   24 577 rows        x 256, 16   13.1 / 13.2       x 512, 16   17.9 / 19.3         x 1024, 16   26.7 / 31.2
+static bool few_rows(long long N, int D, int K) { return N <= 16384 || (N <= 24576 && K <= 16 && D <= 1024); }
 
 hipError_t launch_material_scores(const float* fused, long long N, int D, const float* temb, int K,
                                   const float* y, int P, float temperature, float* scores, float* prop,
@@ -610,8 +623,8 @@ hipError_t launch_material_scores(const float* fused, long long N, int D, const 
   ScoreArgs a{fused, N, D, K, P, y, 1.0f / temperature, unseen_zero, scores, prop, label,
               static_cast<const bf16x8*>(workspace), S};
   const bool aligned = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(fused) & 15) == 0;
-  if (MT <= 2 && few_rows(N, K) && aligned && D % kStepK == 0 && (reinterpret_cast<uintptr_t>(temb) & 15) == 0) {
-    const dim3 grid((unsigned)((N + kTileN - 1) / kTileN)), block(256);
+  if (MT <= 2 && few_rows(N, D, K) && aligned && D % kStepK == 0 && (reinterpret_cast<uintptr_t>(temb) & 15) == 0) {
+    const dim3 grid((unsigned)((N + kTileN - 1) / kTileN)), block((2 + 3 * MT) * kWave);
     if (f16_terms) {
       if (MT == 1) hipLaunchKernelGGL((k_material_scores_split<1, TermH>), grid, block, 0, stream, a, temb);
       else hipLaunchKernelGGL((k_material_scores_split<2, TermH>), grid, block, 0, stream, a, temb);
