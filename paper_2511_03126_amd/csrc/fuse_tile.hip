@@ -826,6 +826,7 @@ struct ProdArgs {
   float* factor;        // [N] or nullptr: what each point's raw tile product was multiplied by
   float norm_eps;
   int mean_only;
+  int pace;             // k_tile_fused: shortest time between two tiles of a workgroup, in ticks of the 100 MHz counter
 };
 
 // DT: 1 bf16, 2 fp16 feature maps.  S waves per workgroup, each owning H pieces of 128 channels:
@@ -1766,6 +1767,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     StepC wc;
     StepQ<H> rq[PF];
     int buf = 0;
+    unsigned long long started = 0;   // when the tile in work began, by the first wave's look at the counter
     if (s_slot[0].tile >= 0)
       open_tile<H, PF>(s_steps[0], min(max(s_slot[0].nsteps, 0), kStage), a.feat, lane_off, lane, g, wa, rq);
 
@@ -1869,6 +1871,12 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
         }
       } else if (lane < kTilePts) {   // nobody sees the tile's points
         s_ss[buf][span][lane] = 0.0f;
+      }
+      if constexpr (!SC) {
+        if (a.pace != 0 && span == 0) {   // see launch_tile (the other waves wait at the barrier; a counter that runs on ends it)
+          while (__builtin_amdgcn_s_memrealtime() - started < (unsigned long long)a.pace) __builtin_amdgcn_s_sleep(4);
+          started = __builtin_amdgcn_s_memrealtime();
+        }
       }
       __syncthreads();   // the one barrier of a tile: the sums are in LDS, the producers have staged the next tile, and
                          // every product wave is done with this tile's buffer
@@ -2034,7 +2042,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
                               hipStream_t stream, bool* scored) {
   const int max_tiles = (max_pts + kTilePts - 1) / kTilePts;
   ProdArgs pa{static_cast<const char*>(a.feat.feat), a.feat.D, ws.hdr, ws.steps, ws.counters + (size_t)ws.obj_base * kXcd,
-              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only};
+              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0};
   int max_views = 0;
   long long tiles = 0;
   for (int t = 0; t < n_obj; ++t) {
@@ -2056,12 +2064,24 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // works on a few objects at a time - their depth and feature maps stay in L2, where with eight workgroups per object
     // all 64 objects of a launch were in progress at once - and no workgroup is left with a fixed share of one object
     // while others have run out (64 objects of 100 000 points and 4 views: the workgroups' end times were spread over
-    // the last quarter of the kernel; fusion call 2.44 ms with 64 workgroups per object, 2.41 with 128, 2.43 with 256 and 384
-    // (2.34 with 256 while the producers were slower: the pace of the row stores sets the time); the combined call,
+    // the last quarter of the kernel; fusion call 2.44 ms with 64 workgroups per object, 2.41 with 128, 2.43 with 256 and 384,
+    // 24 objects of 256 channels 506, 498, 522 and 573 us, 32 objects of 8 views 754, 727, 741 and 741; the combined call,
     // whose workgroups also write the k-steps for the scoring kernel, 3.10 -> 2.94 ms with 64 and slower beyond).
     // At least eight tiles per workgroup beyond the resident ones (22 objects of 153 tiles, 2 views: 249 us with a workgroup
     // per tile, 214 with 24 per object).
     const int per_object = n_obj > 1 ? std::min((keep || scoring) ? 64 : 128, max_tiles / 8 / kXcd * kXcd) : 0;
+    // Where nothing but the row stores sets the time, the workgroups must not run ahead of the memory: tiles that nobody sees
+    // are stored as fast as they can be issued, and the more of that, the less of it memory takes (the faster producers made
+    // such calls slower).  A workgroup then starts no tile sooner than 4.6 us after the last: its 64 KiB, times the 512 resident
+    // workgroups, are 7.3 TB/s, a little above what a fill reaches.  us without / with it (in brackets with the slower producers):
+    //   channels 512, objects x points, views   64 x 100 000, 4   2412 / 2317 (2357)     16 x 100 000, 4   648 / 625 (656)
+    //     64 x 25 000, 4   620 / 598 (615)      40 x 50 000, 2 to 4   788 / 721 (784)    20 x 100 000, 3   793 / 759 (793)
+    //     40 x 30 000, 3   489 / 454 (461)      40 x 30 000, 2   493 / 453 (477)         20 x 30 000, 2   260 / 252 (253)
+    //     16 x 60 000, 1   392 / 379 (408)
+    // Not for others.  More views: the producers are what it waits for (paced, 32 x 60 000, 8 views 721 -> 734).  Few tiles or few
+    // objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 -> 110;
+    // 6 x 300 000, 4 views 708 -> 781).  256 channels 498 -> 508, 768 435 -> 452, 1024 no difference.
+    if (S == 2 && !keep && !scoring && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * (S + np + (scoring ? 1 : 0)));
     const TimingRequest timed = take_timing_request();
