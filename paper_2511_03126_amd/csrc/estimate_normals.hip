@@ -9,7 +9,7 @@
 //
 // Usual path (k up to 256), one sweep over the cloud:
 //   1. an upper bound of the k-th smallest distance that is exact by construction: the k-th smallest distance among
-//      every stride-th quad of points (at most 16384 points, kept in LDS; the k-th smallest of a subset can only be larger);
+//      every stride-th quad of points, or point (at most 16384 points, kept in LDS; the k-th smallest of a subset can only be larger);
 //   2. one sweep over the whole cloud collects the points within that bound (about k * stride of them) in LDS
 //      (a cloud that fits the list goes there whole, without a bound);
 //   3. among those, the k-th smallest distance by a radix select over the bit pattern of d (non-negative floats order
@@ -22,19 +22,17 @@
 // The queries of a call run side by side; the cloud comes from L2 (a few MB) or the last-level cache.
 #include "aura_device.hpp"
 #include "launch.hpp"
+#include "normals_subset.hpp"
 
 namespace aura {
 
 constexpr int kNrmBlock = 1024;   // a sweep over the cloud is shared by 16 waves
 constexpr int kNrmBins = 2048;
-// The strided subset that bounds the k-th distance lies far apart in memory: a read of a wave touches a cache line per
-// lane, 16384 single points three times that.  Quads of neighbouring points (48 bytes, three 16-byte loads) take a quarter of
-// the lines and a sixteenth of the loads; the sweep reads quads too (with the matrices of the last step in registers, 150 queries against 200 000 points 56 -> 46.6 us,
-// against 1 M points 174 -> 154, against 8000, all of them candidates, 26 -> 20).
-// Half the size where the candidates (about k * stride) stay few.
-constexpr int kNrmSubSmall = 8192, kNrmSub = 16384;
-constexpr int kNrmFewCand = 1500;
-constexpr int kNrmCand = 8192;    // candidates the LDS list holds (distance and index: as many words as the subset)
+// The strided subset that bounds the k-th distance (normals_subset.hpp) lies far apart in memory: a read of a wave touches a
+// cache line per lane, 16384 single points three times that.  Quads of neighbouring points (48 bytes, three 16-byte loads) take
+// a quarter of the lines and a sixteenth of the loads; the sweep reads quads too (with the matrices of the last step in
+// registers, 150 queries of 30 neighbours against 200 000 points 56 -> 46.6 us, against 1 M points 174 -> 154, against 8000, all
+// of them candidates, 26 -> 20).
 static_assert(kNrmSub <= 2 * kNrmCand, "the subset lies where the candidates go later");
 constexpr int kNrmSel = 256;      // largest k of the one-sweep path
 
@@ -275,23 +273,32 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
       }
       if (threadIdx.x == 0) { s_cn = n; s_ns = 0; }
     } else {
-      const int small = (n + kNrmSubSmall - 1) / kNrmSubSmall;
-      const int stride = kk * small <= kNrmFewCand ? small : (n + kNrmSub - 1) / kNrmSub;
-      const int n_sub = (n / 4 + stride - 1) / stride;   // quads: at least 1024, at most kNrmSub / 4, and kk <= 256
-      for (int j0 = threadIdx.x; j0 < n_sub; j0 += kTrip * kNrmBlock) {
-        PointQuad q[kTrip];
+      const NrmSubset sub = nrm_subset(n, kk);   // uniform
+      if (sub.run == 4) {
+        for (int j0 = threadIdx.x; j0 < sub.count; j0 += kTrip * kNrmBlock) {
+          PointQuad q[kTrip];
 #pragma unroll
-        for (int e = 0; e < kTrip; ++e) q[e] = quad(4 * stride * min(j0 + e * kNrmBlock, n_sub - 1));
+          for (int e = 0; e < kTrip; ++e) q[e] = quad(4 * sub.stride * min(j0 + e * kNrmBlock, sub.count - 1));
 #pragma unroll
-        for (int e = 0; e < kTrip; ++e) {
-          uint32_t d[4];
-          quad_dist(q[e], qx, qy, qz, d);
-          if (j0 + e * kNrmBlock < n_sub) *reinterpret_cast<uint4*>(s_list + 4 * (j0 + e * kNrmBlock)) = uint4{d[0], d[1], d[2], d[3]};
+          for (int e = 0; e < kTrip; ++e) {
+            uint32_t d[4];
+            quad_dist(q[e], qx, qy, qz, d);
+            if (j0 + e * kNrmBlock < sub.count) *reinterpret_cast<uint4*>(s_list + 4 * (j0 + e * kNrmBlock)) = uint4{d[0], d[1], d[2], d[3]};
+          }
+        }
+      } else {
+        for (int j0 = threadIdx.x; j0 < sub.count; j0 += 8 * kNrmBlock) {
+          uint32_t d[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d[e] = dist(min(j0 + e * kNrmBlock, sub.count - 1) * sub.stride);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (j0 + e * kNrmBlock < sub.count) s_list[j0 + e * kNrmBlock] = d[e];
         }
       }
       __syncthreads();
-      const uint32_t bound = radix_select(4 * n_sub, kk, [&](int j) { return s_list[j]; }, [](int) { return true; }, s_hist,
-                                          s_pick, &n_equal, &need);
+      const uint32_t bound = radix_select(sub.run * sub.count, kk, [&](int j) { return s_list[j]; }, [](int) { return true; },
+                                          s_hist, s_pick, &n_equal, &need);
       if (threadIdx.x == 0) { s_cn = 0; s_ns = 0; }
       __syncthreads();
       const int n_quads = (n + 3) / 4;

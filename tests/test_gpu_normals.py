@@ -162,7 +162,8 @@ def test_candidate_list_full_and_overflowing(orc, n, k):
     assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
 
 
-@pytest.mark.parametrize("n,k", [(8_192, 30), (8_193, 30), (16_385, 256), (409_600, 30), (409_601, 30), (40_000, 256)])
+@pytest.mark.parametrize("n,k", [(8_192, 30), (8_193, 30), (16_385, 256), (409_600, 30), (409_601, 30), (40_000, 256),
+                                 (245_760, 256), (245_761, 256), (245_763, 256)])      # the subset's runs: quads, then points
 def test_subset_sizes(orc, n, k):
     rng = np.random.default_rng(n + k)
     cloud = rng.standard_normal((n, 3)).astype(np.float32) * np.array([1.0, 0.6, 0.3], np.float32)
