@@ -98,8 +98,9 @@ constexpr int kVoxSlots = 1024;                  // 32 KiB of LDS: four workgrou
 // A thread takes 8 consecutive points, which in a spatially sorted cloud mostly share a cube, and goes to the table when
 // the cube changes.  An entry belongs to the first cube that claims it (index modulo 1024: objects of up to 1024 cubes
 // never collide); a cube that finds its entry taken adds to memory directly, so any number of cubes and any order of the
-// points is served.  Integer sums: the result does not depend on the order in which they land.  The next trip's run is
-// requested before this one is added up (whole call 64.0 -> 62.6 us; the kernel 33 us for 77 MB).  Not the bound: the divisions
+// points is served.  Integer sums: the result does not depend on the order in which they land.  The next trip's run, where there
+// is one, is requested before this one is added up (6.4 M points, three trips: whole call 64.0 -> 62.6 us, the kernel 33 us for
+// 77 MB; requested in the last trip too, 1 M points took 24.4 us instead of 22.9, 4 M 47.3 instead of 45.5).  Not the bound: the divisions
 // and the conversions to fixed point (a product with 1 / s and a guard, shifts) and lanes that meet at one entry (sums of up to
 // 16 lanes joined first) - with all three changed the kernel took 37 us.
 __global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab, int trips) {
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(kVoxBlock) void k_vox_bin(VoxArgs a, VoxTable tab, 
     const long long l0 = first + (long long)trip * kVoxTrip + threadIdx.x * kVoxPts;
     if (l0 >= ob.n_pts) break;
     r = r_next;
-    r_next = load(trip + 1);   // on its way while this trip is added up
+    if (trip + 1 < trips) r_next = load(trip + 1);   // (uniform) on its way while this trip is added up
     __builtin_amdgcn_sched_barrier(0);
     const long long l = min(l0, (long long)ob.n_pts - kVoxPts);
     long long q[3] = {0, 0, 0};
