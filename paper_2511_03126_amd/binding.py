@@ -186,10 +186,14 @@ def _hptr(a):
     return None if a is None else a.ctypes.data_as(C.c_void_p)
 
 
-def _stream():
-    # The raw handle of torch's current stream on the current device, without a Stream object around it (made and taken apart
-    # for every call).
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+# The handle of torch's current stream on the current device.  Without a Stream object around it (made and taken apart for every
+# call), where this torch has the two functions that give it so.
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _check(status, what):

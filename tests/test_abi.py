@@ -398,3 +398,20 @@ def test_static_scratch_call_refuses_what_does_not_fit(B):
     assert call(K=129) == -7 and call(P=9) == -7 and call(D=0) == -2
     assert call(dt=5) == -3
     assert call(N=0, fused=None, scores=None) == 0       # (every call above is refused before anything is launched)
+
+
+def test_stream_handle_where_torch_does_not_offer_the_raw_one(B, monkeypatch):
+    """The binding asks torch for the current stream's handle by the shortest way that this torch has; a torch without it is
+    asked through its public interface."""
+    import importlib.util
+    import sys
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    spec = importlib.util.spec_from_file_location("binding_without_raw_streams", B.__file__)
+    m = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, m)
+    spec.loader.exec_module(m)
+    assert m._stream() == 77
