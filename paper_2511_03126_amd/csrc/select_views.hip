@@ -27,17 +27,20 @@ struct SelArgs {
   int* n_sel;          // [N] or nullptr
 };
 
-// S_total of a visible pair: p the projection of the point (x, y, z) by the camera row c, (nx, ny, nz) its normal.
+// S_total of a visible pair: p the projection of the point (x, y, z) by the camera row c, (nx, ny, nz) its normal.  Every sum is
+// written out as the multiply-adds it is (left to the compiler, the two kernels took different ones, and a point's scores
+// depended on how many points the call had).
 __device__ __forceinline__ float view_score(const float* __restrict__ c, const Proj& p, float x, float y, float z, float nx, float ny,
                                             float nz) {
   const float xc = __builtin_fmaf(c[2], z, __builtin_fmaf(c[1], y, __builtin_fmaf(c[0], x, c[9])));
   const float yc = __builtin_fmaf(c[5], z, __builtin_fmaf(c[4], y, __builtin_fmaf(c[3], x, c[10])));
   const float zc = p.z;
-  const float rnx = c[0] * nx + c[1] * ny + c[2] * nz;   // the normal in the camera frame
-  const float rny = c[3] * nx + c[4] * ny + c[5] * nz;
-  const float rnz = c[6] * nx + c[7] * ny + c[8] * nz;
-  const float len = sqrtf(xc * xc + yc * yc + zc * zc);
-  const float s_angle = fmaxf(0.0f, -(xc * rnx + yc * rny + zc * rnz) / len);
+  const float rnx = __builtin_fmaf(c[2], nz, __builtin_fmaf(c[1], ny, c[0] * nx));   // the normal in the camera frame
+  const float rny = __builtin_fmaf(c[5], nz, __builtin_fmaf(c[4], ny, c[3] * nx));
+  const float rnz = __builtin_fmaf(c[8], nz, __builtin_fmaf(c[6], nx, c[7] * ny));
+  const float len = sqrtf(__builtin_fmaf(zc, zc, __builtin_fmaf(xc, xc, yc * yc)));
+  const float facing = __builtin_fmaf(zc, rnz, __builtin_fmaf(rnx, xc, rny * yc));
+  const float s_angle = fmaxf(0.0f, -facing / len);
   return s_angle / (1.0f + zc);
 }
 
@@ -45,7 +48,7 @@ __device__ __forceinline__ float view_score(const float* __restrict__ c, const P
 // together; a visible view's place is the number of visible views that come before it (larger score, of equal scores the
 // lower view), so there is no list and no order to keep.  A thread per point is a chain of projections, depth reads and
 // insertions in one or two workgroups: 16 000 points and less, 16 views 17.0 -> 9.5 us, 64 views 61 -> 16.3, 4 views 9.4 and
-// 9.7 (150 points of 16 views cost a queue 16.5 us, less than its host's 11 now).
+// 9.7; 150 points, GPU time alone, 16 views 11.2 -> 3.0 us, 64 views 45.8 -> 3.2.
 __global__ __launch_bounds__(256) void k_select_views_wave(SelArgs a, ObjTable tab) {
   const ObjRange ob = tab.o[blockIdx.y];
   const int lane = threadIdx.x % kWave;

@@ -103,6 +103,55 @@ def test_a_wave_per_point_chooses_as_a_thread_per_point(name, kw, k):
     assert differ <= 2
 
 
+# The wave has a lane per view, up to 64; a thread per point takes more views, and calls of more than 16 384 points.  Rows of
+# the mask longer than the wave.
+@pytest.mark.parametrize("V,N,k", [(33, 1_001, 3), (64, 1_001, 8), (65, 1_001, 8), (40, 16_384, 4), (40, 16_385, 4)])
+def test_views_in_both_halves_of_the_wave(orc, V, N, k):
+    import paper_2511_03126_amd as aura
+    import gpu_harness as H
+    s, nrm = _scene("c1", n_points=N, overrides=dict(V=V, D=32))
+    d = H.DeviceScene(s)
+    out = [torch.full((N, k), -7, dtype=torch.int32, device=d.dev), torch.full((N, k), float("nan"), device=d.dev),
+           torch.full((N, 80), 9, dtype=torch.uint8, device=d.dev), torch.full((N,), -7, dtype=torch.int32, device=d.dev)]
+    aura.select_views(d.views, d.params, d.xyz, torch.from_numpy(nrm).to(d.dev), k, *out)
+    ref = orc.select_views(s.cam, s.depth, s.xyz, nrm, k, tau=s.tau, z_near=s.z_near, mask_pitch=80)
+    _check_selection(dict(zip(("sel_view", "sel_score", "sel_mask", "n_sel"), (t.cpu().numpy() for t in out))), ref, k)
+    assert ref["sel_view"].max() >= 32
+
+
+def test_equal_scores_in_both_halves_of_the_wave():
+    """Views 32 to 63 are the cameras and depth maps of 0 to 31 again: every choice is a view and its copy, the lower first."""
+    import paper_2511_03126_amd as aura
+    import gpu_harness as H
+    s, nrm = _scene("c1", n_points=3_001, overrides=dict(V=32, D=32))
+    d = H.DeviceScene(s)
+    one = _gpu_select(d, s, nrm, 4)
+    views = aura.Views(cam=torch.cat([d.views.cam] * 2), depth=torch.cat([d.views.depth] * 2), feat=None)
+    sel = torch.full((s.N, 8), -7, dtype=torch.int32, device=d.dev)
+    score = torch.full((s.N, 8), float("nan"), device=d.dev)
+    aura.select_views(views, d.params, d.xyz, torch.from_numpy(nrm).to(d.dev), 8, sel, score)
+    v, sc = one["sel_view"], one["sel_score"]
+    want = np.stack([v, np.where(v >= 0, v + 32, -1)], 2).reshape(s.N, 8)
+    n = 2 * (v >= 0).sum(1)
+    own = np.where(np.arange(8) < n[:, None], want, -1)
+    distinct = ~((sc[:, 1:] == sc[:, :-1]) & (v[:, 1:] >= 0)).any(1)     # (two cameras of one score: both before their copies)
+    assert distinct.mean() > 0.5 and np.array_equal(sel.cpu().numpy()[distinct], own[distinct])
+    assert np.array_equal(score.cpu().numpy(), np.repeat(sc, 2, axis=1))
+
+
+def test_a_point_is_given_the_same_scores_in_any_call():
+    import paper_2511_03126_amd as aura
+    import gpu_harness as H
+    s, nrm = _scene("c1", n_points=20_000, overrides=dict(V=32, D=32))
+    d = H.DeviceScene(s)
+    whole = _gpu_select(d, s, nrm, 8)
+    sel = torch.full((10_000, 8), -7, dtype=torch.int32, device=d.dev)
+    score = torch.full((10_000, 8), float("nan"), device=d.dev)
+    aura.select_views(d.views, d.params, d.xyz[:10_000], torch.from_numpy(nrm[:10_000]).to(d.dev), 8, sel, score)
+    assert np.array_equal(score.cpu().numpy(), whole["sel_score"][:10_000])
+    assert np.array_equal(sel.cpu().numpy(), whole["sel_view"][:10_000])
+
+
 def test_hand_worked_rig_on_the_gpu():
     """Cameras on a line at known distances: S_total = 1 / (1 + distance), nearest first; equal distances by index; a
     camera behind the surface scores 0 and comes last."""
