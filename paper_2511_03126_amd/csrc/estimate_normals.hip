@@ -91,14 +91,15 @@ __device__ uint32_t radix_select(int n, int want, Key key, Eligible eligible, ui
     for (int b = threadIdx.x; b < kNrmBins; b += kNrmBlock) s_hist[b] = 0;
     __syncthreads();
     // four points per thread and trip, so that their reads are in flight together
-    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kNrmBlock) {
+    // (unsigned: past the end of the largest cloud, 2^31 - 1 points, the index has to stay above n)
+    for (uint32_t i0 = threadIdx.x; i0 < (uint32_t)n; i0 += 4 * kNrmBlock) {
       uint32_t kv[4];
       bool cand[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int i = i0 + e * kNrmBlock;
-        cand[e] = i < n && eligible(i);
-        kv[e] = cand[e] ? key(i) : 0u;
+        const uint32_t i = i0 + e * kNrmBlock;
+        cand[e] = i < (uint32_t)n && eligible((int)i);
+        kv[e] = cand[e] ? key((int)i) : 0u;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -301,14 +302,14 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
                                           s_hist, s_pick, &n_equal, &need);
       if (threadIdx.x == 0) { s_cn = 0; s_ns = 0; }
       __syncthreads();
-      const int n_quads = (n + 3) / 4;
+      const int n_quads = nrm_quads(n);
       for (int g0 = threadIdx.x; g0 < n_quads; g0 += kTrip * kNrmBlock) {
         PointQuad q[kTrip];
-        int first[kTrip];   // the last quad may begin before its place: points that the quad before it holds are left out
+        NrmQuad at[kTrip];
 #pragma unroll
         for (int e = 0; e < kTrip; ++e) {
-          first[e] = min(4 * (g0 + e * kNrmBlock), n - 4);
-          q[e] = quad(first[e]);
+          at[e] = nrm_quad(g0 + e * kNrmBlock, n);
+          q[e] = quad(at[e].first);
         }
 #pragma unroll
         for (int e = 0; e < kTrip; ++e) {
@@ -316,9 +317,9 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
           quad_dist(q[e], qx, qy, qz, d);
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            if (d[c] <= bound && first[e] + c >= 4 * (g0 + e * kNrmBlock)) {
+            if (d[c] <= bound && c >= at[e].skip) {
               const int pos = atomicAdd(&s_cn, 1);
-              if (pos < kNrmCand) { s_cd[pos] = d[c]; s_ci[pos] = first[e] + c; }
+              if (pos < kNrmCand) { s_cd[pos] = d[c]; s_ci[pos] = at[e].first + c; }
             }
           }
         }
@@ -369,19 +370,19 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
       last_idx = (int)radix_select(n, need, [](int i) { return (uint32_t)i; }, [&](int i) { return dist(i) == tau; }, s_hist,
                                    s_pick, &e2, &n2);
     }
-    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kNrmBlock) {
+    for (uint32_t i0 = threadIdx.x; i0 < (uint32_t)n; i0 += 4 * kNrmBlock) {   // (unsigned as in radix_select)
       float px[4], py[4], pz[4];
       bool in[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int i = min(i0 + e * kNrmBlock, n - 1);
+        const uint32_t i = min(i0 + e * kNrmBlock, (uint32_t)n - 1u);
         const float* __restrict__ p = pts + 3 * (long long)i;
         px[e] = p[0]; py[e] = p[1]; pz[e] = p[2];
-        in[e] = i0 + e * kNrmBlock < n;
+        in[e] = i0 + e * kNrmBlock < (uint32_t)n;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int i = i0 + e * kNrmBlock;
+        const int i = (int)(i0 + e * kNrmBlock);
         const float pe[3] = {px[e], py[e], pz[e]};
         const uint32_t d = dist_bits(pe, qx, qy, qz);
         if (in[e] && (d < tau || (d == tau && i <= last_idx))) {

@@ -1,4 +1,5 @@
-// Which points of a cloud give k_estimate_normals the upper bound of the k-th smallest distance.  Host and device.
+// Which points of a cloud give k_estimate_normals the upper bound of the k-th smallest distance, and which ones a thread of its
+// sweep reads.  Host and device.
 #pragma once
 
 #include <cmath>
@@ -33,6 +34,21 @@ AURA_HOST_DEVICE NrmSubset nrm_subset(int n, int k) {
   if ((float)stride * ((float)k + sqrtf(96.0f * (float)k) + 48.0f) <= (float)kNrmCand)
     return NrmSubset{4, stride, (n / 4 - 1) / stride + 1};   // at least 1024, at most kNrmSub / 4
   return NrmSubset{1, stride, (n - 1) / stride + 1};
+}
+
+// The sweep over n points (at least 4): nrm_quads(n) quads, of which number g (at most 4 * 1024 beyond the last, for n up to
+// 2^31 - 1) is read from point `first` on and adds its points but for the first `skip`: the last one may begin before its place,
+// those beyond add nothing.
+struct NrmQuad {
+  int first, skip;
+};
+
+AURA_HOST_DEVICE int nrm_quads(int n) { return (n - 1) / 4 + 1; }
+
+AURA_HOST_DEVICE NrmQuad nrm_quad(int g, int n) {
+  const unsigned place = 4u * (unsigned)g, last = (unsigned)n - 4u;
+  const unsigned first = place < last ? place : last;
+  return NrmQuad{(int)first, (int)(place - first)};
 }
 
 }  // namespace aura

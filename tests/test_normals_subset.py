@@ -17,7 +17,10 @@ def subset(tmp_path_factory):
     (d / "s.cpp").write_text('#include "normals_subset.hpp"\n'
                              'extern "C" void subset(int n, int k, int* o) {\n'
                              '  const aura::NrmSubset s = aura::nrm_subset(n, k);\n'
-                             '  o[0] = s.run; o[1] = s.stride; o[2] = s.count; o[3] = aura::kNrmCand; o[4] = aura::kNrmSub;\n}\n')
+                             '  o[0] = s.run; o[1] = s.stride; o[2] = s.count; o[3] = aura::kNrmCand; o[4] = aura::kNrmSub;\n}\n'
+                             'extern "C" void quad(int g, int n, int* o) {\n'
+                             '  const aura::NrmQuad q = aura::nrm_quad(g, n);\n'
+                             '  o[0] = q.first; o[1] = q.skip; o[2] = aura::nrm_quads(n);\n}\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", "-o", str(d / "s.so"), str(d / "s.cpp")], check=True)
     lib = ctypes.CDLL(str(d / "s.so"))
 
@@ -25,6 +28,12 @@ def subset(tmp_path_factory):
         o = (ctypes.c_int * 5)()
         lib.subset(n, k, o)
         return list(o)
+
+    def quad(g, n):
+        o = (ctypes.c_int * 3)()
+        lib.quad(g, n, o)
+        return list(o)
+    call.quad = quad
     return call
 
 
@@ -64,3 +73,18 @@ def test_subset_stays_in_the_cloud_and_in_its_array(subset):
         for k in (1, 2, 30, 64, 200, 256):
             run, stride, count, _, most = subset(n, k)
             assert (count - 1) * run * stride + run <= n and k <= count * run <= most
+
+
+@pytest.mark.parametrize("n", [8_193, 8_194, 8_195, 8_196, 2 ** 31 - 16_384, 2 ** 31 - 4, 2 ** 31 - 3, 2 ** 31 - 2, 2 ** 31 - 1])
+def test_sweep_reads_every_point_once(subset, n):
+    """The first quads and the last, and those that threads beyond the end read: inside the cloud, every point added once."""
+    quads = subset.quad(0, n)[2]
+    assert 4 * (quads - 1) < n <= 4 * quads
+    for g in [0, 1, quads // 2]:
+        assert subset.quad(g, n)[:2] == [4 * g, 0]
+    added = []
+    for g in range(quads - 3, quads + 4 * 1024):
+        first, skip, _ = subset.quad(g, n)
+        assert 0 <= first and first + 4 <= n and skip >= 0
+        added += range(first + min(skip, 4), first + 4)
+    assert added == list(range(4 * (quads - 3), n))
