@@ -359,7 +359,7 @@ hipError_t launch_voxel_downsample(const float* xyz, const VoxObj* objs, int B, 
   hipLaunchKernelGGL(k_vox_count, dim3(a.n_blocks), block, 0, stream, a);
   hipLaunchKernelGGL(k_vox_emit, dim3(a.n_blocks), block, 0, stream, a, tab);
   if (voxel_of_point && max_pts > 0)
-    hipLaunchKernelGGL(k_vox_point, dim3((max_pts + 4 * kVoxBlock - 1) / (4 * kVoxBlock), B), block, 0, stream, a, tab);
+    hipLaunchKernelGGL(k_vox_point, dim3((max_pts - 1) / (4 * kVoxBlock) + 1, B), block, 0, stream, a, tab);
   return hipGetLastError();
 }
 
