@@ -172,3 +172,51 @@ def test_subset_sizes(orc, n, k):
     _, g_w = _gpu(cloud, q, centre, k)
     ref = orc.estimate_normals(cloud, q, centre, k)
     assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
+
+
+@pytest.mark.parametrize("n,k", [(300_000, 30), (1_000_003, 128)])      # quads, then single points
+def test_cloud_in_scanner_order(orc, n, k):
+    """A surface stored row after row, where the points of a quad are next to each other in space."""
+    rng = np.random.default_rng(k)
+    rows = int(np.sqrt(n / 2))
+    cols = -(-n // rows)
+    z = np.repeat(1 - 2 * (np.arange(rows) + 0.5) / rows, cols)[:n]
+    a = np.tile(np.arange(cols) * (2 * np.pi / cols), rows)[:n]
+    r = np.sqrt(1 - z * z)
+    cloud = (np.stack([r * np.cos(a), r * np.sin(a), z], 1) * [1.0, 0.7, 0.45] + 0.1 / rows * rng.standard_normal((n, 3))).astype(np.float32)
+    q = cloud[rng.integers(0, n, 40)]
+    q[0], q[1] = cloud[0], cloud[-1]
+    centre = np.zeros((1, 3), np.float32)
+    g_n, g_w = _gpu(cloud, q, centre, k)
+    ref = orc.estimate_normals(cloud, q, centre, k)
+    _compare(g_n, g_w, ref, q, np.zeros((len(q), 3)), cloud, np.array([0, n]), np.array([0, len(q)]))
+
+
+# Covariances that the rotations meet as special cases: no entry off the diagonal, one, equal entries on the diagonal with a
+# positive and a negative one beside them, equal entries everywhere, one and no dimension.
+_AXES = np.concatenate([np.diag(s * np.array([1.0, 2.0, 4.0])) for s in (1, -1)])
+
+
+@pytest.mark.parametrize("cloud", [
+    pytest.param(_AXES, id="diagonal"),
+    pytest.param(_AXES[:, ::-1], id="diagonal descending"),
+    pytest.param(np.concatenate([np.eye(3), -np.eye(3)]), id="sphere"),
+    pytest.param([[1, 1, 0], [-1, -1, 0], [0, 0, 2], [0, 0, -2]], id="positive in xy"),
+    pytest.param([[1, -1, 0], [-1, 1, 0], [0, 0, 2], [0, 0, -2]], id="negative in xy"),
+    pytest.param([[1, 0, -1], [-1, 0, 1], [0, 2, 0], [0, -2, 0]], id="negative in xz"),
+    pytest.param([[0, 1, -1], [0, -1, 1], [2, 0, 0], [-2, 0, 0]], id="negative in yz"),
+    pytest.param([[1, 1, 1], [-1, -1, -1], [2, 2, 2]], id="line, positive"),
+    pytest.param([[1, -1, 1], [-1, 1, -1], [2, -2, 2]], id="line, mixed signs"),
+    pytest.param([[0, 0, 3], [0, 0, -3]], id="line along an axis"),
+    pytest.param([[0, 0, 0], [0, 0, 0]], id="one place"),
+])
+@pytest.mark.parametrize("scale", [1.0, 1e-17, 1e17])      # fp32 squares of the distances are subnormal, or nearly the largest
+def test_special_covariances(cloud, scale):
+    cloud = (np.asarray(cloud, np.float64) * scale).astype(np.float32)
+    g_n, g_w = _gpu(cloud, np.zeros((1, 3), np.float32), [[0.5, 0.25, -3]], len(cloud))
+    cov = np.cov(cloud.astype(np.float64).T, bias=True)
+    lam = np.linalg.eigvalsh(cov)
+    # sums, rotations and the reference are fp64 with a few dozen operations; eigenvalues are stored as fp32 (half a unit: 6e-8,
+    # below 1.2e-38 half of 1.4e-45)
+    assert np.abs(g_w[0] - lam).max() <= 1e-7 * lam[2] + 1e-45
+    assert abs(np.linalg.norm(g_n[0]) - 1) < 2e-7 and g_n[0] @ cov @ g_n[0] <= lam[0] + 1e-12 * lam[2]
