@@ -46,6 +46,7 @@
 
 #include "aura_device.hpp"
 #include "fuse_args.hpp"
+#include "fuse_tile_groups.hpp"
 #include "launch.hpp"
 #include "scores_epilogue.hpp"
 #include "timing.hpp"
@@ -852,8 +853,6 @@ struct ProdArgs {
 // contiguous range of the object's tiles and its workgroups take the next tile of that range from
 // a counter (tiles differ in length, a fixed split leaves a tail), so that at any time the tiles in
 // flight on an XCD are neighbours and share cell rows in its L2.
-constexpr int kXcd = 8;
-constexpr int kFusedGroupsMax = 512;  // one-kernel form: two workgroups per compute unit
 constexpr int kProdGroupsMax = 768;   // two workgroups fit a compute unit at a time; the rest take over as the first run out of tiles
 
 // The opening reads of a tile whose k-steps are staged at `sb` (n of them, possibly none): the rows of its
@@ -2059,17 +2058,13 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     const bool scoring = scoring_wave_fits(a, np, S);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
-    // Several objects in one launch: many more workgroups per object than are resident at a time.  The workgroups of
-    // an object share its tiles through the per-XCD tickets and are dispatched object after object, so the machine
-    // works on a few objects at a time - their depth and feature maps stay in L2, where with eight workgroups per object
-    // all 64 objects of a launch were in progress at once - and no workgroup is left with a fixed share of one object
-    // while others have run out (64 objects of 100 000 points and 4 views: the workgroups' end times were spread over
-    // the last quarter of the kernel; fusion call 2.44 ms with 64 workgroups per object, 2.41 with 128, 2.43 with 256 and 384,
-    // 24 objects of 256 channels 506, 498, 522 and 573 us, 32 objects of 8 views 754, 727, 741 and 741; the combined call,
-    // whose workgroups also write the k-steps for the scoring kernel, 3.10 -> 2.94 ms with 64 and slower beyond).
-    // At least eight tiles per workgroup beyond the resident ones (22 objects of 153 tiles, 2 views: 249 us with a workgroup
-    // per tile, 214 with 24 per object).
-    const int per_object = n_obj > 1 ? std::min((keep || scoring) ? 64 : 128, max_tiles / 8 / kXcd * kXcd) : 0;
+    // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
+    // of 100 000 points and 4 views with eight per object: the workgroups' end times were spread over the last quarter of the
+    // kernel; fusion call 2.79 ms, 2.44 with 64 per object, 2.41 with 128, 2.43 with 256 and 384).  The combined call, whose
+    // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.
+    const int per_object = n_obj <= 1 ? 0
+                         : (keep || scoring) ? std::min(64, max_tiles / 8 / kXcd * kXcd)
+                                             : fused_groups_per_object(S, np, n_obj, groups_max, max_tiles);
     // Where nothing but the row stores sets the time, the workgroups must not run ahead of the memory: tiles that nobody sees
     // are stored as fast as they can be issued, and the more of that, the less of it memory takes (the faster producers made
     // such calls slower).  A workgroup then starts no tile sooner than 4.6 us after the last: its 64 KiB, times the 512 resident
