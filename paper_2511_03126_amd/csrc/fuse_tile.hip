@@ -2073,10 +2073,17 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     //     64 x 25 000, 4   620 / 598 (615)      40 x 50 000, 2 to 4   788 / 721 (784)    20 x 100 000, 3   793 / 759 (793)
     //     40 x 30 000, 3   489 / 454 (461)      40 x 30 000, 2   493 / 453 (477)         20 x 30 000, 2   260 / 252 (253)
     //     16 x 60 000, 1   392 / 379 (408)
-    // Not for others.  More views: the producers are what it waits for (paced, 32 x 60 000, 8 views 721 -> 734).  Few tiles or few
-    // objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 -> 110;
-    // 6 x 300 000, 4 views 708 -> 781).  256 channels 498 -> 508, 768 435 -> 452, 1024 no difference.
-    if (S == 2 && !keep && !scoring && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
+    //   channels 768, with 6.9 us, the same rate                24 x 50 000, 4   714 / 677 (718)      50 x 40 000, 8   1124 / 1075 (1112)
+    //     24 x 50 000, 8   699 / 674 (696)      50 x 40 000, 3   1154 / 1088 (1135)    20 x 100 000, 6   1125 / 1088 (1121)
+    //     12 x 200 000, 3  1328 / 1294 (1340)   12 x 200 000, 8  1345 / 1299 (1341)
+    // Not for others.  More views: the producers are what it waits for (paced, 512 channels, 32 x 60 000, 8 views 721 -> 734).  Few
+    // tiles or few objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 ->
+    // 110; 6 x 300 000, 4 views 708 -> 781; 768 channels, 16 x 35 000, 6 views 348 -> 355).  256 channels 498 -> 508, 1024 no
+    // difference.
+    if (!keep && !scoring && np == 1) {
+      if (S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
+      if (S == 3 && n_obj >= 12 && tiles >= 64 * kFusedGroupsMax) pa.pace = 690;
+    }
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * (S + np + (scoring ? 1 : 0)));
     const TimingRequest timed = take_timing_request();
