@@ -2080,6 +2080,11 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // tiles or few objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 ->
     // 110; 6 x 300 000, 4 views 708 -> 781; 768 channels, 16 x 35 000, 6 views 348 -> 355).  256 channels 498 -> 508, 1024 no
     // difference.
+    // One object with four producers, one workgroup per compute unit: the same rate again, whatever the number of tiles (1.68 M voxels of
+    // 24 views, nine tiles of ten seen by nobody, 1024 channels 1232 / 1101 (1151), 512 channels 801 / 802 (984); 700 000 voxels, 12
+    // views, 768 channels 397 / 342 (365), 24 views, 1024 channels 525 / 476 (491); 30 000 points, 12 views, 1024 channels 59 / 57
+    // (60)).  Not several objects: 16 x 40 000, 10 views, 768 channels 391 -> 401.
+    if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 115 * S;
     if (!keep && !scoring && np == 1) {
       if (S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
       if (S == 3 && n_obj >= 12 && tiles >= 64 * kFusedGroupsMax) pa.pace = 690;
