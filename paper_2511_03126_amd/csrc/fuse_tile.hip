@@ -1099,10 +1099,15 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
 // orders its LDS traffic with wave-level fences.  Tiles go to workgroups through the per-XCD counters as before; the
 // producer asks for a ticket one tile ahead.  A tile whose list does not fit the buffer goes to the list of push_tile.
 
-constexpr int kPBatch = 16;   // views per pass of the producer waves: two per trip, one per half wave
+constexpr int kPBatch = 16;   // views per pass of the producer waves, at most: two per trip, one per half wave
 constexpr int kMaxProducers = 4;
 constexpr int kCamRows = 32;  // camera rows of the object kept in LDS for the producer
 constexpr int kOneKernelViews = 8;
+// A single producer is launched for up to kOneKernelViews views, so it makes four trips.  (With the eight of a full pass, of which the
+// last four were never made, what a trip holds was kept for all of them and the compiler's code was the longer for it: single
+// pass over 40 objects of 50 000 points and two to four views 660 -> 617 us, 64 of 100 000 and 4 views 1796 -> 1554, with rows as before.)
+template <int NP>
+constexpr int kPassViews = NP == 1 ? kOneKernelViews : kPBatch;
 
 typedef const float __attribute__((address_space(3))) * lds_floats;
 
@@ -1179,9 +1184,9 @@ __device__ __forceinline__ void producers_meet(lds_flags flags, int w, int& seq,
 // the image, the depth texel (requested, maybe still on its way) and, with a given selection, whether the view is kept.
 template <int NP>
 struct ProjectedBatch {
-  Proj pj[kPBatch / 2 / NP];
-  float dep[kPBatch / 2 / NP];
-  bool fr[kPBatch / 2 / NP], kept[kPBatch / 2 / NP];
+  Proj pj[kPassViews<NP> / 2 / NP];
+  float dep[kPassViews<NP> / 2 / NP];
+  bool fr[kPassViews<NP> / 2 / NP], kept[kPassViews<NP> / 2 / NP];
 };
 
 // First every projection and the request for its depth texel (and mask byte), nothing that waits for them: a wave has
@@ -1190,9 +1195,9 @@ struct ProjectedBatch {
 template <bool SEL, int NP>
 __device__ __forceinline__ void project_batch(const FuseArgs& a, const ObjRange& ob, int blk, float3 pt, int vb0,
                                               lds_floats cam_lds, int w, int lane, ProjectedBatch<NP>& f) {
-  constexpr int kTrips = kPBatch / 2 / NP;
+  constexpr int kTrips = kPassViews<NP> / 2 / NP;
   const int p = lane & 31, h = lane >> 5;
-  const int nvb = min(kPBatch, ob.n_views - vb0);
+  const int nvb = min(kPassViews<NP>, ob.n_views - vb0);
   const int li0 = blk * kTilePts;
   const long long ip = ob.pt_begin + li0 + (li0 + p < ob.n_pts ? p : 0);
 #pragma unroll
@@ -1232,7 +1237,7 @@ __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& 
                                              TileSlot<NP>* slot, ProducerScratch* sc, lds_floats cam_lds, lds_flags flags,
                                              const TileWs& ws, int obj, int* pushed, int w, int& seq, int lane) {
   unsigned* status = ws.status;
-  constexpr int kTrips = kPBatch / 2 / NP;   // trips of one wave per batch of views
+  constexpr int kTrips = kPassViews<NP> / 2 / NP;   // trips of one wave per batch of views
   const int p = lane & 31, h = lane >> 5;
   const int Hf = a.feat.Hf, Wf = a.feat.Wf;
   const uint32_t row_bytes = (uint32_t)a.feat.D * 2u;
@@ -1247,8 +1252,8 @@ __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& 
   for (int q = w * kWave + lane; q < dirty * 128; q += NP * kWave)
     reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&st[q >> 7]) + 64)[q & 127] = u32x4{0u, 0u, 0u, 0u};
 
-  for (int vb0 = 0; vb0 < ob.n_views; vb0 += kPBatch) {
-    const int nvb = min(kPBatch, ob.n_views - vb0);
+  for (int vb0 = 0; vb0 < ob.n_views; vb0 += kPassViews<NP>) {
+    const int nvb = min(kPassViews<NP>, ob.n_views - vb0);
     if (vb0 > 0) producers_meet<NP>(flags, w, seq, lane, status);   // the previous batch is done with the tables
     // the maps of this wave's views (view 2 it + h of trip it): 32 words each
 #pragma unroll
@@ -1298,7 +1303,7 @@ __device__ __forceinline__ void produce_tile(const FuseArgs& a, const ObjRange& 
     }
     wave_sync();
     // the next batch's depth texels arrive while this batch's lists and weights are made
-    if (vb0 + kPBatch < ob.n_views) project_batch<SEL, NP>(a, ob, blk, pt, vb0 + kPBatch, cam_lds, w, lane, pre);
+    if (vb0 + kPassViews<NP> < ob.n_views) project_batch<SEL, NP>(a, ob, blk, pt, vb0 + kPassViews<NP>, cam_lds, w, lane, pre);
 
     // ---- B: mark the touched cells of this wave's views that use a map: two cells of a row at a time (a map is as wide as
     // a row, so the second one is in the same word)
