@@ -119,6 +119,16 @@ __device__ __forceinline__ Tap tap_axis(float coord, float pitch, int size_grid)
 // materials).  exp(+0) is exactly 1.
 __device__ __forceinline__ float weight_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f); }
 
+// What the two halves of the wave hold at the same place, in both: x of lane % 32 and x of lane % 32 + 32 (one exchange in the
+// vector unit instead of a trip through the LDS unit).
+struct HalfPair {
+  float lo, hi;
+};
+__device__ __forceinline__ HalfPair half_pair(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return HalfPair{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);

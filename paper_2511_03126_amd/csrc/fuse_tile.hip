@@ -1562,7 +1562,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ __attribute__((aligned(16))) int s_flags[kMaxProducers];   // meeting numbers of the producer waves
   __shared__ int s_job[4];       // see drain_tiles
   __shared__ int s_drain;        // whether this workgroup looks at the lists of push_tile at its end
-  __shared__ float s_ys[SC ? kScoreTileM * kScoreMaxP : 1];   // the property table y[K][P]
+  __shared__ __attribute__((aligned(16))) float s_ys[SC ? kScoreTileM * kScoreMaxP : 1];   // the properties, see stage_properties
   __shared__ ScoreOut s_out[SC ? 2 : 1];                        // scores of the tile before the last, on their way to memory
 
   const ObjRange ob = tab.o[blockIdx.y];
@@ -1706,8 +1706,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       // (a product wave stores them during the next tile) while the rows of G for the next tile are on their way.
       const TileScoring& sc = fa.scoring;
       constexpr uint32_t row_units = S * H / 2;   // D / 256
-      if (sc.prop)
-        for (int t = lane; t < sc.K * sc.P; t += kWave) s_ys[t] = sc.y[t];
+      if (sc.prop) stage_properties<1>(s_ys, sc.y, sc.K, sc.P, lane, kWave);
       if (lane == 0) s_out[0].blk = s_out[1].blk = -1;
       if (!several) clear_stage();
       __syncthreads();
@@ -1739,12 +1738,12 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
           for (int r = 0; r < 16; ++r) acc[0][r] *= factor;
           if (blk >= 0) {   // a product wave stores the results during the next tile
             ScoreOut& o = s_out[buf ^ 1];
-            if (valid && n_prev >= 0)
-              finish_scores<1>(acc, (long long)m, g, sc.K, sc.P, sc.inv_T, s_ys, o.scores, sc.prop ? o.prop : nullptr,
+            if (n_prev >= 0)   // uniform
+              finish_scores<1>(acc, (long long)m, valid, g, sc.K, sc.P, sc.inv_T, s_ys, o.scores, sc.prop ? o.prop : nullptr,
                                sc.label ? o.label : nullptr, sc.unseen_zero != 0);
             if (lane == 0) o.blk = n_prev >= 0 ? blk_prev : -1;
-          } else if (valid && n_prev >= 0) {   // the workgroup's last tile: nobody is left to hand it to
-            finish_scores<1>(acc, ip, g, sc.K, sc.P, sc.inv_T, s_ys, sc.scores, sc.prop, sc.label, sc.unseen_zero != 0);
+          } else if (n_prev >= 0) {   // the workgroup's last tile: nobody is left to hand it to
+            finish_scores<1>(acc, ip, valid, g, sc.K, sc.P, sc.inv_T, s_ys, sc.scores, sc.prop, sc.label, sc.unseen_zero != 0);
           }
         }
         if (blk < 0) break;

@@ -210,13 +210,11 @@ __device__ __forceinline__ float score_products_staged(const float* __restrict__
 template <int MT, int MTK, bool ROWS_ALIGNED>
 __global__ __launch_bounds__(knn_waves(MT) * kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_knn_densify(KnnArgs a) {
   constexpr int kKnnWaves = knn_waves(MT);
-  __shared__ float ys[kScoreMaxK * kScoreMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kScoreTileM * MTK * kScoreMaxP];
   __shared__ float s_ws[kKnnLdsVectors];                // the sources' material vectors, when they fit
   __shared__ float s_out[kKnnWaves * score_stage_floats<16>()];   // per wave: score rows on their way to memory
   __shared__ sc_bf16x8 s_a[ROWS_ALIGNED ? 2 * MT * 2 * 2 * kWave : 1];   // split source features of two macro steps
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MTK>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   const bool ws_in_lds = a.Ns * a.K <= kKnnLdsVectors;   // uniform
   if (ws_in_lds) {
     for (int t = threadIdx.x; t < a.Ns * a.K; t += blockDim.x) s_ws[t] = a.ws[t];

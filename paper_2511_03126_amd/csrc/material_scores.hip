@@ -72,7 +72,6 @@ constexpr int kTileM = 32;      // materials per MFMA tile
 constexpr int kTileN = 32;      // points per wave
 constexpr int kStepK = 32;      // channels per macro step: lane group g = lane / 32 owns 16 of them
 constexpr int kMaxP = 8;
-constexpr int kMaxK = 128;
 
 struct ScoreArgs {
   const float* fused;
@@ -111,10 +110,8 @@ __global__ __launch_bounds__(256) void k_split_embeddings(const float* __restric
 
 template <int MT, bool ROWS_ALIGNED>
 __global__ __launch_bounds__(256) void k_material_scores(ScoreArgs a) {
-  __shared__ float ys[kMaxK * kMaxP];
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   __syncthreads();
 
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -133,8 +130,7 @@ __global__ __launch_bounds__(256) void k_material_scores(ScoreArgs a) {
 
   score_products<MT, ROWS_ALIGNED, false>(row, a.D, a.steps, a.a_split, lane, acc);
 
-  if (!valid) return;   // no cross-lane traffic below except with lane ^ 32, which holds the same point
-  finish_scores<MT>(acc, n, g, a.K, a.P, a.inv_T, ys, a.scores, a.prop, a.label, a.unseen_zero != 0);
+  finish_scores<MT>(acc, valid ? n : a.N - 1, valid, g, a.K, a.P, a.inv_T, ys, a.scores, a.prop, a.label, a.unseen_zero != 0);
 }
 
 // The same contraction for whole macro steps and 16-byte aligned rows, software-pipelined: what step s + 1 needs - the
@@ -146,11 +142,9 @@ __global__ __launch_bounds__(256) void k_material_scores(ScoreArgs a) {
 // read pattern reaches without arithmetic.
 template <int MT, typename T>
 __global__ __launch_bounds__(256) void k_material_scores_few(ScoreArgs a) {
-  __shared__ float ys[kMaxK * kMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
   __shared__ __attribute__((aligned(16))) float s_stage[4][score_stage_floats<16>()];
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   __syncthreads();
 
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -233,16 +227,14 @@ template <int MT, typename T>
 __global__ __launch_bounds__((2 + 3 * MT) * kWave) void k_material_scores_split(ScoreArgs a, const float* __restrict__ temb) {
   constexpr int kReaders = 2 * (1 + MT);   // wave w: operand w / 2 (the rows, then 32 materials each), step w % 2 of a pair
   constexpr int kAhead = 3;
-  __shared__ float ys[MT * kTileM * kMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
   __shared__ __attribute__((aligned(16))) Term8<T> s_op[2][2][1 + MT][2][2][kWave];   // [pair][step][operand][j][hi, lo]
   __shared__ f32x4 s_part[MT > 1 ? MT - 1 : 1][4][kWave];
   __shared__ __attribute__((aligned(16))) float s_stage[score_stage_floats<16>()];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const long long n0 = (long long)blockIdx.x * kTileN;
   const int pairs = (a.steps + 1) / 2;
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   if (wave < kReaders) {
     const int op = wave >> 1, half = wave & 1;
     // (a row or material beyond the last one: the last again, into sums that nobody reads)
@@ -335,13 +327,11 @@ constexpr int kLdsSlots = 32;
 // kLdsWaves waves per workgroup: 16 for up to 32 materials (128 registers per wave), 8 for up to 64.
 template <int MT, int kLdsWaves>
 __global__ __launch_bounds__(kLdsWaves* kWave) void k_material_scores_lds(ScoreArgs a) {
-  __shared__ float ys[MT * kTileM * kMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
   __shared__ __attribute__((aligned(16))) bf16x8 s_a[kLdsSlots * 2 * 2 * kWave];   // 128 KiB
   constexpr int kStageRows = kLdsWaves > 8 ? 8 : 16;
   __shared__ __attribute__((aligned(16))) float s_stage[kLdsWaves][score_stage_floats<kStageRows>()];
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   for (int t = threadIdx.x; t < a.steps * MT * 2 * 2 * kWave; t += blockDim.x) s_a[t] = a.a_split[t];
   __syncthreads();
 
@@ -431,13 +421,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(score_waves
 void k_material_scores_wide(ScoreArgs a) {
   constexpr int kBlock = MT * 2 * 2 * kWave;   // 16-byte operand slots of a step
   constexpr int kCopies = kBlock / 256;        // per thread
-  __shared__ float ys[kMaxK * kMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
   __shared__ __attribute__((aligned(16))) Term8<T> s_a[2][kBlock];
   __shared__ __attribute__((aligned(16))) float s_stage[4][score_stage_floats<16>()];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, g = lane / 32;
-  if (a.prop) {
-    for (int t = tid; t < a.K * a.P; t += 256) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, tid, 256);
   const long long n0 = ((long long)blockIdx.x * 4 + wave) * kTileN;   // a wave beyond the last row takes part in the copies
   const long long n = min(n0 + (lane & 31), a.N - 1);
   const float* __restrict__ row = a.fused + n * a.D + g * 16;

@@ -13,75 +13,120 @@ constexpr int kScoreTileM = 32;   // materials per matrix-core tile
 constexpr int kScoreMaxP = 8;
 constexpr int kScoreMaxK = 128;
 
-// Lane l = 32 g + (point within the wave's 32): accumulator element r of tile mt is the similarity of the
+// The property table in LDS as the epilogues read it: ys[p][m] with the materials padded to whole tiles by zeros, so that the values
+// of a lane's four consecutive materials are one 16-byte read.  ys holds kScoreTileM * MT * P floats, 16-byte aligned; called by all
+// `threads` threads, followed by a barrier.
+template <int MT>
+__device__ __forceinline__ void stage_properties(float* __restrict__ ys, const float* __restrict__ y, int K, int P, int thread,
+                                                 int threads) {
+  constexpr int kPad = kScoreTileM * MT;
+  for (int t = thread; t < kPad * P; t += threads) {
+    const int p = t / kPad, m = t % kPad;
+    ys[t] = m < K ? y[m * P + p] : 0.0f;
+  }
+}
+
+// Label and Eq. 4.  Lane l = 32 g + (point within the wave's 32): accumulator element r of tile mt is the similarity of the
 // lane's point to material mt*32 + 8*(r/4) + 4*g + r%4, so the two lanes l and l ^ 32 hold all K scores of one
-// point between them.  `ys` is y[K][P] in LDS.  Lanes whose point does not exist must not call this.
+// point between them.  `ys`: see stage_properties.  store: whether the lane writes its point's results; all 64 lanes call this.
+// The accumulators are used up.
 // unseen_zero: a point whose similarities are all exactly zero (the fused row of a point that no view sees is all
 // zero) gets zero properties instead of what Eq. 4 gives for equal similarities, the mean of y.
+// One straight line of instructions, with places beyond K holding -inf (weight 0): as a branch per material, eight per
+// material over P and an LDS read waited for in each, Eq. 4 held up whatever scored: single pass over 40 objects of 50 000 points and
+// 24 materials 622 -> 588 us (its scoring wave was what the other waves waited for), 1.68 M voxels and 128 materials 1183 -> 1130,
+// 123 457 points and 45 materials 184 -> 173 (with the stores of finish_scores_staged for any K), 200 000 queries densified 318 -> 307.
 template <int MT>
-__device__ __forceinline__ void finish_scores(const scores_f32x16 (&acc)[MT], long long n, int g, int K, int P, float inv_T,
-                                              const float* __restrict__ ys, float* __restrict__ scores,
-                                              float* __restrict__ prop, int* __restrict__ label, bool unseen_zero = false) {
-  float* __restrict__ srow = scores + n * K;
-  const bool vec_store = (K & 3) == 0 && ((reinterpret_cast<uintptr_t>(scores) & 15) == 0);
-  float best = -INFINITY;
-  int bidx = 0;
+__device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
+                                                  const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
+                                                  bool unseen_zero) {
   bool any_nonzero = false;
+  if (unseen_zero) {   // uniform
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int m0 = mt * kScoreTileM + 8 * q + 4 * g;
-      if (vec_store) {
-        if (m0 < K) {
-          scores_f32x4 v = {acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]};
-          *reinterpret_cast<scores_f32x4*>(srow + m0) = v;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (m0 + e < K) srow[m0 + e] = acc[mt][4 * q + e];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float sc = acc[mt][4 * q + e];
-        if (m0 + e < K && sc > best) { best = sc; bidx = m0 + e; }   // ascending m: lowest index wins ties
-        any_nonzero = any_nonzero || (m0 + e < K && sc != 0.0f);
-      }
-    }
-  {
-    const float ob = __shfl_xor(best, 32, kWave);
-    const int oi = __shfl_xor(bidx, 32, kWave);
-    if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
+      for (int r = 0; r < 16; ++r)
+        any_nonzero = any_nonzero || (mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3) < K && acc[mt][r] != 0.0f);
+    any_nonzero = any_nonzero || __shfl_xor((int)any_nonzero, 32, kWave) != 0;
   }
-  if (label && g == 0) label[n] = bidx;
-  if (!prop) return;
-  const bool zero_row = unseen_zero && !(any_nonzero || __shfl_xor((int)any_nonzero, 32, kWave) != 0);
-
-  float den = 0.0f, num[kScoreMaxP];
+  float best = -INFINITY;
+  int at = 0;   // material index without the lane group's 4 g
 #pragma unroll
-  for (int p = 0; p < kScoreMaxP; ++p) num[p] = 0.0f;
+  for (int mt = 0; mt < MT; ++mt) {
+    if ((mt + 1) * kScoreTileM > K) {   // uniform: the tile has places beyond K
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3) >= K) acc[mt][r] = -INFINITY;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)   // ascending material index within the lane: the lowest index wins ties
+      if (acc[mt][r] > best) {
+        best = acc[mt][r];
+        at = mt * kScoreTileM + 8 * (r >> 2) + (r & 3);
+      }
+  }
+  {
+    const HalfPair b = half_pair(best), i = half_pair(__int_as_float(at + 4 * g));
+    const int lo = __float_as_int(i.lo), hi = __float_as_int(i.hi);
+    const bool first = b.lo > b.hi || (b.lo == b.hi && lo < hi);
+    best = fmaxf(b.lo, b.hi);
+    if (label && store && g == 0) label[n] = first ? lo : hi;
+  }
+  if (!prop) return;
+  float den = 0.0f;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = mt * kScoreTileM + 8 * (r / 4) + 4 * g + (r & 3);
-      if (m < K) {
-        const float e = weight_exp((acc[mt][r] - best) * inv_T);
-        den += e;
+      const float e = weight_exp((acc[mt][r] - best) * inv_T);
+      acc[mt][r] = e;
+      den += e;
+    }
+  const HalfPair d = half_pair(den);
+  den = d.lo + d.hi;
+  const scores_f32x4* __restrict__ yv = reinterpret_cast<const scores_f32x4*>(ys) + g;
+  for (int p = 0; p < P; ++p, yv += kScoreTileM * MT / 4) {
+    float num = 0.0f;
 #pragma unroll
-        for (int p = 0; p < kScoreMaxP; ++p)
-          if (p < P) num[p] = __builtin_fmaf(e, ys[m * P + p], num[p]);
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const scores_f32x4 v = yv[(mt * kScoreTileM + 8 * q) / 4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num = __builtin_fmaf(acc[mt][4 * q + e], v[e], num);
       }
-    }
-  den += __shfl_xor(den, 32, kWave);
-#pragma unroll
-  for (int p = 0; p < kScoreMaxP; ++p) {
-    if (p < P) {
-      const float t = num[p] + __shfl_xor(num[p], 32, kWave);
-      if (g == 0) prop[n * P + p] = zero_row ? 0.0f : t / den;
-    }
+    const HalfPair s = half_pair(num);
+    if (store && g == 0) prop[n * P + p] = unseen_zero && !any_nonzero ? 0.0f : (s.lo + s.hi) / den;
   }
+}
+
+// Stores the scores of the lane's point as they are, then label and Eq. 4.  All 64 lanes call this; those whose point does not exist
+// with store == false.
+template <int MT>
+__device__ __forceinline__ void finish_scores(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
+                                              const float* __restrict__ ys, float* __restrict__ scores,
+                                              float* __restrict__ prop, int* __restrict__ label, bool unseen_zero = false) {
+  float* __restrict__ srow = scores + n * K;
+  const bool vec_store = (K & 3) == 0 && ((reinterpret_cast<uintptr_t>(scores) & 15) == 0);
+  if (store) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m0 = mt * kScoreTileM + 8 * q + 4 * g;
+        if (vec_store) {
+          if (m0 < K) {
+            scores_f32x4 v = {acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]};
+            *reinterpret_cast<scores_f32x4*>(srow + m0) = v;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (m0 + e < K) srow[m0 + e] = acc[mt][4 * q + e];
+        }
+      }
+  }
+  finish_label_prop<MT>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
 // The same for a whole wave whose 32 points are consecutive in memory (n0 .. n0 + rows - 1 exist), with the scores
@@ -89,101 +134,55 @@ __device__ __forceinline__ void finish_scores(const scores_f32x16 (&acc)[MT], lo
 // in the accumulator layout a store instruction writes 32 bytes of each of 32 rows, and those partial-line writes cost
 // the scoring kernels up to a fifth of their time (6.4 M points x 24 materials: 0.53 of 2.9 ms).  ROWS rows at a time
 // (16, or 8 where LDS is short) are laid out as [row][material] in the buffer and copied out sixteen bytes per lane,
-// eight neighbouring lanes per row.  All 64 lanes call this, also those whose point does not exist.
+// eight neighbouring lanes per row; four bytes per lane where K is no multiple of four.  All 64 lanes call this, also those whose
+// point does not exist.
 constexpr int kScoreStagePitch = 36;   // floats: rows start 4 banks apart
 template <int ROWS>
 constexpr int score_stage_floats() { return ROWS * kScoreStagePitch; }
 
 template <int MT, int ROWS>
-__device__ __forceinline__ void finish_scores_staged(const scores_f32x16 (&acc)[MT], long long n0, int rows, int lane, int K,
+__device__ __forceinline__ void finish_scores_staged(scores_f32x16 (&acc)[MT], long long n0, int rows, int lane, int K,
                                                      int P, float inv_T, const float* __restrict__ ys,
                                                      float* __restrict__ scores, float* __restrict__ prop,
                                                      int* __restrict__ label, bool unseen_zero, float* stage) {
   const int pt = lane & 31, g = lane >> 5;
-  const bool valid = pt < rows;
-  const long long n = n0 + (valid ? pt : 0);
-  if ((K & 3) == 0 && ((reinterpret_cast<uintptr_t>(scores) & 15) == 0)) {
+  const bool vec = (K & 3) == 0 && ((reinterpret_cast<uintptr_t>(scores) & 15) == 0);   // 16 bytes per lane, else four
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int cols = min(kScoreTileM, K - mt * kScoreTileM);   // a multiple of 4
-      if (cols <= 0) continue;                                    // uniform
-      const int per_row = cols >> 2;
+  for (int mt = 0; mt < MT; ++mt) {
+    const int cols = min(kScoreTileM, K - mt * kScoreTileM);
+    if (cols <= 0) continue;                                    // uniform
+    // pieces of a row: cols / 4 vectors or cols floats; idx / per_row by a multiplication, exact for idx < 512 and per_row <= 32
+    const int per_row = vec ? cols >> 2 : cols;
+    const uint32_t inv = 65536u / (uint32_t)per_row + 1u;
 #pragma unroll
-      for (int part = 0; part < 32 / ROWS; ++part) {
-        if (pt / ROWS == part) {
+    for (int part = 0; part < 32 / ROWS; ++part) {
+      if (pt / ROWS == part) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<scores_f32x4*>(stage + (pt % ROWS) * kScoreStagePitch + 8 * q + 4 * g) =
-                scores_f32x4{acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]};
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<scores_f32x4*>(stage + (pt % ROWS) * kScoreStagePitch + 8 * q + 4 * g) =
+              scores_f32x4{acc[mt][4 * q], acc[mt][4 * q + 1], acc[mt][4 * q + 2], acc[mt][4 * q + 3]};
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int here = min(ROWS, rows - part * ROWS) * per_row;   // pieces of the rows that exist
+      float* __restrict__ out = scores + (n0 + part * ROWS) * K + mt * kScoreTileM;
+      if (vec) {
+        for (int idx = lane; idx < here; idx += kWave) {
+          const int r = (int)((uint32_t)idx * inv >> 16), c4 = idx - r * per_row;
+          *reinterpret_cast<scores_f32x4*>(out + (long long)r * K + 4 * c4) =
+              *reinterpret_cast<const scores_f32x4*>(stage + r * kScoreStagePitch + 4 * c4);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int idx = lane; idx < ROWS * per_row; idx += kWave) {
-          const int r = idx / per_row, c4 = idx - r * per_row;
-          const int row = part * ROWS + r;
-          if (row < rows)
-            *reinterpret_cast<scores_f32x4*>(scores + (n0 + row) * K + mt * kScoreTileM + 4 * c4) =
-                *reinterpret_cast<const scores_f32x4*>(stage + r * kScoreStagePitch + 4 * c4);
+      } else {
+        for (int idx = lane; idx < here; idx += kWave) {
+          const int r = (int)((uint32_t)idx * inv >> 16), c = idx - r * per_row;
+          out[(long long)r * K + c] = stage[r * kScoreStagePitch + c];
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
       }
-    }
-  } else if (valid) {
-    float* __restrict__ srow = scores + n * K;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3);
-        if (m < K) srow[m] = acc[mt][r];
-      }
-  }
-  // label and Eq. 4 as in finish_scores; the two lanes of a point exchange with each other only
-  float best = -INFINITY;
-  int bidx = 0;
-  bool any_nonzero = false;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {   // ascending material index within the lane: the lowest index wins ties
-      const int m = mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3);
-      const float sc = acc[mt][r];
-      if (m < K && sc > best) { best = sc; bidx = m; }
-      any_nonzero = any_nonzero || (m < K && sc != 0.0f);
-    }
-  {
-    const float ob = __shfl_xor(best, 32, kWave);
-    const int oi = __shfl_xor(bidx, 32, kWave);
-    if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
-  }
-  if (label && g == 0 && valid) label[n] = bidx;
-  if (!prop) return;
-  const bool zero_row = unseen_zero && !(any_nonzero || __shfl_xor((int)any_nonzero, 32, kWave) != 0);
-  float den = 0.0f, num[kScoreMaxP];
-#pragma unroll
-  for (int p = 0; p < kScoreMaxP; ++p) num[p] = 0.0f;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mt * kScoreTileM + 8 * (r / 4) + 4 * g + (r & 3);
-      if (m < K) {
-        const float e = weight_exp((acc[mt][r] - best) * inv_T);
-        den += e;
-#pragma unroll
-        for (int p = 0; p < kScoreMaxP; ++p)
-          if (p < P) num[p] = __builtin_fmaf(e, ys[m * P + p], num[p]);
-      }
-    }
-  den += __shfl_xor(den, 32, kWave);
-#pragma unroll
-  for (int p = 0; p < kScoreMaxP; ++p) {
-    if (p < P) {
-      const float t = num[p] + __shfl_xor(num[p], 32, kWave);
-      if (g == 0 && valid) prop[n * P + p] = zero_row ? 0.0f : t / den;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   }
+  finish_label_prop<MT>(acc, n0 + (pt < rows ? pt : 0), pt < rows, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
 // What finish_scores_staged writes for 32 consecutive points whose similarities are all exactly +0 (a tile that no view
@@ -216,7 +215,7 @@ __device__ __forceinline__ void finish_zero_rows(long long n0, int rows, int lan
         den += 1.0f;
 #pragma unroll
         for (int p = 0; p < kScoreMaxP; ++p)
-          if (p < P) num[p] = __builtin_fmaf(1.0f, ys[m * P + p], num[p]);
+          if (p < P) num[p] = __builtin_fmaf(1.0f, ys[p * kScoreTileM * MT + m], num[p]);
       }
     }
   den += __shfl_xor(den, 32, kWave);

@@ -247,7 +247,7 @@ struct TileScoreArgs {
 
 template <int DT, int MT>
 __global__ __launch_bounds__(256) void k_tile_scores(TileScoreArgs a, ObjTable tab) {
-  __shared__ float ys[kScoreMaxK * kScoreMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kScoreTileM * MT * kScoreMaxP];
   __shared__ __attribute__((aligned(16))) float s_stage[4][score_stage_floats<16>()];
   const ObjRange ob = tab.o[blockIdx.y];
   const int nblk = (ob.n_pts + kTilePts - 1) / kTilePts;
@@ -258,9 +258,7 @@ __global__ __launch_bounds__(256) void k_tile_scores(TileScoreArgs a, ObjTable t
   // a tile that no view sees (k_tile_zero_rows writes its results); a workgroup of such tiles leaves at once.
   const bool mine = nsteps > 0 || (nsteps == 0 && !(0.0f * a.inv_T == 0.0f));
   if (!__syncthreads_or(mine)) return;
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   __syncthreads();
   if (!mine) return;
   const int pt = lane & 31, g = lane >> 5;
@@ -314,16 +312,14 @@ __global__ __launch_bounds__(256) void k_tile_scores(TileScoreArgs a, ObjTable t
 // kernel with 128 materials holds three waves per SIMD.  One wave per tile; workgroups without such a tile leave at once.
 template <int MT>
 __global__ __launch_bounds__(256) void k_tile_zero_rows(TileScoreArgs a, ObjTable tab) {
-  __shared__ float ys[kScoreMaxK * kScoreMaxP];
+  __shared__ __attribute__((aligned(16))) float ys[kScoreTileM * MT * kScoreMaxP];
   const ObjRange ob = tab.o[blockIdx.y];
   const int nblk = (ob.n_pts + kTilePts - 1) / kTilePts;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int tile = blockIdx.x * 4 + wave;
   const bool mine = tile < nblk && a.hdr[ob.tile_begin + (tile < nblk ? tile : 0)].nsteps == 0 && 0.0f * a.inv_T == 0.0f;
   if (!__syncthreads_or(mine)) return;
-  if (a.prop) {
-    for (int t = threadIdx.x; t < a.K * a.P; t += blockDim.x) ys[t] = a.y[t];
-  }
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
   __syncthreads();
   if (!mine) return;
   finish_zero_rows<MT>(ob.pt_begin + (long long)tile * kTilePts, min(kTilePts, ob.n_pts - tile * kTilePts), lane, a.K, a.P, ys,
