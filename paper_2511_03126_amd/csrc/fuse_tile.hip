@@ -116,24 +116,50 @@ __device__ __forceinline__ s16x2 half_wave_reduce(s16x2 v) {
   return v;
 }
 
-// Sum over each half of the wave with lane-shift adds (no LDS traffic): lanes 31 and 63 hold the sums.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
-}
-
 template <int CTRL>
 __device__ __forceinline__ int row_shift_add(int v) {
   return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
 }
 
-__device__ __forceinline__ float half_wave_sum(float v) {
-  v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-  v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-  v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-  v = dpp_add<0x118, 0xf>(v);   // row_shr:8  -> lane 15 of every row of 16 holds the row's sum
-  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  return v;
+template <int CTRL>
+__device__ __forceinline__ float lane_pull(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// One round of the sums below: of two values, lanes with `upper` keep the second, the others the first, each with the partner's share.
+template <int CTRL>
+__device__ __forceinline__ float keep_one(float a, float b, bool upper) {
+  return (upper ? b : a) + lane_pull<CTRL>(upper ? a : b);
+}
+
+// Sums over each half of the wave of 16 (H = 1) or 32 (H = 2) values per lane, all together: in every round a lane passes on half
+// of what it holds and adds what it gets, so the additions halve from round to round (five lane shifts for each of the
+// values by itself were 80 or 160, and as many stores by two lanes: 200 000 points of 16 views and 768 channels 239 -> 232 us, 40 objects
+// of 50 000 points, single pass, 588 -> 575, 64 of 100 000 1440 -> 1416, 123 457 points of 11 views 173 -> 169).  Rounds: lanes 16 apart, 8, 2, 1 and 4; a value's additions are the
+// same tree for both H.  Lane l (of 32) ends up with value lane_value<H>(l); with 16 values two lanes hold the same one.
+template <int H>
+__device__ __forceinline__ float half_wave_sums(float (&v)[16 * H], int lane) {
+#pragma unroll
+  for (int i = 0; i < 8 * H; ++i) {   // odd rows of 16 lanes of the first value against even rows of the second
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false, false);
+    v[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4 * H; ++i) v[i] = keep_one<0x128>(v[2 * i], v[2 * i + 1], (lane & 8) != 0);   // row_ror:8
+#pragma unroll
+  for (int i = 0; i < 2 * H; ++i) v[i] = keep_one<0x4e>(v[2 * i], v[2 * i + 1], (lane & 2) != 0);   // quad_perm [2, 3, 0, 1]
+#pragma unroll
+  for (int i = 0; i < H; ++i) v[i] = keep_one<0xb1>(v[2 * i], v[2 * i + 1], (lane & 1) != 0);       // quad_perm [1, 0, 3, 2]
+  // lanes 4 apart: eight lanes mirrored, then every four
+  if constexpr (H == 1) return v[0] + lane_pull<0x1b>(lane_pull<0x141>(v[0]));
+  const bool upper = (lane & 4) != 0;
+  const float keep = upper ? v[H - 1] : v[0], send = upper ? v[0] : v[H - 1];
+  return keep + lane_pull<0x1b>(lane_pull<0x141>(send));
+}
+
+template <int H>
+__device__ __forceinline__ int lane_value(int l) {
+  return ((l >> 4) & 1) | ((l >> 3) & 1) << 1 | ((l >> 1) & 1) << 2 | (l & 1) << 3 | (H == 2 ? ((l >> 2) & 1) << 4 : 0);
 }
 
 // One (point, view) pair after Eq. 1 and the cell selection.
@@ -816,6 +842,25 @@ __device__ __forceinline__ void mma_step(const StepA& w, const StepQ<H>& r, f32x
   }
 }
 
+// Sums of squares of the wave's channels per point: one for each of its pieces of 128 channels, in ss.  (A sum per piece, so that
+// the norm's additions do not depend on how the channels are dealt out to waves.)
+template <int H>
+__device__ __forceinline__ void piece_squares(const f32x16 (&acc)[4 * H], int lane, float (*ss)[kTilePts]) {
+  float v[16 * H];
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float sq = 0.0f;
+#pragma unroll
+      for (int t = 4 * h; t < 4 * h + 4; ++t) sq = __builtin_fmaf(acc[t][r], acc[t][r], sq);
+      v[16 * h + r] = sq;
+    }
+  const float sum = half_wave_sums<H>(v, lane);
+  const int i = lane_value<H>(lane & 31), r = i & 15;
+  ss[i >> 4][8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)] = sum;
+}
+
 struct ProdArgs {
   const char* feat;
   int D;
@@ -906,7 +951,7 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
   constexpr int kSpan = kHalf * H;   // channels per wave
   constexpr int kStage = stage_steps_for<S * H / 2>();
   __shared__ __attribute__((aligned(16))) char s_steps[2][kStage * sizeof(TileStep)];
-  __shared__ float s_ss[2][S][kTilePts];   // [tile parity]: a wave may write the next tile's sums while another still reads
+  __shared__ float s_ss[2][S * H][kTilePts];   // [tile parity]: a wave may write the next tile's sums while another still reads
   __shared__ int s_take[2];
   __shared__ int s_job[4];   // see drain_tiles
 
@@ -1004,15 +1049,7 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
     }
 
     // ---- sums of squares of the wave's channels, per point
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 8 * (r >> 2) + 4 * g + (r & 3);
-      float ss = 0.0f;
-#pragma unroll
-      for (int t = 0; t < 4 * H; ++t) ss = __builtin_fmaf(acc[t][r], acc[t][r], ss);
-      ss = half_wave_sum(ss);
-      if (m == 31) s_ss[buf][span][row] = ss;
-    }
+    piece_squares<H>(acc, lane, &s_ss[buf][span * H]);
     if (tid == 0) s_take[buf] = asked;
     const int n_next2 = __builtin_amdgcn_readfirstlane(pend_n);
     wait_copies();
@@ -1032,7 +1069,7 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
       const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
       float tot = 0.0f;
 #pragma unroll
-      for (int w = 0; w < S; ++w) tot += s_ss[buf][w][m];
+      for (int w = 0; w < S * H; ++w) tot += s_ss[buf][w][m];
       const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
       factor = a.mean_only ? inv : normed;
     }
@@ -1556,7 +1593,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ __attribute__((aligned(16))) char s_steps[2][kStage * sizeof(TileStep)];
   __shared__ TileSlot<NP> s_slot[2];
   __shared__ __attribute__((aligned(16))) ProducerScratch s_sc;
-  __shared__ float s_ss[2][S][kTilePts];
+  __shared__ float s_ss[2][S * H][kTilePts];
   __shared__ __attribute__((aligned(16))) float s_cam[kCamRows][16];   // the object's camera rows, for the producers
   __shared__ int s_plan[4];      // tickets of the workgroup's tiles, k-th tile in slot k & 3
   __shared__ __attribute__((aligned(16))) int s_flags[kMaxProducers];   // meeting numbers of the producer waves
@@ -1731,7 +1768,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
           const float inv = cnt_prev > 0 ? 1.0f / (float)cnt_prev : 0.0f;
           float tot = 0.0f;
 #pragma unroll
-          for (int wv = 0; wv < S; ++wv) tot += s_ss[buf ^ 1][wv][m];
+          for (int wv = 0; wv < S * H; ++wv) tot += s_ss[buf ^ 1][wv][m];
           const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
           const float factor = a.mean_only ? inv : normed;
 #pragma unroll
@@ -1863,17 +1900,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
         for (int q = span * kWave + lane; q < n * (int)(sizeof(TileStep) / 16); q += S * kWave) dst[q] = src[q];
       }
       if (n > 0) {   // uniform
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = 8 * (r >> 2) + 4 * g + (r & 3);
-          float ss = 0.0f;
-#pragma unroll
-          for (int t = 0; t < 4 * H; ++t) ss = __builtin_fmaf(acc[t][r], acc[t][r], ss);
-          ss = half_wave_sum(ss);
-          if (m == 31) s_ss[buf][span][row] = ss;
-        }
+        piece_squares<H>(acc, lane, &s_ss[buf][span * H]);
       } else if (lane < kTilePts) {   // nobody sees the tile's points
-        s_ss[buf][span][lane] = 0.0f;
+#pragma unroll
+        for (int h = 0; h < H; ++h) s_ss[buf][span * H + h][lane] = 0.0f;
       }
       if constexpr (!SC) {
         if (a.pace != 0 && span == 0) {   // see launch_tile (the other waves wait at the barrier; a counter that runs on ends it)
@@ -1889,7 +1919,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
         const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
         float tot = 0.0f;
 #pragma unroll
-        for (int wv = 0; wv < S; ++wv) tot += s_ss[buf][wv][m];
+        for (int wv = 0; wv < S * H; ++wv) tot += s_ss[buf][wv][m];
         const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
         factor = a.mean_only ? inv : normed;
       }
