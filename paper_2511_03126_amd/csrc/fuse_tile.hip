@@ -2061,12 +2061,17 @@ static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int produc
 
 // Whether the one-kernel form of this launch can score its tiles itself: a scoring wave must fit the workgroup (at most
 // three product waves beside the four producers) and one matrix-core tile must hold the materials.
-static bool scoring_wave_fits(const FuseArgs& a, int producers, int product_waves) {
+static bool scoring_wave_fits(const FuseArgs& a, int producers, int product_waves, int n_obj, long long tiles) {
   // With one producer wave (two workgroups of up to four waves per compute unit) the scoring wave pays where no rows are
   // stored (the single-pass call: C5 2.63 -> 2.45 ms): with rows the call is bound by their stores either way, and the
   // separate scoring kernel keeps the fusion kernel shorter (C5 combined call 3.12 ms against 3.16 ms).
   const bool fits = (producers == 4 && product_waves + 4 + 1 <= 8) ||
                     (producers == 1 && product_waves + 1 + 1 <= 4 && a.fused == nullptr);
+  // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
+  // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20 objects of
+  // 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 / 149, 8 of 100 000
+  // 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100; one object of 330 000 168 / 192.
+  if (product_waves == 1 && n_obj >= 8 && tiles >= 10000) return false;
   return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
 
@@ -2089,7 +2094,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
     // points, 8 views, combined call: 161 us with two, 143 with four), not for one, whose tiles they would share out too
     // thinly (62 500 points of 8 views 66 us with two, 88 with four; 390 625 of 3 views 176 and 185).
-    const bool scoring = scoring_wave_fits(a, np, S);
+    const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
