@@ -528,14 +528,14 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
   s = for_each_table(objs, [&](const aura::ObjTable& tab, int n, int max_pts, int obj_base) {
     tws.obj_base = obj_base;
     const aura::TileScoring want{sws.G, sws.Kpad, K, P, t32, y, 1.0f / params->temperature, unseen_zero, scores, prop, label};
-    bool scored = false;   // the one-kernel form of the fusion scores its tiles itself where it can
+    aura::FuseOutcome did;   // the one-kernel form of the fusion scores its tiles itself where it can
     hipError_t e = aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only,
                                               lay.tile ? &tws : nullptr, tab, n, max_pts, st, lay.by_cells ? sws.factor : nullptr,
                                               vis, vis_pitch, nullptr, 0, (params->flags & AURA_FUSE_TWO_KERNELS) ? 1 : 0,
-                                              lay.by_cells ? &want : nullptr, &scored, clear_status);
-    if (e != hipSuccess || !lay.by_cells || scored) return e;
+                                              lay.by_cells ? &want : nullptr, &did, clear_status);
+    if (e != hipSuccess || !lay.by_cells || did.scored) return e;
     return aura::launch_tile_scores(fa, tws, sws, K, y, P, params->temperature, unseen_zero, scores, prop, label, tab, n,
-                                    max_pts, st);
+                                    max_pts, did.sifted, st);
   });
   if (s != AURA_OK || lay.by_cells) return s;
   return hip_status(aura::launch_material_scores(fused, N, views->D, t32, K, y, P, params->temperature, scores, prop,

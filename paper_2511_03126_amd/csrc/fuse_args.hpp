@@ -58,7 +58,8 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 struct TileHdr {
   int nsteps;               // k-steps written for the tile; -1: none, fused by a gather (push_tile in fuse_tile.hip)
-  int pad_[3];
+  int listed;               // entry of the object's list of seen tiles at the position of this header (k_tile_sift)
+  int pad_[2];
   int cnt[kTilePts];        // views that see each point (nsteps >= 0)
 };
 
@@ -70,12 +71,25 @@ struct __attribute__((aligned(64))) TileStep {
 
 struct TileWs {
   TileHdr* hdr;         // [n_tiles]
-  unsigned* counters;   // [B][8]: tiles handed out so far, per object and XCD
+  unsigned* counters;   // [B][8]: tiles handed out so far, per object and XCD (with a list of seen tiles: kSeenWord)
   unsigned* status;     // 64 words: zero unless a kernel had something to report (see aura_fuse_status_offset), tiles fused
                         // by a gather, and from word 32 the heads of the lists of such tiles
   TileStep* steps;      // [n_tiles][quota]: every tile owns a fixed run of k-steps
   int quota;
   int obj_base;         // index of the launch's first object within the call
+};
+
+// How the eight counters of an object are used after k_tile_sift: word 7 holds the length of its list of seen tiles, or kAllSeen where
+// none was made because nearly all are, and XCDs 6 and 7 count their tickets in the two halves of word 6.  A half holds
+// the tickets of an XCD's share of kSeenListTiles tiles, those asked for beyond it included; larger objects are not sifted.
+constexpr int kSeenWord = 7;
+constexpr unsigned kAllSeen = 0xffffffffu;
+constexpr long long kSeenListTiles = 8 * 49152;
+
+// What a fusion launch did besides the fused rows.
+struct FuseOutcome {
+  bool scored = false;   // what FuseArgs::scoring asks for is written
+  bool sifted = false;   // the objects have lists of seen tiles (kSeenWord), and everything there is to write for the others is written
 };
 
 // Byte offset of a cell row as stored in a k-step (a multiple of 512 * units, units = D / 256 in 1..6) -> cell index.
@@ -100,9 +114,11 @@ hipError_t launch_fuse_tile_clear(const TileWs& ws, int B, hipStream_t stream);
 size_t fuse_tile_status_offset(long long N, int B);   // byte offset of the status word within that workspace
 // Splits a workspace of fuse_tile_workspace_bytes(N, B, n_views) bytes into its parts.
 TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views);
-// ws cleared, ws.obj_base set.  *scored (may be nullptr) tells whether the launch also wrote what a.scoring asks for; if not, the
+// Lists the tiles that some view sees and writes all results of the others (tile_sift.hip); ws cleared, ws.obj_base set.
+hipError_t launch_tile_sift(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_tiles, hipStream_t stream);
+// ws cleared, ws.obj_base set.  *did (may be nullptr) tells whether the launch also wrote what a.scoring asks for; if not, the
 // k-steps and the factors are in the workspace for the scoring kernel.
 hipError_t launch_fuse_tile(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_pts,
-                            hipStream_t stream, bool* scored);
+                            hipStream_t stream, FuseOutcome* did);
 
 }  // namespace aura

@@ -1584,8 +1584,9 @@ __device__ __forceinline__ void store_scores(const ScoreOut& o, const TileScorin
   if (sc.label && lane < rows) sc.label[p0 + lane] = o.label[lane];
 }
 
-// S product waves and NP producer waves per workgroup; with SC one more wave, which scores the tiles (K <= 32).
-template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC>
+// S product waves and NP producer waves per workgroup; with SC one more wave, which scores the tiles (K <= 32).  SIFTED: after
+// k_tile_sift, only the tiles on the object's list.
+template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC, bool SIFTED>
 __global__ __launch_bounds__(kWave* (S + NP + (SC ? 1 : 0))) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   constexpr int kSpan = kHalf * H;
@@ -1595,7 +1596,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ __attribute__((aligned(16))) ProducerScratch s_sc;
   __shared__ float s_ss[2][S * H][kTilePts];
   __shared__ __attribute__((aligned(16))) float s_cam[kCamRows][16];   // the object's camera rows, for the producers
-  __shared__ int s_plan[4];      // tickets of the workgroup's tiles, k-th tile in slot k & 3
+  __shared__ int s_plan[4];      // the workgroup's tiles (their tickets where not SIFTED), k-th tile in slot k & 3
   __shared__ __attribute__((aligned(16))) int s_flags[kMaxProducers];   // meeting numbers of the producer waves
   __shared__ int s_job[4];       // see drain_tiles
   __shared__ int s_drain;        // whether this workgroup looks at the lists of push_tile at its end
@@ -1603,14 +1604,17 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ ScoreOut s_out[SC ? 2 : 1];                        // scores of the tile before the last, on their way to memory
 
   const ObjRange ob = tab.o[blockIdx.y];
-  const int nblk = (ob.n_pts + kTilePts - 1) / kTilePts;
+  // the tiles to fuse: all of the object's, or those on its list (whose positions take the place of the tiles' numbers)
+  const unsigned listed = SIFTED ? a.counters[blockIdx.y * kXcd + kSeenWord] : kAllSeen;
+  const int nblk = listed == kAllSeen ? (ob.n_pts + kTilePts - 1) / kTilePts : (int)listed;
   const int groups = min(nblk, (int)gridDim.x);
   if ((int)blockIdx.x >= groups) return;
   const int xcd = blockIdx.x % kXcd;
   const XcdTiles mine(nblk, xcd);
   const int len = mine.len;
-  auto tile_at = [&](int t) { return mine.at(t); };
-  unsigned* __restrict__ ctr = a.counters + blockIdx.y * kXcd + xcd;
+  // the XCD's tickets: a word of its own, or (see kSeenWord) half of one
+  const int half = SIFTED ? max(xcd - 6, 0) : 0;
+  unsigned* __restrict__ ctr = a.counters + blockIdx.y * kXcd + xcd - half;
 
   const int tid = threadIdx.x, lane = tid % kWave;
   // Wave index: the product waves come first, then the scoring wave if there is one, then the NP producers (waves go
@@ -1648,17 +1652,29 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     else if (NP == 1 && a.fused == nullptr) __builtin_amdgcn_s_setprio(1);
     const int w = span - kFirstProducer;
     int seq = 0;
-    // The first producer wave takes the tickets (the counters are zeroed once per call, before its first launch) and
+    // The last producer wave (the one with the fewest views where they don't come out even) takes the tickets (the counters are zeroed once per call, before its first launch) and
     // publishes them in s_plan, slot k & 3 for the k-th tile of the workgroup, two tiles ahead of the one being built:
     // at the top of a trip every producer knows the tile it builds now and the one after it.  Values of len or more
     // mean that the XCD's range is used up.
     auto ticket = [&]() {
       int t = 0;
-      if (lane == 0) t = (int)atomicAdd(ctr, 1u);
+      if constexpr (SIFTED) {
+        if (lane == 0) t = (int)((atomicAdd(ctr, 1u << (16 * half)) >> (16 * half)) & (xcd >= 6 ? 0xffffu : 0xffffffffu));
+      } else {
+        if (lane == 0) t = (int)atomicAdd(ctr, 1u);
+      }
       return t;
     };
-    int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the first producer)
-    if (w == 0) {
+    // SIFTED: the tile of a ticket (asked for a tile ahead of its turn), and what s_plan holds: it, or -1 past the end.
+    const TileHdr* __restrict__ list = ws.hdr + ob.tile_begin;
+    auto entry = [&](int t) {
+      const int at = mine.at(min(t, len - 1));
+      return listed == kAllSeen ? at : list[at].listed;
+    };
+    auto plan = [&](int t, int e) { return SIFTED ? (t < len ? e : -1) : t; };
+    int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the producer that takes them)
+    int t_next = 0, e_next = 0;   // SIFTED: ticket and entry of that tile, while t_raw is the ticket of the one after it
+    if (w == NP - 1) {
       // (tickets and camera rows in flight together; not beside a scoring wave: 13 888 points of 12 views and 768 channels,
       // combined call, 56.6 us together, 49.1 one after the other)
       auto load_cameras = [&]() {
@@ -1666,21 +1682,31 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       };
       if (SC || several) load_cameras();
       const int t0 = ticket(), t1 = ticket(), t2 = ticket();
+      if constexpr (SIFTED) t_next = ticket();
       t_raw = ticket();
       if (!(SC || several)) load_cameras();
       if (!several) clear_stage();
+      int e0 = 0, e1 = 0, e2 = 0;
+      if constexpr (SIFTED) {
+        e0 = entry(t0);
+        e1 = entry(t1);
+        e2 = entry(t2);
+        e_next = entry(t_next);
+      }
       if (lane == 0) {
-        s_plan[0] = t0;
-        s_plan[1] = t1;
-        s_plan[2] = t2;
+        s_plan[0] = plan(t0, e0);
+        s_plan[1] = plan(t1, e1);
+        s_plan[2] = plan(t2, e2);
         for (int o = 0; o < kMaxProducers; ++o) s_flags[o] = 0;
       }
     }
-    if (w != 0 && !several) clear_stage();
+    if (w != NP - 1 && !several) clear_stage();
     __syncthreads();   // camera rows, the first plans and the meeting flags are in LDS
     const int last_tile = nblk - 1;
+    auto planned = [&](int t) { return SIFTED ? t >= 0 : t < len; };
+    auto tile_at = [&](int t) { return SIFTED ? t : mine.at(t); };
     // a plan past the end reads (and projects) a tile that exists; it is never built
-    auto tile_of = [&](int t) { return min(tile_at(t), last_tile); };
+    auto tile_of = [&](int t) { return SIFTED ? max(t, 0) : min(mine.at(t), last_tile); };
     // Who looks at the lists: the workgroups that pushed, which may be the last to, and those among the launch's last
     // workgroups that find, when they run out of tiles, that somebody has (a workgroup in a launch of many thousands that ends
     // early is replaced by the next one).  The producer asks while the product waves are busy with the last tile: asked by
@@ -1697,7 +1723,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       const float3 pt0 = tile_point(fa, ob, tile_of(t0), lane);
       const float3 pt1 = tile_point(fa, ob, tile_of(t1), lane);
       project_batch<SEL, NP>(fa, ob, tile_of(t0), pt0, 0, cam_lds, w, lane, pre);
-      if (t0 < len) {
+      if (planned(t0)) {
         produce_tile<DT, SEL, NP>(fa, ob, tile_at(t0), pt0, pre, s_steps[0], room, dirty0, &s_slot[0], &s_sc, cam_lds,
                                   (lds_flags)&s_flags[0], ws, blockIdx.y, &s_drain, w, seq, lane);
       } else if (w == 0 && lane == 0) {
@@ -1716,7 +1742,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     while (s_slot[buf].tile >= 0) {
       const int t = s_plan[k & 3], tn = s_plan[(k + 1) & 3];
       const float3 pt_next = tile_point(fa, ob, tile_of(tn), lane);   // requested now, looked at after this tile is built
-      if (t < len) {
+      if (planned(t)) {
         produce_tile<DT, SEL, NP>(fa, ob, tile_at(t), pt, pre, s_steps[buf ^ 1], room, buf ? dirty0 : dirty1, &s_slot[buf ^ 1], &s_sc, cam_lds,
                                   (lds_flags)&s_flags[0], ws, blockIdx.y, &s_drain, w, seq, lane);
       } else if (w == 0 && lane == 0) {
@@ -1726,10 +1752,17 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       }
       pt = pt_next;
       project_batch<SEL, NP>(fa, ob, tile_of(tn), pt, 0, cam_lds, w, lane, pre);   // its depth texels arrive during the barrier
-      if (w == 0) {   // the plan of tile k + 2: its slot (k + 2) & 3 held tile k - 2, which nobody looks at any more
-        const int t3 = __builtin_amdgcn_readfirstlane(t_raw);
-        if (lane == 0) s_plan[(k + 2) & 3] = t3;
-        if (t3 < len) t_raw = ticket();
+      if (w == NP - 1) {   // the plan of tile k + 2: its slot (k + 2) & 3 held tile k - 2, which nobody looks at any more
+        if constexpr (SIFTED) {
+          if (lane == 0) s_plan[(k + 2) & 3] = plan(t_next, e_next);
+          t_next = t_raw;
+          e_next = entry(t_next);
+          if (__builtin_amdgcn_readfirstlane(t_next) < len) t_raw = ticket();
+        } else {
+          const int t3 = __builtin_amdgcn_readfirstlane(t_raw);
+          if (lane == 0) s_plan[(k + 2) & 3] = t3;
+          if (t3 < len) t_raw = ticket();
+        }
       }
       __syncthreads();
       buf ^= 1;
@@ -2075,9 +2108,29 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int product_wave
   return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
 
+// Whether k_tile_sift goes ahead of this launch: calls that store no rows (there the stores set the time, and the unseen rows' are best
+// mixed with the others': 64 objects of 100 000 points and 4 views with rows 2927 us, 3296 sifted), of sizes where the tiles that it
+// finds are worth its launch and the lists.  us without / with it (single pass, 24 materials unless said):
+//   one object, voxels of a solid: 1.68 M, 24 views, 1024 channels, 128 materials 1143 / 633; 400 000, 12 views, 768 channels 198 / 139,
+//     6 views, 512 channels 187 / 123; 150 000, 12 views, 768 channels 107 / 110, 60 000 68 / 93
+//   ... seen from all around (every tile seen, all it costs): 1 M, 16 views, 512 channels 586 / 580; 330 000 248 / 252, 24 views, 1024 channels,
+//     60 materials 407 / 415; 130 000 135 / 141; one producer: 330 000, 6 views, 512 channels 168 / 179, 900 000, 4 views, 256 channels 367 / 378
+//   objects x points of frontal views: 64 x 100 000, 4 1417 / 860; 40 x 50 000 ragged, 2 to 4 564 / 454; 20 x 60 000, 4 347 / 281, 768
+//     channels 378 / 307; 12 x 60 000 240 / 203; 12 x 40 000, 768 channels 203 / 197; 4 x 200 000 212 / 152
+//   ... whose workgroups would be left with few tiles each: 20 x 30 000, 8 views 279 / 310; 64 x 12 000 276 / 303; 8 x 30 000 95 / 121;
+//     2 x 60 000 81 / 89
+static bool sift_tiles(const FuseArgs& a, int producers, int n_obj, int max_tiles, long long tiles) {
+  // The results of a tile that nobody sees are known to be zero: not where a factor of 1 / 0 or a weight of exp(0 * inf) would
+  // make them something else.
+  if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles) return false;
+  if (!(a.mean_only || a.norm_eps >= 1e-30f) || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
+  if (n_obj == 1) return tiles >= (producers > 1 ? 8192 : 16384);
+  return tiles >= 12288 && tiles >= 1250ll * n_obj;
+}
+
 template <int DT, int S, int H, int PF>
 static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_pts,
-                              hipStream_t stream, bool* scored) {
+                              hipStream_t stream, FuseOutcome* did) {
   const int max_tiles = (max_pts + kTilePts - 1) / kTilePts;
   ProdArgs pa{static_cast<const char*>(a.feat.feat), a.feat.D, ws.hdr, ws.steps, ws.counters + (size_t)ws.obj_base * kXcd,
               ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0};
@@ -2096,13 +2149,14 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // thinly (62 500 points of 8 views 66 us with two, 88 with four; 390 625 of 3 views 176 and 185).
     const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
+    const bool sifted = sift_tiles(a, np, n_obj, max_tiles, tiles);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
     // of 100 000 points and 4 views with eight per object: the workgroups' end times were spread over the last quarter of the
     // kernel; fusion call 2.79 ms, 2.44 with 64 per object, 2.41 with 128, 2.43 with 256 and 384).  The combined call, whose
     // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.
     const int per_object = n_obj <= 1 ? 0
-                         : (keep || scoring) ? std::min(64, max_tiles / 8 / kXcd * kXcd)
+                         : (keep || scoring) ? std::min(sifted ? std::max(32, std::min(64, 2048 / n_obj / kXcd * kXcd)) : 64, max_tiles / 8 / kXcd * kXcd)
                                              : fused_groups_per_object(S, np, n_obj, groups_max, max_tiles);
     // Where nothing but the row stores sets the time, the workgroups must not run ahead of the memory: tiles that nobody sees
     // are stored as fast as they can be issued, and the more of that, the less of it memory takes (the faster producers made
@@ -2132,23 +2186,32 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * (S + np + (scoring ? 1 : 0)));
     const TimingRequest timed = take_timing_request();
     if (timed.start) (void)hipEventRecord(timed.start, stream);
+    if (sifted) {
+      const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
+      if (e != hipSuccess) return e;
+      if (did) did->sifted = true;
+    }
+#define AURA_FUSED(sel, np_, sc)                                                                                                          \
+  if (!sel && sifted) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, np_, sc, true>), grid, block, 0, stream, a, pa, ws, keep, tab); \
+  else hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, sel, np_, sc, false>), grid, block, 0, stream, a, pa, ws, keep, tab)
     if (scoring) {
       pa.factor = nullptr;   // nobody reads the factors back
       if (np == 1) {
-        if constexpr (kOneProducer && S + 1 + 1 <= 4) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, 1, true>), grid, block, 0, stream, a, pa, ws, keep, tab);
+        if constexpr (kOneProducer && S + 1 + 1 <= 4) { AURA_FUSED(false, 1, true); }
       } else {
-        if constexpr (kFourProducers && S + 4 + 1 <= 8) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, 4, true>), grid, block, 0, stream, a, pa, ws, keep, tab);
+        if constexpr (kFourProducers && S + 4 + 1 <= 8) { AURA_FUSED(false, 4, true); }
       }
-      if (scored) *scored = true;
+      if (did) did->scored = true;
     } else if (np == 1) {
       if constexpr (kOneProducer) {
-        if (a.in_mask) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, true, 1, false>), grid, block, 0, stream, a, pa, ws, keep, tab);
-        else hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, 1, false>), grid, block, 0, stream, a, pa, ws, keep, tab);
+        if (a.in_mask) { AURA_FUSED(true, 1, false); }
+        else { AURA_FUSED(false, 1, false); }
       }
     } else if constexpr (kFourProducers) {
-      if (a.in_mask) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, true, 4, false>), grid, block, 0, stream, a, pa, ws, keep, tab);
-      else hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, 4, false>), grid, block, 0, stream, a, pa, ws, keep, tab);
+      if (a.in_mask) { AURA_FUSED(true, 4, false); }
+      else { AURA_FUSED(false, 4, false); }
     }
+#undef AURA_FUSED
     const hipError_t e = hipGetLastError();
     if (timed.stop) (void)hipEventRecord(timed.stop, stream);
     return e;
@@ -2170,13 +2233,13 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
 }
 
 hipError_t launch_fuse_tile(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_pts,
-                            hipStream_t stream, bool* scored) {
-  if (scored) *scored = false;
+                            hipStream_t stream, FuseOutcome* did) {
+  if (did) *did = FuseOutcome{};
   // waves x pieces of 128 channels per wave x k-steps of rows requested ahead, for each supported D
 #define AURA_TILE_CASE(d, s, h, pf)                                                           \
   case d:                                                                                     \
-    return a.feat.dtype == 1 ? launch_tile<1, s, h, pf>(a, ws, tab, n_obj, max_pts, stream, scored)   \
-                             : launch_tile<2, s, h, pf>(a, ws, tab, n_obj, max_pts, stream, scored)
+    return a.feat.dtype == 1 ? launch_tile<1, s, h, pf>(a, ws, tab, n_obj, max_pts, stream, did)   \
+                             : launch_tile<2, s, h, pf>(a, ws, tab, n_obj, max_pts, stream, did)
   switch (a.feat.D) {
     AURA_TILE_CASE(256, 1, 2, 2);
     AURA_TILE_CASE(512, 2, 2, 2);

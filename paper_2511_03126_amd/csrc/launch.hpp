@@ -23,6 +23,7 @@ hipError_t launch_project_visibility(const VisArgs& vis, const float* xyz, uint8
                                      int max_pts, hipStream_t stream);
 
 struct TileWs;
+struct FuseOutcome;
 // tile_ws == nullptr: per-point gather kernel; otherwise the matrix-core tile path with that workspace.
 struct TileScoring;
 hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const float* xyz, float* fused,
@@ -33,7 +34,7 @@ hipError_t launch_fuse_features(const VisArgs& vis, const FeatArgs& feat, const 
                                 const uint8_t* in_mask = nullptr, int in_mask_pitch = 0,     // see FuseArgs::in_mask
                                 int two_kernels = 0,                                        // see FuseArgs::two_kernels
                                 const TileScoring* scoring = nullptr,    // tile path only: see FuseArgs::scoring
-                                bool* scored = nullptr,                  // whether the launch did what `scoring` asks for
+                                FuseOutcome* did = nullptr,              // what the launch did besides the fused rows
                                 unsigned* clear_status = nullptr);       // gather kernel only: see FuseArgs::clear_status
 
 // Sec. 3.2.2, view importance-based filtering (select_views.hip).
