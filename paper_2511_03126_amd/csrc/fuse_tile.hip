@@ -1584,10 +1584,21 @@ __device__ __forceinline__ void store_scores(const ScoreOut& o, const TileScorin
   if (sc.label && lane < rows) sc.label[p0 + lane] = o.label[lane];
 }
 
+// With one producer two workgroups share a compute unit, two waves per SIMD, and a product wave has two pieces of 128 channels
+// (H = 2, 128 accumulator registers).  With four producers there is one workgroup, and the product waves are what a tile waits
+// for: their k-steps are a chain of reads from L2 and beyond.  So they have one piece each there (H = 1): twice as many of them,
+// on all SIMDs, three waves per SIMD where they are more than eight in all, each with half the products and half the rows in
+// flight (us with two pieces / one; 16 views, 330 000 points: 512 channels 319 / 285, 24 materials 275 / 230, plain fusion 214 / 192; 768
+// channels 364 / 336, 288 / 270, 247 / 236; 1024 channels 427 / 400, plain 302 / 292; 60 000 points of 20 views 156 / 140, 163 / 159,
+// 187 / 182; three k-steps ahead instead of two gain nothing).
+template <int S, int NP, bool SC>
+constexpr int fused_waves_per_simd() { return S + NP + (SC ? 1 : 0) <= 8 ? 2 : 3; }
+
 // S product waves and NP producer waves per workgroup; with SC one more wave, which scores the tiles (K <= 32).  SIFTED: after
 // k_tile_sift, only the tiles on the object's list.
 template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC, bool SIFTED>
-__global__ __launch_bounds__(kWave* (S + NP + (SC ? 1 : 0))) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(kWave* (S + NP + (SC ? 1 : 0)))
+    __attribute__((amdgpu_waves_per_eu(fused_waves_per_simd<S, NP, SC>(), fused_waves_per_simd<S, NP, SC>())))
 void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   constexpr int kSpan = kHalf * H;
   constexpr int kStage = fused_stage_steps<S, NP, SC>();
@@ -2141,7 +2152,8 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     tiles += (tab.o[t].n_pts + kTilePts - 1) / kTilePts;
   }
   const int np = one_kernel_producers(a, max_views, S, n_obj, tiles);
-  constexpr bool kOneProducer = S + 1 <= 4, kFourProducers = S > 1 && S + 4 <= 8;   // what it can answer (launched below)
+  constexpr bool kOneProducer = S + 1 <= 4, kFourProducers = S > 1 && 2 * S + 4 <= 12;   // what it can answer (launched below)
+  static_assert(H == 2, "four producers take waves of half the channels");
   if (np > 0) {
     // With one producer wave two workgroups fit a compute unit, with four one; several objects in one launch share the
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
@@ -2183,7 +2195,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
       if (S == 3 && n_obj >= 12 && tiles >= 64 * kFusedGroupsMax) pa.pace = 690;
     }
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
-    const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * (S + np + (scoring ? 1 : 0)));
+    const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * ((np > 1 ? 2 * S : S) + np + (scoring ? 1 : 0)));
     const TimingRequest timed = take_timing_request();
     if (timed.start) (void)hipEventRecord(timed.start, stream);
     if (sifted) {
@@ -2191,25 +2203,25 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
       if (e != hipSuccess) return e;
       if (did) did->sifted = true;
     }
-#define AURA_FUSED(sel, np_, sc)                                                                                                          \
-  if (!sel && sifted) hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, false, np_, sc, true>), grid, block, 0, stream, a, pa, ws, keep, tab); \
-  else hipLaunchKernelGGL((k_tile_fused<DT, S, H, PF, sel, np_, sc, false>), grid, block, 0, stream, a, pa, ws, keep, tab)
+#define AURA_FUSED(s_, h_, sel, np_, sc)                                                                                                  \
+  if (!sel && sifted) hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, false, np_, sc, true>), grid, block, 0, stream, a, pa, ws, keep, tab); \
+  else hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, sel, np_, sc, false>), grid, block, 0, stream, a, pa, ws, keep, tab)
     if (scoring) {
       pa.factor = nullptr;   // nobody reads the factors back
       if (np == 1) {
-        if constexpr (kOneProducer && S + 1 + 1 <= 4) { AURA_FUSED(false, 1, true); }
+        if constexpr (kOneProducer && S + 1 + 1 <= 4) { AURA_FUSED(S, H, false, 1, true); }
       } else {
-        if constexpr (kFourProducers && S + 4 + 1 <= 8) { AURA_FUSED(false, 4, true); }
+        if constexpr (kFourProducers && 2 * S + 4 + 1 <= 12) { AURA_FUSED(2 * S, 1, false, 4, true); }
       }
       if (did) did->scored = true;
     } else if (np == 1) {
       if constexpr (kOneProducer) {
-        if (a.in_mask) { AURA_FUSED(true, 1, false); }
-        else { AURA_FUSED(false, 1, false); }
+        if (a.in_mask) { AURA_FUSED(S, H, true, 1, false); }
+        else { AURA_FUSED(S, H, false, 1, false); }
       }
     } else if constexpr (kFourProducers) {
-      if (a.in_mask) { AURA_FUSED(true, 4, false); }
-      else { AURA_FUSED(false, 4, false); }
+      if (a.in_mask) { AURA_FUSED(2 * S, 1, true, 4, false); }
+      else { AURA_FUSED(2 * S, 1, false, 4, false); }
     }
 #undef AURA_FUSED
     const hipError_t e = hipGetLastError();
