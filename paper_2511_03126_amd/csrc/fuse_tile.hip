@@ -771,7 +771,7 @@ __device__ __forceinline__ int load_nsteps(const TileHdr* h) {
 // sufficient.  The workgroup waits for the copies explicitly (wait_copies) before the barrier that
 // publishes a buffer.
 // The one-kernel form's stage: what fits LDS beside the rest with as many workgroups per compute unit as the registers
-// allow (eight waves in all, see k_tile_fused), so that few tiles outgrow it (with 4, 8 and 16 k-steps for 256, 512 and
+// allow (see fused_waves_per_simd), so that few tiles outgrow it (with 4, 8 and 16 k-steps for 256, 512 and
 // more channels, 123 457 points of 11 views took 469 us, 200 000 of 8 views and 256 channels 1080 us; 197 and 187 us now).
 template <int S, int NP, bool SC>
 constexpr int fused_stage_steps() {
@@ -1655,9 +1655,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   const bool several = gridDim.y > 1;   // objects
   if (several) clear_stage();
   if (producer) {
-    // With eight waves in the workgroup every producer shares its SIMD with a product wave, and the tile waits for the
-    // producers: they go first where both are ready (measured on 1024 channels with 24 views: 12 % faster; with seven
-    // waves it does not pay).
+    // With eight waves or more in the workgroup every producer shares its SIMD with product waves: the producers go first where
+    // both are ready (measured on 1024 channels with 24 views, when that was eight waves: 12 % faster).
     if constexpr (S + NP >= 8) __builtin_amdgcn_s_setprio(1);
     // ... and so does a call without rows wait for its one producer (40 objects of two to four views 681 -> 669 us)
     else if (NP == 1 && a.fused == nullptr) __builtin_amdgcn_s_setprio(1);
@@ -2068,22 +2067,39 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
          D / 256 != 5 && feat_bytes <= 0xffffffffll;
 }
 
-// How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  One producer wave keeps up with
-// the product waves for a few views per object; beyond that four share the views of a tile and a compute unit holds one
-// workgroup of at most eight waves (two per SIMD: a product wave needs about 250 registers).
-// Cells of at least 4 x 4 pixels: a tile needs 0.3 to 0.4 k-steps per view on spatially sorted points, so the producers
-// keep up for every number of views they take.  Smaller cells need up to one k-step per view, and many views of them
-// make the producers the longer side: those go to the two kernels above 4 (256 channels), 8 (512) and 16 views.  The line
-// comes from 1 M points with 32 views of pixel-sized cells and 512 channels (1.17 ms against 1.12 ms for the two kernels);
-// with 100 000 points it could lie higher from 512 channels on (cells of 2 pixels, one kernel / two: 512 channels 12 views
-// 85 / 105 us, 1024 channels 24 views 181 / 235 us) and lower for 256 (4 views 86 / 76 us).
-static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int product_waves, int n_obj, long long tiles) {
+// How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  units: channels / 256.  One producer wave
+// keeps up with the product waves for a few views per object; beyond that four share the views of a tile and a compute unit
+// holds one workgroup of up to twelve waves (see fused_waves_per_simd).
+// Cells of at least 4 x 4 pixels: a tile needs 0.3 to 0.4 k-steps per view on spatially sorted points.  Smaller cells need up to
+// one and more, too many for the short stage of the one-producer form and its producer, and the more views the longer the
+// producers take.  Where the lines of one object lie (us, two kernels / one with four producers; 400 000 points unless said, "fine":
+// cells of one or two pixels):
+//   256 channels, fine     50 000 points, 8 views, step 412 / 252 (one producer 648), 100 000 191 / 152 (754), 300 000, 6 views 243 / 193; 16 views,
+//                          cells of 2 pixels, step 386 / 339, 1 pixel 436 / 380, single pass of 24 materials 350 / 267; 20 views 417 / 442 (2 pixels),
+//                          468 / 450 (1 pixel); 32 views, single pass 502 / 574, 725 / 725
+//   256 channels, coarse   10 views, step 303 / 243, plain 246 / 185; 16 views 332 / 282, 254 / 214; 20 views 352 / 385, 266 / 308
+//   512 channels, fine     100 000 points, 6 views, one producer 227, four 206, 8 views, 2 pixels, single pass 154 / 105; 16 views, step 636 / 536; 32
+//                          views, 1 pixel, step 838 / 657, plain 615 / 442; 2 pixels, step 708 / 609, single pass, 40 materials 574 / 604, 24
+//                          materials 530 / 483; 1 M points, 32 views, step 1611 / 1456; 800 000 points, 5 views, step 438 (one producer) / 470
+//   768 channels, fine     32 views, 1 pixel, step 901 / 722, plain 685 / 511; 2 pixels, single pass 600 / 544; 1024 channels, 28 views 1002 / 800;
+//                          24 views of few points (most tiles outgrow their k-steps): 10 000 192 / 219, 25 000 311 / 235
+// Several objects keep the lines that were measured for them with waves of 256 channels (256 channels: 12 objects of 40 000 points and
+// 12 views, single pass 284 / 317, 4 of 100 000 and 16 views 251 / 206).
+static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units, int n_obj, long long tiles) {
   const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
-  if (a.two_kernels || views_per_obj > kCamRows || (!coarse && views_per_obj > (product_waves >= 3 ? 16 : 4 * product_waves))) return 0;
+  if (a.two_kernels || views_per_obj > kCamRows) return 0;
+  if (n_obj == 1) {
+    if (views_per_obj > kPBatch && units == 1) return 0;
+    if (!coarse && views_per_obj > kPBatch && units == 2 && !a.fused && a.scoring.G && a.scoring.Kpad > kScoreTileM) return 0;
+    if (!coarse && views_per_obj > kPBatch && units >= 3 && tiles < 512) return 0;
+    if (!coarse && views_per_obj >= 4 && (units == 1 || (units == 2 && (views_per_obj > kOneKernelViews || !a.fused || tiles <= 10000)))) return 4;
+  } else if (!coarse && views_per_obj > (units >= 3 ? 16 : 4 * units)) {
+    return 0;
+  }
   if (views_per_obj <= kOneKernelViews) {
     // Few views: where two workgroups fit a compute unit.  (Five waves leave three idle: 63 objects of 2 views and 1024
     // channels 708 us as two kernels, 1015 us as one; 300 000 points of 8 views 390 and 426 us.)
-    if (product_waves + 1 > 4) return 0;
+    if (units + 1 > 4) return 0;
     // Up to three views of 512 channels, or seven of 768, the two kernels are ahead until the launch has tiles enough to
     // hide the pipeline's start in every workgroup, one object of which some 100 000 points, many small ones later still,
     // and later again where no rows are stored (times in us, two kernels / one):
@@ -2092,30 +2108,29 @@ static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int produc
     //   ... single pass, 60 materials          200 000 points 159 / 192, 400 000 238 / 260, 800 000 396 / 396
     //   20 objects of 6 views, 768 channels, single pass   200 000 points 199 / 215, 400 000 306 / 290
     long long from = 0;   // tiles
-    if (product_waves == 3 && views_per_obj < 8) from = n_obj == 1 ? 3000 : (n_obj > 8 && !a.fused ? 8000 : 0);
-    if (product_waves == 2 && views_per_obj < 4 && n_obj > 8) from = a.fused ? 4000 : 25000;
+    if (units == 3 && views_per_obj < 8) from = n_obj == 1 ? 3000 : (n_obj > 8 && !a.fused ? 8000 : 0);
+    if (units == 2 && views_per_obj < 4 && n_obj > 8) from = a.fused ? 4000 : 25000;
     return tiles >= from ? 1 : 0;
   }
-  // (one product wave leaves four producers idle: 32 views of 256 channels 413 us, 383 us as two kernels)
-  if (product_waves == 1 || product_waves + 4 > 8) return 0;
+  if (units > 4 || (units == 1 && n_obj > 1)) return 0;
   // (where the scoring kernel wants the k-steps in memory the product waves copy them out: measured 3 to 7 % faster than
   // the two kernels on 768 channels with 16 views and on 1024 channels with 24 views)
   return 4;
 }
 
-// Whether the one-kernel form of this launch can score its tiles itself: a scoring wave must fit the workgroup (at most
-// three product waves beside the four producers) and one matrix-core tile must hold the materials.
-static bool scoring_wave_fits(const FuseArgs& a, int producers, int product_waves, int n_obj, long long tiles) {
+// Whether the one-kernel form of this launch can score its tiles itself: a scoring wave must fit the workgroup (up to 768
+// channels beside four producers) and one matrix-core tile must hold the materials.
+static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n_obj, long long tiles) {
   // With one producer wave (two workgroups of up to four waves per compute unit) the scoring wave pays where no rows are
   // stored (the single-pass call: C5 2.63 -> 2.45 ms): with rows the call is bound by their stores either way, and the
   // separate scoring kernel keeps the fusion kernel shorter (C5 combined call 3.12 ms against 3.16 ms).
-  const bool fits = (producers == 4 && product_waves + 4 + 1 <= 8) ||
-                    (producers == 1 && product_waves + 1 + 1 <= 4 && a.fused == nullptr);
+  const bool fits = (producers == 4 && 2 * units + 4 + 1 <= 12) ||
+                    (producers == 1 && units + 1 + 1 <= 4 && a.fused == nullptr);
   // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
   // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20 objects of
   // 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 / 149, 8 of 100 000
   // 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100; one object of 330 000 168 / 192.
-  if (product_waves == 1 && n_obj >= 8 && tiles >= 10000) return false;
+  if (producers == 1 && units == 1 && n_obj >= 8 && tiles >= 10000) return false;
   return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
 
@@ -2152,7 +2167,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     tiles += (tab.o[t].n_pts + kTilePts - 1) / kTilePts;
   }
   const int np = one_kernel_producers(a, max_views, S, n_obj, tiles);
-  constexpr bool kOneProducer = S + 1 <= 4, kFourProducers = S > 1 && 2 * S + 4 <= 12;   // what it can answer (launched below)
+  constexpr bool kOneProducer = S + 1 <= 4, kFourProducers = 2 * S + 4 <= 12;   // what it can answer (launched below)
   static_assert(H == 2, "four producers take waves of half the channels");
   if (np > 0) {
     // With one producer wave two workgroups fit a compute unit, with four one; several objects in one launch share the
