@@ -2069,7 +2069,8 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
 
 // How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  units: channels / 256.  One producer wave
 // keeps up with the product waves for a few views per object; beyond that four share the views of a tile and a compute unit
-// holds one workgroup of up to twelve waves (see fused_waves_per_simd).
+// holds one workgroup of up to twelve waves (see fused_waves_per_simd), which is the faster form of few views too where the launch
+// is one object.
 // Cells of at least 4 x 4 pixels: a tile needs 0.3 to 0.4 k-steps per view on spatially sorted points.  Smaller cells need up to
 // one and more, too many for the short stage of the one-producer form and its producer, and the more views the longer the
 // producers take.  Where the lines of one object lie (us, two kernels / one with four producers; 400 000 points unless said, "fine":
@@ -2083,32 +2084,49 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
 //                          materials 530 / 483; 1 M points, 32 views, step 1611 / 1456; 800 000 points, 5 views, step 438 (one producer) / 470
 //   768 channels, fine     32 views, 1 pixel, step 901 / 722, plain 685 / 511; 2 pixels, single pass 600 / 544; 1024 channels, 28 views 1002 / 800;
 //                          24 views of few points (most tiles outgrow their k-steps): 10 000 192 / 219, 25 000 311 / 235
-// Several objects keep the lines that were measured for them with waves of 256 channels (256 channels: 12 objects of 40 000 points and
-// 12 views, single pass 284 / 317, 4 of 100 000 and 16 views 251 / 206).
+// Few views (up to eight): four producers for one object and for two, one producer / four, 200 000 points: 256 channels, 5 views, step
+// 146 / 138, plain 104 / 96; 512 channels 154 / 144, 108 / 98, single pass 149 / 136; 768 channels 197 / 167, 152 / 112, 153 / 144; 1024 channels
+// (two kernels / four producers) 272 / 200, 223 / 154, 193 / 156; 60 000 points of 8 views, 512 channels 108 / 91, 65 / 50; 30 000 of 5 views 82 / 51; 2 objects of
+// 60 000 points, 6 views, 768 channels 138 / 95.  Not for many points of many views, which make the producers' trips longer than the
+// product waves' turn: 700 000 points of 8 views, 512 channels, step 382 / 401, 256 channels, single pass 375 / 390.
+// More objects share the machine, and one workgroup per compute unit leaves every start of a workgroup uncovered, which two cover:
+//   1024 channels always (two kernels / four producers): 20 objects of 60 000 points and 4 views, step 1301 / 971, plain 1213 / 892, single
+//     pass 800 / 449; 64 of 5000 and 3 views 391 / 312, 336 / 255, 290 / 244
+//   768 channels with rows: 24 of 50 000, 4 views, step 785 / 653, plain 691 / 647; 8 of 30 000, 6 views 203 / 161, 170 / 150; 50 of 40 000, 8 views, plain
+//     1067 / 1044, but step 1378 / 1470; 64 of 4000, 4 views, step, 24 materials 265 / 233, 60 materials 288 / 292; without rows 24 of 50 000 377 / 460
+//   512 channels with rows, up to four: 4 of 150 000, 4 views, step 295 / 261, plain 263 / 252; 6 of 30 000, step 125 / 130; without rows 131 / 143
+//   256 channels: 4 of 150 000, plain 155 / 239
 static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units, int n_obj, long long tiles) {
   const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
+  const bool many_materials = a.scoring.G && a.scoring.Kpad > kScoreTileM;
   if (a.two_kernels || views_per_obj > kCamRows) return 0;
   if (n_obj == 1) {
     if (views_per_obj > kPBatch && units == 1) return 0;
-    if (!coarse && views_per_obj > kPBatch && units == 2 && !a.fused && a.scoring.G && a.scoring.Kpad > kScoreTileM) return 0;
+    if (!coarse && views_per_obj > kPBatch && units == 2 && !a.fused && many_materials) return 0;
     if (!coarse && views_per_obj > kPBatch && units >= 3 && tiles < 512) return 0;
-    if (!coarse && views_per_obj >= 4 && (units == 1 || (units == 2 && (views_per_obj > kOneKernelViews || !a.fused || tiles <= 10000)))) return 4;
   } else if (!coarse && views_per_obj > (units >= 3 ? 16 : 4 * units)) {
     return 0;
   }
   if (views_per_obj <= kOneKernelViews) {
-    // Few views: where two workgroups fit a compute unit.  (Five waves leave three idle: 63 objects of 2 views and 1024
-    // channels 708 us as two kernels, 1015 us as one; 300 000 points of 8 views 390 and 426 us.)
+    if (n_obj <= 2) {
+      const bool one = (units == 2 && a.fused && tiles > (coarse ? 12000 : 10000) && views_per_obj > (coarse ? 5 : 3)) ||
+                       (units == 1 && many_materials && tiles > 12000 && views_per_obj > 5 && coarse);
+      if (units <= 4 && !one) return 4;
+    } else {
+      if (units == 4) return 4;
+      if (units == 3 && a.fused && (!a.scoring.G || ((views_per_obj <= 6 || tiles <= 32768) && (!many_materials || n_obj <= 32)))) return 4;
+      if (units == 2 && a.fused && n_obj <= 4) return 4;
+    }
+    // One producer, where two workgroups fit a compute unit.
     if (units + 1 > 4) return 0;
     // Up to three views of 512 channels, or seven of 768, the two kernels are ahead until the launch has tiles enough to
-    // hide the pipeline's start in every workgroup, one object of which some 100 000 points, many small ones later still,
-    // and later again where no rows are stored (times in us, two kernels / one):
-    //   one object of 6 views, 768 channels    16 000 points 38 / 53, 60 000 69 / 76, 200 000 180 / 155
+    // hide the pipeline's start in every workgroup, many small objects later, and later again where no rows are stored (times
+    // in us, two kernels / one):
     //   20 objects of 3 views, 512 channels    100 000 points 82 / 90, 200 000 145 / 139, 400 000 267 / 193
     //   ... single pass, 60 materials          200 000 points 159 / 192, 400 000 238 / 260, 800 000 396 / 396
     //   20 objects of 6 views, 768 channels, single pass   200 000 points 199 / 215, 400 000 306 / 290
     long long from = 0;   // tiles
-    if (units == 3 && views_per_obj < 8) from = n_obj == 1 ? 3000 : (n_obj > 8 && !a.fused ? 8000 : 0);
+    if (units == 3 && views_per_obj < 8 && n_obj > 8 && !a.fused) from = 8000;
     if (units == 2 && views_per_obj < 4 && n_obj > 8) from = a.fused ? 4000 : 25000;
     return tiles >= from ? 1 : 0;
   }
