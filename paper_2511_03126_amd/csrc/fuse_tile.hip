@@ -2222,7 +2222,10 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // 24 views, nine tiles of ten seen by nobody, 1024 channels 1232 / 1101 (1151), 512 channels 801 / 802 (984); 700 000 voxels, 12
     // views, 768 channels 397 / 342 (365), 24 views, 1024 channels 525 / 476 (491); 30 000 points, 12 views, 1024 channels 59 / 57
     // (60)).  Not several objects: 16 x 40 000, 10 views, 768 channels 391 -> 401.
-    if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 115 * S;
+    // 1.2 us since the product waves have 128 channels (1.15 / 1.2 us): 1.68 M voxels, 24 views, 1024 channels 1138 / 1091; 700 000, 12 views, 1024
+    // channels 513 / 487, 768 channels 356 / 342; 500 000 points, 4 views, 1024 channels 368 / 346; 700 000, 5 views, 768 channels 339 / 343; with 1.3 us
+    // 1120, 476, 365, 347, 366, without any 1218, 519, 395, 373, 370.
+    if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 120 * S;
     if (!keep && !scoring && np == 1) {
       if (S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
       if (S == 3 && n_obj >= 12 && tiles >= 64 * kFusedGroupsMax) pa.pace = 690;
