@@ -35,8 +35,8 @@ def fuse_algorithmic_bytes(s):
 # HBM bytes per launch of the dominant kernel from the rocprofv3 counter runs summarised under profiles/ (FETCH_SIZE and
 # WRITE_SIZE, each scaled by the reading of the 256 MiB calibration copy in the same run), per workload.  Valid only for
 # the kernel source the counters were taken with: any change to that file makes the figure null until they are taken again.
-TRAFFIC_BYTES = {'c5': 13697012831}
-TRAFFIC_SOURCE_SHA256 = "e1fe5d6b2d94033b57062c11d55f1138ecce021724b20f8875ef3263c33b3e2a"
+TRAFFIC_BYTES = {'c5': 13696974755}
+TRAFFIC_SOURCE_SHA256 = "5e4e6d3da2054e084613695e72be042059efba3ea19bbcf2483ef246829703a3"
 
 
 def measured_traffic(workload):
@@ -482,7 +482,7 @@ def measure(torch, s, name, steps, warmup, step="combined", flags=0, want_single
     fuse_bytes = single_pass_algorithmic_bytes(s) if step == "single_pass" else fuse_algorithmic_bytes(s)
     achieved = fuse_bytes / (kernel_ms * 1e-3) / 1e9
     fusion_call = names[1] if staged else names[0]
-    kernel = (f"matrix-core fusion <{s.feat_dtype}, {s.D // 256} product waves> inside {fusion_call} "
+    kernel = (f"matrix-core fusion <{s.feat_dtype}, {s.D} channels> inside {fusion_call} "
               "(k_tile_fused; k_tile_prepare + k_tile_product where the lists do not fit the one-kernel form)"
               if tile else f"k_fuse_gather inside {names[1] if staged else names[0]}")
     out = {
