@@ -115,6 +115,14 @@ def test_special_cases(orc):
     assert np.abs(gpu["wq"] - ref["wq"]).max() <= TOL * np.abs(ws).max()
 
 
+@pytest.mark.parametrize("K", [3, 24, 45, 100])
+def test_an_infinite_temperature_gives_the_mean(K):
+    """Every material has weight exp(0), whether or not the materials fill their last tile.  Bound: a sum of K fp32 terms."""
+    fq, fs, ws, y = _inputs(700, 70, 96, K, 2, seed=K)
+    gpu = _run_gpu(fq, fs, ws, y, 5, T=np.inf)
+    assert (np.abs(gpu["prop"] - y.astype(np.float64).mean(0)) <= K * 2.0 ** -24 * y.max()).all()
+
+
 def test_on_fused_features_of_a_scene_and_full_size_sample(orc):
     """The densification as the path uses it: queries = fused rows of workload c2 (200 000 x 768), sources =
     150 of its points with their material scores; the oracle recomputes a sample of queries one by one."""
