@@ -188,16 +188,19 @@ __device__ __forceinline__ void widen_16(uint32_t w, float& lo, float& hi) {
   }
 }
 
-// SCORES: whether such a call can want scores.
-template <int DT, bool SCORES>
+// SCORES: whether such a call can want scores.  SWEEPS: of 512 channels each.  In the kernels of three waves per SIMD, whose 168 registers
+// three sweeps outgrow, as many as the channels fill (three with 100 bytes of scratch memory / two: 200 000 points in no order,
+// 16 views, 768 channels 2447 / 2237 us; as one kernel of two waves per SIMD it was 2357); elsewhere three (16 ragged objects of 3000
+// points and 256 channels 813 us, 902 with one).
+template <int DT, bool SCORES, int SWEEPS>
 __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& ob, int li, int lane) {
   const TileScoring& sc = a.scoring;
   const int D = a.feat.D, Hf = a.feat.Hf, Wf = a.feat.Wf;
   const long long i = ob.pt_begin + li;
   const float x = a.xyz[3 * i], y = a.xyz[3 * i + 1], z = a.xyz[3 * i + 2];
-  float acc[kGatherSweeps][8];
+  float acc[SWEEPS][8];
 #pragma unroll
-  for (int s = 0; s < kGatherSweeps; ++s)
+  for (int s = 0; s < SWEEPS; ++s)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[s][e] = 0.0f;
   int cnt = 0;
@@ -241,9 +244,9 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
         cell[q][0] = first + sy0 * Wf + sx0; cell[q][1] = first + sy0 * Wf + sx1;
         cell[q][2] = first + sy1 * Wf + sx0; cell[q][3] = first + sy1 * Wf + sx1;
       }
-      u32x4 raw[kGatherSweeps][2][4];
+      u32x4 raw[SWEEPS][2][4];
 #pragma unroll
-      for (int s = 0; s < kGatherSweeps; ++s) {
+      for (int s = 0; s < SWEEPS; ++s) {
         if (s * 8 * kWave >= D) break;   // uniform
         const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
 #pragma unroll
@@ -256,7 +259,7 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
       for (int q = 0; q < 2; ++q) {
         if (q == 1 && !two) break;   // uniform
 #pragma unroll
-        for (int s = 0; s < kGatherSweeps; ++s) {
+        for (int s = 0; s < SWEEPS; ++s) {
           if (s * 8 * kWave >= D) break;   // uniform
 #pragma unroll
           for (int c = 0; c < 4; ++c)
@@ -275,7 +278,7 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
   const float inv = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
   float ss = 0.0f;
 #pragma unroll
-  for (int s = 0; s < kGatherSweeps; ++s) {
+  for (int s = 0; s < SWEEPS; ++s) {
     const bool own = s * 8 * kWave + 8 * lane < D;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -286,14 +289,14 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
   if (!a.mean_only) {
     const float scale = 1.0f / fmaxf(sqrtf(wave_sum(ss)), a.norm_eps);
 #pragma unroll
-    for (int s = 0; s < kGatherSweeps; ++s)
+    for (int s = 0; s < SWEEPS; ++s)
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[s][e] *= scale;
   }
   if (a.fused) {
     float* __restrict__ out_row = a.fused + i * D;
 #pragma unroll
-    for (int s = 0; s < kGatherSweeps; ++s) {
+    for (int s = 0; s < SWEEPS; ++s) {
       const int ch = s * 8 * kWave + 8 * lane;
       if (ch < D) {
         *reinterpret_cast<f32x4*>(out_row + ch) = f32x4{acc[s][0], acc[s][1], acc[s][2], acc[s][3]};
@@ -306,20 +309,29 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
   if (SCORES && sc.G) {
     // Sec. 3.4.1 for this point, eight materials at a time (their reads in flight together): a dot product per lane over
     // its channels, then the sums over the wave.  Lane l keeps the similarities of materials l and l + 64.
+    // With two sweeps (768 and 1024 channels, three waves per SIMD) the next eight materials' first reads go ahead of the sums: 168
+    // registers do not hold the reads of both sweeps at a time as 256 do (points in no order, without / with: 12 objects of 33 333 points,
+    // 768 channels and 60 materials 1213 / 1120 us, 200 000 points and 128 materials 4752 / 4227).  Not elsewhere: sorted points
+    // of 32 pixel maps 1460 -> 1467 us.
+    constexpr bool kAhead = SWEEPS == 2;
     float mine[2] = {-INFINITY, -INFINITY};
+    auto request = [&](f32x4 (&t)[8][2], int m0, int s) {
+      const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const f32x4* e = reinterpret_cast<const f32x4*>(sc.temb + (long long)min(m0 + q, sc.K - 1) * D + ch);
+        t[q][0] = e[0];
+        t[q][1] = e[1];
+      }
+    };
+    f32x4 t[8][2];
+    if constexpr (kAhead) request(t, 0, 0);
     for (int m0 = 0; m0 < sc.K; m0 += 8) {
       float dot[8] = {};
 #pragma unroll
-      for (int s = 0; s < kGatherSweeps; ++s) {
+      for (int s = 0; s < SWEEPS; ++s) {
         if (s * 8 * kWave >= D) break;   // uniform
-        const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
-        f32x4 t[8][2];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const f32x4* e = reinterpret_cast<const f32x4*>(sc.temb + (long long)min(m0 + q, sc.K - 1) * D + ch);
-          t[q][0] = e[0];
-          t[q][1] = e[1];
-        }
+        if (s > 0 || !kAhead) request(t, m0, s);
         if (s * 8 * kWave + 8 * lane < D) {
 #pragma unroll
           for (int q = 0; q < 8; ++q)
@@ -330,6 +342,7 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
             }
         }
       }
+      if constexpr (kAhead) request(t, m0 + 8, 0);   // (past the last material: the last one again)
       // the eight sums in one: in each of three rounds a lane passes on the half it will not hold, and from there every
       // eight lanes hold one material
 #pragma unroll
@@ -417,7 +430,7 @@ __device__ __forceinline__ void push_tile(const TileWs& ws, int tile, int obj, i
 // Called by all waves of a workgroup together, at the end of its life: the first wave takes as many parts as there are waves,
 // four points each (those 16 objects, combined call: 359 us; half as many parts 420 us, whole tiles 407 us), and all share
 // their points.  `turn`: the list where the workgroup looks first; `job`: four words of LDS.
-template <int DT, bool SCORES>
+template <int DT, bool SCORES, int SWEEPS>
 __device__ __forceinline__ void drain_tiles(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, unsigned turn, int* job,
                                             int wave, int n_waves, int lane) {
   static_assert(kLists == 32, "lanes 0 .. 31 look at one list each");
@@ -465,7 +478,7 @@ __device__ __forceinline__ void drain_tiles(const FuseArgs& a, const TileWs& ws,
     if (parts == 0) return;
     const ObjRange ob = tab.o[obj];
     const int li0 = (tile - ob.tile_begin) * kTilePts + first * kPartPts;
-    for (int li = li0 + wave; li < min(li0 + parts * kPartPts, ob.n_pts); li += n_waves) gather_point<DT, SCORES>(a, ob, li, lane);
+    for (int li = li0 + wave; li < min(li0 + parts * kPartPts, ob.n_pts); li += n_waves) gather_point<DT, SCORES, SWEEPS>(a, ob, li, lane);
   }
 }
 
@@ -1122,7 +1135,7 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
     n_next = n_next2;
     buf ^= 1;
   }
-  if (gathered != 0u) drain_tiles<DT, true>(fa, ws, tab, blockIdx.y * gridDim.x + blockIdx.x, s_job, span, S, lane);
+  if (gathered != 0u) drain_tiles<DT, true, kGatherSweeps>(fa, ws, tab, blockIdx.y * gridDim.x + blockIdx.x, s_job, span, S, lane);
 }
 
 // ------------------------------------------------------------------------------------ one kernel
@@ -2007,7 +2020,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       if (span == (S > 1 ? 1 : 0)) store_scores(s_out[buf], fa.scoring, ob, lane);
     }
   }
-  if (s_drain != 0) drain_tiles<DT, !SEL>(fa, ws, tab, group, s_job, span, (int)(blockDim.x / kWave), lane);
+  if (s_drain != 0) {
+    constexpr int kSweeps = fused_waves_per_simd<S, NP, SC>() == 2 ? kGatherSweeps : (kSpan * S + 511) / 512;
+    drain_tiles<DT, !SEL, kSweeps>(fa, ws, tab, group, s_job, span, (int)(blockDim.x / kWave), lane);
+  }
 }
 
 __global__ void k_clear_words(unsigned* words, int n) {
