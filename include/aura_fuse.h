@@ -550,7 +550,8 @@ aura_status_t aura_thickness_integrate(const float* scores, int64_t N, int32_t K
  * Timing aid (not part of the method).  The next call of aura_fuse_features, aura_fuse_selected, aura_fuse_scores or
  * aura_fuse_score_integrate made by this host thread records start_event on its stream right before, and stop_event
  * right after, the launch of its fusion kernel (the kernel that evaluates Eq. 1-2 and writes the fused rows; both
- * kernels where the matrix-core fusion runs as two; of a call with more than 64 objects the first launch).  The time
+ * kernels where the matrix-core fusion runs as two, or where one in front of it leaves out what no view sees; of a call with
+ * more than 64 objects the first launch).  stop_event is recorded also where a launch in between fails.  The time
  * between the two events is the kernel's duration plus what the two stream markers cost (some microseconds).  One shot:
  * the request is consumed by that launch.  Both NULL withdraws a pending request.  The benchmark uses it to time the
  * dominant kernel inside a call that launches several.

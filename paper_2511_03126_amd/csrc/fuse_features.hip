@@ -281,15 +281,12 @@ static hipError_t launch_width(const FuseArgs& a, const ObjTable& tab, int n_obj
   const int pts_per_wave = (int)std::min<long long>(kFusePtsPerWave, std::max<long long>(1, pts / 8192));
   const int pts_per_block = kFuseWaves * pts_per_wave;
   dim3 grid((unsigned)(((long long)max_pts + pts_per_block - 1) / pts_per_block), n_obj), block(kFuseWaves * kWave);
-  const TimingRequest timed = take_timing_request();
-  if (timed.start) (void)hipEventRecord(timed.start, stream);
+  const TimedLaunch timed(stream);
   if (pts_per_wave < kFusePtsPerWave)
     hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, WIDTH, true>), grid, block, 0, stream, a, pts_per_wave, tab);
   else
     hipLaunchKernelGGL((k_fuse_gather<DT, VEC, PASSES, WIDTH, false>), grid, block, 0, stream, a, pts_per_wave, tab);
-  const hipError_t e = hipGetLastError();
-  if (timed.stop) (void)hipEventRecord(timed.stop, stream);
-  return e;
+  return hipGetLastError();
 }
 
 template <int DT, int VEC, int PASSES>

@@ -2255,8 +2255,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     }
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * ((np > 1 ? 2 * S : S) + np + (scoring ? 1 : 0)));
-    const TimingRequest timed = take_timing_request();
-    if (timed.start) (void)hipEventRecord(timed.start, stream);
+    const TimedLaunch timed(stream);
     if (sifted) {
       const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
       if (e != hipSuccess) return e;
@@ -2283,24 +2282,19 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
       else { AURA_FUSED(2 * S, 1, false, 4, false); }
     }
 #undef AURA_FUSED
-    const hipError_t e = hipGetLastError();
-    if (timed.stop) (void)hipEventRecord(timed.stop, stream);
-    return e;
+    return hipGetLastError();
   }
-  const TimingRequest timed = take_timing_request();   // two kernels: the events go around the pair
-  if (timed.start) (void)hipEventRecord(timed.start, stream);
+  const TimedLaunch timed(stream);   // two kernels: the events go around the pair
   if (a.in_mask)
     hipLaunchKernelGGL((k_tile_prepare<DT, true>), dim3(max_tiles, n_obj), dim3(kPrepThreads), 0, stream, a, ws, tab);
   else
     hipLaunchKernelGGL((k_tile_prepare<DT, false>), dim3(max_tiles, n_obj), dim3(kPrepThreads), 0, stream, a, ws, tab);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // several objects in one launch share the machine: fewer workgroups per object
   const int groups = std::max(kXcd, std::min(max_tiles, (kProdGroupsMax / n_obj + kXcd - 1) / kXcd * kXcd));
   hipLaunchKernelGGL((k_tile_product<DT, S, H, PF>), dim3(std::min(groups, max_tiles), n_obj), dim3(kWave * S), 0, stream, a, pa, ws, tab);
-  e = hipGetLastError();
-  if (timed.stop) (void)hipEventRecord(timed.stop, stream);
-  return e;
+  return hipGetLastError();
 }
 
 hipError_t launch_fuse_tile(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_pts,

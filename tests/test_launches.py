@@ -1,0 +1,60 @@
+"""What the fusion calls launch, without a GPU: launch_recorder.cpp stands in for the HIP runtime."""
+import re
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+PKG = ROOT / "paper_2511_03126_amd"
+F16, TWO_KERNELS, GATHER = 2, 8, 4
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    from paper_2511_03126_amd import build
+    if not build.LIB.exists():
+        build.build()
+    exe = tmp_path_factory.mktemp("recorder") / "recorder"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", str(ROOT / "tests" / "launch_recorder.cpp"), "-o", str(exe), f"-L{PKG}",
+                    "-l:libaura_fuse.so", f"-Wl,-rpath,{PKG}", "-Wl,--allow-shlib-undefined"], check=True)
+
+    def run(lines):
+        """Per line its status and its launches: (kernel with template arguments, grid x, grid y, block), "S" and "E"."""
+        out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(out) == len(lines)
+        return [(int(o.split()[0]), [_launch(x) for x in o.split()[1:]]) for o in out]
+    run.names = lambda: subprocess.run([str(exe), "names"], capture_output=True, text=True, check=True).stdout.split()
+    return run
+
+
+def _launch(text):
+    m = re.fullmatch(r"(\S+)\((\d+),(\d+),(\d+)\)", text)
+    return (_short(m[1]), int(m[2]), int(m[3]), int(m[4])) if m else text
+
+
+def _short(mangled):
+    """k_tile_fused<2,4,1,2,0,4,1,1> of its mangled name."""
+    m = re.match(r"_ZN4aura(\d+)", mangled)
+    end = m.end() + int(m[1])
+    args = re.findall(r"L[ib](\d+)E", re.split(r"EEv", mangled[end:])[0] + "E")
+    return mangled[m.end():end] + (f"<{','.join(args)}>" if args else "")
+
+
+def _call(call="single", N=1_000_000, B=1, V=8, H=448, Hf=56, D=512, dtype=F16, K=24, P=1, flags=0, fail="-"):
+    return f"{call} {N} {B} {V} {H} {Hf} {D} {dtype} {K} {P} {flags} {fail}"
+
+
+@pytest.mark.parametrize("kw,kernels", [
+    (dict(), ["k_tile_sift", "k_tile_fused"]),
+    (dict(call="scores"), ["k_tile_fused"]),
+    (dict(call="fuse", flags=TWO_KERNELS), ["k_tile_prepare", "k_tile_product"]),
+    (dict(call="fuse", N=10_000, V=2, Hf=16), ["k_fuse_gather"]),
+])
+def test_both_events_are_recorded_whichever_launch_fails(recorder, kw, kernels):
+    """A caller that timed a call waits for the second event: it is recorded on every way out once the first one is."""
+    for fail in ["-"] + kernels:
+        (status, log), = recorder([_call(**kw, fail=fail)])
+        assert (status == 0) == (fail == "-") and log.count("S") == log.count("E") == 1, (fail, log)
+        inside = [x[0].split("<")[0] for x in log[log.index("S") + 1:log.index("E")]]
+        assert inside == (kernels if fail == "-" else kernels[:kernels.index(fail) + 1])
