@@ -2234,13 +2234,9 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     //     64 x 25 000, 4   620 / 598 (615)      40 x 50 000, 2 to 4   788 / 721 (784)    20 x 100 000, 3   793 / 759 (793)
     //     40 x 30 000, 3   489 / 454 (461)      40 x 30 000, 2   493 / 453 (477)         20 x 30 000, 2   260 / 252 (253)
     //     16 x 60 000, 1   392 / 379 (408)
-    //   channels 768, with 6.9 us, the same rate                24 x 50 000, 4   714 / 677 (718)      50 x 40 000, 8   1124 / 1075 (1112)
-    //     24 x 50 000, 8   699 / 674 (696)      50 x 40 000, 3   1154 / 1088 (1135)    20 x 100 000, 6   1125 / 1088 (1121)
-    //     12 x 200 000, 3  1328 / 1294 (1340)   12 x 200 000, 8  1345 / 1299 (1341)
     // Not for others.  More views: the producers are what it waits for (paced, 512 channels, 32 x 60 000, 8 views 721 -> 734).  Few
     // tiles or few objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 ->
-    // 110; 6 x 300 000, 4 views 708 -> 781; 768 channels, 16 x 35 000, 6 views 348 -> 355).  256 channels 498 -> 508, 1024 no
-    // difference.
+    // 110; 6 x 300 000, 4 views 708 -> 781).  256 channels 498 -> 508.
     // One object with four producers, one workgroup per compute unit: the same rate again, whatever the number of tiles (1.68 M voxels of
     // 24 views, nine tiles of ten seen by nobody, 1024 channels 1232 / 1101 (1151), 512 channels 801 / 802 (984); 700 000 voxels, 12
     // views, 768 channels 397 / 342 (365), 24 views, 1024 channels 525 / 476 (491); 30 000 points, 12 views, 1024 channels 59 / 57
@@ -2249,10 +2245,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // channels 513 / 487, 768 channels 356 / 342; 500 000 points, 4 views, 1024 channels 368 / 346; 700 000, 5 views, 768 channels 339 / 343; with 1.3 us
     // 1120, 476, 365, 347, 366, without any 1218, 519, 395, 373, 370.
     if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 120 * S;
-    if (!keep && !scoring && np == 1) {
-      if (S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
-      if (S == 3 && n_obj >= 12 && tiles >= 64 * kFusedGroupsMax) pa.pace = 690;
-    }
+    if (!keep && !scoring && np == 1 && S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * ((np > 1 ? 2 * S : S) + np + (scoring ? 1 : 0)));
     const TimedLaunch timed(stream);
@@ -2274,8 +2267,9 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
       if (did) did->scored = true;
     } else if (np == 1) {
       if constexpr (kOneProducer) {
-        if (a.in_mask) { AURA_FUSED(S, H, true, 1, false); }
-        else { AURA_FUSED(S, H, false, 1, false); }
+        if (a.in_mask) {   // (768 channels with rows and no scores take four producers)
+          if constexpr (S < 3) { AURA_FUSED(S, H, true, 1, false); }
+        } else { AURA_FUSED(S, H, false, 1, false); }
       }
     } else if constexpr (kFourProducers) {
       if (a.in_mask) { AURA_FUSED(2 * S, 1, true, 4, false); }

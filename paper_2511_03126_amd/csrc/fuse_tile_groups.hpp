@@ -13,7 +13,7 @@ constexpr int kFusedGroupsMax = 512;   // two workgroups per compute unit
 // with a fixed share of one object while others have run out.  128 where that makes four rounds of resident workgroups, six of
 // those with four producers (one per compute unit), 256 where it makes fewer: the launch ends when the last, partly filled round
 // has shared out its object.  256 channels take 128 always (their tiles are short, and every workgroup begins with one that
-// nothing overlaps), 768 with one producer 256.
+// nothing overlaps).
 // us with 128 / 256, in brackets before the producers became faster (with 256):
 //   512 channels, 5 objects of 200 000 points, 4 views 458 / 404 (429), 8 views 512 / 434 (471), 16 views 481 / 412 (438);
 //     8 of 200 000, 3 views 671 / 621 (635); 12 of 200 000, 3 views 946 / 912 (909); 24 of 50 000, 8 views 477 / 491 (562);
@@ -23,8 +23,9 @@ constexpr int kFusedGroupsMax = 512;   // two workgroups per compute unit
 //   1024 channels, 8 of 100 000, 20 views 620 / 580 (580); with 128 12 of 50 000, 20 views 450 (475), 24 of 30 000 570 (605)
 // At least eight tiles per workgroup beyond the resident ones (22 objects of 153 tiles, 2 views: 249 us with a workgroup per
 // tile, 214 with 24 per object).
-inline int fused_groups_per_object(int product_waves, int producers, int n_obj, int resident, int max_tiles) {
-  const bool few = product_waves == 1 || (128 * n_obj >= (producers == 1 ? 4 : 6) * resident && !(product_waves == 3 && producers == 1));
+// units: channels / 256.
+inline int fused_groups_per_object(int units, int producers, int n_obj, int resident, int max_tiles) {
+  const bool few = units == 1 || 128 * n_obj >= (producers == 1 ? 4 : 6) * resident;
   const int want = few ? 128 : 256, most = max_tiles / 8 / kXcd * kXcd;
   return want < most ? want : most;
 }
