@@ -1,6 +1,6 @@
 // Runs library calls on a machine without a GPU and prints what they would launch.  The HIP entry points that libaura_fuse.so uses are
 // defined here, in the program, so the library finds these instead of the runtime's.  One call per line of standard input:
-//   call N B n_views H Hf D dtype K P flags fail
+//   call N B n_views H Hf D dtype K P flags norm_eps temperature fail
 // (call: single, scores, fuse, selected; B objects of equal shares; fail: the kernel whose launch shall fail, or -).  Per call one line:
 //   status kernel(grid x, grid y, block) ... with S and E where the events of aura_time_next_fusion are recorded.
 #include <cstdint>
@@ -78,14 +78,15 @@ int main(int argc, char** argv) {
   long long N;
   int B, V, H, Hf, D, dtype, K, P;
   unsigned flags;
-  while (scanf("%15s %lld %d %d %d %d %d %d %d %d %u %63s", call, &N, &B, &V, &H, &Hf, &D, &dtype, &K, &P, &flags, fail) == 12) {
+  float eps, T;
+  while (scanf("%15s %lld %d %d %d %d %d %d %d %d %u %f %f %63s", call, &N, &B, &V, &H, &Hf, &D, &dtype, &K, &P, &flags, &eps, &T, fail) == 14) {
     // (nothing here is read or written by the host: any aligned address does)
     char* const at = reinterpret_cast<char*>(uintptr_t(1) << 40);
     float* const f = reinterpret_cast<float*>(at);
     int32_t* const i = reinterpret_cast<int32_t*>(at);
     uint8_t* const m = reinterpret_cast<uint8_t*>(at);
     aura_views_t views{V, H, H, Hf, Hf, D, dtype, f, f, at};
-    aura_params_t par{0.01f, 1e-6f, 0.1f, 1e-12f, flags};
+    aura_params_t par{0.01f, 1e-6f, T, eps, flags};
     std::vector<int64_t> pts(B + 1);
     std::vector<int32_t> vs(B + 1);
     for (int b = 0; b <= B; ++b) {

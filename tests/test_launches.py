@@ -7,7 +7,7 @@ import pytest
 
 ROOT = Path(__file__).resolve().parent.parent
 PKG = ROOT / "paper_2511_03126_amd"
-F16, TWO_KERNELS, GATHER = 2, 8, 4
+F16, MEAN_ONLY, GATHER, TWO_KERNELS = 2, 2, 4, 8
 
 
 @pytest.fixture(scope="module")
@@ -41,8 +41,8 @@ def _short(mangled):
     return mangled[m.end():end] + (f"<{','.join(args)}>" if args else "")
 
 
-def _call(call="single", N=1_000_000, B=1, V=8, H=448, Hf=56, D=512, dtype=F16, K=24, P=1, flags=0, fail="-"):
-    return f"{call} {N} {B} {V} {H} {Hf} {D} {dtype} {K} {P} {flags} {fail}"
+def _call(call="single", N=1_000_000, B=1, V=8, H=448, Hf=56, D=512, dtype=F16, K=24, P=1, flags=0, eps=1e-12, T=0.1, fail="-"):
+    return f"{call} {N} {B} {V} {H} {Hf} {D} {dtype} {K} {P} {flags} {eps} {T} {fail}"
 
 
 @pytest.mark.parametrize("kw,kernels", [
@@ -68,3 +68,18 @@ def test_every_instance_of_the_one_kernel_fusion_is_launched_by_some_call(record
              for Hf in (28, 224) for K in (24, 45)]
     launched = {x[0] for status, log in recorder(calls) if status == 0 for x in log if x[0].startswith("k_tile_fused<")}
     assert launched == {_short(n) for n in recorder.names() if "k_tile_fused" in n}
+
+
+@pytest.mark.parametrize("kw,sieve", [
+    (dict(), True), (dict(K=100), True), (dict(T="inf"), True),        # (weights of exp(0 * 0))
+    (dict(eps=0.0), False), (dict(eps=1e-31), False),                  # a factor of 1 / 0, or of more than fp32 holds
+    (dict(eps=0.0, flags=MEAN_ONLY), True),                            # ... that is not used
+    (dict(T=1e-39), False),                                            # exp(0 * inf)
+    (dict(call="scores"), False), (dict(N=262_112), False), (dict(N=262_113), True),
+    (dict(N=8 * 49_152 * 32), True), (dict(N=8 * 49_152 * 32 + 1), False),   # what a ticket of half a word counts
+])
+def test_the_sieve_is_left_out_where_unseen_tiles_are_not_zero_or_not_worth_it(recorder, kw, sieve):
+    (status, log), = recorder([_call(**kw)])
+    kernels = [x[0] for x in log if x not in ("S", "E")]
+    fused, = [k for k in kernels if k.startswith("k_tile_fused<")]
+    assert status == 0 and ("k_tile_sift" in kernels) == sieve and fused.endswith(",1>" if sieve else ",0>")
