@@ -36,17 +36,17 @@ __device__ __forceinline__ void stage_properties(float* __restrict__ ys, const f
 // material over P and an LDS read waited for in each, Eq. 4 held up whatever scored: single pass over 40 objects of 50 000 points and
 // 24 materials 622 -> 588 us (its scoring wave was what the other waves waited for), 1.68 M voxels and 128 materials 1183 -> 1130,
 // 123 457 points and 45 materials 184 -> 173 (with the stores of finish_scores_staged for any K), 200 000 queries densified 318 -> 307.
-template <int MT>
-__device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
-                                                  const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
-                                                  bool unseen_zero) {
+// QUADS: the first groups of eight places, four per lane group, that K may reach into.
+template <int MT, int QUADS>
+__device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
+                                             const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
+                                             bool unseen_zero) {
+  constexpr int kRows = 4 * QUADS;   // accumulator elements that can hold a material: acc[r / 16][r % 16]
+  auto material = [&](int r) { return 8 * (r >> 2) + 4 * g + (r & 3); };
   bool any_nonzero = false;
   if (unseen_zero) {   // uniform
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        any_nonzero = any_nonzero || (mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3) < K && acc[mt][r] != 0.0f);
+    for (int r = 0; r < kRows; ++r) any_nonzero = any_nonzero || (material(r) < K && acc[r >> 4][r & 15] != 0.0f);
     any_nonzero = any_nonzero || __shfl_xor((int)any_nonzero, 32, kWave) != 0;
   }
   float best = -INFINITY;
@@ -55,14 +55,14 @@ __device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long
   for (int mt = 0; mt < MT; ++mt) {
     if ((mt + 1) * kScoreTileM > K) {   // uniform: the tile has places beyond K
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3) >= K) acc[mt][r] = -INFINITY;
+      for (int r = 16 * mt; r < min(16 * mt + 16, kRows); ++r)
+        if (material(r) >= K) acc[mt][r & 15] = -INFINITY;
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r)   // ascending material index within the lane: the lowest index wins ties
-      if (acc[mt][r] > best) {
-        best = acc[mt][r];
-        at = mt * kScoreTileM + 8 * (r >> 2) + (r & 3);
+    for (int r = 16 * mt; r < min(16 * mt + 16, kRows); ++r)   // ascending material index within the lane: the lowest index wins ties
+      if (acc[mt][r & 15] > best) {
+        best = acc[mt][r & 15];
+        at = 8 * (r >> 2) + (r & 3);
       }
   }
   {
@@ -78,38 +78,44 @@ __device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long
     // multiplied here, without those places.  (Selecting the weights of the last tile by index instead: 1.68 M voxels and 128
     // materials 631 -> 645 us, 200 000 points and 100 materials 238 -> 251; as it is 631 and 237.)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3) < K) acc[mt][r] = (acc[mt][r] - best) * inv_T;
+    for (int r = 0; r < kRows; ++r)
+      if (material(r) < K) acc[r >> 4][r & 15] = (acc[r >> 4][r & 15] - best) * inv_T;
     best = 0.0f;
     inv_T = 1.0f;
   }
   float den = 0.0f;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float e = weight_exp((acc[mt][r] - best) * inv_T);
-      acc[mt][r] = e;
-      den += e;
-    }
+  for (int r = 0; r < kRows; ++r) {
+    const float e = weight_exp((acc[r >> 4][r & 15] - best) * inv_T);
+    acc[r >> 4][r & 15] = e;
+    den += e;
+  }
   const HalfPair d = half_pair(den);
   den = d.lo + d.hi;
   const scores_f32x4* __restrict__ yv = reinterpret_cast<const scores_f32x4*>(ys) + g;
   for (int p = 0; p < P; ++p, yv += kScoreTileM * MT / 4) {
     float num = 0.0f;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int q = 0; q < QUADS; ++q) {
+      const scores_f32x4 v = yv[2 * q];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const scores_f32x4 v = yv[(mt * kScoreTileM + 8 * q) / 4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) num = __builtin_fmaf(acc[mt][4 * q + e], v[e], num);
-      }
+      for (int e = 0; e < 4; ++e) num = __builtin_fmaf(acc[q >> 2][4 * (q & 3) + e], v[e], num);
+    }
     const HalfPair s = half_pair(num);
     if (store && g == 0) prop[n * P + p] = unseen_zero && !any_nonzero ? 0.0f : (s.lo + s.hi) / den;
   }
+}
+
+// Up to 16 materials fill half of the only tile's places, and the line above goes over those alone.  Over all of them the step of 20 000
+// points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 56.1 now), 117 371
+// queries densified with 6 materials 67.6 -> 68.3 (67.9); single pass, 10 materials, 330 000 points of 16 views 221 -> 214, 40 objects of
+// 50 000 points 381 -> 376.  Same bits.
+template <int MT>
+__device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
+                                                  const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
+                                                  bool unseen_zero) {
+  if (MT == 1 && K <= 16) finish_quads<MT, 2>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);   // uniform
+  else finish_quads<MT, 4 * MT>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
 // Stores the scores of the lane's point as they are, then label and Eq. 4.  All 64 lanes call this; those whose point does not exist
