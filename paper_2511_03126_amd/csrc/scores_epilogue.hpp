@@ -108,8 +108,8 @@ __device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long
 
 // Up to 16 materials fill half of the only tile's places, and the line above goes over those alone.  Over all of them the step of 20 000
 // points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 56.1 now), 117 371
-// queries densified with 6 materials 67.6 -> 68.3 (67.9); single pass, 10 materials, 330 000 points of 16 views 221 -> 214, 40 objects of
-// 50 000 points 381 -> 376.  Same bits.
+// queries densified with 6 materials 67.6 -> 68.3 (67.9).  Same bits.  Only for kernels that end here: in k_tile_fused, whose scoring wave
+// comes here once per tile, the second copy of these lines made the step of 200 000 points and 32 materials 220.2 -> 221.5.
 template <int MT>
 __device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
                                                   const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
@@ -144,7 +144,7 @@ __device__ __forceinline__ void finish_scores(scores_f32x16 (&acc)[MT], long lon
         }
       }
   }
-  finish_label_prop<MT>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);
+  finish_quads<MT, 4 * MT>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
 // The same for a whole wave whose 32 points are consecutive in memory (n0 .. n0 + rows - 1 exist), with the scores
