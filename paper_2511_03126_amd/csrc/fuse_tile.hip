@@ -1695,7 +1695,11 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       }
       return t;
     };
-    // SIFTED: the tile of a ticket (asked for a tile ahead of its turn), and what s_plan holds: it, or -1 past the end.
+    // SIFTED: the tile of a ticket, and what s_plan holds: it, or -1 past the end.  The ticket is looked at at the top of the trip after
+    // the one that asked for it, and the list's entry arrives while the tile is built, so no more tiles are spoken for in advance than
+    // without a list: with one more the last workgroups had more left to do (us: objects that are seen everywhere, without the sieve / with
+    // one more / now: 265 000 points of 16 views, 512 channels 177 / 190 / 186, 330 000 205 / 220 / 216, 6 views 165 / 174 / 169; 64
+    // objects of 100 000 points 1002 / 987, 20 of 60 000, 768 channels, 288 / 286, 400 000 voxels of 12 views 146 / 144).
     const TileHdr* __restrict__ list = ws.hdr + ob.tile_begin;
     auto entry = [&](int t) {
       const int at = mine.at(min(t, len - 1));
@@ -1703,7 +1707,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     };
     auto plan = [&](int t, int e) { return SIFTED ? (t < len ? e : -1) : t; };
     int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the producer that takes them)
-    int t_next = 0, e_next = 0;   // SIFTED: ticket and entry of that tile, while t_raw is the ticket of the one after it
+    int e_next = 0;  // SIFTED: its tile
     if (w == NP - 1) {
       // (tickets and camera rows in flight together; not beside a scoring wave: 13 888 points of 12 views and 768 channels,
       // combined call, 56.6 us together, 49.1 one after the other)
@@ -1712,7 +1716,6 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       };
       if (SC || several) load_cameras();
       const int t0 = ticket(), t1 = ticket(), t2 = ticket();
-      if constexpr (SIFTED) t_next = ticket();
       t_raw = ticket();
       if (!(SC || several)) load_cameras();
       if (!several) clear_stage();
@@ -1721,7 +1724,6 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
         e0 = entry(t0);
         e1 = entry(t1);
         e2 = entry(t2);
-        e_next = entry(t_next);
       }
       if (lane == 0) {
         s_plan[0] = plan(t0, e0);
@@ -1772,6 +1774,9 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     while (s_slot[buf].tile >= 0) {
       const int t = s_plan[k & 3], tn = s_plan[(k + 1) & 3];
       const float3 pt_next = tile_point(fa, ob, tile_of(tn), lane);   // requested now, looked at after this tile is built
+      if constexpr (SIFTED) {
+        if (w == NP - 1) e_next = entry(t_raw);
+      }
       if (planned(t)) {
         produce_tile<DT, SEL, NP>(fa, ob, tile_at(t), pt, pre, s_steps[buf ^ 1], room, buf ? dirty0 : dirty1, &s_slot[buf ^ 1], &s_sc, cam_lds,
                                   (lds_flags)&s_flags[0], ws, blockIdx.y, &s_drain, w, seq, lane);
@@ -1784,10 +1789,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       project_batch<SEL, NP>(fa, ob, tile_of(tn), pt, 0, cam_lds, w, lane, pre);   // its depth texels arrive during the barrier
       if (w == NP - 1) {   // the plan of tile k + 2: its slot (k + 2) & 3 held tile k - 2, which nobody looks at any more
         if constexpr (SIFTED) {
-          if (lane == 0) s_plan[(k + 2) & 3] = plan(t_next, e_next);
-          t_next = t_raw;
-          e_next = entry(t_next);
-          if (__builtin_amdgcn_readfirstlane(t_next) < len) t_raw = ticket();
+          if (lane == 0) s_plan[(k + 2) & 3] = plan(t_raw, e_next);
+          if (__builtin_amdgcn_readfirstlane(t_raw) < len) t_raw = ticket();
         } else {
           const int t3 = __builtin_amdgcn_readfirstlane(t_raw);
           if (lane == 0) s_plan[(k + 2) & 3] = t3;
