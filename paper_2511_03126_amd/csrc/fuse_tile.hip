@@ -2173,28 +2173,30 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n
   // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
   // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20 objects of
   // 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 / 149, 8 of 100 000
-  // 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100; one object of 330 000 168 / 192.
+  // 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100.
   if (producers == 1 && units == 1 && n_obj >= 8 && tiles >= 10000) return false;
   return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
 
-// Whether k_tile_sift goes ahead of this launch: calls that store no rows (there the stores set the time, and the unseen rows' are best
-// mixed with the others': 64 objects of 100 000 points and 4 views with rows 2927 us, 3296 sifted), of sizes where the tiles that it
-// finds are worth its launch and the lists.  us without / with it (single pass, 24 materials unless said):
-//   one object, voxels of a solid: 1.68 M, 24 views, 1024 channels, 128 materials 1143 / 633; 400 000, 12 views, 768 channels 198 / 139,
-//     6 views, 512 channels 187 / 123; 150 000, 12 views, 768 channels 107 / 110, 60 000 68 / 93
-//   ... seen from all around (every tile seen, all it costs): 1 M, 16 views, 512 channels 586 / 580; 330 000 248 / 252, 24 views, 1024 channels,
-//     60 materials 407 / 415; 130 000 135 / 141; one producer: 330 000, 6 views, 512 channels 168 / 179, 900 000, 4 views, 256 channels 367 / 378
-//   objects x points of frontal views: 64 x 100 000, 4 1417 / 860; 40 x 50 000 ragged, 2 to 4 564 / 454; 20 x 60 000, 4 347 / 281, 768
-//     channels 378 / 307; 12 x 60 000 240 / 203; 12 x 40 000, 768 channels 203 / 197; 4 x 200 000 212 / 152
-//   ... whose workgroups would be left with few tiles each: 20 x 30 000, 8 views 279 / 310; 64 x 12 000 276 / 303; 8 x 30 000 95 / 121;
-//     2 x 60 000 81 / 89
-static bool sift_tiles(const FuseArgs& a, int producers, int n_obj, int max_tiles, long long tiles) {
+// Whether k_tile_sift goes ahead of this launch: calls that store no rows, of sizes where the tiles that it finds are worth its
+// launch and the lists.  (With rows the stores set the time, and the unseen rows' are best mixed with the others': 64 objects of
+// 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said:
+//   one object, voxels of a solid   1.68 M, 24 views, 1024 channels, 128 materials 1096 / 609; 400 000, 12 views, 768 channels 197 / 144,
+//     6 views, 512 channels 182 / 116, 6 views, 256 channels and 40 materials (one producer) 215 / 138; 300 000, 12 views, 768
+//     channels 151 / 124; 265 000, 24 views, 1024 channels, 100 materials 263 / 242; 150 000, 12 views, 768 channels 98 / 105
+//   ... seen from all around (every tile seen: all it costs)   265 000, 16 views, 512 channels 177 / 186; 330 000 205 / 216, 6 views
+//     165 / 169, 24 views, 1024 channels, 60 materials 410 / 422; 500 000, 12 views, 768 channels 279 / 282; 1 M, 16 views, 512
+//     channels 496 / 512; 256 channels, 40 materials, one producer: 400 000 points of 6 views 224 / 226, of 8 views 226 / 231
+//   objects x points of frontal views   64 x 100 000, 4 views 1430 / 992; 40 x 50 000 ragged, 2 to 4 510 / 398; 20 x 60 000, 4, 768
+//     channels 365 / 285; 12 x 60 000, 4 238 / 183; 12 x 40 000, 4, 768 channels 190 / 172; 4 x 200 000, 4 214 / 157
+//   ... whose workgroups would be left with few tiles each   20 x 30 000, 8 views 286 / 316; 64 x 12 000, 4 280 / 301; 8 x 30 000, 4
+//     94 / 113; 2 x 60 000, 4 76 / 73
+static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long tiles) {
   // The results of a tile that nobody sees are known to be zero: not where a factor of 1 / 0 or a weight of exp(0 * inf) would
   // make them something else.
   if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles) return false;
   if (!(a.mean_only || a.norm_eps >= 1e-30f) || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
-  if (n_obj == 1) return tiles >= (producers > 1 ? 8192 : 16384);
+  if (n_obj == 1) return tiles >= 8192;
   return tiles >= 12288 && tiles >= 1250ll * n_obj;
 }
 
@@ -2216,18 +2218,23 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   if (np > 0) {
     // With one producer wave two workgroups fit a compute unit, with four one; several objects in one launch share the
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
-    // points, 8 views, combined call: 161 us with two, 143 with four), not for one, whose tiles they would share out too
-    // thinly (62 500 points of 8 views 66 us with two, 88 with four; 390 625 of 3 views 176 and 185).
+    // points, 8 views, combined call: 161 us with two, 143 with four), not for one (more than 32 materials, 400 000 points of 8
+    // views: single pass 224 us with two, 230 with four, step 226 and 235; 1 M points of 6 views 503 and 503, 514 and 525).
     const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
-    const bool sifted = sift_tiles(a, np, n_obj, max_tiles, tiles);
+    const bool sifted = sift_tiles(a, n_obj, max_tiles, tiles);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
     // of 100 000 points and 4 views with eight per object: the workgroups' end times were spread over the last quarter of the
     // kernel; fusion call 2.79 ms, 2.44 with 64 per object, 2.41 with 128, 2.43 with 256 and 384).  The combined call, whose
-    // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.
+    // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.  With lists of seen tiles
+    // (half of the tiles or fewer) 2048 workgroups in all, at least 32 per object; us with 64 / 32 / as it is, single pass: 64 objects of
+    // 100 000 points 983 / 991 / 992; 50 of 45 000 496 / 488 / 479; 40 of 50 000, 256 channels 334 / 363 / 321, ragged 403 / 404 / 400;
+    // 30 of 60 000, 3 views 338 / 314 / 338; 20 of 60 000 259 / 291 / 259; 10 of 100 000, 1024 channels 276 / 315 / 276; with 16 all
+    // are slower (64 of 100 000 1201), with 128 too (1123).
+    const int most = !sifted ? 64 : std::max(32, std::min(64, 2048 / n_obj / kXcd * kXcd));
     const int per_object = n_obj <= 1 ? 0
-                         : (keep || scoring) ? std::min(sifted ? std::max(32, std::min(64, 2048 / n_obj / kXcd * kXcd)) : 64, max_tiles / 8 / kXcd * kXcd)
+                         : (keep || scoring) ? std::min(most, max_tiles / 8 / kXcd * kXcd)
                                              : fused_groups_per_object(S, np, n_obj, groups_max, max_tiles);
     // Where nothing but the row stores sets the time, the workgroups must not run ahead of the memory: tiles that nobody sees
     // are stored as fast as they can be issued, and the more of that, the less of it memory takes (the faster producers made

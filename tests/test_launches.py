@@ -76,6 +76,7 @@ def test_every_instance_of_the_one_kernel_fusion_is_launched_by_some_call(record
     (dict(eps=0.0, flags=MEAN_ONLY), True),                            # ... that is not used
     (dict(T=1e-39), False),                                            # exp(0 * inf)
     (dict(call="scores"), False), (dict(N=262_112), False), (dict(N=262_113), True),
+    (dict(N=384_033, V=6, D=256, K=40), True), (dict(N=262_112, V=6, D=256, K=40), False),   # one producer, four
     (dict(N=8 * 49_152 * 32), True), (dict(N=8 * 49_152 * 32 + 1), False),   # what a ticket of half a word counts
 ])
 def test_the_sieve_is_left_out_where_unseen_tiles_are_not_zero_or_not_worth_it(recorder, kw, sieve):
