@@ -358,7 +358,7 @@ __global__ __launch_bounds__(knn_waves(MT) * kWave) __attribute__((amdgpu_waves_
       for (int r = 0; r < 16; ++r) out[mt][r] *= inv_den;
   }
   const int rows = (int)min((long long)32, a.Nq - n0);
-  finish_scores_staged<MTK, 16>(out, n0, rows, lane, a.K, a.P, a.inv_T, ys, a.wq, a.prop, a.label, false,
+  finish_scores_staged<MTK, 16, true>(out, n0, rows, lane, a.K, a.P, a.inv_T, ys, a.wq, a.prop, a.label, false,
                                 s_out + wave * score_stage_floats<16>());
 }
 

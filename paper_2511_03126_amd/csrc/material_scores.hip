@@ -313,7 +313,7 @@ __global__ __launch_bounds__((2 + 3 * MT) * kWave) void k_material_scores_split(
         for (int e = 0; e < 4; ++e) acc[t][4 * q + e] = part[e];
       }
   }
-  finish_scores_staged<MT, 16>(acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
+  finish_scores_staged<MT, 16, true>(acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
                                a.prop, a.label, a.unseen_zero != 0, s_stage);
 }
 

@@ -106,18 +106,6 @@ __device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long
   }
 }
 
-// Up to 16 materials fill half of the only tile's places, and the line above goes over those alone.  Over all of them the step of 20 000
-// points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 56.1 now), 117 371
-// queries densified with 6 materials 67.6 -> 68.3 (67.9).  Same bits.  Only for kernels that end here: in k_tile_fused, whose scoring wave
-// comes here once per tile, the second copy of these lines made the step of 200 000 points and 32 materials 220.2 -> 221.5.
-template <int MT>
-__device__ __forceinline__ void finish_label_prop(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
-                                                  const float* __restrict__ ys, float* __restrict__ prop, int* __restrict__ label,
-                                                  bool unseen_zero) {
-  if (MT == 1 && K <= 16) finish_quads<MT, 2>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);   // uniform
-  else finish_quads<MT, 4 * MT>(acc, n, store, g, K, P, inv_T, ys, prop, label, unseen_zero);
-}
-
 // Stores the scores of the lane's point as they are, then label and Eq. 4.  All 64 lanes call this; those whose point does not exist
 // with store == false.
 template <int MT>
@@ -158,7 +146,12 @@ constexpr int kScoreStagePitch = 36;   // floats: rows start 4 banks apart
 template <int ROWS>
 constexpr int score_stage_floats() { return ROWS * kScoreStagePitch; }
 
-template <int MT, int ROWS>
+// SHORT: up to 16 materials fill half of the only tile's places, and label and Eq. 4 go over those alone.  Over all of them the step of
+// 20 000 points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 55.9 now),
+// 117 371 queries densified with 6 materials 67.6 -> 68.3 (67.9).  Same bits.  Only for kernels that a wave leaves after these lines
+// and that are short of waves: in k_tile_scores the second copy of them costs more than it saves (6.4 M points and 24 materials 143 ->
+// 150 us), in the scoring wave of k_tile_fused too (step of 200 000 points and 32 materials 220.2 -> 221.5).
+template <int MT, int ROWS, bool SHORT = false>
 __device__ __forceinline__ void finish_scores_staged(scores_f32x16 (&acc)[MT], long long n0, int rows, int lane, int K,
                                                      int P, float inv_T, const float* __restrict__ ys,
                                                      float* __restrict__ scores, float* __restrict__ prop,
@@ -200,7 +193,9 @@ __device__ __forceinline__ void finish_scores_staged(scores_f32x16 (&acc)[MT], l
       __builtin_amdgcn_wave_barrier();
     }
   }
-  finish_label_prop<MT>(acc, n0 + (pt < rows ? pt : 0), pt < rows, g, K, P, inv_T, ys, prop, label, unseen_zero);
+  const long long n = n0 + (pt < rows ? pt : 0);
+  if (SHORT && MT == 1 && K <= 16) finish_quads<MT, 2>(acc, n, pt < rows, g, K, P, inv_T, ys, prop, label, unseen_zero);   // uniform
+  else finish_quads<MT, 4 * MT>(acc, n, pt < rows, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
 // What finish_scores_staged writes for 32 consecutive points whose similarities are all exactly +0 (a tile that no view
