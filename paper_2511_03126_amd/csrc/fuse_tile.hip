@@ -126,7 +126,8 @@ __device__ __forceinline__ float lane_pull(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
-// One round of the sums below: of two values, lanes with `upper` keep the second, the others the first, each with the partner's share.
+// One round of the sums below: of two values, lanes with `upper` keep the second, the others the first, each with the partner's
+// share.
 template <int CTRL>
 __device__ __forceinline__ float keep_one(float a, float b, bool upper) {
   return (upper ? b : a) + lane_pull<CTRL>(upper ? a : b);
@@ -134,9 +135,10 @@ __device__ __forceinline__ float keep_one(float a, float b, bool upper) {
 
 // Sums over each half of the wave of 16 (H = 1) or 32 (H = 2) values per lane, all together: in every round a lane passes on half
 // of what it holds and adds what it gets, so the additions halve from round to round (five lane shifts for each of the
-// values by itself were 80 or 160, and as many stores by two lanes: 200 000 points of 16 views and 768 channels 239 -> 232 us, 40 objects
-// of 50 000 points, single pass, 588 -> 575, 64 of 100 000 1440 -> 1416, 123 457 points of 11 views 173 -> 169).  Rounds: lanes 16 apart, 8, 2, 1 and 4; a value's additions are the
-// same tree for both H.  Lane l (of 32) ends up with value lane_value<H>(l); with 16 values two lanes hold the same one.
+// values by itself were 80 or 160, and as many stores by two lanes: 200 000 points of 16 views and 768 channels 239 -> 232 us, 40
+// objects of 50 000 points, single pass, 588 -> 575, 64 of 100 000 1440 -> 1416, 123 457 points of 11 views 173 -> 169).  Rounds:
+// lanes 16 apart, 8, 2, 1 and 4; a value's additions are the same tree for both H.  Lane l (of 32) ends up with value
+// lane_value<H>(l); with 16 values two lanes hold the same one.
 template <int H>
 __device__ __forceinline__ float half_wave_sums(float (&v)[16 * H], int lane) {
 #pragma unroll
@@ -188,10 +190,10 @@ __device__ __forceinline__ void widen_16(uint32_t w, float& lo, float& hi) {
   }
 }
 
-// SCORES: whether such a call can want scores.  SWEEPS: of 512 channels each.  In the kernels of three waves per SIMD, whose 168 registers
-// three sweeps outgrow, as many as the channels fill (three with 100 bytes of scratch memory / two: 200 000 points in no order,
-// 16 views, 768 channels 2447 / 2237 us; as one kernel of two waves per SIMD it was 2357); elsewhere three (16 ragged objects of 3000
-// points and 256 channels 813 us, 902 with one).
+// SCORES: whether such a call can want scores.  SWEEPS: of 512 channels each.  In the kernels of three waves per SIMD, whose 168
+// registers three sweeps outgrow, as many as the channels fill (three with 100 bytes of scratch memory / two: 200 000 points in no
+// order, 16 views, 768 channels 2447 / 2237 us; as one kernel of two waves per SIMD it was 2357); elsewhere three (16 ragged objects
+// of 3000 points and 256 channels 813 us, 902 with one).
 template <int DT, bool SCORES, int SWEEPS>
 __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& ob, int li, int lane) {
   const TileScoring& sc = a.scoring;
@@ -310,9 +312,9 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
     // Sec. 3.4.1 for this point, eight materials at a time (their reads in flight together): a dot product per lane over
     // its channels, then the sums over the wave.  Lane l keeps the similarities of materials l and l + 64.
     // With two sweeps (768 and 1024 channels, three waves per SIMD) the next eight materials' first reads go ahead of the sums: 168
-    // registers do not hold the reads of both sweeps at a time as 256 do (points in no order, without / with: 12 objects of 33 333 points,
-    // 768 channels and 60 materials 1213 / 1120 us, 200 000 points and 128 materials 4752 / 4227).  Not elsewhere: sorted points
-    // of 32 pixel maps 1460 -> 1467 us.
+    // registers do not hold the reads of both sweeps at a time as 256 do (points in no order, without / with: 12 objects of 33 333
+    // points, 768 channels and 60 materials 1213 / 1120 us, 200 000 points and 128 materials 4752 / 4227).  Not elsewhere: sorted
+    // points of 32 pixel maps 1460 -> 1467 us.
     constexpr bool kAhead = SWEEPS == 2;
     float mine[2] = {-INFINITY, -INFINITY};
     auto request = [&](f32x4 (&t)[8][2], int m0, int s) {
@@ -433,9 +435,9 @@ __device__ __forceinline__ void push_tile(const TileWs& ws, int tile, int obj, i
   }
 }
 
-// Called by all waves of a workgroup together, at the end of its life: the first wave takes as many parts as there are waves (see kManyPushed),
-// four points each (those 16 objects, combined call: 359 us; half as many parts 420 us, whole tiles 407 us), and all share
-// their points.  `turn`: the list where the workgroup looks first; `job`: four words of LDS.
+// Called by all waves of a workgroup together, at the end of its life: the first wave takes as many parts as there are waves (see
+// kManyPushed), four points each (those 16 objects, combined call: 359 us; half as many parts 420 us, whole tiles 407 us), and all
+// share their points.  `turn`: the list where the workgroup looks first; `job`: four words of LDS.
 template <int DT, bool SCORES, int SWEEPS>
 __device__ __forceinline__ void drain_tiles(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, unsigned turn, int* job,
                                             int wave, int n_waves, int lane) {
@@ -944,7 +946,8 @@ __device__ __forceinline__ void open_tile(const char* sb, int n_staged, const ch
 // tiles still meet in one L2, and every XCD gets a sample of the whole object instead of one contiguous eighth, whose
 // k-steps per tile can differ (1 M points on six ellipsoids, 32 views: the eighths finished between 665 and 775 us).
 // The tiles behind the last whole round of chunks are split into eight contiguous parts, so that the XCDs' shares
-// differ by one tile at most and the first XCDs hold the larger ones (handed out as whole chunks, 6250 tiles gave two XCDs 832 and 810 tiles and the others 768).
+// differ by one tile at most and the first XCDs hold the larger ones (handed out as whole chunks, 6250 tiles gave two XCDs 832 and
+// 810 tiles and the others 768).
 struct XcdTiles {
   int sh, xcd_sh, full, rest_at, len;   // chunk = 2^sh; tickets below `full` are chunked, the others contiguous
   __device__ XcdTiles(int nblk, int xcd) {
@@ -1160,9 +1163,10 @@ constexpr int kPBatch = 16;   // views per pass of the producer waves, at most: 
 constexpr int kMaxProducers = 4;
 constexpr int kCamRows = 32;  // camera rows of the object kept in LDS for the producer
 constexpr int kOneKernelViews = 8;
-// A single producer is launched for up to kOneKernelViews views, so it makes four trips.  (With the eight of a full pass, of which the
-// last four were never made, what a trip holds was kept for all of them and the compiler's code was the longer for it: single
-// pass over 40 objects of 50 000 points and two to four views 660 -> 617 us, 64 of 100 000 and 4 views 1796 -> 1554, with rows as before.)
+// A single producer is launched for up to kOneKernelViews views, so it makes four trips.  (With the eight of a full pass, of which
+// the last four were never made, what a trip holds was kept for all of them and the compiler's code was the longer for it: single
+// pass over 40 objects of 50 000 points and two to four views 660 -> 617 us, 64 of 100 000 and 4 views 1796 -> 1554, with rows as
+// before.)
 template <int NP>
 constexpr int kPassViews = NP == 1 ? kOneKernelViews : kPBatch;
 
@@ -1608,9 +1612,9 @@ __device__ __forceinline__ void store_scores(const ScoreOut& o, const TileScorin
 // (H = 2, 128 accumulator registers).  With four producers there is one workgroup, and the product waves are what a tile waits
 // for: their k-steps are a chain of reads from L2 and beyond.  So they have one piece each there (H = 1): twice as many of them,
 // on all SIMDs, three waves per SIMD where they are more than eight in all, each with half the products and half the rows in
-// flight (us with two pieces / one; 16 views, 330 000 points: 512 channels 319 / 285, 24 materials 275 / 230, plain fusion 214 / 192; 768
-// channels 364 / 336, 288 / 270, 247 / 236; 1024 channels 427 / 400, plain 302 / 292; 60 000 points of 20 views 156 / 140, 163 / 159,
-// 187 / 182; three k-steps ahead instead of two gain nothing).
+// flight (us with two pieces / one; 16 views, 330 000 points: 512 channels 319 / 285, 24 materials 275 / 230, plain fusion 214 / 192;
+// 768 channels 364 / 336, 288 / 270, 247 / 236; 1024 channels 427 / 400, plain 302 / 292; 60 000 points of 20 views 156 / 140, 163 /
+// 159, 187 / 182; three k-steps ahead instead of two gain nothing).
 template <int S, int NP, bool SC>
 constexpr int fused_waves_per_simd() { return S + NP + (SC ? 1 : 0) <= 8 ? 2 : 3; }
 
@@ -1682,10 +1686,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     else if (NP == 1 && a.fused == nullptr) __builtin_amdgcn_s_setprio(1);
     const int w = span - kFirstProducer;
     int seq = 0;
-    // The last producer wave (the one with the fewest views where they don't come out even) takes the tickets (the counters are zeroed once per call, before its first launch) and
-    // publishes them in s_plan, slot k & 3 for the k-th tile of the workgroup, two tiles ahead of the one being built:
-    // at the top of a trip every producer knows the tile it builds now and the one after it.  Values of len or more
-    // mean that the XCD's range is used up.
+    // The last producer wave (the one with the fewest views where they don't come out even) takes the tickets (the counters are
+    // zeroed once per call, before its first launch) and publishes them in s_plan, slot k & 3 for the k-th tile of the workgroup, two
+    // tiles ahead of the one being built: at the top of a trip every producer knows the tile it builds now and the one after it.
+    // Values of len or more mean that the XCD's range is used up.
     auto ticket = [&]() {
       int t = 0;
       if constexpr (SIFTED) {
@@ -1695,11 +1699,12 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       }
       return t;
     };
-    // SIFTED: the tile of a ticket, and what s_plan holds: it, or -1 past the end.  The ticket is looked at at the top of the trip after
-    // the one that asked for it, and the list's entry arrives while the tile is built, so no more tiles are spoken for in advance than
-    // without a list: with one more the last workgroups had more left to do (us: objects that are seen everywhere, without the sieve / with
-    // one more / now: 265 000 points of 16 views, 512 channels 177 / 190 / 186, 330 000 205 / 220 / 216, 6 views 165 / 174 / 169; 64
-    // objects of 100 000 points 1002 / 987, 20 of 60 000, 768 channels, 288 / 286, 400 000 voxels of 12 views 146 / 144).
+    // SIFTED: the tile of a ticket, and what s_plan holds: it, or -1 past the end.  The ticket is looked at at the top of the trip
+    // after the one that asked for it, and the list's entry arrives while the tile is built, so no more tiles are spoken for in
+    // advance than without a list: with one more the last workgroups had more left to do (us: objects that are seen everywhere,
+    // without the sieve / with one more / now: 265 000 points of 16 views, 512 channels 177 / 190 / 186, 330 000 205 / 220 / 216, 6
+    // views 165 / 174 / 169; 64 objects of 100 000 points 1002 / 987, 20 of 60 000, 768 channels, 288 / 286, 400 000 voxels of 12
+    // views 146 / 144).
     const TileHdr* __restrict__ list = ws.hdr + ob.tile_begin;
     auto entry = [&](int t) {
       const int at = mine.at(min(t, len - 1));
@@ -2101,26 +2106,31 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
 // one and more, too many for the short stage of the one-producer form and its producer, and the more views the longer the
 // producers take.  Where the lines of one object lie (us, two kernels / one with four producers; 400 000 points unless said, "fine":
 // cells of one or two pixels):
-//   256 channels, fine     50 000 points, 8 views, step 412 / 252 (one producer 648), 100 000 191 / 152 (754), 300 000, 6 views 243 / 193; 16 views,
-//                          cells of 2 pixels, step 386 / 339, 1 pixel 436 / 380, single pass of 24 materials 350 / 267; 20 views 417 / 442 (2 pixels),
-//                          468 / 450 (1 pixel); 32 views, single pass 502 / 574, 725 / 725
+//   256 channels, fine     50 000 points, 8 views, step 412 / 252 (one producer 648), 100 000 191 / 152 (754), 300 000, 6 views 243 /
+//                          193; 16 views, cells of 2 pixels, step 386 / 339, 1 pixel 436 / 380, single pass of 24 materials 350 /
+//                          267; 20 views 417 / 442 (2 pixels), 468 / 450 (1 pixel); 32 views, single pass 502 / 574, 725 / 725
 //   256 channels, coarse   10 views, step 303 / 243, plain 246 / 185; 16 views 332 / 282, 254 / 214; 20 views 352 / 385, 266 / 308
-//   512 channels, fine     100 000 points, 6 views, one producer 227, four 206, 8 views, 2 pixels, single pass 154 / 105; 16 views, step 636 / 536; 32
-//                          views, 1 pixel, step 838 / 657, plain 615 / 442; 2 pixels, step 708 / 609, single pass, 40 materials 574 / 604, 24
-//                          materials 530 / 483; 1 M points, 32 views, step 1611 / 1456; 800 000 points, 5 views, step 438 (one producer) / 470
-//   768 channels, fine     32 views, 1 pixel, step 901 / 722, plain 685 / 511; 2 pixels, single pass 600 / 544; 1024 channels, 28 views 1002 / 800;
-//                          24 views of few points (most tiles outgrow their k-steps): 10 000 192 / 219, 25 000 311 / 235
-// Few views (up to eight): four producers for one object and for two, one producer / four, 200 000 points: 256 channels, 5 views, step
-// 146 / 138, plain 104 / 96; 512 channels 154 / 144, 108 / 98, single pass 149 / 136; 768 channels 197 / 167, 152 / 112, 153 / 144; 1024 channels
-// (two kernels / four producers) 272 / 200, 223 / 154, 193 / 156; 60 000 points of 8 views, 512 channels 108 / 91, 65 / 50; 30 000 of 5 views 82 / 51; 2 objects of
-// 60 000 points, 6 views, 768 channels 138 / 95.  Not for many points of many views, which make the producers' trips longer than the
-// product waves' turn: 700 000 points of 8 views, 512 channels, step 382 / 401, 256 channels, single pass 375 / 390.
+//   512 channels, fine     100 000 points, 6 views, one producer 227, four 206, 8 views, 2 pixels, single pass 154 / 105; 16 views,
+//                          step 636 / 536; 32 views, 1 pixel, step 838 / 657, plain 615 / 442; 2 pixels, step 708 / 609, single pass,
+//                          40 materials 574 / 604, 24 materials 530 / 483; 1 M points, 32 views, step 1611 / 1456; 800 000 points, 5
+//                          views, step 438 (one producer) / 470
+//   768 channels, fine     32 views, 1 pixel, step 901 / 722, plain 685 / 511; 2 pixels, single pass 600 / 544; 1024 channels, 28
+//                          views 1002 / 800; 24 views of few points (most tiles outgrow their k-steps): 10 000 192 / 219, 25 000 311
+//                          / 235
+// Few views (up to eight): four producers for one object and for two, one producer / four, 200 000 points: 256 channels, 5 views,
+// step 146 / 138, plain 104 / 96; 512 channels 154 / 144, 108 / 98, single pass 149 / 136; 768 channels 197 / 167, 152 / 112, 153 /
+// 144; 1024 channels (two kernels / four producers) 272 / 200, 223 / 154, 193 / 156; 60 000 points of 8 views, 512 channels 108 / 91,
+// 65 / 50; 30 000 of 5 views 82 / 51; 2 objects of 60 000 points, 6 views, 768 channels 138 / 95.  Not for many points of many views,
+// which make the producers' trips longer than the product waves' turn: 700 000 points of 8 views, 512 channels, step 382 / 401, 256
+// channels, single pass 375 / 390.
 // More objects share the machine, and one workgroup per compute unit leaves every start of a workgroup uncovered, which two cover:
-//   1024 channels always (two kernels / four producers): 20 objects of 60 000 points and 4 views, step 1301 / 971, plain 1213 / 892, single
-//     pass 800 / 449; 64 of 5000 and 3 views 391 / 312, 336 / 255, 290 / 244
-//   768 channels with rows: 24 of 50 000, 4 views, step 785 / 653, plain 691 / 647; 8 of 30 000, 6 views 203 / 161, 170 / 150; 50 of 40 000, 8 views, plain
-//     1067 / 1044, but step 1378 / 1470; 64 of 4000, 4 views, step, 24 materials 265 / 233, 60 materials 288 / 292; without rows 24 of 50 000 377 / 460
-//   512 channels with rows, up to four: 4 of 150 000, 4 views, step 295 / 261, plain 263 / 252; 6 of 30 000, step 125 / 130; without rows 131 / 143
+//   1024 channels always (two kernels / four producers): 20 objects of 60 000 points and 4 views, step 1301 / 971, plain 1213 / 892,
+//     single pass 800 / 449; 64 of 5000 and 3 views 391 / 312, 336 / 255, 290 / 244
+//   768 channels with rows: 24 of 50 000, 4 views, step 785 / 653, plain 691 / 647; 8 of 30 000, 6 views 203 / 161, 170 / 150; 50 of
+//     40 000, 8 views, plain 1067 / 1044, but step 1378 / 1470; 64 of 4000, 4 views, step, 24 materials 265 / 233, 60 materials 288 /
+//     292; without rows 24 of 50 000 377 / 460
+//   512 channels with rows, up to four: 4 of 150 000, 4 views, step 295 / 261, plain 263 / 252; 6 of 30 000, step 125 / 130; without
+//     rows 131 / 143
 //   256 channels: 4 of 150 000, plain 155 / 239
 static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units, int n_obj, long long tiles) {
   const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
@@ -2171,9 +2181,9 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n
   const bool fits = (producers == 4 && 2 * units + 4 + 1 <= 12) ||
                     (producers == 1 && units + 1 + 1 <= 4 && a.fused == nullptr);
   // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
-  // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20 objects of
-  // 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 / 149, 8 of 100 000
-  // 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100.
+  // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20
+  // objects of 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 /
+  // 149, 8 of 100 000 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100.
   if (producers == 1 && units == 1 && n_obj >= 8 && tiles >= 10000) return false;
   return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
@@ -2181,8 +2191,8 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n
 // Whether k_tile_sift goes ahead of this launch: calls that store no rows, of sizes where the tiles that it finds are worth its
 // launch and the lists.  (With rows the stores set the time, and the unseen rows' are best mixed with the others': 64 objects of
 // 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said:
-//   one object, voxels of a solid   1.68 M, 24 views, 1024 channels, 128 materials 1096 / 609; 400 000, 12 views, 768 channels 197 / 144,
-//     6 views, 512 channels 182 / 116, 6 views, 256 channels and 40 materials (one producer) 215 / 138; 300 000, 12 views, 768
+//   one object, voxels of a solid   1.68 M, 24 views, 1024 channels, 128 materials 1096 / 609; 400 000, 12 views, 768 channels 197 /
+//     144, 6 views, 512 channels 182 / 116, 6 views, 256 channels and 40 materials (one producer) 215 / 138; 300 000, 12 views, 768
 //     channels 151 / 124; 265 000, 24 views, 1024 channels, 100 materials 263 / 242; 150 000, 12 views, 768 channels 98 / 105
 //   ... seen from all around (every tile seen: all it costs)   265 000, 16 views, 512 channels 177 / 186; 330 000 205 / 216, 6 views
 //     165 / 169, 24 views, 1024 channels, 60 materials 410 / 422; 500 000, 12 views, 768 channels 279 / 282; 1 M, 16 views, 512
@@ -2228,10 +2238,10 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // of 100 000 points and 4 views with eight per object: the workgroups' end times were spread over the last quarter of the
     // kernel; fusion call 2.79 ms, 2.44 with 64 per object, 2.41 with 128, 2.43 with 256 and 384).  The combined call, whose
     // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.  With lists of seen tiles
-    // (half of the tiles or fewer) 2048 workgroups in all, at least 32 per object; us with 64 / 32 / as it is, single pass: 64 objects of
-    // 100 000 points 983 / 991 / 992; 50 of 45 000 496 / 488 / 479; 40 of 50 000, 256 channels 334 / 363 / 321, ragged 403 / 404 / 400;
-    // 30 of 60 000, 3 views 338 / 314 / 338; 20 of 60 000 259 / 291 / 259; 10 of 100 000, 1024 channels 276 / 315 / 276; with 16 all
-    // are slower (64 of 100 000 1201), with 128 too (1123).
+    // (half of the tiles or fewer) 2048 workgroups in all, at least 32 per object; us with 64 / 32 / as it is, single pass: 64
+    // objects of 100 000 points 983 / 991 / 992; 50 of 45 000 496 / 488 / 479; 40 of 50 000, 256 channels 334 / 363 / 321, ragged 403
+    // / 404 / 400; 30 of 60 000, 3 views 338 / 314 / 338; 20 of 60 000 259 / 291 / 259; 10 of 100 000, 1024 channels 276 / 315 / 276;
+    // with 16 all are slower (64 of 100 000 1201), with 128 too (1123).
     const int most = !sifted ? 64 : std::max(32, std::min(64, 2048 / n_obj / kXcd * kXcd));
     const int per_object = n_obj <= 1 ? 0
                          : (keep || scoring) ? std::min(most, max_tiles / 8 / kXcd * kXcd)
@@ -2247,13 +2257,13 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // Not for others.  More views: the producers are what it waits for (paced, 512 channels, 32 x 60 000, 8 views 721 -> 734).  Few
     // tiles or few objects: part of the machine is idle at the end, and the rest must not be held back (8 x 20 000, 3 views 102 ->
     // 110; 6 x 300 000, 4 views 708 -> 781).  256 channels 498 -> 508.
-    // One object with four producers, one workgroup per compute unit: the same rate again, whatever the number of tiles (1.68 M voxels of
-    // 24 views, nine tiles of ten seen by nobody, 1024 channels 1232 / 1101 (1151), 512 channels 801 / 802 (984); 700 000 voxels, 12
-    // views, 768 channels 397 / 342 (365), 24 views, 1024 channels 525 / 476 (491); 30 000 points, 12 views, 1024 channels 59 / 57
-    // (60)).  Not several objects: 16 x 40 000, 10 views, 768 channels 391 -> 401.
-    // 1.2 us since the product waves have 128 channels (1.15 / 1.2 us): 1.68 M voxels, 24 views, 1024 channels 1138 / 1091; 700 000, 12 views, 1024
-    // channels 513 / 487, 768 channels 356 / 342; 500 000 points, 4 views, 1024 channels 368 / 346; 700 000, 5 views, 768 channels 339 / 343; with 1.3 us
-    // 1120, 476, 365, 347, 366, without any 1218, 519, 395, 373, 370.
+    // One object with four producers, one workgroup per compute unit: the same rate again, whatever the number of tiles (1.68 M
+    // voxels of 24 views, nine tiles of ten seen by nobody, 1024 channels 1232 / 1101 (1151), 512 channels 801 / 802 (984); 700 000
+    // voxels, 12 views, 768 channels 397 / 342 (365), 24 views, 1024 channels 525 / 476 (491); 30 000 points, 12 views, 1024 channels
+    // 59 / 57 (60)).  Not several objects: 16 x 40 000, 10 views, 768 channels 391 -> 401.
+    // 1.2 us since the product waves have 128 channels (1.15 / 1.2 us): 1.68 M voxels, 24 views, 1024 channels 1138 / 1091; 700 000,
+    // 12 views, 1024 channels 513 / 487, 768 channels 356 / 342; 500 000 points, 4 views, 1024 channels 368 / 346; 700 000, 5 views,
+    // 768 channels 339 / 343; with 1.3 us 1120, 476, 365, 347, 366, without any 1218, 519, 395, 373, 370.
     if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 120 * S;
     if (!keep && !scoring && np == 1 && S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));

@@ -35,7 +35,8 @@ __device__ __forceinline__ void stage_properties(float* __restrict__ ys, const f
 // One straight line of instructions, with places beyond K holding -inf (weight 0): as a branch per material, eight per
 // material over P and an LDS read waited for in each, Eq. 4 held up whatever scored: single pass over 40 objects of 50 000 points and
 // 24 materials 622 -> 588 us (its scoring wave was what the other waves waited for), 1.68 M voxels and 128 materials 1183 -> 1130,
-// 123 457 points and 45 materials 184 -> 173 (with the stores of finish_scores_staged for any K), 200 000 queries densified 318 -> 307.
+// 123 457 points and 45 materials 184 -> 173 (with the stores of finish_scores_staged for any K), 200 000 queries densified 318 ->
+// 307.
 // QUADS: the first groups of eight places, four per lane group, that K may reach into.
 template <int MT, int QUADS>
 __device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long n, bool store, int g, int K, int P, float inv_T,
@@ -74,8 +75,8 @@ __device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long
   }
   if (!prop) return;
   if (__builtin_expect(inv_T == 0.0f, 0)) {
-    // Uniform, an infinite temperature: places beyond K must keep their weight of 0, but -inf * 0 is not a number.  The differences are
-    // multiplied here, without those places.  (Selecting the weights of the last tile by index instead: 1.68 M voxels and 128
+    // Uniform, an infinite temperature: places beyond K must keep their weight of 0, but -inf * 0 is not a number.  The differences
+    // are multiplied here, without those places.  (Selecting the weights of the last tile by index instead: 1.68 M voxels and 128
     // materials 631 -> 645 us, 200 000 points and 100 materials 238 -> 251; as it is 631 and 237.)
 #pragma unroll
     for (int r = 0; r < kRows; ++r)
@@ -146,11 +147,11 @@ constexpr int kScoreStagePitch = 36;   // floats: rows start 4 banks apart
 template <int ROWS>
 constexpr int score_stage_floats() { return ROWS * kScoreStagePitch; }
 
-// SHORT: up to 16 materials fill half of the only tile's places, and label and Eq. 4 go over those alone.  Over all of them the step of
-// 20 000 points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 55.9 now),
-// 117 371 queries densified with 6 materials 67.6 -> 68.3 (67.9).  Same bits.  Only for kernels that a wave leaves after these lines
-// and that are short of waves: in k_tile_scores the second copy of them costs more than it saves (6.4 M points and 24 materials 143 ->
-// 150 us), in the scoring wave of k_tile_fused too (step of 200 000 points and 32 materials 220.2 -> 221.5).
+// SHORT: up to 16 materials fill half of the only tile's places, and label and Eq. 4 go over those alone.  Over all of them the step
+// of 20 000 points, 512 fp32 channels and 12 materials had become slower than with a branch per material (57.5 -> 58.2 us, 55.9 now),
+// 117 371 queries densified with 6 materials 67.6 -> 68.3 (67.9).  Same bits.  Only where these lines are the end of a
+// wave with few others beside it: in k_tile_scores the second copy of them costs more than it saves (6.4 M points and 24 materials 143
+// -> 150 us), in the scoring wave of k_tile_fused too (step of 200 000 points and 32 materials 220.2 -> 221.5).
 template <int MT, int ROWS, bool SHORT = false>
 __device__ __forceinline__ void finish_scores_staged(scores_f32x16 (&acc)[MT], long long n0, int rows, int lane, int K,
                                                      int P, float inv_T, const float* __restrict__ ys,

@@ -95,10 +95,10 @@ __global__ __launch_bounds__(256) void k_split_for_cells(CellArgs a) {
 
 // One workgroup of four waves per 128 cells, all materials, all channels: wave w multiplies the rows of cells
 // 32 w .. 32 w + 31.  The table above passes through LDS in chunks of 16 KiB (8 / MT groups of 16 channels), double
-// buffered (four workgroups fit a compute unit): the workgroup copies the next chunk in while it multiplies with this one, so the table comes from L2 once per
-// 128 cells (with one workgroup per 32 cells, every wave reading its operands from L2, it was 16 KiB of table per cell
-// against 2 KiB of features for 1024 channels and 128 materials, and a 48 KiB buffer for the partial sums held a compute
-// unit to three workgroups).  A operand: lane (cell i = l % 32, kg = l / 32) holds channels 16 s + 8 kg .. + 7 of cell i
+// buffered (four workgroups fit a compute unit): the workgroup copies the next chunk in while it multiplies with this one, so the
+// table comes from L2 once per 128 cells (with one workgroup per 32 cells, every wave reading its operands from L2, it was 16 KiB of
+// table per cell against 2 KiB of features for 1024 channels and 128 materials, and a 48 KiB buffer for the partial sums held a
+// compute unit to three workgroups).  A operand: lane (cell i = l % 32, kg = l / 32) holds channels 16 s + 8 kg .. + 7 of cell i
 // (16 contiguous bytes of the stored map), requested one chunk ahead; B operand: the same channels of material
 // n = l % 32.  One chain of partial sums per (cell, material): channel groups in ascending order, hi then lo.
 template <int DT, int MT>

@@ -81,8 +81,8 @@ __global__ __launch_bounds__(kSiftWaves* kWave) void k_tile_sift(FuseArgs a, Til
   };
   constexpr std::integral_constant<int, kSiftAhead> several{};
 
-  // ---- A sample first, the same in every workgroup of the object: a pair of tiles per wave, up to eight views.  Where all are seen so
-  // are nearly all of the object's, and the list is not worth making: k_tile_fused takes every tile, as without the sieve.
+  // ---- A sample first, the same in every workgroup of the object: a pair of tiles per wave, up to eight views.  Where all are seen
+  // so are nearly all of the object's, and the list is not worth making: k_tile_fused takes every tile, as without the sieve.
   {
     const int pairs = (nblk + 1) >> 1, tile = 2 * (int)((2 * wave + 1) * (long long)pairs / (2 * kSiftWaves));
     const uint32_t all = tile + 1 < nblk ? 3u : 1u;
