@@ -527,7 +527,7 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
   }
   s = for_each_table(objs, [&](const aura::ObjTable& tab, int n, int max_pts, int obj_base) {
     tws.obj_base = obj_base;
-    const aura::TileScoring want{sws.G, sws.Kpad, K, P, t32, y, 1.0f / params->temperature, unseen_zero, scores, prop, label};
+    const aura::TileScoring want{sws.G, sws.Kpad, K, P, t32, y, aura::inverse_temperature(params->temperature), unseen_zero, scores, prop, label};
     aura::FuseOutcome did;   // the one-kernel form of the fusion scores its tiles itself where it can
     hipError_t e = aura::launch_fuse_features(va, fa, xyz, fused, count, params->norm_eps, mean_only,
                                               lay.tile ? &tws : nullptr, tab, n, max_pts, st, lay.by_cells ? sws.factor : nullptr,

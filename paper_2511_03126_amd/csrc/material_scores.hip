@@ -608,7 +608,7 @@ hipError_t launch_material_scores(const float* fused, long long N, int D, const 
   int MT = tiles_m(K);
   if (MT == 3) MT = 4;
   const int S = steps_k(D);
-  ScoreArgs a{fused, N, D, K, P, y, 1.0f / temperature, unseen_zero, scores, prop, label,
+  ScoreArgs a{fused, N, D, K, P, y, inverse_temperature(temperature), unseen_zero, scores, prop, label,
               static_cast<const bf16x8*>(workspace), S};
   const bool aligned = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(fused) & 15) == 0;
   if (MT <= 2 && few_rows(N, D, K) && aligned && D % kStepK == 0 && (reinterpret_cast<uintptr_t>(temb) & 15) == 0) {

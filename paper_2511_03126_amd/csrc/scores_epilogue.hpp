@@ -74,16 +74,6 @@ __device__ __forceinline__ void finish_quads(scores_f32x16 (&acc)[MT], long long
     if (label && store && g == 0) label[n] = first ? lo : hi;
   }
   if (!prop) return;
-  if (__builtin_expect(inv_T == 0.0f, 0)) {
-    // Uniform, an infinite temperature: places beyond K must keep their weight of 0, but -inf * 0 is not a number.  The differences
-    // are multiplied here, without those places.  (Selecting the weights of the last tile by index instead: 1.68 M voxels and 128
-    // materials 631 -> 645 us, 200 000 points and 100 materials 238 -> 251; as it is 631 and 237.)
-#pragma unroll
-    for (int r = 0; r < kRows; ++r)
-      if (material(r) < K) acc[r >> 4][r & 15] = (acc[r >> 4][r & 15] - best) * inv_T;
-    best = 0.0f;
-    inv_T = 1.0f;
-  }
   float den = 0.0f;
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {

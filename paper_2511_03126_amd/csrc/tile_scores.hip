@@ -418,7 +418,7 @@ hipError_t launch_tile_scores(const FeatArgs& feat, const TileWs& tws, const Til
                               float* prop, int* label, const ObjTable& tab, int n_obj, int max_pts, bool sifted, hipStream_t stream) {
   if (n_obj == 0 || max_pts == 0) return hipSuccess;
   TileScoreArgs a{tws.hdr, tws.steps, sifted ? tws.counters + (size_t)tws.obj_base * 8 : nullptr, tws.quota, ws.G, ws.Kpad, (uint32_t)(feat.D / 256), ws.factor,
-                  feat.D, K, P, y, 1.0f / temperature, unseen_zero, scores, prop, label};
+                  feat.D, K, P, y, inverse_temperature(temperature), unseen_zero, scores, prop, label};
   return feat.dtype == 1 ? launch_ts<1>(a, tab, n_obj, max_pts, stream) : launch_ts<2>(a, tab, n_obj, max_pts, stream);
 }
 
