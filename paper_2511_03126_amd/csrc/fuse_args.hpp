@@ -80,7 +80,7 @@ struct TileWs {
 };
 
 // How the eight counters of an object are used after k_tile_sift: word 7 holds the length of its list of seen tiles, or kAllSeen where
-// none was made because nearly all are, and XCDs 6 and 7 count their tickets in the two halves of word 6.  A half holds
+// none was made because nearly all are, and where there are several XCDs 6 and 7 count their tickets in the two halves of word 6.  A half holds
 // the tickets of an XCD's share of kSeenListTiles tiles, those asked for beyond it included; larger objects are not sifted.
 constexpr int kSeenWord = 7;
 constexpr unsigned kAllSeen = 0xffffffffu;

@@ -1647,9 +1647,17 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   const int xcd = blockIdx.x % kXcd;
   const XcdTiles mine(nblk, xcd);
   const int len = mine.len;
-  // the XCD's tickets: a word of its own, or (see kSeenWord) half of one
-  const int half = SIFTED ? max(xcd - 6, 0) : 0;
-  unsigned* __restrict__ ctr = a.counters + blockIdx.y * kXcd + xcd - half;
+  // Tickets of the XCD: the workgroups of an XCD take its first four tiles each without asking, and the counter counts those behind
+  // them.  An atomic operation on a word takes 11.5 ns, on other words of the same 32 bytes as well, 5 ns on others of the same 128
+  // bytes: the 1024 that 256 workgroups had begun with were 12 us.  One object has a word for each XCD in 32 bytes of its own (the
+  // words that a call clears are 512 bytes at least), several have eight words each, or seven and the halves of one (see
+  // kSeenWord).  us before / now: one object, single pass, 60 000 points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6
+  // / 43.7, 50 000 of 10 views 65 / 55, 123 457 of 11 views, 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000
+  // points, 768 channels 206 / 203; 64 objects of 100 000 points 2923 / 2892 (with one tile given in place of four 2901).
+  constexpr int kGiven = 4;
+  const int half = SIFTED && gridDim.y > 1 ? max(xcd - 6, 0) : 0;
+  unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? xcd * kXcd : blockIdx.y * kXcd + xcd - half);
+  const int team = (groups - xcd + kXcd - 1) / kXcd, member = (int)blockIdx.x / kXcd;   // the XCD's workgroups; which of them this is
 
   const int tid = threadIdx.x, lane = tid % kWave;
   // Wave index: the product waves come first, then the scoring wave if there is one, then the NP producers (waves go
@@ -1665,10 +1673,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   if (tid == 0) s_drain = 0;
   const int room = min(kStage, ws.quota);   // k-steps a tile may have: the same bound as where they go to memory
   // Zero weights everywhere, by all waves (the barrier that follows in every branch publishes them); from then on the
-  // producers clear what a buffer's last tile wrote.  A launch of one object is short, and its first producer asks for its
-  // tickets and camera rows before it helps (the other way round, 20 833 points of 8 views and 768 channels take 69 us, 61 so).
-  // With several objects other workgroups hide a start, and the tickets are better taken late (64 objects of 100 000 points,
-  // combined call and integral: 2998 us asked first, 2978 so).
+  // producers clear what a buffer's last tile wrote.  A launch of one object is short, and its last producer asks for the camera rows
+  // before it helps.
   auto clear_stage = [&]() {
     for (int q = tid; q < room * (int)(sizeof(TileStep) / 16); q += kWave * (S + NP + (SC ? 1 : 0))) {
       reinterpret_cast<u32x4*>(s_steps[0])[q] = u32x4{0u, 0u, 0u, 0u};
@@ -1693,11 +1699,11 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     auto ticket = [&]() {
       int t = 0;
       if constexpr (SIFTED) {
-        if (lane == 0) t = (int)((atomicAdd(ctr, 1u << (16 * half)) >> (16 * half)) & (xcd >= 6 ? 0xffffu : 0xffffffffu));
+        if (lane == 0) t = (int)((atomicAdd(ctr, 1u << (16 * half)) >> (16 * half)) & (gridDim.y > 1 && xcd >= 6 ? 0xffffu : 0xffffffffu));
       } else {
         if (lane == 0) t = (int)atomicAdd(ctr, 1u);
       }
-      return t;
+      return t + kGiven * team;
     };
     // SIFTED: the tile of a ticket, and what s_plan holds: it, or -1 past the end.  The ticket is looked at at the top of the trip
     // after the one that asked for it, and the list's entry arrives while the tile is built, so no more tiles are spoken for in
@@ -1714,15 +1720,9 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the producer that takes them)
     int e_next = 0;  // SIFTED: its tile
     if (w == NP - 1) {
-      // (tickets and camera rows in flight together; not beside a scoring wave: 13 888 points of 12 views and 768 channels,
-      // combined call, 56.6 us together, 49.1 one after the other)
-      auto load_cameras = [&]() {
-        for (int q = lane; q < ob.n_views * 16; q += kWave) s_cam[q >> 4][q & 15] = fa.vis.cam[(long long)ob.view_begin * 16 + q];
-      };
-      if (SC || several) load_cameras();
-      const int t0 = ticket(), t1 = ticket(), t2 = ticket();
-      t_raw = ticket();
-      if (!(SC || several)) load_cameras();
+      for (int q = lane; q < ob.n_views * 16; q += kWave) s_cam[q >> 4][q & 15] = fa.vis.cam[(long long)ob.view_begin * 16 + q];
+      const int t0 = member, t1 = member + team, t2 = member + 2 * team;
+      t_raw = member + 3 * team;
       if (!several) clear_stage();
       int e0 = 0, e1 = 0, e2 = 0;
       if constexpr (SIFTED) {
