@@ -9,7 +9,7 @@ from pathlib import Path
 PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libaura_fuse.so"
-SOURCES = ["aura_abi.hip", "project_visibility.hip", "fuse_features.hip", "fuse_tile.hip", "tile_sift.hip", "material_scores.hip",
+SOURCES = ["aura_abi.hip", "project_visibility.hip", "fuse_features.hip", "fuse_tile.hip", "tile_sift.hip", "tile_waves.hip", "material_scores.hip",
            "tile_scores.hip", "knn_densify.hip", "thickness_integrate.hip", "select_views.hip", "voxel_downsample.hip", "patch_batch.hip", "estimate_normals.hip", "property_integrate.hip", "calibrate.hip", "no_alloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-fast-math",
@@ -18,7 +18,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-fast-math"
 # fuse_tile.hip: the product kernel asks for its tile tickets (an atomic add by one lane) long before it
 # reads the answer; the compiler's wave-level rewrite of atomics would make the wave wait for the answer
 # on the spot.
-EXTRA_FLAGS = {"fuse_tile.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
+EXTRA_FLAGS = {"tile_waves.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"], "fuse_tile.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 
 
 def _compile(src: str) -> Path:

@@ -535,7 +535,7 @@ static aura_status_t run_fuse_scores(const aura_views_t* views, const aura_param
                                               lay.by_cells ? &want : nullptr, &did, clear_status);
     if (e != hipSuccess || !lay.by_cells || did.scored) return e;
     return aura::launch_tile_scores(fa, tws, sws, K, y, P, params->temperature, unseen_zero, scores, prop, label, tab, n,
-                                    max_pts, did.sifted, st);
+                                    max_pts, did.unlisted_only, st);
   });
   if (s != AURA_OK || lay.by_cells) return s;
   return hip_status(aura::launch_material_scores(fused, N, views->D, t32, K, y, P, params->temperature, scores, prop,

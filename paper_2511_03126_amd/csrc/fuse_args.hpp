@@ -79,9 +79,8 @@ struct TileWs {
   int obj_base;         // index of the launch's first object within the call
 };
 
-// How the eight counters of an object are used after k_tile_sift: word 7 holds the length of its list of seen tiles, or kAllSeen where
-// none was made because nearly all are, and where there are several XCDs 6 and 7 count their tickets in the two halves of word 6.  A half holds
-// the tickets of an XCD's share of kSeenListTiles tiles, those asked for beyond it included; larger objects are not sifted.
+// Word 7 of an object's eight counters after k_tile_sift: the length of its list of seen tiles, or kAllSeen where none was made because
+// nearly all are.  (Longer lists than kSeenListTiles have not been measured.)
 constexpr int kSeenWord = 7;
 constexpr unsigned kAllSeen = 0xffffffffu;
 constexpr long long kSeenListTiles = 8 * 49152;
@@ -89,7 +88,8 @@ constexpr long long kSeenListTiles = 8 * 49152;
 // What a fusion launch did besides the fused rows.
 struct FuseOutcome {
   bool scored = false;   // what FuseArgs::scoring asks for is written
-  bool sifted = false;   // the objects have lists of seen tiles (kSeenWord), and everything there is to write for the others is written
+  bool unlisted_only = false;   // the k-steps are in the workspace for the scoring kernel where word kSeenWord of the object holds kAllSeen;
+                                // elsewhere everything is written
 };
 
 // Byte offset of a cell row as stored in a k-step (a multiple of 512 * units, units = D / 256 in 1..6) -> cell index.
@@ -116,6 +116,12 @@ size_t fuse_tile_status_offset(long long N, int B);   // byte offset of the stat
 TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views);
 // Lists the tiles that some view sees and writes all results of the others (tile_sift.hip); ws cleared, ws.obj_base set.
 hipError_t launch_tile_sift(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_tiles, hipStream_t stream);
+// The fusion of calls that keep no rows and score from per-cell similarities (tile_waves.hip): up to kWaveViews views per object, 1024
+// channels; ws cleared, ws.obj_base set, after launch_tile_sift where `sifted`.  Writes everything that a.scoring asks for (lists_only: of
+// objects with a list).
+constexpr int kWaveViews = 32;
+hipError_t launch_tile_waves(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_views, long long tiles,
+                             bool sifted, bool lists_only, hipStream_t stream);
 // ws cleared, ws.obj_base set.  *did (may be nullptr) tells whether the launch also wrote what a.scoring asks for; if not, the
 // k-steps and the factors are in the workspace for the scoring kernel.
 hipError_t launch_fuse_tile(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, int n_obj, int max_pts,

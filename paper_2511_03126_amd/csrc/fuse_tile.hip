@@ -46,19 +46,14 @@
 
 #include "aura_device.hpp"
 #include "fuse_args.hpp"
+#include "fuse_tile_core.hpp"
 #include "fuse_tile_groups.hpp"
+#include "fuse_tile_lists.hpp"
 #include "launch.hpp"
 #include "scores_epilogue.hpp"
 #include "timing.hpp"
 
 namespace aura {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kViewBatch = 32;                 // views handled per pass over the point tile
 constexpr int kPrepThreads = 256;
@@ -73,423 +68,13 @@ constexpr int kNIT = kViewBatch / kSlots;      // (point, view) pairs per thread
 constexpr int kChunkSteps = AURA_CHUNK;        // k-steps of the weight matrix held in LDS
 constexpr int kChunk = kChunkSteps * kStepCells;
 constexpr int kPitch = kChunk + 8;             // row pitch in 16-bit elements (rows start 4 banks apart)
-constexpr int kHalf = 128;                     // channels of one half wave's row piece: 32 lanes x 4 channels
-constexpr int kWinSide = 32;                   // side of the per-view cell map: one 32-bit word per row
 
 static_assert(kSlots * kTilePts == kPrepThreads && kNIT * kSlots == kViewBatch, "thread mapping");
-static_assert(sizeof(TileStep) == 64 + 2048, "k-step layout");
-
-template <int DT>
-__device__ __forceinline__ void split_weight(float w, uint16_t& hi, uint16_t& lo) {
-  if constexpr (DT == 1) {
-    __bf16 h = (__bf16)w;
-    __bf16 l = (__bf16)(w - (float)h);
-    hi = __builtin_bit_cast(uint16_t, h);
-    lo = __builtin_bit_cast(uint16_t, l);
-  } else {
-    _Float16 h = (_Float16)w;
-    _Float16 l = (_Float16)(w - (float)h);
-    hi = __builtin_bit_cast(uint16_t, h);
-    lo = __builtin_bit_cast(uint16_t, l);
-  }
-}
-
-// ---- half-wave reductions on the data-parallel-primitive lanes: after the call, lane 31 holds
-// the result over lanes 0..31 and lane 63 the result over lanes 32..63.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ s16x2 dpp_pull(s16x2 identity, s16x2 v) {
-  return __builtin_bit_cast(s16x2, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, identity), __builtin_bit_cast(int, v),
-                                                                CTRL, ROW_MASK, 0xf, false));
-}
-
-template <bool IS_MIN>
-__device__ __forceinline__ s16x2 half_wave_reduce(s16x2 v) {
-  const s16x2 id = IS_MIN ? s16x2{0x7fff, 0x7fff} : s16x2{-0x8000, -0x8000};
-#define AURA_RED_STEP(ctrl, mask)                                                                  \
-  v = IS_MIN ? __builtin_elementwise_min(v, dpp_pull<ctrl, mask>(id, v)) : __builtin_elementwise_max(v, dpp_pull<ctrl, mask>(id, v))
-  AURA_RED_STEP(0x111, 0xf);   // row_shr:1
-  AURA_RED_STEP(0x112, 0xf);   // row_shr:2
-  AURA_RED_STEP(0x114, 0xf);   // row_shr:4
-  AURA_RED_STEP(0x118, 0xf);   // row_shr:8  -> lane 15 of every row of 16 holds the row's result
-  AURA_RED_STEP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
-#undef AURA_RED_STEP
-  return v;
-}
-
-template <int CTRL>
-__device__ __forceinline__ int row_shift_add(int v) {
-  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float lane_pull(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-// One round of the sums below: of two values, lanes with `upper` keep the second, the others the first, each with the partner's
-// share.
-template <int CTRL>
-__device__ __forceinline__ float keep_one(float a, float b, bool upper) {
-  return (upper ? b : a) + lane_pull<CTRL>(upper ? a : b);
-}
-
-// Sums over each half of the wave of 16 (H = 1) or 32 (H = 2) values per lane, all together: in every round a lane passes on half
-// of what it holds and adds what it gets, so the additions halve from round to round (five lane shifts for each of the
-// values by itself were 80 or 160, and as many stores by two lanes: 200 000 points of 16 views and 768 channels 239 -> 232 us, 40
-// objects of 50 000 points, single pass, 588 -> 575, 64 of 100 000 1440 -> 1416, 123 457 points of 11 views 173 -> 169).  Rounds:
-// lanes 16 apart, 8, 2, 1 and 4; a value's additions are the same tree for both H.  Lane l (of 32) ends up with value
-// lane_value<H>(l); with 16 values two lanes hold the same one.
-template <int H>
-__device__ __forceinline__ float half_wave_sums(float (&v)[16 * H], int lane) {
-#pragma unroll
-  for (int i = 0; i < 8 * H; ++i) {   // odd rows of 16 lanes of the first value against even rows of the second
-    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false, false);
-    v[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4 * H; ++i) v[i] = keep_one<0x128>(v[2 * i], v[2 * i + 1], (lane & 8) != 0);   // row_ror:8
-#pragma unroll
-  for (int i = 0; i < 2 * H; ++i) v[i] = keep_one<0x4e>(v[2 * i], v[2 * i + 1], (lane & 2) != 0);   // quad_perm [2, 3, 0, 1]
-#pragma unroll
-  for (int i = 0; i < H; ++i) v[i] = keep_one<0xb1>(v[2 * i], v[2 * i + 1], (lane & 1) != 0);       // quad_perm [1, 0, 3, 2]
-  // lanes 4 apart: eight lanes mirrored, then every four
-  if constexpr (H == 1) return v[0] + lane_pull<0x1b>(lane_pull<0x141>(v[0]));
-  const bool upper = (lane & 4) != 0;
-  const float keep = upper ? v[H - 1] : v[0], send = upper ? v[0] : v[H - 1];
-  return keep + lane_pull<0x1b>(lane_pull<0x141>(send));
-}
-
-template <int H>
-__device__ __forceinline__ int lane_value(int l) {
-  return ((l >> 4) & 1) | ((l >> 3) & 1) << 1 | ((l >> 1) & 1) << 2 | (l & 1) << 3 | (H == 2 ? ((l >> 2) & 1) << 4 : 0);
-}
-
 // One (point, view) pair after Eq. 1 and the cell selection.
 struct PairRec {
   int xy;        // y0 << 16 | x0 of the first cell, -1: the view does not see the point
   float ax, ay;  // weights of the second cell per axis
 };
-
-// The slow way out when a tile needs more k-steps than it owns (points far apart): one wave fuses a point by a gather
-// (lanes over channels, 512 channels per sweep, the whole row in registers; the rows of two views in flight together).
-// The row is stored when the call has a place for it (FuseArgs::fused).  When the call wants scores as well
-// (FuseArgs::scoring), they are taken here from the row in registers, so that no later kernel needs the row: omega_k is
-// the fp32 dot product with the fp32 text embedding (largest error 1.2e-7 on 10 601 points of 512 channels; blended from
-// the per-cell similarities, which hold two 16-bit terms, it was 1.2e-6 for bf16 maps), then Eq. 4 and the label with
-// lanes over the materials.
-constexpr int kGatherSweeps = 3;   // 512 channels each: D <= 1536 on this path
-
-template <int DT>
-__device__ __forceinline__ void widen_16(uint32_t w, float& lo, float& hi) {
-  if constexpr (DT == 1) {
-    lo = __uint_as_float(w << 16);
-    hi = __uint_as_float(w & 0xffff0000u);
-  } else {
-    lo = (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));
-    hi = (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
-  }
-}
-
-// SCORES: whether such a call can want scores.  SWEEPS: of 512 channels each.  In the kernels of three waves per SIMD, whose 168
-// registers three sweeps outgrow, as many as the channels fill (three with 100 bytes of scratch memory / two: 200 000 points in no
-// order, 16 views, 768 channels 2447 / 2237 us; as one kernel of two waves per SIMD it was 2357); elsewhere three (16 ragged objects
-// of 3000 points and 256 channels 813 us, 902 with one).
-template <int DT, bool SCORES, int SWEEPS>
-__device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& ob, int li, int lane) {
-  const TileScoring& sc = a.scoring;
-  const int D = a.feat.D, Hf = a.feat.Hf, Wf = a.feat.Wf;
-  const long long i = ob.pt_begin + li;
-  const float x = a.xyz[3 * i], y = a.xyz[3 * i + 1], z = a.xyz[3 * i + 2];
-  float acc[SWEEPS][8];
-#pragma unroll
-  for (int s = 0; s < SWEEPS; ++s)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[s][e] = 0.0f;
-  int cnt = 0;
-  for (int vb = 0; vb < ob.n_views; vb += kWave) {
-    bool seen = false;
-    int x0 = 0, y0 = 0;
-    float ax = 0.0f, ay = 0.0f;
-    if (vb + lane < ob.n_views) {
-      const int v = ob.view_begin + vb + lane;
-      const Proj p = project(a.vis.cam + (long long)v * 16, x, y, z);
-      const float* dv = a.vis.depth ? a.vis.depth + (long long)v * a.vis.H * a.vis.W : nullptr;
-      seen = visible(a.vis, dv, p) && view_kept(a, i, vb + lane);
-      if (a.out_vis) a.out_vis[i * a.vis_pitch + vb + lane] = seen ? 1 : 0;
-      if (seen) {
-        const Tap tx = tap_axis(p.u, a.feat.pitch_x, Wf), ty = tap_axis(p.v, a.feat.pitch_y, Hf);
-        x0 = tx.i0; ax = tx.a;
-        y0 = ty.i0; ay = ty.a;
-      }
-    }
-    unsigned long long m = __ballot(seen);
-    cnt += __popcll(m);
-    while (m) {
-      // two views; of a single one left the second is the first again, its weights zero and its rows not added
-      const int src0 = __builtin_ctzll(m);
-      m &= m - 1;
-      const bool two = m != 0;
-      const int src1 = two ? __builtin_ctzll(m) : src0;
-      m &= m - 1;
-      float wgt[2][4];
-      long long cell[2][4];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int src = q ? src1 : src0;
-        const int sx0 = __builtin_amdgcn_readlane(x0, src), sy0 = __builtin_amdgcn_readlane(y0, src);
-        const float sax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ax), src));
-        const float say = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ay), src));
-        const int sx1 = sx0 + 1 < Wf ? sx0 + 1 : Wf - 1, sy1 = sy0 + 1 < Hf ? sy0 + 1 : Hf - 1;
-        wgt[q][0] = (1.0f - sax) * (1.0f - say); wgt[q][1] = sax * (1.0f - say);
-        wgt[q][2] = (1.0f - sax) * say;          wgt[q][3] = sax * say;
-        const long long first = (long long)(ob.view_begin + vb + src) * Hf * Wf;
-        cell[q][0] = first + sy0 * Wf + sx0; cell[q][1] = first + sy0 * Wf + sx1;
-        cell[q][2] = first + sy1 * Wf + sx0; cell[q][3] = first + sy1 * Wf + sx1;
-      }
-      u32x4 raw[SWEEPS][2][4];
-#pragma unroll
-      for (int s = 0; s < SWEEPS; ++s) {
-        if (s * 8 * kWave >= D) break;   // uniform
-        const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            raw[s][q][c] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.feat.feat) + (cell[q][c] * D + ch) * 2);
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        if (q == 1 && !two) break;   // uniform
-#pragma unroll
-        for (int s = 0; s < SWEEPS; ++s) {
-          if (s * 8 * kWave >= D) break;   // uniform
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              float lo, hi;
-              widen_16<DT>(raw[s][q][c][j], lo, hi);
-              acc[s][2 * j] = __builtin_fmaf(wgt[q][c], lo, acc[s][2 * j]);
-              acc[s][2 * j + 1] = __builtin_fmaf(wgt[q][c], hi, acc[s][2 * j + 1]);
-            }
-        }
-      }
-    }
-  }
-  // mean over the visible views (Eq. 2), then the L2 normalisation
-  const float inv = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
-  float ss = 0.0f;
-#pragma unroll
-  for (int s = 0; s < SWEEPS; ++s) {
-    const bool own = s * 8 * kWave + 8 * lane < D;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      acc[s][e] = own ? acc[s][e] * inv : 0.0f;
-      ss = __builtin_fmaf(acc[s][e], acc[s][e], ss);
-    }
-  }
-  if (!a.mean_only) {
-    const float scale = 1.0f / fmaxf(sqrtf(wave_sum(ss)), a.norm_eps);
-#pragma unroll
-    for (int s = 0; s < SWEEPS; ++s)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[s][e] *= scale;
-  }
-  if (a.fused) {
-    float* __restrict__ out_row = a.fused + i * D;
-#pragma unroll
-    for (int s = 0; s < SWEEPS; ++s) {
-      const int ch = s * 8 * kWave + 8 * lane;
-      if (ch < D) {
-        *reinterpret_cast<f32x4*>(out_row + ch) = f32x4{acc[s][0], acc[s][1], acc[s][2], acc[s][3]};
-        *reinterpret_cast<f32x4*>(out_row + ch + 4) = f32x4{acc[s][4], acc[s][5], acc[s][6], acc[s][7]};
-      }
-    }
-  }
-  if (a.out_count && lane == 0) a.out_count[i] = cnt;
-
-  if (SCORES && sc.G) {
-    // Sec. 3.4.1 for this point, eight materials at a time (their reads in flight together): a dot product per lane over
-    // its channels, then the sums over the wave.  Lane l keeps the similarities of materials l and l + 64.
-    // With two sweeps (768 and 1024 channels, three waves per SIMD) the next eight materials' first reads go ahead of the sums: 168
-    // registers do not hold the reads of both sweeps at a time as 256 do (points in no order, without / with: 12 objects of 33 333
-    // points, 768 channels and 60 materials 1213 / 1120 us, 200 000 points and 128 materials 4752 / 4227).  Not elsewhere: sorted
-    // points of 32 pixel maps 1460 -> 1467 us.
-    constexpr bool kAhead = SWEEPS == 2;
-    float mine[2] = {-INFINITY, -INFINITY};
-    auto request = [&](f32x4 (&t)[8][2], int m0, int s) {
-      const int ch = min(s * 8 * kWave + 8 * lane, D - 8);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const f32x4* e = reinterpret_cast<const f32x4*>(sc.temb + (long long)min(m0 + q, sc.K - 1) * D + ch);
-        t[q][0] = e[0];
-        t[q][1] = e[1];
-      }
-    };
-    f32x4 t[8][2];
-    if constexpr (kAhead) request(t, 0, 0);
-    for (int m0 = 0; m0 < sc.K; m0 += 8) {
-      float dot[8] = {};
-#pragma unroll
-      for (int s = 0; s < SWEEPS; ++s) {
-        if (s * 8 * kWave >= D) break;   // uniform
-        if (s > 0 || !kAhead) request(t, m0, s);
-        if (s * 8 * kWave + 8 * lane < D) {
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              dot[q] = __builtin_fmaf(acc[s][e], t[q][0][e], dot[q]);
-              dot[q] = __builtin_fmaf(acc[s][4 + e], t[q][1][e], dot[q]);
-            }
-        }
-      }
-      if constexpr (kAhead) request(t, m0 + 8, 0);   // (past the last material: the last one again)
-      // the eight sums in one: in each of three rounds a lane passes on the half it will not hold, and from there every
-      // eight lanes hold one material
-#pragma unroll
-      for (int n = 4, o = kWave / 2; n > 0; n >>= 1, o >>= 1) {
-        const bool upper = (lane & o) != 0;
-#pragma unroll
-        for (int q = 0; q < n; ++q) dot[q] = (upper ? dot[n + q] : dot[q]) + __shfl_xor(upper ? dot[q] : dot[n + q], o, kWave);
-      }
-#pragma unroll
-      for (int o = 4; o > 0; o >>= 1) dot[0] += __shfl_xor(dot[0], o, kWave);
-      const float here = __shfl(dot[0], 8 * (lane & 7), kWave);   // material m0 + lane % 8
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (m0 == ((lane + kWave * h) & ~7) && lane + kWave * h < sc.K) mine[h] = here;
-    }
-    float best = fmaxf(mine[0], mine[1]);
-    int bidx = mine[1] > mine[0] ? lane + 64 : lane;   // a lane without a material holds -inf
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      const float ob_ = __shfl_xor(best, o, kWave);
-      const int oi = __shfl_xor(bidx, o, kWave);
-      if (ob_ > best || (ob_ == best && oi < bidx)) { best = ob_; bidx = oi; }   // lowest index wins ties
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int m = lane + 64 * h;
-      if (m < sc.K) sc.scores[i * sc.K + m] = mine[h];
-    }
-    if (sc.label && lane == 0) sc.label[i] = bidx;
-    if (sc.prop) {
-      float e[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) e[h] = lane + 64 * h < sc.K ? weight_exp((mine[h] - best) * sc.inv_T) : 0.0f;
-      const float den = wave_sum(e[0] + e[1]);
-      // all similarities exactly zero (nobody sees the point): zero properties where the caller asks for that
-      const bool zero_row = sc.unseen_zero && __ballot((lane < sc.K && mine[0] != 0.0f) || (lane + 64 < sc.K && mine[1] != 0.0f)) == 0;
-      for (int p = 0; p < sc.P; ++p) {
-        float num = 0.0f;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          if (lane + 64 * h < sc.K) num = __builtin_fmaf(e[h], sc.y[(lane + 64 * h) * sc.P + p], num);
-        num = wave_sum(num);
-        if (lane == 0) sc.prop[i * sc.P + p] = zero_row ? 0.0f : num / den;
-      }
-    }
-  }
-}
-
-// Tiles without k-steps go to lists that the workgroups of the launch empty together when they have run out of tiles.
-// Fused on the spot by the waves that found out, a single such tile held its workgroup up for hundreds of microseconds
-// (32 points one after the other), and with it the end of the kernel (8 tiles of 8000 points, 20 views, 768 channels:
-// 671 us for the step, 169 us with the lists).
-// kLists stacks: word kListWord + l of TileWs::status holds the tile last pushed to list l, plus one (0: empty).  Of
-// TileHdr::cnt, which such a tile does not use, word 0 holds the entry below it, word 1 its object and word 2 how many of its
-// kParts parts have been taken.  Parts are taken by adding to that word, which every comer can do at once; only whoever
-// finds all of them taken moves the head to the entry below.  (Popped part by part, by exchanges on the heads that fail
-// whenever another one came first, the 6250 tiles of 200 000 points in no order took 18.8 ms, 2.5 ms now; 566 of 1504 tiles of
-// 16 objects of 3000 points, 8 views and 256 channels 2520 us, 360 us now.)  A tile is
-// pushed once per launch, so a head never returns to an entry that it has left, and the exchanges cannot be fooled by a
-// reused one.  Nobody waits: a workgroup that finds the lists empty leaves, and one that pushed, or that took parts, looks
-// at the lists again afterwards: all parts of all tiles are taken, and the lists empty, when the last one leaves.
-// Everything the workgroups share goes through agent-scope atomics, which act on memory that all XCDs see, so no cache has
-// to be written back or dropped: the words of an entry are complete (s_waitcnt) before the exchange that publishes it, and
-// their readers take their address from what the exchange left.
-constexpr int kParts = 8, kPartPts = kTilePts / kParts;
-constexpr int kLists = 32, kListWord = 32;
-// A workgroup of two or three waves takes four parts where this many tiles have been pushed: there the words that everybody adds to
-// are what the lists wait for.  As many parts as waves / four, points in no order: 16 objects of 3000 points, 8 views and 256
-// channels, one producer, 884 / 799 us (850 before the gather became faster), 20 of 10 000 and 4 views 2390 / 2081 (2345), 40 of
-// 5000, 4 views, 512 channels, plain fusion 2504 / 2221.  With few tiles on the lists they are better spread over all who look:
-// 8 sorted objects of 10 000 points 119 / 147.
-constexpr unsigned kManyPushed = 1024;
-
-__device__ __forceinline__ void push_tile(const TileWs& ws, int tile, int obj, int lane) {   // one lane of a wave
-  if (lane == 0) {
-    int* words = ws.hdr[tile].cnt;
-    unsigned* head = ws.status + kListWord + tile % kLists;
-    __hip_atomic_store(&words[1], obj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&words[2], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned top = __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    bool done = false;
-    while (!done) {
-      __hip_atomic_store(&words[0], (int)top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      done = __hip_atomic_compare_exchange_strong(head, &top, (unsigned)tile + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    atomicAdd(ws.status + 1, 1u);   // second status word: tiles fused by the gather
-  }
-}
-
-// Called by all waves of a workgroup together, at the end of its life: the first wave takes as many parts as there are waves (see
-// kManyPushed), four points each (those 16 objects, combined call: 359 us; half as many parts 420 us, whole tiles 407 us), and all
-// share their points.  `turn`: the list where the workgroup looks first; `job`: four words of LDS.
-template <int DT, bool SCORES, int SWEEPS>
-__device__ __forceinline__ void drain_tiles(const FuseArgs& a, const TileWs& ws, const ObjTable& tab, unsigned turn, int* job,
-                                            int wave, int n_waves, int lane) {
-  static_assert(kLists == 32, "lanes 0 .. 31 look at one list each");
-  const int rot = (int)(turn % kLists);
-  while (true) {
-    if (wave == 0) {
-      const unsigned pushed = __hip_atomic_load(ws.status + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int want = min(kParts, max(n_waves, pushed >= kManyPushed ? 4 : 0));
-      int parts = 0, tile = 0, obj = 0, first = 0;
-      while (true) {
-        unsigned top = 0u;
-        if (lane < kLists) top = __hip_atomic_load(ws.status + kListWord + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t full = (uint32_t)__ballot(top != 0u);
-        if (full == 0u) break;   // every list is empty
-        const uint32_t rotated = rot ? (full >> rot) | (full << (kLists - rot)) : full;
-        const int list = (rot + __builtin_ctz(rotated)) % kLists;   // the first list at or after `rot` that holds something
-        tile = __builtin_amdgcn_readlane((int)top, list) - 1;
-        int* words = ws.hdr[tile].cnt;
-        int below = 0;
-        if (lane == 0) {
-          first = __hip_atomic_fetch_add(&words[2], want, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          below = __hip_atomic_load(&words[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          obj = __hip_atomic_load(&words[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        first = __builtin_amdgcn_readfirstlane(first);
-        parts = min(want, kParts - first);
-        if (parts > 0) break;
-        if (lane == 0) {
-          unsigned entry = (unsigned)tile + 1u;
-          __hip_atomic_compare_exchange_strong(ws.status + kListWord + list, &entry, (unsigned)below, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);   // (another one was faster: as good)
-        }
-        parts = 0;
-      }
-      if (lane == 0) {
-        job[0] = parts;
-        job[1] = tile;
-        job[2] = first;
-        job[3] = obj;
-      }
-    }
-    __syncthreads();
-    const int parts = __builtin_amdgcn_readfirstlane(job[0]), tile = __builtin_amdgcn_readfirstlane(job[1]);
-    const int first = __builtin_amdgcn_readfirstlane(job[2]), obj = __builtin_amdgcn_readfirstlane(job[3]);
-    __syncthreads();   // everybody has read the job before the next one is written
-    if (parts == 0) return;
-    const ObjRange ob = tab.o[obj];
-    const int li0 = (tile - ob.tile_begin) * kTilePts + first * kPartPts;
-    for (int li = li0 + wave; li < min(li0 + parts * kPartPts, ob.n_pts); li += n_waves) gather_point<DT, SCORES, SWEEPS>(a, ob, li, lane);
-  }
-}
 
 // DT: 1 bf16, 2 fp16 feature maps (decides the 16-bit format of the weights).  SEL: the views of each point are
 // given (FuseArgs::in_mask) instead of decided by the depth test; a variant of its own so that the usual path does
@@ -746,31 +331,6 @@ void k_tile_prepare(FuseArgs a, TileWs ws, ObjTable tab) {
 
 // ------------------------------------------------------------------------------------ product
 
-template <int DT>
-__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
-  if constexpr (DT == 1)
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-// Operands of one k-step in registers: the two weight operands, the lane's 8 cell offsets, and
-// 8 cell rows.
-struct StepA {
-  u32x4 hi, lo;
-};
-
-struct StepC {
-  u32x4 lo, hi;   // byte offsets of the lane's cells: 8 g .. 8 g + 3 and 8 g + 4 .. 8 g + 7
-};
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-template <int H>
-struct StepQ {
-  u32x2 q[H][8];   // [128-channel piece of the wave's span][cell]: 4 channels each
-};
-
 // What the prepare kernel wrote is constant for the product kernel: reading the tile header
 // through the constant address space keeps the wave-uniform read on the scalar unit even inside
 // the tile loop, where the compiler must otherwise assume that the stores of fused rows alias it.
@@ -846,24 +406,6 @@ __device__ __forceinline__ void load_q(const char* __restrict__ feat, const Step
   }
 }
 
-// The matrix-core instructions of one k-step: operand t = 4 h + j holds channel 128 h + 4 m + j of
-// the 8 cells.
-template <int DT, int H>
-__device__ __forceinline__ void mma_step(const StepA& w, const StepQ<H>& r, f32x16 (&acc)[4 * H]) {
-#pragma unroll
-  for (int t = 0; t < 4 * H; ++t) {
-    u32x4 b;
-#pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      // bytes 0..3 of the selector index the first cell's dword, 4..7 the second cell's
-      const uint32_t lo = r.q[t >> 2][2 * e2][(t >> 1) & 1], hi = r.q[t >> 2][2 * e2 + 1][(t >> 1) & 1];
-      b[e2] = __builtin_amdgcn_perm(hi, lo, (t & 1) ? 0x07060302u : 0x05040100u);
-    }
-    acc[t] = mma<DT>(w.hi, b, acc[t]);
-    acc[t] = mma<DT>(w.lo, b, acc[t]);
-  }
-}
-
 // Sums of squares of the wave's channels per point: one for each of its pieces of 128 channels, in ss.  (A sum per piece, so that
 // the norm's additions do not depend on how the channels are dealt out to waves.)
 template <int H>
@@ -895,6 +437,7 @@ struct ProdArgs {
   float norm_eps;
   int mean_only;
   int pace;             // k_tile_fused: shortest time between two tiles of a workgroup, in ticks of the 100 MHz counter
+  const unsigned* unlisted;   // k_tile_fused, may be nullptr: the word that holds kAllSeen where this launch has anything to do
 };
 
 // DT: 1 bf16, 2 fp16 feature maps.  S waves per workgroup, each owning H pieces of 128 channels:
@@ -940,33 +483,6 @@ __device__ __forceinline__ void open_tile(const char* sb, int n_staged, const ch
   }
   lds_a(sb, 0, lane, wa[0]);
 }
-
-// Which of an object's tiles an XCD works on, in the order of its tickets.  The tiles go to the XCDs in chunks of
-// consecutive tiles taken in turn (ticket t of XCD x is tile ((t / chunk) * 8 + x) * chunk + t % chunk): neighbouring
-// tiles still meet in one L2, and every XCD gets a sample of the whole object instead of one contiguous eighth, whose
-// k-steps per tile can differ (1 M points on six ellipsoids, 32 views: the eighths finished between 665 and 775 us).
-// The tiles behind the last whole round of chunks are split into eight contiguous parts, so that the XCDs' shares
-// differ by one tile at most and the first XCDs hold the larger ones (handed out as whole chunks, 6250 tiles gave two XCDs 832 and
-// 810 tiles and the others 768).
-struct XcdTiles {
-  int sh, xcd_sh, full, rest_at, len;   // chunk = 2^sh; tickets below `full` are chunked, the others contiguous
-  __device__ XcdTiles(int nblk, int xcd) {
-    sh = 31 - __builtin_clz(max(1, min(64, nblk / (8 * kXcd))));   // chunk = 2^sh tiles: 64, fewer for small objects
-    const int rounds = nblk >> (sh + 3);                            // kXcd = 8 chunks per round
-    static_assert(kXcd == 8, "rounds of eight chunks");
-    full = rounds << sh;
-    const int base = rounds << (sh + 3), rest = nblk - base;
-    // XCD x takes rest / 8 of them and one more while x < rest % 8: an object of fewer than eight tiles has workgroups on
-    // its first XCDs only
-    const int q = rest >> 3, extra = rest & 7;
-    rest_at = base + xcd * q + min(xcd, extra) - full;
-    len = full + q + (xcd < extra ? 1 : 0);
-    xcd_sh = xcd << sh;
-  }
-  __device__ int at(int t) const {
-    return t < full ? ((((t >> sh) * kXcd) << sh) + xcd_sh + (t & ((1 << sh) - 1))) : rest_at + t;
-  }
-};
 
 template <int DT, int S, int H, int PF>
 __global__ __launch_bounds__(kWave* S) __attribute__((amdgpu_waves_per_eu(H == 1 ? 3 : 2, H == 1 ? 3 : 2)))
@@ -1190,14 +706,6 @@ struct TileSlot {    // what the product waves need to know about a staged tile
   int cnt[NP][kTilePts];   // views that see each point, per producer wave
   uint32_t vmask[kCamRows];           // per view of the object: which of the tile's 32 points it sees (Eq. 1)
 };
-
-// Orders the producer wave's LDS traffic for the compiler.  The LDS unit handles the instructions of one wave in
-// program order, so a later read by any lane sees an earlier write by any other lane of the same wave: no wait and
-// no barrier instruction is needed, only that the compiler keeps the order.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // The point that lane `lane` of a producer wave handles in tile `blk` (lane % 32; the tile's first point where the
 // object has no such point).
@@ -1618,9 +1126,8 @@ __device__ __forceinline__ void store_scores(const ScoreOut& o, const TileScorin
 template <int S, int NP, bool SC>
 constexpr int fused_waves_per_simd() { return S + NP + (SC ? 1 : 0) <= 8 ? 2 : 3; }
 
-// S product waves and NP producer waves per workgroup; with SC one more wave, which scores the tiles (K <= 32).  SIFTED: after
-// k_tile_sift, only the tiles on the object's list.
-template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC, bool SIFTED>
+// S product waves and NP producer waves per workgroup; with SC one more wave, which scores the tiles (K <= 32).
+template <int DT, int S, int H, int PF, bool SEL, int NP, bool SC>
 __global__ __launch_bounds__(kWave* (S + NP + (SC ? 1 : 0)))
     __attribute__((amdgpu_waves_per_eu(fused_waves_per_simd<S, NP, SC>(), fused_waves_per_simd<S, NP, SC>())))
 void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
@@ -1631,7 +1138,7 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ __attribute__((aligned(16))) ProducerScratch s_sc;
   __shared__ float s_ss[2][S * H][kTilePts];
   __shared__ __attribute__((aligned(16))) float s_cam[kCamRows][16];   // the object's camera rows, for the producers
-  __shared__ int s_plan[4];      // the workgroup's tiles (their tickets where not SIFTED), k-th tile in slot k & 3
+  __shared__ int s_plan[4];      // the workgroup's tickets, k-th tile in slot k & 3
   __shared__ __attribute__((aligned(16))) int s_flags[kMaxProducers];   // meeting numbers of the producer waves
   __shared__ int s_job[4];       // see drain_tiles
   __shared__ int s_drain;        // whether this workgroup looks at the lists of push_tile at its end
@@ -1639,9 +1146,8 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   __shared__ ScoreOut s_out[SC ? 2 : 1];                        // scores of the tile before the last, on their way to memory
 
   const ObjRange ob = tab.o[blockIdx.y];
-  // the tiles to fuse: all of the object's, or those on its list (whose positions take the place of the tiles' numbers)
-  const unsigned listed = SIFTED ? a.counters[blockIdx.y * kXcd + kSeenWord] : kAllSeen;
-  const int nblk = listed == kAllSeen ? (ob.n_pts + kTilePts - 1) / kTilePts : (int)listed;
+  if (a.unlisted && *a.unlisted != kAllSeen) return;   // uniform
+  const int nblk = (ob.n_pts + kTilePts - 1) / kTilePts;
   const int groups = min(nblk, (int)gridDim.x);
   if ((int)blockIdx.x >= groups) return;
   const int xcd = blockIdx.x % kXcd;
@@ -1650,13 +1156,12 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   // Tickets of the XCD: the workgroups of an XCD take its first four tiles each without asking, and the counter counts those behind
   // them.  An atomic operation on a word takes 11.5 ns, on other words of the same 32 bytes as well, 5 ns on others of the same 128
   // bytes: the 1024 that 256 workgroups had begun with were 12 us.  One object has a word for each XCD in 32 bytes of its own (the
-  // words that a call clears are 512 bytes at least), several have eight words each, or seven and the halves of one (see
-  // kSeenWord).  us before / now: one object, single pass, 60 000 points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6
-  // / 43.7, 50 000 of 10 views 65 / 55, 123 457 of 11 views, 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000
-  // points, 768 channels 206 / 203; 64 objects of 100 000 points 2923 / 2892 (with one tile given in place of four 2901).
+  // words that a call clears are 512 bytes at least), several have eight words each.  us before / now: one object, single pass, 60 000
+  // points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6 / 43.7, 50 000 of 10 views 65 / 55, 123 457 of 11 views,
+  // 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000 points, 768 channels 206 / 203; 64 objects of 100 000 points
+  // 2923 / 2892 (with one tile given in place of four 2901).
   constexpr int kGiven = 4;
-  const int half = SIFTED && gridDim.y > 1 ? max(xcd - 6, 0) : 0;
-  unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? xcd * kXcd : blockIdx.y * kXcd + xcd - half);
+  unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? xcd * kXcd : blockIdx.y * kXcd + xcd);
   const int team = (groups - xcd + kXcd - 1) / kXcd, member = (int)blockIdx.x / kXcd;   // the XCD's workgroups; which of them this is
 
   const int tid = threadIdx.x, lane = tid % kWave;
@@ -1698,52 +1203,26 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     // Values of len or more mean that the XCD's range is used up.
     auto ticket = [&]() {
       int t = 0;
-      if constexpr (SIFTED) {
-        if (lane == 0) t = (int)((atomicAdd(ctr, 1u << (16 * half)) >> (16 * half)) & (gridDim.y > 1 && xcd >= 6 ? 0xffffu : 0xffffffffu));
-      } else {
-        if (lane == 0) t = (int)atomicAdd(ctr, 1u);
-      }
-      return t + kGiven * team;
+      if (lane == 0) t = (int)atomicAdd(ctr, 1u) + kGiven * team;
+      return t;
     };
-    // SIFTED: the tile of a ticket, and what s_plan holds: it, or -1 past the end.  The ticket is looked at at the top of the trip
-    // after the one that asked for it, and the list's entry arrives while the tile is built, so no more tiles are spoken for in
-    // advance than without a list: with one more the last workgroups had more left to do (us: objects that are seen everywhere,
-    // without the sieve / with one more / now: 265 000 points of 16 views, 512 channels 177 / 190 / 186, 330 000 205 / 220 / 216, 6
-    // views 165 / 174 / 169; 64 objects of 100 000 points 1002 / 987, 20 of 60 000, 768 channels, 288 / 286, 400 000 voxels of 12
-    // views 146 / 144).
-    const TileHdr* __restrict__ list = ws.hdr + ob.tile_begin;
-    auto entry = [&](int t) {
-      const int at = mine.at(min(t, len - 1));
-      return listed == kAllSeen ? at : list[at].listed;
-    };
-    auto plan = [&](int t, int e) { return SIFTED ? (t < len ? e : -1) : t; };
     int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the producer that takes them)
-    int e_next = 0;  // SIFTED: its tile
     if (w == NP - 1) {
       for (int q = lane; q < ob.n_views * 16; q += kWave) s_cam[q >> 4][q & 15] = fa.vis.cam[(long long)ob.view_begin * 16 + q];
-      const int t0 = member, t1 = member + team, t2 = member + 2 * team;
       t_raw = member + 3 * team;
       if (!several) clear_stage();
-      int e0 = 0, e1 = 0, e2 = 0;
-      if constexpr (SIFTED) {
-        e0 = entry(t0);
-        e1 = entry(t1);
-        e2 = entry(t2);
-      }
       if (lane == 0) {
-        s_plan[0] = plan(t0, e0);
-        s_plan[1] = plan(t1, e1);
-        s_plan[2] = plan(t2, e2);
+        for (int k = 0; k < 3; ++k) s_plan[k] = member + k * team;
         for (int o = 0; o < kMaxProducers; ++o) s_flags[o] = 0;
       }
     }
     if (w != NP - 1 && !several) clear_stage();
     __syncthreads();   // camera rows, the first plans and the meeting flags are in LDS
     const int last_tile = nblk - 1;
-    auto planned = [&](int t) { return SIFTED ? t >= 0 : t < len; };
-    auto tile_at = [&](int t) { return SIFTED ? t : mine.at(t); };
+    auto planned = [&](int t) { return t < len; };
+    auto tile_at = [&](int t) { return mine.at(t); };
     // a plan past the end reads (and projects) a tile that exists; it is never built
-    auto tile_of = [&](int t) { return SIFTED ? max(t, 0) : min(mine.at(t), last_tile); };
+    auto tile_of = [&](int t) { return min(mine.at(t), last_tile); };
     // Who looks at the lists: the workgroups that pushed, which may be the last to, and those among the launch's last
     // workgroups that find, when they run out of tiles, that somebody has (a workgroup in a launch of many thousands that ends
     // early is replaced by the next one).  The producer asks while the product waves are busy with the last tile: asked by
@@ -1779,9 +1258,6 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     while (s_slot[buf].tile >= 0) {
       const int t = s_plan[k & 3], tn = s_plan[(k + 1) & 3];
       const float3 pt_next = tile_point(fa, ob, tile_of(tn), lane);   // requested now, looked at after this tile is built
-      if constexpr (SIFTED) {
-        if (w == NP - 1) e_next = entry(t_raw);
-      }
       if (planned(t)) {
         produce_tile<DT, SEL, NP>(fa, ob, tile_at(t), pt, pre, s_steps[buf ^ 1], room, buf ? dirty0 : dirty1, &s_slot[buf ^ 1], &s_sc, cam_lds,
                                   (lds_flags)&s_flags[0], ws, blockIdx.y, &s_drain, w, seq, lane);
@@ -1793,14 +1269,9 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
       pt = pt_next;
       project_batch<SEL, NP>(fa, ob, tile_of(tn), pt, 0, cam_lds, w, lane, pre);   // its depth texels arrive during the barrier
       if (w == NP - 1) {   // the plan of tile k + 2: its slot (k + 2) & 3 held tile k - 2, which nobody looks at any more
-        if constexpr (SIFTED) {
-          if (lane == 0) s_plan[(k + 2) & 3] = plan(t_raw, e_next);
-          if (__builtin_amdgcn_readfirstlane(t_raw) < len) t_raw = ticket();
-        } else {
-          const int t3 = __builtin_amdgcn_readfirstlane(t_raw);
-          if (lane == 0) s_plan[(k + 2) & 3] = t3;
-          if (t3 < len) t_raw = ticket();
-        }
+        const int t3 = __builtin_amdgcn_readfirstlane(t_raw);
+        if (lane == 0) s_plan[(k + 2) & 3] = t3;
+        if (t3 < len) t_raw = ticket();
       }
       __syncthreads();
       buf ^= 1;
@@ -2174,23 +1645,16 @@ static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units,
 
 // Whether the one-kernel form of this launch can score its tiles itself: a scoring wave must fit the workgroup (up to 768
 // channels beside four producers) and one matrix-core tile must hold the materials.
-static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n_obj, long long tiles) {
-  // With one producer wave (two workgroups of up to four waves per compute unit) the scoring wave pays where no rows are
-  // stored (the single-pass call: C5 2.63 -> 2.45 ms): with rows the call is bound by their stores either way, and the
-  // separate scoring kernel keeps the fusion kernel shorter (C5 combined call 3.12 ms against 3.16 ms).
-  const bool fits = (producers == 4 && 2 * units + 4 + 1 <= 12) ||
-                    (producers == 1 && units + 1 + 1 <= 4 && a.fused == nullptr);
-  // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
-  // without it four workgroups fit a compute unit instead of two.  us with / without it (single pass, 24 materials, 4 views): 20
-  // objects of 60 000 points 346 / 264, 64 of 12 000 263 / 209, 12 of 60 000 238 / 162, 16 of 20 000 122 / 98, 40 of 10 000 170 /
-  // 149, 8 of 100 000 198 / 193; few objects or tiles: 4 of 200 000 205 / 219, 30 of 10 000 123 / 127, 8 of 30 000 90 / 100.
-  if (producers == 1 && units == 1 && n_obj >= 8 && tiles >= 10000) return false;
-  return fits && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
+static bool scoring_wave_fits(const FuseArgs& a, int producers, int units) {
+  // (not with one producer wave: with rows the call is bound by their stores either way, and the separate scoring kernel keeps the
+  // fusion kernel shorter: 64 objects of 100 000 points and 4 views, combined call, 3.12 ms against 3.16 ms)
+  return producers == 4 && 2 * units + 4 + 1 <= 12 && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
 }
 
 // Whether k_tile_sift goes ahead of this launch: calls that store no rows, of sizes where the tiles that it finds are worth its
 // launch and the lists.  (With rows the stores set the time, and the unseen rows' are best mixed with the others': 64 objects of
-// 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said:
+// 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said, both with the
+// form with producers behind it:
 //   one object, voxels of a solid   1.68 M, 24 views, 1024 channels, 128 materials 1096 / 609; 400 000, 12 views, 768 channels 197 /
 //     144, 6 views, 512 channels 182 / 116, 6 views, 256 channels and 40 materials (one producer) 215 / 138; 300 000, 12 views, 768
 //     channels 151 / 124; 265 000, 24 views, 1024 channels, 100 materials 263 / 242; 150 000, 12 views, 768 channels 98 / 105
@@ -2201,13 +1665,44 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n
 //     channels 365 / 285; 12 x 60 000, 4 238 / 183; 12 x 40 000, 4, 768 channels 190 / 172; 4 x 200 000, 4 214 / 157
 //   ... whose workgroups would be left with few tiles each   20 x 30 000, 8 views 286 / 316; 64 x 12 000, 4 280 / 301; 8 x 30 000, 4
 //     94 / 113; 2 x 60 000, 4 76 / 73
+constexpr long long kSiftOneObject = 8192;   // tiles
 static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long tiles) {
   // The results of a tile that nobody sees are known to be zero: not where a factor of 1 / 0 or a weight of exp(0 * inf) would
   // make them something else.
   if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles) return false;
   if (!(a.mean_only || a.norm_eps >= 1e-30f) || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
-  if (n_obj == 1) return tiles >= 8192;
+  if (n_obj == 1) return tiles >= kSiftOneObject;
   return tiles >= 12288 && tiles >= 1250ll * n_obj;
+}
+
+// Which calls without rows take k_tile_fused of tile_waves.hip, a tile per wave.  Its waves hide each other's waits, so it wants many
+// tiles, and it keeps a tile's k-steps in a wave's share of LDS, so it wants them short.  What a tile needs is estimated from what
+// sorted points on closed surfaces need: 0.3 k-steps per view and 17 more per point that there is for each cell of a view (330 000 points,
+// 16 views of 32 x 32 cells 5.8, 123 457 of 11 views of 37 x 37 5.3, 60 000 of 20 13.6).  us by producers / by waves, 24 materials:
+//   one object, up to eight views   60 000 points, 5 views, 512 channels 46 / 35; 20 000 of 4 views, 1024 channels 44 / 38; 80 000, 7
+//     views of 37 x 37 cells, 768 channels 65 / 59; 120 000, 8 views of 56 x 56, 1024 channels 116 / 103; 800 000, 6 views, 256
+//     channels 399 / 194; but 30 000, 6 views, 768 channels 42 / 48; 40 000, 8 views of 37 x 37 45 / 61; 100 000, 8 views of 112 x 112,
+//     30 materials 127 / 138
+//   one object, more views   400 000, 10 views 211 / 172, 24 views 364 / 308; 1 M, 16 views 512 / 369, 20 views, 1024 channels 887 /
+//     567; 330 000, 16 views 204 / 196; 300 000, 24 views of 112 x 112 331 / 320; 270 000, 32 views of 56 x 56, 256 channels 442 / 325;
+//     with fewer tiles than the sieve takes 200 000, 16 views, 768 channels 160 / 204; 100 000, 10 views 77 / 82
+//   several objects   40 x 50 000 ragged, 2 to 4 views 457 / 289; 64 x 100 000, 4 987 / 562; 16 x 3000, 8, 256 channels 292 / 144; 2 x
+//     60 000, 12 96 / 75; 5 x 100 000, 16 439 / 257; 6 x 60 000, 20 365 / 277; 24 x 50 000, 6, 1024 channels, 128 materials 685 / 458;
+//     but 3 x 40 000, 24 views of 37 x 37, 768 channels 175 / 226
+// Long lists in one object of many views: where the sieve has sampled none but seen tiles, they are as long as the estimate, and the
+// launch with four producers follows, which leaves at once where there is a list (*both; 300 000 points, 32 views of 56 x 56, 1024
+// channels, seen from all around 510 / 682, voxels of a solid 271 / 256; the launch that leaves costs 5).
+static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, bool sifted, bool* both) {
+  *both = false;
+  if (a.fused || !a.scoring.G || a.in_mask || a.two_kernels || views > kWaveViews || units > 4) return false;
+  const double steps = views * (0.3 + 17.0 * a.feat.Hf * a.feat.Wf * n_obj / ((double)kTilePts * std::max(1ll, tiles)));
+  if (n_obj > 1) return sifted || steps <= 12.0;
+  if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
+  if (tiles < kSiftOneObject) return false;
+  const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
+  const bool longer = coarse && steps > 10.0 && (units > 2 || (units == 2 && a.scoring.Kpad == kScoreTileM));
+  *both = sifted && longer;
+  return sifted || !longer;
 }
 
 template <int DT, int S, int H, int PF>
@@ -2215,12 +1710,28 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
                               hipStream_t stream, FuseOutcome* did) {
   const int max_tiles = (max_pts + kTilePts - 1) / kTilePts;
   ProdArgs pa{static_cast<const char*>(a.feat.feat), a.feat.D, ws.hdr, ws.steps, ws.counters + (size_t)ws.obj_base * kXcd,
-              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0};
+              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0, nullptr};
   int max_views = 0;
   long long tiles = 0;
   for (int t = 0; t < n_obj; ++t) {
     max_views = std::max(max_views, tab.o[t].n_views);
     tiles += (tab.o[t].n_pts + kTilePts - 1) / kTilePts;
+  }
+  const TimedLaunch timed(stream);
+  const bool sifted = !a.two_kernels && sift_tiles(a, n_obj, max_tiles, tiles);
+  bool both = false;
+  if (tile_per_wave(a, max_views, S, n_obj, tiles, sifted, &both)) {
+    if (sifted) {
+      const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
+      if (e != hipSuccess) return e;
+    }
+    const hipError_t e = launch_tile_waves(a, ws, tab, n_obj, max_views, tiles, sifted, both, stream);
+    if (e != hipSuccess || !both) {
+      if (did) did->scored = true;
+      return e;
+    }
+    pa.unlisted = pa.counters + kSeenWord;
+    if (did) did->unlisted_only = true;
   }
   const int np = one_kernel_producers(a, max_views, S, n_obj, tiles);
   constexpr bool kOneProducer = S + 1 <= 4, kFourProducers = 2 * S + 4 <= 12;   // what it can answer (launched below)
@@ -2230,21 +1741,15 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
     // points, 8 views, combined call: 161 us with two, 143 with four), not for one (more than 32 materials, 400 000 points of 8
     // views: single pass 224 us with two, 230 with four, step 226 and 235; 1 M points of 6 views 503 and 503, 514 and 525).
-    const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles);
+    const bool scoring = scoring_wave_fits(a, np, S);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
-    const bool sifted = sift_tiles(a, n_obj, max_tiles, tiles);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
     // of 100 000 points and 4 views with eight per object: the workgroups' end times were spread over the last quarter of the
     // kernel; fusion call 2.79 ms, 2.44 with 64 per object, 2.41 with 128, 2.43 with 256 and 384).  The combined call, whose
-    // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.  With lists of seen tiles
-    // (half of the tiles or fewer) 2048 workgroups in all, at least 32 per object; us with 64 / 32 / as it is, single pass: 64
-    // objects of 100 000 points 983 / 991 / 992; 50 of 45 000 496 / 488 / 479; 40 of 50 000, 256 channels 334 / 363 / 321, ragged 403
-    // / 404 / 400; 30 of 60 000, 3 views 338 / 314 / 338; 20 of 60 000 259 / 291 / 259; 10 of 100 000, 1024 channels 276 / 315 / 276;
-    // with 16 all are slower (64 of 100 000 1201), with 128 too (1123).
-    const int most = !sifted ? 64 : std::max(32, std::min(64, 2048 / n_obj / kXcd * kXcd));
+    // workgroups also write the k-steps for the scoring kernel: 3.10 -> 2.94 ms with 64 and slower beyond.
     const int per_object = n_obj <= 1 ? 0
-                         : (keep || scoring) ? std::min(most, max_tiles / 8 / kXcd * kXcd)
+                         : (keep || scoring) ? std::min(64, max_tiles / 8 / kXcd * kXcd)
                                              : fused_groups_per_object(S, np, n_obj, groups_max, max_tiles);
     // Where nothing but the row stores sets the time, the workgroups must not run ahead of the memory: tiles that nobody sees
     // are stored as fast as they can be issued, and the more of that, the less of it memory takes (the faster producers made
@@ -2268,22 +1773,11 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     if (!keep && !scoring && np == 1 && S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * ((np > 1 ? 2 * S : S) + np + (scoring ? 1 : 0)));
-    const TimedLaunch timed(stream);
-    if (sifted) {
-      const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
-      if (e != hipSuccess) return e;
-      if (did) did->sifted = true;
-    }
-#define AURA_FUSED(s_, h_, sel, np_, sc)                                                                                                  \
-  if (!sel && sifted) hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, false, np_, sc, true>), grid, block, 0, stream, a, pa, ws, keep, tab); \
-  else hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, sel, np_, sc, false>), grid, block, 0, stream, a, pa, ws, keep, tab)
+#define AURA_FUSED(s_, h_, sel, np_, sc) \
+  hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, sel, np_, sc>), grid, block, 0, stream, a, pa, ws, keep, tab)
     if (scoring) {
       pa.factor = nullptr;   // nobody reads the factors back
-      if (np == 1) {
-        if constexpr (kOneProducer && S + 1 + 1 <= 4) { AURA_FUSED(S, H, false, 1, true); }
-      } else {
-        if constexpr (kFourProducers && 2 * S + 4 + 1 <= 12) { AURA_FUSED(2 * S, 1, false, 4, true); }
-      }
+      if constexpr (kFourProducers && 2 * S + 4 + 1 <= 12) { AURA_FUSED(2 * S, 1, false, 4, true); }
       if (did) did->scored = true;
     } else if (np == 1) {
       if constexpr (kOneProducer) {
@@ -2298,7 +1792,6 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
 #undef AURA_FUSED
     return hipGetLastError();
   }
-  const TimedLaunch timed(stream);   // two kernels: the events go around the pair
   if (a.in_mask)
     hipLaunchKernelGGL((k_tile_prepare<DT, true>), dim3(max_tiles, n_obj), dim3(kPrepThreads), 0, stream, a, ws, tab);
   else

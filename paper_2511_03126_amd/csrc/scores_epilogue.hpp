@@ -189,6 +189,31 @@ __device__ __forceinline__ void finish_scores_staged(scores_f32x16 (&acc)[MT], l
   else finish_quads<MT, 4 * MT>(acc, n, pt < rows, g, K, P, inv_T, ys, prop, label, unseen_zero);
 }
 
+// Eq. 4 on equal similarities, for a point that no view sees: the epilogue's sums in its order with every weight 1, hence its bits (or
+// zeros, with unseen_zero).  By one wave; out holds kScoreMaxP values, in LDS.
+__device__ __forceinline__ void unseen_properties(int K, int P, const float* __restrict__ y, bool unseen_zero, int lane, float* out) {
+  const int g = lane >> 5;
+  float den = 0.0f, num[kScoreMaxP];
+#pragma unroll
+  for (int p = 0; p < kScoreMaxP; ++p) num[p] = 0.0f;
+  for (int mt = 0; mt * kScoreTileM < K; ++mt)
+    for (int r = 0; r < 16; ++r) {
+      const int m = mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3);
+      if (m < K) {
+        den += 1.0f;
+#pragma unroll
+        for (int p = 0; p < kScoreMaxP; ++p)
+          if (p < P) num[p] = __builtin_fmaf(1.0f, y[m * P + p], num[p]);
+      }
+    }
+  den += __shfl_xor(den, 32, kWave);
+#pragma unroll
+  for (int p = 0; p < kScoreMaxP; ++p) {
+    const float t = num[p] + __shfl_xor(num[p], 32, kWave);
+    if (lane == 0) out[p] = unseen_zero ? 0.0f : t / den;
+  }
+}
+
 // What finish_scores_staged writes for 32 consecutive points whose similarities are all exactly +0 (a tile that no view
 // sees), without its exponentials: scores 0, label 0, and the properties Eq. 4 gives for equal similarities - the same
 // sums in the same order (every weight is exp(0 * inv_T) = 1, so a fused multiply-add by it is an addition), hence the

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_cell_scores_small(CellArgs a) {
 struct TileScoreArgs {
   const TileHdr* hdr;
   const TileStep* steps;
-  const unsigned* seen;  // [objects][8], word kSeenWord: length of the object's list of seen tiles, or kAllSeen; nullptr: not sifted
+  const unsigned* seen;  // [objects][8]: only objects whose word kSeenWord holds kAllSeen; nullptr: all
   int quota;
   const uint32_t* G;
   int Kpad;
@@ -253,15 +253,12 @@ __global__ __launch_bounds__(256) void k_tile_scores(TileScoreArgs a, ObjTable t
   const ObjRange ob = tab.o[blockIdx.y];
   const int nblk = (ob.n_pts + kTilePts - 1) / kTilePts;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  // with a list of seen tiles the waves take those, and the workgroups beyond it leave
-  const int at = blockIdx.x * 4 + wave;
-  const unsigned listed = a.seen ? a.seen[8 * blockIdx.y + kSeenWord] : kAllSeen;   // uniform
-  const int n_tiles = listed == kAllSeen ? nblk : (int)listed;
-  const int tile = listed != kAllSeen && at < n_tiles ? a.hdr[ob.tile_begin + at].listed : at;
-  const int nsteps = at < n_tiles ? a.hdr[ob.tile_begin + tile].nsteps : -1;
+  if (a.seen && a.seen[8 * blockIdx.y + kSeenWord] != kAllSeen) return;   // uniform
+  const int tile = blockIdx.x * 4 + wave;
+  const int nsteps = tile < nblk ? a.hdr[ob.tile_begin + tile].nsteps : -1;
   // Nothing to do here for a tile fused by a gather inside the fusion kernel (nsteps < 0: scored there as well) and for
-  // a tile that no view sees (k_tile_zero_rows writes its results, k_tile_sift those of the tiles that it left out; where it made
-  // no list because nearly every tile is seen the few others are scored here); a workgroup of such tiles leaves at once.
+  // a tile that no view sees (k_tile_zero_rows writes its results; where nearly every tile is seen the few others are scored here); a
+  // workgroup of such tiles leaves at once.
   const bool mine = nsteps > 0 || (nsteps == 0 && (a.seen || !(0.0f * a.inv_T == 0.0f)));
   if (!__syncthreads_or(mine)) return;
   if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
@@ -415,9 +412,9 @@ static hipError_t launch_ts(const TileScoreArgs& a, const ObjTable& tab, int n_o
 
 hipError_t launch_tile_scores(const FeatArgs& feat, const TileWs& tws, const TileScoreWs& ws,
                               int K, const float* y, int P, float temperature, int unseen_zero, float* scores,
-                              float* prop, int* label, const ObjTable& tab, int n_obj, int max_pts, bool sifted, hipStream_t stream) {
+                              float* prop, int* label, const ObjTable& tab, int n_obj, int max_pts, bool unlisted_only, hipStream_t stream) {
   if (n_obj == 0 || max_pts == 0) return hipSuccess;
-  TileScoreArgs a{tws.hdr, tws.steps, sifted ? tws.counters + (size_t)tws.obj_base * 8 : nullptr, tws.quota, ws.G, ws.Kpad, (uint32_t)(feat.D / 256), ws.factor,
+  TileScoreArgs a{tws.hdr, tws.steps, unlisted_only ? tws.counters + (size_t)tws.obj_base * 8 : nullptr, tws.quota, ws.G, ws.Kpad, (uint32_t)(feat.D / 256), ws.factor,
                   feat.D, K, P, y, inverse_temperature(temperature), unseen_zero, scores, prop, label};
   return feat.dtype == 1 ? launch_ts<1>(a, tab, n_obj, max_pts, stream) : launch_ts<2>(a, tab, n_obj, max_pts, stream);
 }

@@ -22,9 +22,9 @@ TileScoreWs tile_scores_workspace(void* workspace, long long N, long long n_cell
 hipError_t launch_cell_scores(const FeatArgs& feat, long long n_cells, const float* temb, int K, const TileScoreWs& ws,
                               const TileWs& tws, int B, hipStream_t stream);
 // Scores, labels and properties of the objects of one launch table from the k-steps in `tws` (after the
-// product kernel of the same table has run with ws.factor as its factor output).  sifted: FuseOutcome::sifted.
+// product kernel of the same table has run with ws.factor as its factor output).  unlisted_only: see FuseOutcome.
 hipError_t launch_tile_scores(const FeatArgs& feat, const TileWs& tws, const TileScoreWs& ws,
                               int K, const float* y, int P, float temperature, int unseen_zero, float* scores,
-                              float* prop, int* label, const ObjTable& tab, int n_obj, int max_pts, bool sifted, hipStream_t stream);
+                              float* prop, int* label, const ObjTable& tab, int n_obj, int max_pts, bool unlisted_only, hipStream_t stream);
 
 }  // namespace aura

@@ -2,11 +2,10 @@
 //
 // A tile that nobody sees (the inside of a voxelised solid: eight of ten; the far side of an object with frontal views: every
 // second one) needs no k-steps and no products: its mask, counts, scores and labels are zero, its properties those of equal
-// similarities.  k_tile_fused nevertheless spent a whole turn of a workgroup on each, 3 us and more of projections, depth texels and
-// meetings with nobody to hide behind.  Here a wave tests two tiles at a time, with many waves in flight, and only until the
+// similarities.  Here a wave tests two tiles at a time, with many waves in flight, and only until the
 // first hit; it begins with the view that saw its last tiles, so a tile that is seen costs little more than one projection per
 // point.  The unseen tiles' results are written here, as plain runs of stores; the others go to their object's list, in groups of
-// neighbours, and k_tile_fused and k_tile_scores work through that.
+// neighbours, and k_tile_fused (tile_waves.hip) works through that.
 #include <type_traits>
 
 #include "aura_device.hpp"
@@ -137,27 +136,7 @@ __global__ __launch_bounds__(kSiftWaves* kWave) void k_tile_sift(FuseArgs a, Til
   // ---- the seen ones on the list
   if (threadIdx.x == 0 && seen != 0u) s_at = (int)atomicAdd(seen_word, (unsigned)__popc(seen));
   if (wave == 1 && others != 0u && sc.prop) {
-    // Eq. 4 on equal similarities: the epilogue's sums with every weight 1, in its order
-    const int g = lane >> 5;
-    float den = 0.0f, num[kScoreMaxP];
-#pragma unroll
-    for (int p = 0; p < kScoreMaxP; ++p) num[p] = 0.0f;
-    for (int mt = 0; mt * kScoreTileM < sc.K; ++mt)
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * kScoreTileM + 8 * (r >> 2) + 4 * g + (r & 3);
-        if (m < sc.K) {
-          den += 1.0f;
-#pragma unroll
-          for (int p = 0; p < kScoreMaxP; ++p)
-            if (p < sc.P) num[p] = __builtin_fmaf(1.0f, sc.y[m * sc.P + p], num[p]);
-        }
-      }
-    den += __shfl_xor(den, 32, kWave);
-#pragma unroll
-    for (int p = 0; p < kScoreMaxP; ++p) {
-      const float t = num[p] + __shfl_xor(num[p], 32, kWave);
-      if (lane == 0) s_prop[p] = sc.unseen_zero ? 0.0f : t / den;
-    }
+    unseen_properties(sc.K, sc.P, sc.y, sc.unseen_zero != 0, lane, s_prop);
   }
   __syncthreads();
   if (threadIdx.x < kSiftTiles && ((seen >> threadIdx.x) & 1u))

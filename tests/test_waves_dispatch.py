@@ -1,0 +1,42 @@
+"""Which calls without rows take k_tile_fused with a tile per wave, without a GPU (launch_recorder.cpp stands in for the HIP runtime)."""
+import pytest
+
+from test_launches import F16, MEAN_ONLY, TWO_KERNELS, _call, recorder  # noqa: F401
+
+
+def _kernels(recorder, **kw):
+    (status, log), = recorder([_call(**kw)])
+    assert status == 0
+    return [x[0] for x in log if x not in ("S", "E")]
+
+
+def _by_waves(name):
+    return name.startswith("k_tile_fused<") and name.count(",") == 3
+
+
+@pytest.mark.parametrize("kw,waves", [
+    (dict(N=60_000, V=5, Hf=16), True), (dict(N=20_000, V=4, D=1024, Hf=16), True), (dict(N=40_000, V=8, Hf=37), False),
+    (dict(N=262_113, V=8, Hf=224), True), (dict(N=262_112, V=12, Hf=16), False), (dict(N=262_113, V=12, Hf=16), True),
+    (dict(N=60_000, V=16, B=2, Hf=16), True), (dict(N=120_000, V=24 * 3, B=3, Hf=37), False),
+    (dict(N=1_000_000, V=33, Hf=16), False), (dict(D=1536), False), (dict(flags=TWO_KERNELS), False), (dict(call="scores"), False),
+])
+def test_who_takes_a_tile_per_wave(recorder, kw, waves):
+    names = _kernels(recorder, **kw)
+    assert any(_by_waves(n) for n in names) == waves
+    if waves:
+        assert names[-1] in ("k_mass_final", "k_mass_points_small") and not any(n.startswith("k_tile_scores") for n in names)
+
+
+def test_views_and_materials_choose_the_instance(recorder):
+    for V, K, dtype in ((8, 32, F16), (9, 32, 1), (8, 33, 1), (9, 128, F16)):
+        name, = [n for n in _kernels(recorder, N=1_000_000, V=V, Hf=16, K=K, dtype=dtype) if _by_waves(n)]
+        assert name == f"k_tile_fused<{dtype},{int(V > 8)},{4 if K > 32 else 1},1>"
+
+
+@pytest.mark.parametrize("kw,both", [(dict(K=24), True), (dict(K=24, D=512), True), (dict(K=40, D=512), False), (dict(K=40), True),
+                                     (dict(D=256), False), (dict(N=5_000_000), False)])
+def test_long_lists_are_left_to_the_producers_where_all_tiles_are_seen(recorder, kw, both):
+    names = _kernels(recorder, **dict(dict(N=262_145, V=32, Hf=56, D=768), **kw))
+    fused = [n for n in names if n.startswith("k_tile_fused<")]
+    assert _by_waves(fused[0]) and len(fused) == 1 + both
+    assert any(n.startswith("k_tile_scores") for n in names) == (both and kw.get("K", 24) > 32)
