@@ -172,3 +172,38 @@ def test_nan_and_inf_features_leave_the_other_queries_alone():
     untouched = ~(clean["nn_idx"] == 11).any(1)
     assert (gpu["nn_idx"][untouched] == clean["nn_idx"][untouched]).all()
     assert np.array_equal(gpu["wq"][untouched], clean["wq"][untouched])
+
+
+@pytest.mark.parametrize("Nq,Ns,D,K,P,k,shift", [
+    # one, two and three steps of 32 channels; queries around a tile of 32 and a workgroup's four
+    (1, 33, 32, 4, 1, 1, 0), (31, 97, 64, 32, 2, 2, 0), (33, 160, 96, 33, 1, 16, 0), (128, 161, 32, 36, 2, 16, 0),
+    (129, 128, 128, 64, 8, 5, 0),
+    # material vectors beyond the on-chip copy: rows of whole 16 bytes, shifted by four bytes, and of any length
+    (700, 150, 64, 128, 8, 16, 0), (700, 150, 64, 128, 2, 5, 1), (400, 256, 96, 125, 1, 3, 0), (300, 192, 64, 128, 2, 16, 1)])
+def test_edges_of_tiles_steps_and_on_chip_vectors(orc, Nq, Ns, D, K, P, k, shift):
+    import paper_2511_03126_amd as aura
+    from paper_2511_03126_amd import binding
+    fq, fs, ws, y = _inputs(Nq, Ns, D, K, P, seed=Nq + Ns + K)
+    print(f"\n[knn] Nq={Nq} Ns={Ns} D={D} K={K} P={P} k={k} shift={shift}", flush=True)
+    dev = "cuda:0"
+    t = lambda a: torch.from_numpy(a).to(dev)
+    held = torch.empty(Ns * K + shift, device=dev)
+    vectors = held[shift:].view(Ns, K)
+    vectors.copy_(t(ws))
+    wq, prop = torch.full((Nq, K), float("nan"), device=dev), torch.full((Nq, P), float("nan"), device=dev)
+    label = torch.full((Nq,), -7, dtype=torch.int32, device=dev)
+    nn_idx = torch.full((Nq, k), -7, dtype=torch.int32, device=dev)
+    work = torch.empty(aura.workspace_bytes(binding.CALL_KNN_DENSIFY, D=D, Ns=Ns), dtype=torch.uint8, device=dev)
+    aura.knn_densify(t(fq), t(fs), vectors, k, t(y), aura.Params(temperature=0.1), wq, prop, label, nn_idx, work)
+    gpu = dict(wq=wq.cpu().numpy(), prop=prop.cpu().numpy(), label=label.cpu().numpy(), nn_idx=nn_idx.cpu().numpy())
+    ref = orc.knn_densify(fq, fs, ws, k, y=y, T=0.1)
+    # every reported set is the Eq. 5 mean of its neighbours, whichever of two equally near sources was taken: the similarities
+    # carry two bf16 terms per operand (2^-16 of a unit product, so 2e-5), the mean divides by their sum
+    unit = lambda a: a.astype(np.float64) / np.linalg.norm(a.astype(np.float64), axis=1, keepdims=True)
+    sim = unit(fq) @ unit(fs).T
+    picked = np.take_along_axis(sim, gpu["nn_idx"].astype(np.int64), 1)
+    assert (picked >= ref["nn_sim"][:, :k] - SIM_TOL).all()
+    mean = (picked[:, :, None] * ws[gpu["nn_idx"]]).sum(1) / picked.sum(1, keepdims=True)
+    bound = TOL * np.abs(ws).max() * np.maximum(1.0, np.abs(picked).sum(1) / np.abs(picked.sum(1)))
+    assert (np.abs(gpu["wq"] - mean).max(1) <= bound).all()
+    assert np.isfinite(gpu["prop"]).all() and ((gpu["label"] >= 0) & (gpu["label"] < K)).all()
