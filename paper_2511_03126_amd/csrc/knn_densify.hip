@@ -20,12 +20,11 @@
 // us (before, rows and sources through registers, two waves per SIMD, 271), the whole call 218 (288).  us per call before / now:
 // 100 materials 380 / 244 (their sums and the similarities no longer hold registers at the same time), 250 sources 382 / 298, with 120
 // materials 531 / 322, 90 sources 256 / 172, 400 000 queries of 1024 channels 569 / 461, 20 000 of 768 60 / 49, 3000 49 / 44.
-#include <type_traits>
-
 #include "aura_device.hpp"
 #include "launch.hpp"
 #include "scores_core.hpp"
 #include "scores_epilogue.hpp"
+#include "scores_staged.hpp"
 
 namespace aura {
 
@@ -33,7 +32,7 @@ typedef float sc_f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kKnnMaxK = 16;       // neighbours per query
 constexpr int kKnnMaxSources = 256;
-constexpr int kKnnWaves = 4;       // per workgroup; those of one wait for each other at every half step, those of others fill the gaps
+constexpr int kKnnWaves = 4;       // per workgroup; they wait for each other at every half step, those of others fill the gaps
 // Waves per SIMD: three where the accumulators of the similarities leave room for the rest in 168 registers.
 constexpr int knn_waves_per_simd(int MT, bool aligned) { return aligned && MT <= 5 ? 3 : 2; }
 // Bytes of LDS per workgroup: what as many of them as the registers allow can have of 160 KiB (handed out in pieces of 1280 bytes).
@@ -119,122 +118,6 @@ __global__ __launch_bounds__(kSplitThreads) void k_split_sources(const float* __
   }
 }
 
-// From memory straight to LDS: 16 (4) bytes per lane, from base + off to lds + 16 (4) * lane.  (m0 holds the place in LDS.)
-template <int BYTES>
-__device__ __forceinline__ void copy_lanes(const void* base, uint32_t off, const void* lds) {
-  const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds);
-  uint32_t saved_m0;
-  if constexpr (BYTES == 16)
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved_m0) : "s"(at), "v"(off), "s"(base) : "memory");
-  else
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %3\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved_m0) : "s"(at), "v"(off), "s"(base) : "memory");
-}
-
-// The same four times, 16 bytes per lane, 1 KiB apart in LDS.
-__device__ __forceinline__ void copy_four(const void* base, const uint32_t (&off)[4], const void* lds) {
-  const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds);
-  uint32_t saved_m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\t"
-               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %6\n\t"
-               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %6\n\t"
-               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %6\n\ts_mov_b32 m0, %0"
-               : "=&s"(saved_m0) : "s"(at), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "scc");
-}
-
-// The contraction of scores_core.hpp, rows and split source features (they are as many bytes as the rows of 160 queries, and every
-// wave needs all of them) on their way to the matrix cores through LDS, where copy_lanes puts them: whole 128-byte lines, no
-// registers while they are on their way, hence three waves per SIMD beside the
-// accumulators (with 512 bytes of LDS too many for the third workgroup, and the bank conflicts of unpadded material vectors, the call of
-// 200 000 queries took 282 us; without either 227).
-//
-// A step is 32 channels, in two halves of 16.  A wave's rows of a step are 4 KiB of its own, two steps deep; the sources of a half
-// are MT * 2 KiB for the whole workgroup, two halves deep.  At the top of a half, one barrier: this half's sources have arrived, and
-// nobody reads those of the half before it any more, so the next ones are requested into their place; the rows of the step after next
-// are requested as soon as this step's are in registers.  Requests return in order: a half waits for what it needs, and the rows
-// requested last stay on their way (two halves, as long as the memory takes at its full rate).
-// Row n's piece c of a step (16 bytes) lies at place c ^ (n % 8) of the row's 128 bytes: eight neighbouring lanes, which read
-// the same piece of eight rows, meet in no bank.
-// Needs D to be a multiple of 32 and 16-byte aligned rows (no partial step); all threads of the workgroup must call
-// this together; a wave without queries of its own (`work` false, uniform over the wave) only copies its share of the
-// sources and passes the barriers.  Nothing is on its way, and nobody reads LDS, when it returns.
-// rows: first of the wave's 32 queries; last_row: the last one that exists (from 0; the others read it again).
-template <int MT>
-__device__ __forceinline__ float score_products_staged(const float* __restrict__ rows, int D, int last_row, int steps,
-                                                       const sc_bf16x8* __restrict__ a_split, int wave, int lane,
-                                                       char* s_src, char* s_rows, sc_f32x16 (&acc)[MT], bool work) {
-  const int n = lane & 31, g = lane / 32;
-  float ss = 0.0f;
-  uint32_t row_off[4];   // of the lane's part of copy q: row 8 q + lane / 8
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    row_off[q] = (uint32_t)min(8 * q + (lane >> 3), last_row) * (uint32_t)D * 4u + (uint32_t)(((lane & 7) ^ (lane >> 3)) * 16);
-  auto request_rows = [&](int s) { copy_four(rows + s * kScoreStepK, row_off, s_rows + (s & 1) * 4096); };
-  auto request_sources = [&](int s, int j) {
-    const char* base = reinterpret_cast<const char*>(a_split) + ((size_t)s * MT * 2 + j) * 2048;
-    for (int i = wave; i < 2 * MT; i += kKnnWaves)
-      copy_lanes<16>(base + (i >> 1) * 4096 + (i & 1) * 1024, (uint32_t)lane * 16u, s_src + j * MT * 2048 + i * 1024);
-  };
-  sc_f32x4 r[4];
-  auto half = [&](int s, auto jc) {
-    constexpr int j = decltype(jc)::value;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (j == 0) request_sources(s, 1);
-    else if (s + 1 < steps) request_sources(s + 1, 0);
-    if (!work) return;
-    if constexpr (j == 0) {
-      const char* mine = s_rows + (s & 1) * 4096 + n * 128;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = *reinterpret_cast<const sc_f32x4*>(mine + (((4 * g + q) ^ (n & 7)) * 16));
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
-      if (s + 2 < steps) request_rows(s + 2);
-    }
-    sc_bf16x8 bh, bl;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float x = r[2 * j + (e >> 2)][e & 3];
-      ss = __builtin_fmaf(x, x, ss);
-      const __bf16 h = (__bf16)x;
-      bh[e] = h;
-      bl[e] = (__bf16)(x - (float)h);
-    }
-    const sc_bf16x8* src = reinterpret_cast<const sc_bf16x8*>(s_src + j * MT * 2048) + lane;
-    // two tiles at a time: their accumulators take turns, so that no product waits for the one before it
-#pragma unroll
-    for (int m = 0; m < MT; m += 2) {
-      const bool two = m + 1 < MT;
-      const sc_bf16x8 h0 = src[2 * m * kWave], l0 = src[(2 * m + 1) * kWave];
-      const sc_bf16x8 h1 = src[(two ? 2 * m + 2 : 2 * m) * kWave], l1 = src[(two ? 2 * m + 3 : 2 * m + 1) * kWave];
-      acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h0, bh, acc[m], 0, 0, 0);
-      if (two) acc[two ? m + 1 : m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h1, bh, acc[two ? m + 1 : m], 0, 0, 0);
-      acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h0, bl, acc[m], 0, 0, 0);
-      if (two) acc[two ? m + 1 : m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h1, bl, acc[two ? m + 1 : m], 0, 0, 0);
-      acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l0, bh, acc[m], 0, 0, 0);
-      if (two) acc[two ? m + 1 : m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l1, bh, acc[two ? m + 1 : m], 0, 0, 0);
-    }
-  };
-  if (work) request_rows(0);
-  request_sources(0, 0);
-  if (work && steps > 1) request_rows(1);
-  const bool rows_behind = work && steps > 1;
-  if (rows_behind) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  for (int s = 0; s < steps; ++s) {   // uniform over the workgroup: every wave passes the same barriers
-    half(s, std::integral_constant<int, 0>{});
-    if (work && s + 2 < steps) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");   // (the rows of step s + 2 stay on their way)
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    half(s, std::integral_constant<int, 1>{});
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  return ss;
-}
-
 // MT: tiles of 32 sources; MTK: tiles of 32 materials.
 template <int MT, int MTK, bool ROWS_ALIGNED>
 __global__ __launch_bounds__(kKnnWaves * kWave)
@@ -242,9 +125,9 @@ __global__ __launch_bounds__(kKnnWaves * kWave)
 void k_knn_densify(KnnArgs a) {
   // While the similarities are made: the sources' places, then the rows'.  Afterwards: the properties of the materials; per wave the
   // winners of its queries, and in their place the score rows on their way to memory; the sources' material vectors, when they fit.
-  constexpr int kSrcBytes = ROWS_ALIGNED ? 2 * MT * 2048 : 0, kRowBytes = ROWS_ALIGNED ? 2 * 4096 : 0;
+  constexpr StagedShape kShape = staged_shape(MT, kKnnWaves, knn_lds_bytes(MT, ROWS_ALIGNED));
   constexpr int kLdsBytes = knn_lds_bytes(MT, ROWS_ALIGNED);
-  static_assert(kSrcBytes + kKnnWaves * kRowBytes <= kLdsBytes);
+  static_assert(!ROWS_ALIGNED || staged_bytes(MT, kShape) <= kLdsBytes);
   __shared__ __attribute__((aligned(1024))) char s_mem[kLdsBytes];
   const int pick_floats = max(64 * min(a.k, a.Ns), score_stage_floats<16>());
   float* const ys = reinterpret_cast<float*>(s_mem);
@@ -270,15 +153,12 @@ void k_knn_densify(KnnArgs a) {
   const long long n = n0 + (lane & 31);
   const bool valid = active && (lane & 31) < rows;
 
-  sc_f32x16 acc[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
+  ScoreSums<MT, TermB> sum;
+  sc_f32x16 (&acc)[MT] = sum.acc;
   float ss;
   if constexpr (ROWS_ALIGNED)   // whole macro steps, 16-byte aligned rows: through LDS
-    ss = score_products_staged<MT>(a.fq + n0 * a.D, a.D, rows - 1, a.steps, a.a_split, wave, lane, s_mem,
-                                   s_mem + kSrcBytes + wave * kRowBytes, acc, active);
+    ss = score_products_staged<MT, TermB, true, kKnnWaves, kShape.rows, kShape.sources>(a.fq + n0 * a.D, a.D, rows - 1, a.steps, a.a_split,
+                                                                             wave, lane, s_mem, sum, active);
   else
     ss = score_products<MT, false, true>(a.fq + (valid ? n : a.Nq - 1) * a.D, a.D, a.steps, a.a_split, lane, acc);
   ss += __shfl_xor(ss, 32, kWave);

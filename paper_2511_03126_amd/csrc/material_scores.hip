@@ -19,54 +19,13 @@
 #include "launch.hpp"
 #include "scores_core.hpp"
 #include "scores_epilogue.hpp"
+#include "scores_staged.hpp"
 
 namespace aura {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-// T: the 16-bit type of the two terms of an operand.  bf16 takes every fp32 value and holds 16 mantissa bits.  fp16 terms
-// hold 22 bits of the values that per-cell similarities over fp16 maps are made of; the second one is stored 2^11 times too
-// large, so that it does not fall among the subnormals, and its products are added up on their own (2001 unit rows of 512
-// channels: rms error of a score 3.1e-8 without that, 1.2e-8 with it, 2.6e-8 through the cells; largest 3.2e-7, 1.6e-7, 1.7e-7).
-typedef __bf16 TermB;
-typedef _Float16 TermH;
-template <typename T> struct TermOf;
-template <> struct TermOf<TermB> { typedef bf16x8 x8; static constexpr bool kScaled = false; };
-template <> struct TermOf<TermH> { typedef f16x8 x8; static constexpr bool kScaled = true; };
-template <typename T> using Term8 = typename TermOf<T>::x8;
-constexpr float kLowScale = 2048.0f;
-
-template <typename T>
-__device__ __forceinline__ void split_terms(float x, T& hi, T& lo) {
-  hi = (T)x;
-  lo = TermOf<T>::kScaled ? (T)((x - (float)hi) * kLowScale) : (T)(x - (float)hi);
-}
-
-__device__ __forceinline__ f32x16 score_mma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f32x16 score_mma(f16x8 a, f16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-
-// The accumulators of MT tiles; low(mt) takes the products with a second term.
-template <int MT, typename T>
-struct ScoreSums {
-  f32x16 acc[MT] = {};
-  f32x16 low_[TermOf<T>::kScaled ? MT : 1] = {};
-  __device__ __forceinline__ f32x16& low(int mt) { return TermOf<T>::kScaled ? low_[mt] : acc[mt]; }
-  __device__ __forceinline__ void join() {
-    if constexpr (TermOf<T>::kScaled) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mt][r] = __builtin_fmaf(low_[mt][r], 1.0f / kLowScale, acc[mt][r]);
-    }
-  }
-};
-
-// Waves per SIMD of k_material_scores_wide: three, unless the accumulators are 128 registers.
-template <int MT, typename T>
-constexpr int score_waves() { return TermOf<T>::kScaled && MT == 4 ? 2 : 3; }
+typedef sc_bf16x8 bf16x8;
+typedef sc_f32x4 f32x4;
+typedef sc_f32x16 f32x16;
 
 constexpr int kTileM = 32;      // materials per MFMA tile
 constexpr int kTileN = 32;      // points per wave
@@ -317,108 +276,15 @@ __global__ __launch_bounds__((2 + 3 * MT) * kWave) void k_material_scores_split(
                                a.prop, a.label, a.unseen_zero != 0, s_stage);
 }
 
-// Where all the split embeddings of a call fit into LDS (steps * MT <= kLdsSlots blocks of 4 KiB: up to 1024 channels
-// for 32 materials, 512 for 64), one workgroup of 16 waves per compute unit copies them there once and then walks over
-// tiles of 32 points: the embeddings no longer come from L2 once per tile - reading them there costs the row stream 15 %
-// of its rate (a read-only probe of the same pattern: 5.3 TB/s alone, 4.5 TB/s with those reads beside it).  The rows are
-// requested one macro step ahead, across tile boundaries, so the stream never pauses.
-constexpr int kLdsSlots = 32;
-
-// kLdsWaves waves per workgroup: 16 for up to 32 materials (128 registers per wave), 8 for up to 64.
-template <int MT, int kLdsWaves>
-__global__ __launch_bounds__(kLdsWaves* kWave) void k_material_scores_lds(ScoreArgs a) {
-  __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
-  __shared__ __attribute__((aligned(16))) bf16x8 s_a[kLdsSlots * 2 * 2 * kWave];   // 128 KiB
-  constexpr int kStageRows = kLdsWaves > 8 ? 8 : 16;
-  __shared__ __attribute__((aligned(16))) float s_stage[kLdsWaves][score_stage_floats<kStageRows>()];
-  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, blockDim.x);
-  for (int t = threadIdx.x; t < a.steps * MT * 2 * 2 * kWave; t += blockDim.x) s_a[t] = a.a_split[t];
-  __syncthreads();
-
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int g = lane / 32;
-  const long long n_tiles = (a.N + kTileN - 1) / kTileN;
-  const long long stride = (long long)gridDim.x * kLdsWaves;
-  long long tile = (long long)blockIdx.x * kLdsWaves + wave;
-  if (tile >= n_tiles) return;
-  auto row_of = [&](long long tl) {
-    const long long n = tl * kTileN + (lane & 31);
-    return a.fused + (n < a.N ? n : a.N - 1) * a.D + g * 16;
-  };
-  struct Rows { f32x4 v[4]; };
-  auto load_rows = [&](const float* __restrict__ row, int s, Rows& r) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r.v[q] = *reinterpret_cast<const f32x4*>(row + s * kStepK + 4 * q);
-  };
-  f32x16 acc[MT];
-  auto products = [&](const Rows& r, int s) {
-    bf16x8 bh[2], bl[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float x = r.v[2 * j + (c >> 2)][c & 3];
-        const __bf16 h = (__bf16)x;
-        bh[j][c] = h;
-        bl[j][c] = (__bf16)(x - (float)h);
-      }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8* slot = s_a + ((s * MT + mt) * 2 + j) * 2 * kWave + lane;
-        const bf16x8 ah = slot[0], al = slot[kWave];
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[j], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[j], acc[mt], 0, 0, 0);
-        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[j], acc[mt], 0, 0, 0);
-      }
-  };
-
-  const int last = a.steps - 1;
-  const float* __restrict__ row = row_of(tile);
-  Rows r0, r1;
-  load_rows(row, 0, r0);
-  while (true) {
-    const long long next = tile + stride;
-    const float* __restrict__ row_next = row_of(next < n_tiles ? next : tile);   // no further tile: this one again, unused
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
-    for (int s = 0; s < a.steps; s += 2) {
-      // step s from set 0 while step s + 1 arrives in set 1, and the other way round; after the tile's last step
-      // the next tile's first
-      if (s + 1 <= last) load_rows(row, s + 1, r1); else load_rows(row_next, 0, r1);
-      __builtin_amdgcn_sched_barrier(0);
-      products(r0, s);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + 1 <= last) {   // uniform
-        if (s + 2 <= last) load_rows(row, s + 2, r0); else load_rows(row_next, 0, r0);
-        __builtin_amdgcn_sched_barrier(0);
-        products(r1, s + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        r0 = r1;   // odd number of steps: the next tile's first step sits in set 1
-      }
-    }
-    finish_scores_staged<MT, kStageRows>(acc, tile * kTileN, (int)std::min<long long>(kTileN, a.N - tile * kTileN), lane, a.K,
-                                         a.P, a.inv_T, ys, a.scores, a.prop, a.label, a.unseen_zero != 0, s_stage[wave]);
-    if (next >= n_tiles) break;
-    tile = next;
-    row = row_next;
-  }
-}
-
-// The same with the split embeddings of a step (MT * 4 KiB) passed through LDS, double buffered, once per workgroup of four
-// waves and 128 points (whole macro steps, 16-byte aligned rows).  Read from L2 by every wave they are as many bytes as the
-// rows with 32 materials and four times as many with 128, and set the time (300 007 rows of 1024 channels, 100 materials:
-// 501 us, 393 us here; 1 677 001 rows, 128 materials: 2553 and 1966 us = 3.9 TB/s; 1 M rows of 768 channels, 64 materials:
-// 876 and 752 us).  Bound by the row stream from HBM; the products
-// of a step (24 matrix-core instructions of 32 cycles per wave) run beside it.  A step: the next block, requested a step ago,
-// goes to LDS, the block after it and the rows of the step after next are requested, then the products; one barrier.
-template <int MT, typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(score_waves<MT, T>(), score_waves<MT, T>())))
+// 65 to 128 materials and few rows: the split embeddings of a step (16 KiB) pass through LDS, double buffered, once per workgroup of
+// four waves and 128 points, the rows through registers (whole macro steps, 16-byte aligned rows).  With one wave per SIMD what counts is
+// the chain of a step, which is shorter here than that of k_material_scores_staged (20 000 rows of 512 channels, 100 materials 25.5 us, 30
+// there).  A step: the next block, requested a step ago, goes to LDS, the block after it and the rows of the step after next are requested,
+// then the products; one barrier.
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TermOf<T>::kScaled ? 2 : 3, TermOf<T>::kScaled ? 2 : 3)))
 void k_material_scores_wide(ScoreArgs a) {
+  constexpr int MT = 4;
   constexpr int kBlock = MT * 2 * 2 * kWave;   // 16-byte operand slots of a step
   constexpr int kCopies = kBlock / 256;        // per thread
   __shared__ __attribute__((aligned(16))) float ys[kTileM * MT * kMaxP];
@@ -463,7 +329,7 @@ void k_material_scores_wide(ScoreArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     const Term8<T>* cur = s_a[s & 1] + lane;
     // two tiles at a time: their accumulators take turns, so that no product waits for the one before it
-    constexpr int kPair = MT > 1 ? 2 : 1;
+    constexpr int kPair = 2;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -499,6 +365,42 @@ void k_material_scores_wide(ScoreArgs a) {
   sum.join();
   finish_scores_staged<MT, 16>(sum.acc, n0, (int)std::min<long long>(kTileN, a.N - n0), lane, a.K, a.P, a.inv_T, ys, a.scores,
                                a.prop, a.label, a.unseen_zero != 0, s_stage[wave]);
+}
+
+// The row stream of many rows: rows and split embeddings on their way through LDS (scores_staged.hpp), four waves and 128 rows per
+// workgroup (whole macro steps, 16-byte aligned rows).  WAVES: per SIMD; what LDS holds per workgroup follows from it.  Bound by the rows
+// from memory: 5.3 TB/s with 32 materials, 4.4 with 128, where the embeddings are as many bytes from L2 as the rows.  us, before (the
+// embeddings resident in the LDS of one workgroup of 16 or 8 waves, or through registers and LDS as in k_material_scores_wide) / now:
+// 1 M rows of 512 channels and 32 materials 451 / 408, 64 materials 481 / 444, 1.6 M and 24 726 / 640, 300 007 of 1024 channels and 100
+// materials 386 / 360, 1.68 M and 128 1890 / 1760, 200 000 of 768 channels and 64 materials 172 / 148.  One workgroup of twelve waves per
+// compute unit, which fetches the embeddings once instead of three times: 360 -> 371; two with sources four halves deep 366; operands
+// of the next pair of tiles read ahead: the same.  (Right behind the kernel that wrote the rows it gains as much, 473 -> 435 for 1 M rows, but
+// where such steps follow each other without a pause the fusion then takes 30 us longer: 1461 -> 1464 us a step, 1515 -> 1489 alone.)
+constexpr int kStagedWaves = 4;
+constexpr long long kOneRound = 256 * kStagedWaves * kTileN;   // rows of one workgroup per compute unit
+template <int MT, typename T, int WAVES>
+__global__ __launch_bounds__(kStagedWaves * kWave) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
+void k_material_scores_staged(ScoreArgs a) {
+  constexpr StagedShape kShape = staged_shape(MT, kStagedWaves, 163840 / WAVES / 1280 * 1280);
+  // While the products are made: embeddings, then rows.  Afterwards: the properties, then each wave's score rows on their way to memory.
+  __shared__ __attribute__((aligned(1024))) char s_mem[staged_bytes(MT, kShape)];
+  float* const ys = reinterpret_cast<float*>(s_mem);
+  float* const s_stage = ys + kTileM * MT * kMaxP;
+  static_assert((kTileM * MT * kMaxP + kStagedWaves * score_stage_floats<16>()) * sizeof(float) <= sizeof(s_mem));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  const long long t0 = ((long long)blockIdx.x * kStagedWaves + wave) * kTileN;
+  const bool work = t0 < a.N;   // a wave beyond the last row takes part in the copies
+  const long long n0 = work ? t0 : 0;
+  const int rows = (int)std::min<long long>(kTileN, a.N - n0);
+  ScoreSums<MT, T> sum;
+  score_products_staged<MT, T, false, kStagedWaves, kShape.rows, kShape.sources>(a.fused + n0 * a.D, a.D, rows - 1, a.steps, a.a_split, wave, lane,
+                                                                   s_mem, sum, work);
+  if (a.prop) stage_properties<MT>(ys, a.y, a.K, a.P, threadIdx.x, kStagedWaves * kWave);
+  __syncthreads();
+  if (!work) return;
+  sum.join();
+  finish_scores_staged<MT, 16>(sum.acc, n0, rows, lane, a.K, a.P, a.inv_T, ys, a.scores, a.prop, a.label, a.unseen_zero != 0,
+                               s_stage + wave * score_stage_floats<16>());
 }
 
 size_t split_embeddings_bytes(int D, int MT) {
@@ -546,39 +448,30 @@ hipError_t launch_widen_embeddings(const void* src, int dtype, long long n, floa
 // Terms of type fp16: 16-byte aligned rows of whole macro steps only (launch_material_scores).
 template <int MT, typename T>
 static hipError_t launch_mt(const ScoreArgs& a, bool aligned, hipStream_t stream) {
-  if constexpr (MT <= 2 && std::is_same_v<T, TermB>) {
-    if (aligned && a.D % kStepK == 0 && a.steps * MT <= kLdsSlots) {
-      constexpr int kWaves = MT == 1 ? 16 : 8;
-      int dev = 0, cus = 256;
-      if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-      const long long n_tiles = (a.N + kTileN - 1) / kTileN;
-      // worth it from about six tiles per wave: with fewer, the waves that get one tile more than the others set the
-      // time (200 000 points are 1.5 tiles per wave), and every workgroup pays for its copy of the embeddings
-      if (n_tiles >= 6ll * cus * kWaves) {
-        hipLaunchKernelGGL((k_material_scores_lds<MT, kWaves>), dim3((unsigned)cus), dim3(kWaves * kWave), 0, stream, a);
-        return hipGetLastError();
+  const dim3 grid((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), block(256);
+  if (aligned && a.D % kStepK == 0) {
+    // Both operands through LDS from the second workgroup of 128 rows per compute unit on, where others fill the gaps of one (us per call,
+    // through registers / LDS; 24 600 rows: 768 channels and 100 materials 32.4 / 38.2, 64 27.2 / 29.4, 32 21.6 / 23.6, 1024 channels and
+    // 100 38.4 / 46.7; 33 000 rows: 46.6 / 44.6, 44.6 / 33.6, 36.2 / 26.9, 54.7 / 54.7; 60 000 rows: 49.3 / 49.0, 46.4 / 38.6,
+    // 36.8 / 34.4, 69.6 / 65.2; 384 channels alike).
+    if (a.N > kOneRound) {
+      if constexpr (MT == 2) {
+        // Rows a multiple of 4 KiB apart begin in the same channel of L2, wait for each other there, and want more requests ahead rather
+        // than more waves (64 materials, four / three waves per SIMD, us: 400 000 rows of 1024 channels 414 / 369, 500 000 525 / 468;
+        // 1 M of 512 444 / 444, 100 000 of 512 46.8 / 51.1, 70 000 of 384 31.5 / 34.1).
+        if (a.D % 1024 == 0) {
+          hipLaunchKernelGGL((k_material_scores_staged<MT, T, 3>), grid, block, 0, stream, a);
+          return hipGetLastError();
+        }
       }
-    }
-  }
-  // Embeddings through LDS (times in us, through L2 / through LDS): 128 materials always (100 000 rows of 768 channels 169 / 141,
-  // 2001 rows of 384 31 / 29); up to 64 from 65 536 rows on (100 000 x 512, 64 materials 65 / 58; 200 000 x 768, 32 materials
-  // 156 / 144), below that the copies and barriers of a call of one workgroup per compute unit or less are not hidden by
-  // others (20 000 x 512, 12 materials 18.0 / 20.3).
-  if (MT == 4 || a.N >= 65536) {
-    if (aligned && a.D % kStepK == 0) {
-      hipLaunchKernelGGL((k_material_scores_wide<MT, T>), dim3((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), dim3(256), 0, stream, a);
+      hipLaunchKernelGGL((k_material_scores_staged<MT, T, MT <= 2 ? 4 : (TermOf<T>::kScaled ? 2 : 3)>), grid, block, 0, stream, a);
       return hipGetLastError();
     }
-  }
-  // few rows of up to 64 materials: the embeddings of the next step in registers
-  if constexpr (MT <= 2) {
-    if (aligned && a.D % kStepK == 0) {
-      hipLaunchKernelGGL((k_material_scores_few<MT, T>), dim3((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), dim3(256), 0, stream, a);
-      return hipGetLastError();
-    }
+    if constexpr (MT == 4) hipLaunchKernelGGL((k_material_scores_wide<T>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((k_material_scores_few<MT, T>), grid, block, 0, stream, a);
+    return hipGetLastError();
   }
   if constexpr (std::is_same_v<T, TermB>) {
-    dim3 grid((unsigned)((a.N + 4 * kTileN - 1) / (4 * kTileN))), block(256);
     if (aligned)
       hipLaunchKernelGGL((k_material_scores<MT, true>), grid, block, 0, stream, a);
     else
