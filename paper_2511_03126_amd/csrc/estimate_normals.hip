@@ -77,10 +77,15 @@ __device__ __forceinline__ void quad_dist(const PointQuad& q, float qx, float qy
   }
 }
 
-// Among the elements i of [0, n) with eligible(i), the `want`-th smallest key(i) (want >= 1, at most the number of
-// eligible elements): returns the key; *n_equal = how many eligible elements have that key, *need = how many of them
-// belong to the `want` smallest.  All threads of the workgroup call it and get the same answer.
-template <typename Key, typename Eligible>
+// Among the elements i of [0, n) with eligible(i), the `want` smallest by key(i) (want >= 1, at most the number of
+// eligible elements): those below the key returned and *need of the *n_equal that have it.  All threads of the workgroup call it
+// and get the same answer.
+// EARLY: it ends with the pass that finds a bin which belongs to the `want` smallest as a whole, with the bin's largest key (*need =
+// *n_equal; no key is larger and still in the bin).  Mostly that is the second of three, the bins of 22 bits of a distance are 1e-4
+// wide.  A pass over a list in LDS is five barriers: 150 queries, three passes / ending early, us: 200 000 points and k = 30 41.9 /
+// 39.3, k = 200 61.0 / 58.3, 1 M points 144.9 / 140.6, 50 000 26.7 / 24.5, 2000 13.8 / 12.5.  Not over the whole cloud: the loop's second way
+// out makes the compiler request a thread's four points one after the other (200 000 points, k = 300 180 / 214; 1 M, 1000 974 / 884).
+template <bool EARLY, typename Key, typename Eligible>
 __device__ uint32_t radix_select(int n, int want, Key key, Eligible eligible, uint32_t* s_hist, int* s_pick, int* n_equal,
                                  int* need) {
   uint32_t prefix = 0, mask = 0;
@@ -143,6 +148,10 @@ __device__ uint32_t radix_select(int n, int want, Key key, Eligible eligible, ui
     remaining -= s_pick[1];
     *n_equal = s_pick[2];
     __syncthreads();   // s_pick and s_hist are free again
+    if (EARLY && remaining == *n_equal) {   // uniform
+      prefix |= ~mask;
+      break;
+    }
   }
   *need = remaining;
   return prefix;
@@ -298,7 +307,7 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
         }
       }
       __syncthreads();
-      const uint32_t bound = radix_select(sub.run * sub.count, kk, [&](int j) { return s_list[j]; }, [](int) { return true; },
+      const uint32_t bound = radix_select<true>(sub.run * sub.count, kk, [&](int j) { return s_list[j]; }, [](int) { return true; },
                                           s_hist, s_pick, &n_equal, &need);
       if (threadIdx.x == 0) { s_cn = 0; s_ns = 0; }
       __syncthreads();
@@ -328,12 +337,12 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
     __syncthreads();
     const int cn = s_cn;
     if (cn <= kNrmCand) {   // uniform; otherwise the general path below
-      const uint32_t tau = radix_select(cn, kk, [&](int j) { return s_cd[j]; }, [](int) { return true; }, s_hist, s_pick,
+      const uint32_t tau = radix_select<true>(cn, kk, [&](int j) { return s_cd[j]; }, [](int) { return true; }, s_hist, s_pick,
                                         &n_equal, &need);
       int last_idx = 0x7fffffff;   // points at distance tau are taken up to this index
       if (need < n_equal) {
         int e2, n2;
-        last_idx = (int)radix_select(cn, need, [&](int j) { return (uint32_t)s_ci[j]; }, [&](int j) { return s_cd[j] == tau; },
+        last_idx = (int)radix_select<true>(cn, need, [&](int j) { return (uint32_t)s_ci[j]; }, [&](int j) { return s_cd[j] == tau; },
                                      s_hist, s_pick, &e2, &n2);
       }
       for (int j = threadIdx.x; j < cn; j += kNrmBlock)
@@ -352,7 +361,8 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
       }
       __syncthreads();
       if (threadIdx.x == 0) {
-        for (int j = 0; j < kk; ++j) {
+#pragma unroll 4
+        for (int j = 0; j < kk; ++j) {   // (several points' reads in flight; the sums keep their order)
           const double rx = (double)s_pt[j][0] - (double)qx, ry = (double)s_pt[j][1] - (double)qy, rz = (double)s_pt[j][2] - (double)qz;
           s1[0] += rx; s1[1] += ry; s1[2] += rz;
           s2[0] += rx * rx; s2[1] += rx * ry; s2[2] += rx * rz;
@@ -363,11 +373,11 @@ __global__ __launch_bounds__(kNrmBlock) void k_estimate_normals(NrmArgs a, NrmTa
     }
   }
   if (!summed) {   // uniform
-    const uint32_t tau = radix_select(n, kk, dist, [](int) { return true; }, s_hist, s_pick, &n_equal, &need);
+    const uint32_t tau = radix_select<false>(n, kk, dist, [](int) { return true; }, s_hist, s_pick, &n_equal, &need);
     int last_idx = 0x7fffffff;   // points at distance tau are taken up to this index
     if (need < n_equal) {
       int e2, n2;
-      last_idx = (int)radix_select(n, need, [](int i) { return (uint32_t)i; }, [&](int i) { return dist(i) == tau; }, s_hist,
+      last_idx = (int)radix_select<false>(n, need, [](int i) { return (uint32_t)i; }, [&](int i) { return dist(i) == tau; }, s_hist,
                                    s_pick, &e2, &n2);
     }
     for (uint32_t i0 = threadIdx.x; i0 < (uint32_t)n; i0 += 4 * kNrmBlock) {   // (unsigned as in radix_select)

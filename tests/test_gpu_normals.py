@@ -192,6 +192,26 @@ def test_cloud_in_scanner_order(orc, n, k):
     _compare(g_n, g_w, ref, q, np.zeros((len(q), 3)), cloud, np.array([0, n]), np.array([0, len(q)]))
 
 
+# The selects end with the first of three passes (11, 11 and 10 bits of the distance) that separates the k-th from the next: pairs
+# that each of them separates, neighbouring floats, and a tie.  The two points lie along different axes, so taking the
+# wrong one changes the eigenvalues by far more than the bar.
+@pytest.mark.parametrize("n,k", [(3_000, 5), (10_000, 200), (10_000, 300)])      # whole cloud in the list, one sweep, general path
+@pytest.mark.parametrize("next_r", [1.25, 0.8015, 0.80001, "float", "tie"])
+def test_distances_that_each_pass_of_the_select_separates(orc, n, k, next_r):
+    rng = np.random.default_rng(k)
+    r = np.float32(0.8)
+    r_next = {"float": np.nextafter(r, np.float32(1)), "tie": r}.get(next_r, next_r)
+    d = rng.standard_normal((n, 3))
+    d *= np.concatenate([rng.uniform(0.2, 0.5, k - 1), [1, 1], rng.uniform(2, 3, n - k - 1)])[:, None] / np.linalg.norm(d, axis=1, keepdims=True)
+    cloud = d.astype(np.float32)
+    cloud[k - 1], cloud[k] = [r, 0, 0], [0, r_next, 0]
+    cloud = cloud[rng.permutation(n)]
+    q = np.zeros((1, 3), np.float32)
+    _, g_w = _gpu(cloud, q, [[0, 0, -1]], k)
+    ref = orc.estimate_normals(cloud, q, [[0, 0, -1]], k)
+    assert np.abs(g_w - ref["evals"]).max() <= 1e-5 * ref["evals"][:, 2].max()
+
+
 # Covariances that the rotations meet as special cases: no entry off the diagonal, one, equal entries on the diagonal with a
 # positive and a negative one beside them, equal entries everywhere, one and no dimension.
 _AXES = np.concatenate([np.diag(s * np.array([1.0, 2.0, 4.0])) for s in (1, -1)])
