@@ -83,8 +83,8 @@ __device__ __forceinline__ void quad_dist(const PointQuad& q, float qx, float qy
 // EARLY: it ends with the pass that finds a bin which belongs to the `want` smallest as a whole, with the bin's largest key (*need =
 // *n_equal; no key is larger and still in the bin).  Mostly that is the second of three, the bins of 22 bits of a distance are 1e-4
 // wide.  A pass over a list in LDS is five barriers: 150 queries, three passes / ending early, us: 200 000 points and k = 30 41.9 /
-// 39.3, k = 200 61.0 / 58.3, 1 M points 144.9 / 140.6, 50 000 26.7 / 24.5, 2000 13.8 / 12.5.  Not over the whole cloud: the loop's second way
-// out makes the compiler request a thread's four points one after the other (200 000 points, k = 300 180 / 214; 1 M, 1000 974 / 884).
+// 39.3, k = 200 61.0 / 58.3, 1 M points 144.9 / 140.6, 50 000 26.7 / 24.5, 2000 13.8 / 12.5.  Not over the whole cloud, where it
+// measured 180 / 214 (200 000 points, k = 300) and 974 / 884 (1 M, k = 1000) with the same loads and waits in the passes; why is not known.
 template <bool EARLY, typename Key, typename Eligible>
 __device__ uint32_t radix_select(int n, int want, Key key, Eligible eligible, uint32_t* s_hist, int* s_pick, int* n_equal,
                                  int* need) {
