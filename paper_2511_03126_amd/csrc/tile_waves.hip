@@ -424,6 +424,10 @@ void k_tile_fused(FuseArgs fa, TileWs ws, int n_obj, int lists_only, ObjTable ta
       }
     }
     if (n > ws.quota) {   // uniform
+      if (fa.out_vis && lane < rows) {   // mask columns beyond the object's views (the others: gather_point)
+        uint8_t* __restrict__ vrow = fa.out_vis + (i0 + lane) * fa.vis_pitch;
+        for (int v = nv; v < fa.vis_pitch; ++v) vrow[v] = 0;
+      }
       push_tile(ws, ob.tile_begin + blk, here, lane);
       if (lane == 0) s_drain = 1;
       continue;

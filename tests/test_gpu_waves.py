@@ -107,3 +107,18 @@ def test_long_lists_of_one_object(H, blind):
     assert np.abs(one["scores"] - two["scores"]).max() <= tol
     assert (np.abs(one["prop"] - two["prop"]) / np.abs(s.y).max(0)).max() <= tol
     assert np.abs(one["mass"] - two["mass"]).max() <= tol * np.abs(two["mass"]).max()
+
+
+@pytest.mark.parametrize("views", [(8, 3), (2, 6)])
+def test_mask_columns_beyond_the_views_of_an_object_whose_tiles_outgrow_their_lists(H, orc, views):
+    """Rows of the mask are as wide as the object with the most views; a tile that is fused point by point clears the rest of them too."""
+    s = _objects((20_001, 20_033), views, D=512, K=24, grid=24, dtype="f16")
+    at = (np.arange(3, 1250, 20)[:, None] * 32 + np.arange(32)).ravel()
+    s.xyz[at] = s.xyz[np.random.default_rng(1).permutation(at)]
+    (two, one), n, d = _run(H, s, flags=1)
+    widths = np.repeat(views, np.diff(s.pt_offsets))
+    assert n.min() < 0 and not two["vis"][np.arange(max(views)) >= widths[:, None]].any()
+    assert d.status_words(word=1)["fuse_score_integrate"] == (n < 0).sum()
+    for k in KEYS:
+        assert np.array_equal(one[k].view(np.uint8), two[k].view(np.uint8)), k
+    H.compare_points(one, H.oracle_points(orc, s, flags=1), s, no_fused=True)
