@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
       }
       if constexpr (!GENERIC) {
         float scale = 1.0f;
-        if (!a.mean_only) {
+        if (!a.mean_only && cnt > 0) {   // uniform
           const float nrm = sqrtf(wave_sum(ss));
           scale = 1.0f / fmaxf(nrm, a.norm_eps);
         }
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kFuseWaves* kWave) void k_fuse_gather(FuseArgs a, i
     }
 
     if constexpr (GENERIC) {
-      if (!a.mean_only) {
+      if (!a.mean_only && cnt > 0) {
         const float nrm = sqrtf(wave_sum(ss));
         const float scale = 1.0f / fmaxf(nrm, a.norm_eps);
         // every lane rescales exactly the channels it stored above (VEC == 1, PASSES == 1)

@@ -605,12 +605,10 @@ void k_tile_product(FuseArgs fa, ProdArgs a, TileWs ws, ObjTable tab) {
     // rows from those lanes.
     float factor;
     {
-      const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
       float tot = 0.0f;
 #pragma unroll
       for (int w = 0; w < S * H; ++w) tot += s_ss[buf][w][m];
-      const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
-      factor = a.mean_only ? inv : normed;
+      factor = point_factor(my_cnt, tot, a.norm_eps, a.mean_only);
     }
     {   // the factor of every point of the tile, for the scoring kernel (lanes 0..31 of the first wave; all
         // other lanes, and every lane when no factor array was given, fall outside the buffer)
@@ -1307,12 +1305,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
           const bool valid = li < ob.n_pts;
           const long long ip = ob.pt_begin + (valid ? li : ob.n_pts - 1);
           // (a tile without k-steps, n_prev < 0, gets its scores in gather_point)
-          const float inv = cnt_prev > 0 ? 1.0f / (float)cnt_prev : 0.0f;
           float tot = 0.0f;
 #pragma unroll
           for (int wv = 0; wv < S * H; ++wv) tot += s_ss[buf ^ 1][wv][m];
-          const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
-          const float factor = a.mean_only ? inv : normed;
+          const float factor = point_factor(cnt_prev, tot, a.norm_eps, a.mean_only);
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[0][r] *= factor;
           if (blk >= 0) {   // a product wave stores the results during the next tile
@@ -1458,12 +1454,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
 
       float factor;
       {
-        const float inv = my_cnt > 0 ? 1.0f / (float)my_cnt : 0.0f;
         float tot = 0.0f;
 #pragma unroll
         for (int wv = 0; wv < S * H; ++wv) tot += s_ss[buf][wv][m];
-        const float normed = inv / fmaxf(sqrtf(tot) * inv, a.norm_eps);
-        factor = a.mean_only ? inv : normed;
+        factor = point_factor(my_cnt, tot, a.norm_eps, a.mean_only);
       }
       {
         const int rows_f = a.factor ? min(kTilePts, ob.n_pts - blk * kTilePts) : 0;
@@ -1667,10 +1661,9 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units) {
 //     94 / 113; 2 x 60 000, 4 76 / 73
 constexpr long long kSiftOneObject = 8192;   // tiles
 static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long tiles) {
-  // The results of a tile that nobody sees are known to be zero: not where a factor of 1 / 0 or a weight of exp(0 * inf) would
-  // make them something else.
-  if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles) return false;
-  if (!(a.mean_only || a.norm_eps >= 1e-30f) || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
+  // The results of a tile that nobody sees are known to be zero (point_factor): not where a weight of exp(0 * inf) would make them
+  // something else.
+  if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
   if (n_obj == 1) return tiles >= kSiftOneObject;
   return tiles >= 12288 && tiles >= 1250ll * n_obj;
 }

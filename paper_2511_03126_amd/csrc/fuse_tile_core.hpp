@@ -105,6 +105,14 @@ __device__ __forceinline__ int lane_value(int l) {
   return ((l >> 4) & 1) | ((l >> 3) & 1) << 1 | ((l >> 1) & 1) << 2 | (l & 1) << 3 | (H == 2 ? ((l >> 2) & 1) << 4 : 0);
 }
 
+// What a point's sum of feature rows is multiplied by: one over the views that see it, and over the L2 norm of that mean or its lower
+// bound.  0 where no view sees the point, whatever the bound (0 / 0 otherwise, where it is 0).  squares: of the sum.
+__device__ __forceinline__ float point_factor(int seen_by, float squares, float norm_eps, bool mean_only) {
+  const float inv = seen_by > 0 ? 1.0f / (float)seen_by : 0.0f;
+  const float normed = inv / fmaxf(sqrtf(squares) * inv, norm_eps);
+  return mean_only || seen_by == 0 ? inv : normed;
+}
+
 template <int DT>
 __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
   if constexpr (DT == 1)

@@ -125,7 +125,7 @@ __device__ __forceinline__ void gather_point(const FuseArgs& a, const ObjRange& 
       ss = __builtin_fmaf(acc[s][e], acc[s][e], ss);
     }
   }
-  if (!a.mean_only) {
+  if (!a.mean_only && cnt > 0) {   // uniform
     const float scale = 1.0f / fmaxf(sqrtf(wave_sum(ss)), a.norm_eps);
 #pragma unroll
     for (int s = 0; s < SWEEPS; ++s)

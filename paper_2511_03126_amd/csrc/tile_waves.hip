@@ -570,9 +570,7 @@ void k_tile_fused(FuseArgs fa, TileWs ws, int n_obj, int lists_only, ObjTable ta
       wave_sync();
       tot[8 * (r >> 2) + 4 * h + (r & 3)] = sum;
       wave_sync();
-      const float inv = seen_by > 0 ? 1.0f / (float)seen_by : 0.0f;
-      const float normed = inv / fmaxf(sqrtf(tot[p]) * inv, fa.norm_eps);
-      factor = fa.mean_only ? inv : normed;
+      factor = point_factor(seen_by, tot[p], fa.norm_eps, fa.mean_only);
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)

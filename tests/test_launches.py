@@ -72,8 +72,7 @@ def test_every_instance_of_the_one_kernel_fusion_is_launched_by_some_call(record
 
 @pytest.mark.parametrize("kw,sieve", [
     (dict(), True), (dict(K=100), True), (dict(T="inf"), True),        # (weights of exp(0 * 0))
-    (dict(eps=0.0), False), (dict(eps=1e-31), False),                  # a factor of 1 / 0, or of more than fp32 holds
-    (dict(eps=0.0, flags=MEAN_ONLY), True),                            # ... that is not used
+    (dict(eps=0.0), True), (dict(eps=1e-31), True), (dict(eps=0.0, flags=MEAN_ONLY), True),   # (the factor of an unseen point is 0)
     (dict(T=1e-39), False),                                            # exp(0 * inf)
     (dict(call="scores"), False), (dict(N=262_112), False), (dict(N=262_113), True),
     (dict(N=384_033, V=6, D=256, K=40), True), (dict(N=262_112, V=6, D=256, K=40), False),   # one producer, four
