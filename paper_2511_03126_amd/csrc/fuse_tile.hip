@@ -437,6 +437,7 @@ struct ProdArgs {
   float norm_eps;
   int mean_only;
   int pace;             // k_tile_fused: shortest time between two tiles of a workgroup, in ticks of the 100 MHz counter
+  int given_groups;     // k_tile_fused: the first workgroups of the launch, which begin with tiles that they need not ask for
   const unsigned* unlisted;   // k_tile_fused, may be nullptr: the word that holds kAllSeen where this launch has anything to do
 };
 
@@ -1151,16 +1152,17 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   const int xcd = blockIdx.x % kXcd;
   const XcdTiles mine(nblk, xcd);
   const int len = mine.len;
-  // Tickets of the XCD: the workgroups of an XCD take its first four tiles each without asking, and the counter counts those behind
-  // them.  An atomic operation on a word takes 11.5 ns, on other words of the same 32 bytes as well, 5 ns on others of the same 128
-  // bytes: the 1024 that 256 workgroups had begun with were 12 us.  One object has a word for each XCD in 32 bytes of its own (the
-  // words that a call clears are 512 bytes at least), several have eight words each.  us before / now: one object, single pass, 60 000
-  // points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6 / 43.7, 50 000 of 10 views 65 / 55, 123 457 of 11 views,
-  // 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000 points, 768 channels 206 / 203; 64 objects of 100 000 points
-  // 2923 / 2892 (with one tile given in place of four 2901).
-  constexpr int kGiven = 4;
+  // Tickets of the XCD: its workgroups take the first four tiles each without asking (those behind the launch's first given_groups ask for
+  // them too), and the counter counts the tiles behind them.  An atomic operation on a word takes 11.5 ns, on other words of the same 32
+  // bytes as well, 5 ns on others of the same 128 bytes: the 1024 that 256 workgroups had begun with were 12 us.  One object has a word
+  // for each XCD in 32 bytes of its own (the words that a call clears are 512 bytes at least), several have eight words each.  us before
+  // / now: one object, single pass, 60 000 points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6 / 43.7, 50 000 of 10 views
+  // 65 / 55, 123 457 of 11 views, 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000 points, 768 channels 206 / 203; 64
+  // objects of 100 000 points 2920 / 2892.
   unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? xcd * kXcd : blockIdx.y * kXcd + xcd);
-  const int team = (groups - xcd + kXcd - 1) / kXcd, member = (int)blockIdx.x / kXcd;   // the XCD's workgroups; which of them this is
+  constexpr int kGiven = 4;
+  const int given = max(0, min(groups, a.given_groups - (int)(blockIdx.y * gridDim.x)));   // of the object's workgroups
+  const int team = (given - xcd + kXcd - 1) / kXcd, member = (int)blockIdx.x / kXcd;   // those of the XCD; which of its workgroups this is
 
   const int tid = threadIdx.x, lane = tid % kWave;
   // Wave index: the product waves come first, then the scoring wave if there is one, then the NP producers (waves go
@@ -1207,10 +1209,19 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
     int t_raw = 0;   // the ticket of tile k + 3 while tile k + 1 is built (lane 0 of the producer that takes them)
     if (w == NP - 1) {
       for (int q = lane; q < ob.n_views * 16; q += kWave) s_cam[q >> 4][q & 15] = fa.vis.cam[(long long)ob.view_begin * 16 + q];
+      int t0 = member, t1 = member + team, t2 = member + 2 * team;
       t_raw = member + 3 * team;
+      if ((int)blockIdx.x >= given) {   // uniform
+        t0 = ticket();
+        t1 = ticket();
+        t2 = ticket();
+        t_raw = ticket();
+      }
       if (!several) clear_stage();
       if (lane == 0) {
-        for (int k = 0; k < 3; ++k) s_plan[k] = member + k * team;
+        s_plan[0] = t0;
+        s_plan[1] = t1;
+        s_plan[2] = t2;
         for (int o = 0; o < kMaxProducers; ++o) s_flags[o] = 0;
       }
     }
@@ -1563,6 +1574,12 @@ bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes)
          D / 256 != 5 && feat_bytes <= 0xffffffffll;
 }
 
+// K-steps of a tile, estimated from what sorted points on closed surfaces need: 0.3 per view and 17 more per point that there is for each
+// cell of a view (330 000 points, 16 views of 32 x 32 cells 5.8, 123 457 of 11 views of 37 x 37 5.3, 60 000 of 20 13.6).
+static double tile_steps(const FuseArgs& a, int views, int n_obj, long long tiles) {
+  return views * (0.3 + 17.0 * a.feat.Hf * a.feat.Wf * n_obj / ((double)kTilePts * std::max(1ll, tiles)));
+}
+
 // How many producer waves the one-kernel form takes for this launch; 0: the two kernels.  units: channels / 256.  One producer wave
 // keeps up with the product waves for a few views per object; beyond that four share the views of a tile and a compute unit
 // holds one workgroup of up to twelve waves (see fused_waves_per_simd), which is the faster form of few views too where the launch
@@ -1669,9 +1686,7 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 }
 
 // Which calls without rows take k_tile_fused of tile_waves.hip, a tile per wave.  Its waves hide each other's waits, so it wants many
-// tiles, and it keeps a tile's k-steps in a wave's share of LDS, so it wants them short.  What a tile needs is estimated from what
-// sorted points on closed surfaces need: 0.3 k-steps per view and 17 more per point that there is for each cell of a view (330 000 points,
-// 16 views of 32 x 32 cells 5.8, 123 457 of 11 views of 37 x 37 5.3, 60 000 of 20 13.6).  us by producers / by waves, 24 materials:
+// tiles, and it keeps a tile's k-steps in a wave's share of LDS, so it wants them short (tile_steps).  us by producers / by waves, 24 materials:
 //   one object, up to eight views   60 000 points, 5 views, 512 channels 46 / 35; 20 000 of 4 views, 1024 channels 44 / 38; 80 000, 7
 //     views of 37 x 37 cells, 768 channels 65 / 59; 120 000, 8 views of 56 x 56, 1024 channels 116 / 103; 800 000, 6 views, 256
 //     channels 399 / 194; but 30 000, 6 views, 768 channels 42 / 48; 40 000, 8 views of 37 x 37 45 / 61; 100 000, 8 views of 112 x 112,
@@ -1688,7 +1703,7 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, bool sifted, bool* both) {
   *both = false;
   if (a.fused || !a.scoring.G || a.in_mask || a.two_kernels || views > kWaveViews || units > 4) return false;
-  const double steps = views * (0.3 + 17.0 * a.feat.Hf * a.feat.Wf * n_obj / ((double)kTilePts * std::max(1ll, tiles)));
+  const double steps = tile_steps(a, views, n_obj, tiles);
   if (n_obj > 1) return sifted || steps <= 12.0;
   if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
   if (tiles < kSiftOneObject) return false;
@@ -1703,7 +1718,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
                               hipStream_t stream, FuseOutcome* did) {
   const int max_tiles = (max_pts + kTilePts - 1) / kTilePts;
   ProdArgs pa{static_cast<const char*>(a.feat.feat), a.feat.D, ws.hdr, ws.steps, ws.counters + (size_t)ws.obj_base * kXcd,
-              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0, nullptr};
+              ws.quota, a.fused, a.out_factor, a.norm_eps, a.mean_only, 0, 0, nullptr};
   int max_views = 0;
   long long tiles = 0;
   for (int t = 0; t < n_obj; ++t) {
@@ -1765,6 +1780,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     if (!keep && !scoring && np > 1 && n_obj == 1) pa.pace = 120 * S;
     if (!keep && !scoring && np == 1 && S == 2 && n_obj >= 16 && max_views <= 4 && tiles >= 32 * kFusedGroupsMax) pa.pace = 460;
     const int groups = std::max(kXcd, std::min(max_tiles, std::max((groups_max / n_obj + kXcd - 1) / kXcd * kXcd, per_object)));
+    pa.given_groups = given_groups(std::min(groups, max_tiles) * n_obj, groups_max);
     const dim3 grid(std::min(groups, max_tiles), n_obj), block(kWave * ((np > 1 ? 2 * S : S) + np + (scoring ? 1 : 0)));
 #define AURA_FUSED(s_, h_, sel, np_, sc) \
   hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, sel, np_, sc>), grid, block, 0, stream, a, pa, ws, keep, tab)

@@ -1,6 +1,7 @@
-"""How many workgroups an object gets in one launch of the one-kernel fusion over several objects, on the CPU: the launch must
-not end in a last round that is a small part of what the machine holds."""
+"""How many workgroups an object gets in one launch of the one-kernel fusion over several objects, and which of them begin with tiles of
+their own, on the CPU: the launch must not end in a last round that is a small part of what the machine holds."""
 import ctypes
+import heapq
 import subprocess
 from pathlib import Path
 
@@ -14,9 +15,13 @@ def groups(tmp_path_factory):
     d = tmp_path_factory.mktemp("groups")
     (d / "g.cpp").write_text('#include "fuse_tile_groups.hpp"\n'
                              'extern "C" int groups(int s, int np, int n, int resident, int tiles) {\n'
-                             '  return aura::fused_groups_per_object(s, np, n, resident, tiles);\n}\n')
+                             '  return aura::fused_groups_per_object(s, np, n, resident, tiles);\n}\n'
+                             'extern "C" int given(int all, int resident) {\n'
+                             '  return aura::given_groups(all, resident);\n}\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", "-o", str(d / "g.so"), str(d / "g.cpp")], check=True)
-    return ctypes.CDLL(str(d / "g.so")).groups
+    lib = ctypes.CDLL(str(d / "g.so"))
+    lib.groups.given = lib.given
+    return lib.groups
 
 
 # (channels / 256, producers, resident workgroups) of the forms that store rows
@@ -30,3 +35,40 @@ def test_few_objects_keep_the_larger_number(groups, s, np, resident):
         for tiles in (1, 63, 64, 153, 1000, 1500):     # at least eight tiles per workgroup, whole rounds of the XCDs
             got = groups(s, np, n, resident, tiles)
             assert got * 8 <= tiles and got % 8 == 0 and got <= 256
+
+
+def _end_of_launch(groups, n, resident, tiles, given):
+    """When the last tile of a launch is done, in tiles: workgroups start in order as places become free; the first `given` of them
+    begin with four tiles of their own, the others and the rest of an object's tiles find each other by asking."""
+    free = [(0, i) for i in range(resident)]
+    waiting = [(o, k) for o in range(n) for k in range(groups)]
+    begins = [max(0, min(groups, given - o * groups)) for o in range(n)]   # workgroups of each object that begin with tiles
+    left = [max(0, tiles - 4 * b) for b in begins]
+    events, end = [], 0
+    while waiting or events:
+        while waiting and free:
+            t, place = heapq.heappop(free)
+            o, k = waiting.pop(0)
+            own = sum(k + q * begins[o] < tiles for q in range(4)) if k < begins[o] else 0
+            heapq.heappush(events, (t, place, o, own))
+        t, place, o, own = heapq.heappop(events)
+        if own > 0:
+            heapq.heappush(events, (t + 1, place, o, own - 1))
+        elif left[o] > 0:
+            left[o] -= 1
+            heapq.heappush(events, (t + 1, place, o, 0))
+        else:
+            heapq.heappush(free, (t, place))
+            end = max(end, t)
+    return end
+
+
+# workgroups per object, objects, resident workgroups.  No later than if every tile were asked for, by more than a turn (given to all, 9
+# turns were 6).
+@pytest.mark.parametrize("g,n,resident", [(88, 3, 256), (56, 5, 256), (40, 7, 256), (24, 11, 256), (104, 5, 512), (88, 6, 512), (48, 6, 256),
+                                          (128, 2, 256), (64, 4, 256), (64, 64, 512), (128, 64, 512), (48, 40, 512)])
+@pytest.mark.parametrize("per_group", [1, 2, 3, 5, 8, 15, 16, 40])
+def test_given_tiles_do_not_wait_for_workgroups_that_begin_last(groups, g, n, resident, per_group):
+    tiles, given = g * per_group - 3, groups.given(g * n, resident)
+    assert given in (resident, g * n) and (given == g * n or resident < g * n)
+    assert _end_of_launch(g, n, resident, tiles, given) <= _end_of_launch(g, n, resident, tiles, 0) + 1
