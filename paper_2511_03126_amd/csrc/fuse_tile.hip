@@ -1654,12 +1654,24 @@ static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units,
   return 4;
 }
 
-// Whether the one-kernel form of this launch can score its tiles itself: a scoring wave must fit the workgroup (up to 768
-// channels beside four producers) and one matrix-core tile must hold the materials.
-static bool scoring_wave_fits(const FuseArgs& a, int producers, int units) {
-  // (not with one producer wave: with rows the call is bound by their stores either way, and the separate scoring kernel keeps the
-  // fusion kernel shorter: 64 objects of 100 000 points and 4 views, combined call, 3.12 ms against 3.16 ms)
-  return producers == 4 && 2 * units + 4 + 1 <= 12 && a.out_factor && a.scoring.G && a.scoring.Kpad == kScoreTileM && !a.in_mask;
+// Whether the one-kernel form of this launch scores its tiles itself: a scoring wave must fit the workgroup (up to 768 channels beside
+// four producers, 512 beside one) and one matrix-core tile must hold the materials.
+static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n_obj, long long tiles, double steps, int quota) {
+  if (!a.out_factor || !a.scoring.G || a.scoring.Kpad != kScoreTileM || a.in_mask) return false;
+  if (producers == 4) return 2 * units + 4 + 1 <= 12;
+  // With one producer wave (two workgroups of up to four waves per compute unit) it pays where no rows are stored: with rows the call is
+  // bound by their stores either way, and the separate scoring kernel keeps the fusion kernel shorter (64 objects of 100 000 points and 4
+  // views, combined call, 3.12 ms against 3.16 ms).  us with / without, single pass: 512 channels, 16 x 3000 points, 8 views 71 / 84; 40 x
+  // 3000, 4 views of 24 x 24 cells 116 / 128; 64 x 3000 151 / 179; 13 x 8615, 4 views of 37 x 37 97 / 114; 30 x 22 933, 4 views of 112 x 112
+  // 556 / 591; 256 channels, 51 x 2211, 3 views of 32 x 32 222 / 250.
+  if (units + 1 + 1 > 4 || a.fused) return false;
+  // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
+  // without it four workgroups fit a compute unit instead of two (21 x 8512 points, 2 views 93 / 68; with views that leave more tiles to a
+  // workgroup see tile_per_wave).
+  if (units == 1 && n_obj >= 8 && tiles >= 10000) return false;
+  // Nor where tiles may have more k-steps than the stage beside a scoring wave holds (12 instead of 16) and need them: 512 channels, 8 views of
+  // 24 x 24 cells, 35 x 2038 points 146 / 132, 13 x 1639 190 / 150; 33 x 18 457, of 56 x 56 817 / 610.
+  return quota < 16 || steps <= 16.0;
 }
 
 // Whether k_tile_sift goes ahead of this launch: calls that store no rows, of sizes where the tiles that it finds are worth its
@@ -1700,10 +1712,9 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 // Long lists in one object of many views: where the sieve has sampled none but seen tiles, they are as long as the estimate, and the
 // launch with four producers follows, which leaves at once where there is a list (*both; 300 000 points, 32 views of 56 x 56, 1024
 // channels, seen from all around 510 / 682, voxels of a solid 271 / 256; the launch that leaves costs 5).
-static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, bool sifted, bool* both) {
+static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, double steps, bool sifted, bool* both) {
   *both = false;
   if (a.fused || !a.scoring.G || a.in_mask || a.two_kernels || views > kWaveViews || units > 4) return false;
-  const double steps = tile_steps(a, views, n_obj, tiles);
   if (n_obj > 1) return sifted || steps <= 12.0;
   if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
   if (tiles < kSiftOneObject) return false;
@@ -1725,10 +1736,11 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     max_views = std::max(max_views, tab.o[t].n_views);
     tiles += (tab.o[t].n_pts + kTilePts - 1) / kTilePts;
   }
+  const double steps = tile_steps(a, max_views, n_obj, tiles);
   const TimedLaunch timed(stream);
   const bool sifted = !a.two_kernels && sift_tiles(a, n_obj, max_tiles, tiles);
   bool both = false;
-  if (tile_per_wave(a, max_views, S, n_obj, tiles, sifted, &both)) {
+  if (tile_per_wave(a, max_views, S, n_obj, tiles, steps, sifted, &both)) {
     if (sifted) {
       const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
       if (e != hipSuccess) return e;
@@ -1749,7 +1761,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
     // points, 8 views, combined call: 161 us with two, 143 with four), not for one (more than 32 materials, 400 000 points of 8
     // views: single pass 224 us with two, 230 with four, step 226 and 235; 1 M points of 6 views 503 and 503, 514 and 525).
-    const bool scoring = scoring_wave_fits(a, np, S);
+    const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles, steps, ws.quota);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects
@@ -1786,7 +1798,11 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   hipLaunchKernelGGL((k_tile_fused<DT, s_, h_, PF, sel, np_, sc>), grid, block, 0, stream, a, pa, ws, keep, tab)
     if (scoring) {
       pa.factor = nullptr;   // nobody reads the factors back
-      if constexpr (kFourProducers && 2 * S + 4 + 1 <= 12) { AURA_FUSED(2 * S, 1, false, 4, true); }
+      if (np == 1) {
+        if constexpr (kOneProducer && S + 1 + 1 <= 4) { AURA_FUSED(S, H, false, 1, true); }
+      } else {
+        if constexpr (kFourProducers && 2 * S + 4 + 1 <= 12) { AURA_FUSED(2 * S, 1, false, 4, true); }
+      }
       if (did) did->scored = true;
     } else if (np == 1) {
       if constexpr (kOneProducer) {

@@ -40,3 +40,23 @@ def test_long_lists_are_left_to_the_producers_where_all_tiles_are_seen(recorder,
     fused = [n for n in names if n.startswith("k_tile_fused<")]
     assert _by_waves(fused[0]) and len(fused) == 1 + both
     assert any(n.startswith("k_tile_scores") for n in names) == (both and kw.get("K", 24) > 32)
+
+
+def _form(name):
+    """(product waves, producers, scoring wave) of an instance with producers."""
+    a = name[len("k_tile_fused<"):-1].split(",")
+    return int(a[1]), int(a[5]), int(a[6])
+
+
+@pytest.mark.parametrize("kw,scoring", [
+    # 256 and 512 channels, one producer, no rows: from eight objects with 10 000 tiles on not with 256; not where the stage beside it is short
+    (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16), 1), (dict(N=64 * 3000, B=64, V=64 * 4, Hf=24), 1), (dict(N=8 * 6000, B=8, V=8 * 3, Hf=48, D=256), 1),
+    (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16, K=33), 0), (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16, call="scores"), 0),
+    (dict(N=6 * 10_000, B=6, V=6 * 6, D=768, Hf=40), 0), (dict(N=10 * 36_000, B=10, V=10 * 2, D=256, Hf=128, H=512), 0),
+    (dict(N=30 * 2000, B=30, V=30 * 8, Hf=24), 0), (dict(N=30 * 2000, B=30, V=30 * 7, Hf=24), 1),
+])
+def test_one_producer_scores_its_tiles_where_it_pays(recorder, kw, scoring):
+    names = _kernels(recorder, **kw)
+    fused, = [n for n in names if n.startswith("k_tile_fused<")]
+    assert not _by_waves(fused) and _form(fused)[1:] == (1, scoring)
+    assert any(n.startswith("k_tile_scores") for n in names) == (not scoring)
