@@ -1656,7 +1656,7 @@ static int one_kernel_producers(const FuseArgs& a, int views_per_obj, int units,
 
 // Whether the one-kernel form of this launch scores its tiles itself: a scoring wave must fit the workgroup (up to 768 channels beside
 // four producers, 512 beside one) and one matrix-core tile must hold the materials.
-static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n_obj, long long tiles, double steps, int quota) {
+static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, double steps, int quota) {
   if (!a.out_factor || !a.scoring.G || a.scoring.Kpad != kScoreTileM || a.in_mask) return false;
   if (producers == 4) return 2 * units + 4 + 1 <= 12;
   // With one producer wave (two workgroups of up to four waves per compute unit) it pays where no rows are stored: with rows the call is
@@ -1665,11 +1665,7 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, int n
   // 3000, 4 views of 24 x 24 cells 116 / 128; 64 x 3000 151 / 179; 13 x 8615, 4 views of 37 x 37 97 / 114; 30 x 22 933, 4 views of 112 x 112
   // 556 / 591; 256 channels, 51 x 2211, 3 views of 32 x 32 222 / 250.
   if (units + 1 + 1 > 4 || a.fused) return false;
-  // 256 channels, many tiles of many objects: with the one product wave's little to do the scoring wave is what a tile waits for, and
-  // without it four workgroups fit a compute unit instead of two (21 x 8512 points, 2 views 93 / 68; with views that leave more tiles to a
-  // workgroup see tile_per_wave).
-  if (units == 1 && n_obj >= 8 && tiles >= 10000) return false;
-  // Nor where tiles may have more k-steps than the stage beside a scoring wave holds (12 instead of 16) and need them: 512 channels, 8 views of
+  // Not where tiles may have more k-steps than the stage beside a scoring wave holds (12 instead of 16) and need them: 512 channels, 8 views of
   // 24 x 24 cells, 35 x 2038 points 146 / 132, 13 x 1639 190 / 150; 33 x 18 457, of 56 x 56 817 / 610.
   return quota < 16 || steps <= 16.0;
 }
@@ -1706,16 +1702,32 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 //   one object, more views   400 000, 10 views 211 / 172, 24 views 364 / 308; 1 M, 16 views 512 / 369, 20 views, 1024 channels 887 /
 //     567; 330 000, 16 views 204 / 196; 300 000, 24 views of 112 x 112 331 / 320; 270 000, 32 views of 56 x 56, 256 channels 442 / 325;
 //     with fewer tiles than the sieve takes 200 000, 16 views, 768 channels 160 / 204; 100 000, 10 views 77 / 82
-//   several objects   40 x 50 000 ragged, 2 to 4 views 457 / 289; 64 x 100 000, 4 987 / 562; 16 x 3000, 8, 256 channels 292 / 144; 2 x
-//     60 000, 12 96 / 75; 5 x 100 000, 16 439 / 257; 6 x 60 000, 20 365 / 277; 24 x 50 000, 6, 1024 channels, 128 materials 685 / 458;
-//     but 3 x 40 000, 24 views of 37 x 37, 768 channels 175 / 226
+//   several objects, 512 channels and more   40 x 50 000 ragged, 2 to 4 views 457 / 289; 64 x 100 000, 4 987 / 562; 2 x 60 000, 12 96 / 75; 5
+//     x 100 000, 16 439 / 257; 6 x 60 000, 20 365 / 277; 24 x 50 000, 6, 1024 channels, 128 materials 685 / 458; but 3 x 40 000, 24 views
+//     of 37 x 37, 768 channels 175 / 226.  The more k-steps the less, and less where the views look at the same points (on a frontal arc,
+//     where the estimate is short) than from all around: over 480 batches, waves / producers, on an arc 8 to 12 k-steps 0.89 (0.5 to
+//     1.5), 12 to 18 0.99 (to 1.7), more 1.15 (to 2.5); from all around 0.68, 0.69, 0.83 (to 1.7).  Of up to eight views and fewer than 3000
+//     tiles, where eight k-steps are the line, 8 to 10 on an arc 1.25 (6 x 9851, 2 to 7 views of 24 x 24, 768 channels, 60 materials 143 /
+//     210; 4 x 16 637, 2 to 5 of 37 x 37, 60 materials 141 / 199), up to 8 0.83, from all around 8 to 10 0.75
+//   ... 256 channels, whose one producer has a stage of eight k-steps   16 x 3000, 8 views of 16 x 16 135 / 60; 30 x 6000, 8 of 24 x 24 338 / 109; 64
+//     x 3000, 8 of 24 x 24 927 / 227; 53 x 22 641, 24 of 37 x 37 1145 / 617; 39 x 1782, 7 of 16 x 16, 100 materials 357 / 103; 55 x 9056, 32 of
+//     16 x 16 471 / 342; up to 40 k-steps (3 x 8331, 24 of 24 x 24, 45 of them 168 / 234), with many tiles any number (35 x 11 559, 8 of 56 x
+//     56 2672 / 517; 5 of 112 x 112, 3 x 54 203 230 / 197)
+//   ... whose tiles need more k-steps than they own, half as many again by the estimate, so that most are fused point by point: few of them are better
+//     left to the producers (6 x 6181, 2 views of 37 x 37, 1024 channels 92 / 148; 55 x 1590, 2 of 16 x 16, 256 channels, 100 materials 132 /
+//     171; 18 x 3257, 3 of 24 x 24 149 / 195), many not (34 x 20 938, 2 of 56 x 56, 463 / 239; 21 x 11 986, 1024 channels 269 / 206)
 // Long lists in one object of many views: where the sieve has sampled none but seen tiles, they are as long as the estimate, and the
 // launch with four producers follows, which leaves at once where there is a list (*both; 300 000 points, 32 views of 56 x 56, 1024
 // channels, seen from all around 510 / 682, voxels of a solid 271 / 256; the launch that leaves costs 5).
-static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, double steps, bool sifted, bool* both) {
+static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, double steps, int quota, bool sifted,
+                          bool* both) {
   *both = false;
   if (a.fused || !a.scoring.G || a.in_mask || a.two_kernels || views > kWaveViews || units > 4) return false;
-  if (n_obj > 1) return sifted || steps <= 12.0;
+  if (n_obj > 1) {
+    const bool many = tiles >= 5000;
+    const double most = units > 1 ? (views <= kOneKernelViews && tiles < 3000 ? 8.0 : 12.0) : (many ? 1e9 : 40.0);
+    return sifted || (steps <= most && (many || steps <= 1.5 * quota));
+  }
   if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
   if (tiles < kSiftOneObject) return false;
   const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
@@ -1740,7 +1752,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   const TimedLaunch timed(stream);
   const bool sifted = !a.two_kernels && sift_tiles(a, n_obj, max_tiles, tiles);
   bool both = false;
-  if (tile_per_wave(a, max_views, S, n_obj, tiles, steps, sifted, &both)) {
+  if (tile_per_wave(a, max_views, S, n_obj, tiles, steps, ws.quota, sifted, &both)) {
     if (sifted) {
       const hipError_t e = launch_tile_sift(a, ws, tab, n_obj, max_tiles, stream);
       if (e != hipSuccess) return e;
@@ -1761,7 +1773,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
     // machine.  Where the workgroup has just the two waves four fit: worth it for several objects (10 objects of 300 000
     // points, 8 views, combined call: 161 us with two, 143 with four), not for one (more than 32 materials, 400 000 points of 8
     // views: single pass 224 us with two, 230 with four, step 226 and 235; 1 M points of 6 views 503 and 503, 514 and 525).
-    const bool scoring = scoring_wave_fits(a, np, S, n_obj, tiles, steps, ws.quota);
+    const bool scoring = scoring_wave_fits(a, np, S, steps, ws.quota);
     const int groups_max = np > 1 ? kFusedGroupsMax / 2 : (S == 1 && !scoring && n_obj > 1 ? 2 * kFusedGroupsMax : kFusedGroupsMax);
     const int keep = a.out_factor != nullptr && !scoring;   // the scoring kernel follows and reads the k-steps
     // Several objects in one launch: many more workgroups per object than are resident at a time (fuse_tile_groups.hpp: 64 objects

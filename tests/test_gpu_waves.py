@@ -51,15 +51,23 @@ def _run(H, s, flags=0):
     return out, steps, d
 
 
-# sizes, views: objects; steps: what the longest lists of the scene must reach (5 and 7 k-steps fit a wave's LDS, up to eight views and beyond)
-@pytest.mark.parametrize("sizes,views,D,K,P,grid,dtype,steps", [
-    ((16_001, 16_033), (8, 8), 512, 24, 1, 32, "f16", 6),
-    ((16_001, 20_000), (8, 5), 1024, 33, 3, 32, "bf16", 6),
+# sizes, views: objects; steps: what the longest lists of the scene must reach (5 and 7 k-steps fit a wave's LDS, up to eight views and
+# beyond).  (test_waves_dispatch.py checks that all these take the kernel.)
+SAME_BITS = [
+    ((30_001, 30_033), (8, 8), 512, 24, 1, 32, "f16", 6),
+    ((30_001, 28_000), (8, 5), 1024, 33, 3, 32, "bf16", 6),
     ((27_001, 26_500), (12, 9), 256, 40, 2, 32, "f16", 8),
-    ((30_001, 27_000), (16, 7), 768, 65, 1, 32, "bf16", 8),
+    ((45_001, 39_000), (16, 7), 768, 65, 1, 32, "bf16", 8),
     ((25_003, 0, 33, 31_000), (9, 2, 0, 10), 512, 128, 8, 24, "f16", 5),
     ((40_001, 40_001), (4, 1), 1024, 1, 1, 16, "bf16", 1),
-])
+    ((12_001, 11_950, 12_033), (8, 3, 8), 256, 9, 1, 32, "f16", 6),
+]
+MORE_VIEWS = [((40_001, 38_000), (17, 24), 256, 24, 24), ((65_000, 60_001), (32, 25), 512, 40, 16)]
+QUOTA = [24, 70]
+MASK_VIEWS = [(8, 3), (2, 6)]
+
+
+@pytest.mark.parametrize("sizes,views,D,K,P,grid,dtype,steps", SAME_BITS)
 def test_same_bits_as_two_kernels(H, orc, sizes, views, D, K, P, grid, dtype, steps):
     s = _objects(sizes, views, D=D, K=K, P=P, grid=grid, dtype=dtype)
     (two, one), n, d = _run(H, s)
@@ -70,16 +78,16 @@ def test_same_bits_as_two_kernels(H, orc, sizes, views, D, K, P, grid, dtype, st
     assert not d.status_words()["fuse_score_integrate"]
 
 
-@pytest.mark.parametrize("sizes,views,D,K", [((40_001, 38_000), (17, 24), 256, 24), ((60_000, 45_001), (32, 25), 512, 40)])
-def test_more_views_than_a_list_is_filled_up_for(H, orc, sizes, views, D, K):
-    s = _objects(sizes, views, D=D, K=K, grid=24, dtype="f16")
+@pytest.mark.parametrize("sizes,views,D,K,grid", MORE_VIEWS)
+def test_more_views_than_a_list_is_filled_up_for(H, orc, sizes, views, D, K, grid):
+    s = _objects(sizes, views, D=D, K=K, grid=grid, dtype="f16")
     (two, one), n, _ = _run(H, s)
     assert n.max() > 7
     assert all(np.array_equal(one[k], two[k]) for k in ("vis", "count"))
     H.compare_points(one, H.oracle_points(orc, s), s, no_fused=True)
 
 
-@pytest.mark.parametrize("K", [24, 70])
+@pytest.mark.parametrize("K", QUOTA)
 def test_lists_longer_than_the_quota(H, orc, K):
     """Every 20th tile's points in no order and no depth test: such tiles are fused point by point, the others as they are."""
     s = _objects((20_001, 20_033), (8, 8), D=512, K=K, grid=24, dtype="f16")
@@ -109,7 +117,7 @@ def test_long_lists_of_one_object(H, blind):
     assert np.abs(one["mass"] - two["mass"]).max() <= tol * np.abs(two["mass"]).max()
 
 
-@pytest.mark.parametrize("views", [(8, 3), (2, 6)])
+@pytest.mark.parametrize("views", MASK_VIEWS)
 def test_mask_columns_beyond_the_views_of_an_object_whose_tiles_outgrow_their_lists(H, orc, views):
     """Rows of the mask are as wide as the object with the most views; a tile that is fused point by point clears the rest of them too."""
     s = _objects((20_001, 20_033), views, D=512, K=24, grid=24, dtype="f16")

@@ -64,7 +64,7 @@ def test_every_instance_of_the_one_kernel_fusion_is_launched_by_some_call(record
     """Over channels, types, objects, points, views, cells and materials on both sides of every line of the dispatch."""
     calls = [_call(call, N=N, B=B, V=V * B, Hf=Hf, D=D, dtype=dtype, K=K)
              for call in ("single", "scores", "fuse", "selected") for dtype in (1, F16) for D in (256, 512, 768, 1024)
-             for B in (1, 2, 3, 12, 64) for N in (20_000, 300_000, 1_000_000, 3_000_000) for V in (2, 4, 7, 12)
+             for B in (1, 2, 3, 12, 64) for N in (20_000, 100_000, 300_000, 1_000_000, 3_000_000) for V in (2, 4, 7, 12)
              for Hf in (28, 224) for K in (24, 45)]
     launched = {x[0] for status, log in recorder(calls) if status == 0 for x in log if x[0].startswith("k_tile_fused<")}
     assert launched == {_short(n) for n in recorder.names() if "k_tile_fused" in n}

@@ -18,6 +18,15 @@ def _by_waves(name):
     (dict(N=60_000, V=5, Hf=16), True), (dict(N=20_000, V=4, D=1024, Hf=16), True), (dict(N=40_000, V=8, Hf=37), False),
     (dict(N=262_113, V=8, Hf=224), True), (dict(N=262_112, V=12, Hf=16), False), (dict(N=262_113, V=12, Hf=16), True),
     (dict(N=60_000, V=16, B=2, Hf=16), True), (dict(N=120_000, V=24 * 3, B=3, Hf=37), False),
+    # several objects: 512 channels and more up to 12 k-steps (8 of up to eight views and 3000 tiles), 256 up to 40 or any number where
+    # there are 5000 tiles; not where a few tiles outgrow theirs
+    (dict(N=30 * 4800, B=30, V=30 * 8, Hf=16, K=40), True), (dict(N=30 * 3500, B=30, V=30 * 8, Hf=16, K=40), False),
+    (dict(N=2 * 16_000, B=2, V=16, Hf=32, H=224), False), (dict(N=2 * 26_000, B=2, V=16, Hf=32, H=224), True),
+    (dict(N=2 * 32_000, B=2, V=20, Hf=32, H=224), True),
+    (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16, D=256), True), (dict(N=30 * 6000, B=30, V=30 * 8, Hf=24, D=256), True),
+    (dict(N=64 * 3000, B=64, V=64 * 6, Hf=16, D=256), True), (dict(N=64 * 3000, B=64, V=64 * 8, Hf=24, D=256), True),
+    (dict(N=16 * 3000, B=16, V=16 * 24, Hf=16, D=256), False), (dict(N=16 * 3700, B=16, V=16 * 24, Hf=16, D=256, K=40), True),
+    (dict(N=6 * 6200, B=6, V=12, Hf=37, D=1024), False), (dict(N=21 * 12_000, B=21, V=42, Hf=56, D=1024), True),
     (dict(N=1_000_000, V=33, Hf=16), False), (dict(D=1536), False), (dict(flags=TWO_KERNELS), False), (dict(call="scores"), False),
 ])
 def test_who_takes_a_tile_per_wave(recorder, kw, waves):
@@ -25,6 +34,15 @@ def test_who_takes_a_tile_per_wave(recorder, kw, waves):
     assert any(_by_waves(n) for n in names) == waves
     if waves:
         assert names[-1] in ("k_mass_final", "k_mass_points_small") and not any(n.startswith("k_tile_scores") for n in names)
+
+
+def test_the_scenes_of_the_gpu_tests_take_it(recorder):
+    import test_gpu_waves as g
+    cases = [(sizes, views, D, K, grid) for sizes, views, D, K, _, grid, _, _ in g.SAME_BITS] + g.MORE_VIEWS
+    cases += [((20_001, 20_033), (8, 8), 512, K, 24) for K in g.QUOTA] + [((20_001, 20_033), v, 512, 24, 24) for v in g.MASK_VIEWS]
+    for sizes, views, D, K, grid in cases:   # (as many objects, each with the most views)
+        names = _kernels(recorder, N=sum(sizes), B=len(sizes), V=len(sizes) * max(views), H=224, Hf=grid, D=D, K=K)
+        assert any(_by_waves(n) for n in names), (sizes, views)
 
 
 def test_views_and_materials_choose_the_instance(recorder):
@@ -49,10 +67,10 @@ def _form(name):
 
 
 @pytest.mark.parametrize("kw,scoring", [
-    # 256 and 512 channels, one producer, no rows: from eight objects with 10 000 tiles on not with 256; not where the stage beside it is short
+    # 256 and 512 channels, one producer, no rows; not where the stage beside it is short
     (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16), 1), (dict(N=64 * 3000, B=64, V=64 * 4, Hf=24), 1), (dict(N=8 * 6000, B=8, V=8 * 3, Hf=48, D=256), 1),
     (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16, K=33), 0), (dict(N=16 * 3000, B=16, V=16 * 8, Hf=16, call="scores"), 0),
-    (dict(N=6 * 10_000, B=6, V=6 * 6, D=768, Hf=40), 0), (dict(N=10 * 36_000, B=10, V=10 * 2, D=256, Hf=128, H=512), 0),
+    (dict(N=6 * 10_000, B=6, V=6 * 6, D=768, Hf=40), 0),
     (dict(N=30 * 2000, B=30, V=30 * 8, Hf=24), 0), (dict(N=30 * 2000, B=30, V=30 * 7, Hf=24), 1),
 ])
 def test_one_producer_scores_its_tiles_where_it_pays(recorder, kw, scoring):
