@@ -1718,7 +1718,12 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 //     171; 18 x 3257, 3 of 24 x 24 149 / 195), many not (34 x 20 938, 2 of 56 x 56, 463 / 239; 21 x 11 986, 1024 channels 269 / 206)
 // Long lists in one object of many views: where the sieve has sampled none but seen tiles, they are as long as the estimate, and the
 // launch with four producers follows, which leaves at once where there is a list (*both; 300 000 points, 32 views of 56 x 56, 1024
-// channels, seen from all around 510 / 682, voxels of a solid 271 / 256; the launch that leaves costs 5).
+// channels, seen from all around 510 / 682, voxels of a solid 271 / 256; the launch that leaves costs 5).  Beyond ten k-steps where cells are
+// coarse; for smaller ones the estimate is too long, and it is twelve with cells of three pixels and 36 with one or two, up to 32
+// materials and 16 384 tiles (producers / waves, 24 materials, cells of 3 pixels: 288 000 points, 25 views, 512 channels 415 / 477, 299 000 of
+// 12, 768 channels 252 / 277, 388 000 of 25, 1024 channels 700 / 760; of 1 pixel: 420 000 of 23, 512 channels 644 / 722, 330 000 of 16, 768
+// channels 513 / 531, 378 000 of 24 827 / 972, 324 000 of 23, 1024 channels 1110 / 1275; but 387 000 of 31, 512 channels, 40 k-steps 772 / 714, 360 000
+// of 23, 100 materials 1031 / 972, 700 000 of 24, 1024 channels, 40 materials 1362 / 1295).
 static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, long long tiles, double steps, int quota, bool sifted,
                           bool* both) {
   *both = false;
@@ -1730,8 +1735,10 @@ static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, lo
   }
   if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
   if (tiles < kSiftOneObject) return false;
-  const bool coarse = a.feat.pitch_x >= 4.0f && a.feat.pitch_y >= 4.0f;
-  const bool longer = coarse && steps > 10.0 && (units > 2 || (units == 2 && a.scoring.Kpad == kScoreTileM));
+  const float pitch = std::min(a.feat.pitch_x, a.feat.pitch_y);
+  const bool few_materials = a.scoring.Kpad == kScoreTileM;
+  const bool longer = pitch >= 4.0f ? steps > 10.0 && (units > 2 || (units == 2 && few_materials))
+                                    : steps > (pitch >= 3.0f ? 12.0 : 36.0) && units >= 2 && few_materials && tiles < 16384;
   *both = sifted && longer;
   return sifted || !longer;
 }

@@ -101,11 +101,12 @@ def test_lists_longer_than_the_quota(H, orc, K):
     H.compare_points(one, H.oracle_points(orc, s, flags=1), s, no_fused=True)
 
 
-@pytest.mark.parametrize("blind", [False, True])
-def test_long_lists_of_one_object(H, blind):
-    """32 views over 56 x 56 cells and 262 145 points: where the sieve makes no list, the launch with four producers does the work that the
+@pytest.mark.parametrize("blind,kw", [(False, dict(V=32, D=768, grid=56)), (True, dict(V=32, D=768, grid=56)),
+                                      (False, dict(V=16, D=512, grid=112, HW=336, f=375.0))])   # cells of eight and of three pixels
+def test_long_lists_of_one_object(H, blind, kw):
+    """Many views and 262 145 points: where the sieve makes no list, the launch with four producers does the work that the
     waves leave; with tiles that nobody sees in the sample, the waves do it."""
-    s = make_scene("c2", n_points=262_145, overrides=dict(V=32, D=768, K=24, G=0, grid=56))
+    s = make_scene("c2", n_points=262_145, overrides=dict(K=24, G=0, **kw))
     if blind:
         s.xyz[32 * 512:32 * 1100] = s.cam[0, 6:9] * 1e4   # (far behind every object that the cameras look at)
     (two, one), n, _ = _run(H, s)

@@ -52,7 +52,11 @@ def test_views_and_materials_choose_the_instance(recorder):
 
 
 @pytest.mark.parametrize("kw,both", [(dict(K=24), True), (dict(K=24, D=512), True), (dict(K=40, D=512), False), (dict(K=40), True),
-                                     (dict(D=256), False), (dict(N=5_000_000), False)])
+                                     (dict(D=256), False), (dict(N=5_000_000), False),
+                                     # cells of one, two and three pixels
+                                     (dict(N=330_000, V=16, H=224, Hf=224), True), (dict(N=330_000, V=16, H=224, Hf=224, D=512, K=40), False),
+                                     (dict(N=330_000, V=11, H=224, Hf=224), False), (dict(N=600_000, V=24, H=224, Hf=224), False),
+                                     (dict(N=288_000, V=25, H=224, Hf=112), False), (dict(N=288_000, V=25, H=336, Hf=112, D=512), True)])
 def test_long_lists_are_left_to_the_producers_where_all_tiles_are_seen(recorder, kw, both):
     names = _kernels(recorder, **dict(dict(N=262_145, V=32, Hf=56, D=768), **kw))
     fused = [n for n in names if n.startswith("k_tile_fused<")]
