@@ -57,21 +57,21 @@ constexpr int kStepCells = 16;      // cells per k-step (K of the matrix-core pr
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 struct TileHdr {
-  int nsteps;               // k-steps written for the tile; -1: none, fused by a gather (push_tile in fuse_tile.hip)
+  int nsteps;               // k-steps written for the tile; -1: none, fused by a gather (push_tile in fuse_tile_lists.hpp)
   int listed;               // entry of the object's list of seen tiles at the position of this header (k_tile_sift)
   int pad_[2];
   int cnt[kTilePts];        // views that see each point (nsteps >= 0)
 };
 
 struct __attribute__((aligned(64))) TileStep {
-  uint32_t cell[kStepCells];   // byte offset of each cell row from the first feature element
+  uint32_t cell[kStepCells];   // byte offset of each cell row from the first feature element (tile_waves.hip: the cell's number)
   u32x4_t a_hi[64];            // lane l = 32 g + m: weights of point m for cells 8 g .. 8 g + 7 (16-bit)
   u32x4_t a_lo[64];            // second term of the two-term split of the same weights
 };
 
 struct TileWs {
   TileHdr* hdr;         // [n_tiles]
-  unsigned* counters;   // [B][8]: tiles handed out so far, per object and XCD (with a list of seen tiles: kSeenWord)
+  unsigned* counters;   // counter_words(B): tiles handed out so far, per object or launch and XCD (fuse_tile_groups.hpp), and kSeenWord
   unsigned* status;     // 64 words: zero unless a kernel had something to report (see aura_fuse_status_offset), tiles fused
                         // by a gather, and from word 32 the heads of the lists of such tiles
   TileStep* steps;      // [n_tiles][quota]: every tile owns a fixed run of k-steps

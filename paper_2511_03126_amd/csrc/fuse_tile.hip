@@ -1155,11 +1155,10 @@ void k_tile_fused(FuseArgs fa, ProdArgs a, TileWs ws, int keep, ObjTable tab) {
   // Tickets of the XCD: its workgroups take the first four tiles each without asking (those behind the launch's first given_groups ask for
   // them too), and the counter counts the tiles behind them.  An atomic operation on a word takes 11.5 ns, on other words of the same 32
   // bytes as well, 5 ns on others of the same 128 bytes: the 1024 that 256 workgroups had begun with were 12 us.  One object has a word
-  // for each XCD in 32 bytes of its own (the words that a call clears are 512 bytes at least), several have eight words each.  us before
-  // / now: one object, single pass, 60 000 points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6 / 43.7, 50 000 of 10 views
+  // for each XCD in 32 bytes of its own, several have eight words each.  us before / now: one object, single pass, 60 000 points of 5 views 56 / 46, 20 000 of 4 views and 1024 channels 56.6 / 43.7, 50 000 of 10 views
   // 65 / 55, 123 457 of 11 views, 45 materials 150 / 141, 200 000 of 16 views 145 / 138; step of 200 000 points, 768 channels 206 / 203; 64
   // objects of 100 000 points 2920 / 2892.
-  unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? xcd * kXcd : blockIdx.y * kXcd + xcd);
+  unsigned* __restrict__ ctr = a.counters + (gridDim.y == 1 ? launch_ticket_word(xcd, 1) : blockIdx.y * kXcd + xcd);
   constexpr int kGiven = 4;
   const int given = max(0, min(groups, a.given_groups - (int)(blockIdx.y * gridDim.x)));   // of the object's workgroups
   const int team = (given - xcd + kXcd - 1) / kXcd, member = (int)blockIdx.x / kXcd;   // those of the XCD; which of its workgroups this is
@@ -1533,11 +1532,12 @@ static int steps_quota(int B, int n_views) {
   return (int)(2 * per_obj < 4 ? 4 : (2 * per_obj > 32 ? 32 : 2 * per_obj));
 }
 
+static_assert(kMaxObjPerLaunch % kXcd == 0, "launches begin with a group of eight objects' counters");
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 size_t fuse_tile_workspace_bytes(long long N, int B, int n_views) {
   const size_t tiles = (size_t)tile_count_bound(N, B);
-  return round256(tiles * sizeof(TileHdr)) + round256((size_t)B * 8 * sizeof(unsigned)) + 256 +
+  return round256(tiles * sizeof(TileHdr)) + (size_t)counter_words(B) * sizeof(unsigned) + 256 +
          tiles * (size_t)steps_quota(B, n_views) * sizeof(TileStep);
 }
 
@@ -1547,7 +1547,7 @@ TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views) {
   ws.hdr = reinterpret_cast<TileHdr*>(base);
   base += round256((size_t)tile_count_bound(N, B) * sizeof(TileHdr));
   ws.counters = reinterpret_cast<unsigned*>(base);
-  base += round256((size_t)B * 8 * sizeof(unsigned));
+  base += (size_t)counter_words(B) * sizeof(unsigned);
   ws.status = reinterpret_cast<unsigned*>(base);
   base += 256;
   ws.steps = reinterpret_cast<TileStep*>(base);
@@ -1556,7 +1556,7 @@ TileWs fuse_tile_workspace(void* workspace, long long N, int B, int n_views) {
   return ws;
 }
 
-int fuse_tile_clear_words(int B) { return (int)((round256((size_t)B * 8 * sizeof(unsigned)) + 256) / sizeof(unsigned)); }
+int fuse_tile_clear_words(int B) { return counter_words(B) + 256 / (int)sizeof(unsigned); }
 
 hipError_t launch_fuse_tile_clear(const TileWs& ws, int B, hipStream_t stream) {
   const int n = fuse_tile_clear_words(B);
@@ -1565,7 +1565,7 @@ hipError_t launch_fuse_tile_clear(const TileWs& ws, int B, hipStream_t stream) {
 }
 
 size_t fuse_tile_status_offset(long long N, int B) {
-  return round256((size_t)tile_count_bound(N, B) * sizeof(TileHdr)) + round256((size_t)B * 8 * sizeof(unsigned));
+  return round256((size_t)tile_count_bound(N, B) * sizeof(TileHdr)) + (size_t)counter_words(B) * sizeof(unsigned);
 }
 
 bool fuse_tile_supported(int dtype, int D, int Hf, int Wf, long long feat_bytes) {

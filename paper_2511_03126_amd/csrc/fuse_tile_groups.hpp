@@ -1,11 +1,19 @@
 // How many workgroups an object gets where one launch of k_tile_fused fuses several objects and only rows leave it (aura_fuse_features,
-// aura_fuse_selected), and how many tiles each begins with.  Host only.
+// aura_fuse_selected), which of them begin with tiles of their own, and where the tickets of the others are counted.
 #pragma once
 
 namespace aura {
 
 constexpr int kXcd = 8;
 constexpr int kFusedGroupsMax = 512;   // two workgroups per compute unit
+
+// The ticket counters of a call (TileWs::counters): eight words per object, one per XCD.  Where the XCDs of a launch have one count each
+// for all its objects, that lies 32 bytes from the next (operations on words of the same 32 bytes wait for each other): eight words times
+// as many as there are groups of eight objects, so for a launch of one object, or of a number that is no multiple of eight, behind the
+// words of its objects.  Hence whole groups of eight objects, and launches that begin with one.
+constexpr int counter_words(int n_obj) { return (n_obj + kXcd - 1) / kXcd * kXcd * kXcd; }
+constexpr int launch_ticket_word(int xcd, int n_obj) { return xcd * (counter_words(n_obj) / kXcd); }   // from the words of the launch's first object
+static_assert(launch_ticket_word(kXcd - 1, 1) < counter_words(1) && launch_ticket_word(1, 1) == kXcd);
 
 // Many more workgroups per object than are resident at a time: those of an object share its tiles through the per-XCD tickets and
 // are dispatched object after object, so the machine works on a few objects at a time - their depth and feature maps stay in

@@ -191,7 +191,7 @@ void k_tile_fused(FuseArgs fa, TileWs ws, int n_obj, int lists_only, ObjTable ta
   const int xcd = blockIdx.x % kXcd;
   const XcdTiles mine(total, xcd);
   const int waves = (int)gridDim.x / kXcd * kTeam;   // of the XCD
-  unsigned* __restrict__ ctr = ws.counters + 8 * (ws.obj_base + xcd * ((n_obj + kXcd - 1) / kXcd));
+  unsigned* __restrict__ ctr = ws.counters + 8 * ws.obj_base + launch_ticket_word(xcd, n_obj);
   auto ticket = [&]() {
     int t = 0;
     if (lane == 0) t = (int)atomicAdd(ctr, 1u) + 2 * waves;

@@ -1,5 +1,6 @@
-"""How many workgroups an object gets in one launch of the one-kernel fusion over several objects, and which of them begin with tiles of
-their own, on the CPU: the launch must not end in a last round that is a small part of what the machine holds."""
+"""How many workgroups an object gets in one launch of the one-kernel fusion over several objects, which of them begin with tiles of their
+own, and where tickets are counted, on the CPU: the launch must not end in a last round that is a small part of what the machine holds,
+and no count may lie on another's place."""
 import ctypes
 import heapq
 import subprocess
@@ -17,10 +18,12 @@ def groups(tmp_path_factory):
                              'extern "C" int groups(int s, int np, int n, int resident, int tiles) {\n'
                              '  return aura::fused_groups_per_object(s, np, n, resident, tiles);\n}\n'
                              'extern "C" int given(int all, int resident) {\n'
-                             '  return aura::given_groups(all, resident);\n}\n')
+                             '  return aura::given_groups(all, resident);\n}\n'
+                             'extern "C" int counter_words(int n) { return aura::counter_words(n); }\n'
+                             'extern "C" int ticket_word(int xcd, int n) { return aura::launch_ticket_word(xcd, n); }\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", "-o", str(d / "g.so"), str(d / "g.cpp")], check=True)
     lib = ctypes.CDLL(str(d / "g.so"))
-    lib.groups.given = lib.given
+    lib.groups.given, lib.groups.counter_words, lib.groups.ticket_word = lib.given, lib.counter_words, lib.ticket_word
     return lib.groups
 
 
@@ -72,3 +75,22 @@ def test_given_tiles_do_not_wait_for_workgroups_that_begin_last(groups, g, n, re
     tiles, given = g * per_group - 3, groups.given(g * n, resident)
     assert given in (resident, g * n) and (given == g * n or resident < g * n)
     assert _end_of_launch(g, n, resident, tiles, given) <= _end_of_launch(g, n, resident, tiles, 0) + 1
+
+
+SEEN_WORD = 7   # of an object's eight words: the length of its list of seen tiles
+
+
+@pytest.mark.parametrize("B", [1, 2, 7, 8, 9, 57, 63, 64, 65, 71, 72, 73, 128, 129, 130, 200, 4096])
+def test_every_count_of_a_call_has_a_word_of_its_own_in_front_of_the_status_words(groups, B):
+    """Launches of up to 64 objects of a call, one after the other: words that a launch counts in belong to no other launch of the call, to
+    no object's list, and lie within what the workspace has for the counters."""
+    size, taken = groups.counter_words(B), set()
+    assert 8 * B <= size < 8 * B + 64 and size % 64 == 0   # (256 bytes each, as the workspace is divided)
+    for first in range(0, B, 64):
+        n = min(64, B - first)
+        objects = set(range(8 * first, 8 * (first + n)))
+        launch = [8 * first + groups.ticket_word(x, n) for x in range(8)]
+        lists = {8 * (first + b) + SEEN_WORD for b in range(n)}
+        assert len(set(launch)) == 8 and all(b - a >= 8 for a, b in zip(launch, launch[1:])) and max(launch) < size
+        assert not lists & set(launch) and not taken & (objects | set(launch))
+        taken |= objects | set(launch)
