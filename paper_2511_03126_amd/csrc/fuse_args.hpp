@@ -80,10 +80,9 @@ struct TileWs {
 };
 
 // Word 7 of an object's eight counters after k_tile_sift: the length of its list of seen tiles, or kAllSeen where none was made because
-// nearly all are.  (Longer lists than kSeenListTiles have not been measured.)
+// nearly all are.
 constexpr int kSeenWord = 7;
 constexpr unsigned kAllSeen = 0xffffffffu;
-constexpr long long kSeenListTiles = 8 * 49152;
 
 // What a fusion launch did besides the fused rows.
 struct FuseOutcome {

@@ -1672,25 +1672,29 @@ static bool scoring_wave_fits(const FuseArgs& a, int producers, int units, doubl
 
 // Whether k_tile_sift goes ahead of this launch: calls that store no rows, of sizes where the tiles that it finds are worth its
 // launch and the lists.  (With rows the stores set the time, and the unseen rows' are best mixed with the others': 64 objects of
-// 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said, both with the
-// form with producers behind it:
-//   one object, voxels of a solid   1.68 M, 24 views, 1024 channels, 128 materials 1096 / 609; 400 000, 12 views, 768 channels 197 /
-//     144, 6 views, 512 channels 182 / 116, 6 views, 256 channels and 40 materials (one producer) 215 / 138; 300 000, 12 views, 768
-//     channels 151 / 124; 265 000, 24 views, 1024 channels, 100 materials 263 / 242; 150 000, 12 views, 768 channels 98 / 105
-//   ... seen from all around (every tile seen: all it costs)   265 000, 16 views, 512 channels 177 / 186; 330 000 205 / 216, 6 views
-//     165 / 169, 24 views, 1024 channels, 60 materials 410 / 422; 500 000, 12 views, 768 channels 279 / 282; 1 M, 16 views, 512
-//     channels 496 / 512; 256 channels, 40 materials, one producer: 400 000 points of 6 views 224 / 226, of 8 views 226 / 231
-//   objects x points of frontal views   64 x 100 000, 4 views 1430 / 992; 40 x 50 000 ragged, 2 to 4 510 / 398; 20 x 60 000, 4, 768
-//     channels 365 / 285; 12 x 60 000, 4 238 / 183; 12 x 40 000, 4, 768 channels 190 / 172; 4 x 200 000, 4 214 / 157
-//   ... whose workgroups would be left with few tiles each   20 x 30 000, 8 views 286 / 316; 64 x 12 000, 4 280 / 301; 8 x 30 000, 4
-//     94 / 113; 2 x 60 000, 4 76 / 73
-constexpr long long kSiftOneObject = 8192;   // tiles
-static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long tiles) {
+// 100 000 points and 4 views with rows 2927 us, 3296 sifted.)  us without / with it, single pass, 24 materials unless said, a tile per wave
+// behind it both times:
+//   one object, voxels of a solid   14 M, 12 views, 512 channels 2222 / 1007; 1.68 M, 24 views, 1024 channels, 128 materials 565 / 538; 1.45 M,
+//     8 views, 768 channels 263 / 130; 951 000, 6 views, 512 channels 183 / 101; 400 000, 12 views, 768 channels 140 / 125; 300 000 129 / 122;
+//     265 000, 24 views, 1024 channels, 100 materials 258 / 260; fewer 200 000, 6 views, 512 channels 66 / 64; 150 000, 12 views, 768
+//     channels 100 / 107
+//   ... seen from all around (every tile seen: all it costs)   262 200, 6 views, 512 channels 99 / 104, 16 views 167 / 172; 330 000, 24 views, 1024
+//     channels, 60 materials 428 / 440; 1 M, 16 views, 512 channels 353 / 358; 14 M, 12 views 2844 / 2882; 400 000, 6 views, 256 channels, 40
+//     materials 127 / 132
+//   objects x points of frontal views   64 x 100 000, 4 views 693 / 684; 30 x 100 000 291 / 280; 12 x 110 000 155 / 146; 8 x 100 000 161 / 134; 4
+//     x 200 000 157 / 130; 3 x 400 000 216 / 148; 6 x 150 000, 8, 768 channels 198 / 186; solids 9 x 123 000, 3 views 119 / 96, 2 x 265 000, 4 111 /
+//     68; from all around 30 x 100 000, 6 441 / 473; 4 x 200 000 170 / 194
+//   ... of fewer than 2500 tiles each   40 x 50 000 ragged, 2 to 4 278 / 285; 12 x 60 000, 4 112 / 120; 12 x 40 000, 4, 768 channels 105 / 111; 30 x
+//     45 000 167 / 175; from all around 20 x 60 000, 6, 768 channels 233 / 259; 64 x 12 000, 4 155 / 176; 20 x 30 000, 8 150 / 177
+//   ... of few such objects the ones gain what the others lose   frontal 3 x 102 000, 8 views 89 / 72; 2 x 112 000, 6, 1024 channels 73 / 67; from all
+//     around 2 x 184 000, 8, 1024 channels, 100 materials 185 / 191; solids 3 x 128 000, 12, 256 channels 117 / 133, 3 x 80 000, 5, 1024 channels 100 / 84
+constexpr long long kSiftOneObject = 8192, kSiftSeveral = 12288;   // tiles
+static bool sift_tiles(const FuseArgs& a, int n_obj, long long tiles) {
   // The results of a tile that nobody sees are known to be zero (point_factor): not where a weight of exp(0 * inf) would make them
   // something else.
-  if (a.fused || !a.scoring.G || a.in_mask || max_tiles > kSeenListTiles || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
+  if (a.fused || !a.scoring.G || a.in_mask || !(0.0f * a.scoring.inv_T == 0.0f)) return false;
   if (n_obj == 1) return tiles >= kSiftOneObject;
-  return tiles >= 12288 && tiles >= 1250ll * n_obj;
+  return tiles >= kSiftSeveral && tiles >= 2500ll * n_obj;
 }
 
 // Which calls without rows take k_tile_fused of tile_waves.hip, a tile per wave.  Its waves hide each other's waits, so it wants many
@@ -1709,6 +1713,8 @@ static bool sift_tiles(const FuseArgs& a, int n_obj, int max_tiles, long long ti
 //     1.5), 12 to 18 0.99 (to 1.7), more 1.15 (to 2.5); from all around 0.68, 0.69, 0.83 (to 1.7).  Of up to eight views and fewer than 3000
 //     tiles, where eight k-steps are the line, 8 to 10 on an arc 1.25 (6 x 9851, 2 to 7 views of 24 x 24, 768 channels, 60 materials 143 /
 //     210; 4 x 16 637, 2 to 5 of 37 x 37, 60 materials 141 / 199), up to 8 0.83, from all around 8 to 10 0.75
+//     (with 1250 tiles per object and 12 288 in all whatever their lists: 16 x 67 000, 20 views of 37 x 37, 1024 channels 1205 / 1101; 10 x 41 000, 10
+//     of 112 x 112 845 / 717; 6 x 79 000, 10 of 112 x 112, 100 materials 754 / 659; but 8 x 70 000, 32 of 32 x 32, 1024 channels 710 / 805)
 //   ... 256 channels, whose one producer has a stage of eight k-steps   16 x 3000, 8 views of 16 x 16 135 / 60; 30 x 6000, 8 of 24 x 24 338 / 109; 64
 //     x 3000, 8 of 24 x 24 927 / 227; 53 x 22 641, 24 of 37 x 37 1145 / 617; 39 x 1782, 7 of 16 x 16, 100 materials 357 / 103; 55 x 9056, 32 of
 //     16 x 16 471 / 342; up to 40 k-steps (3 x 8331, 24 of 24 x 24, 45 of them 168 / 234), with many tiles any number (35 x 11 559, 8 of 56 x
@@ -1731,7 +1737,7 @@ static bool tile_per_wave(const FuseArgs& a, int views, int units, int n_obj, lo
   if (n_obj > 1) {
     const bool many = tiles >= 5000;
     const double most = units > 1 ? (views <= kOneKernelViews && tiles < 3000 ? 8.0 : 12.0) : (many ? 1e9 : 40.0);
-    return sifted || (steps <= most && (many || steps <= 1.5 * quota));
+    return (tiles >= kSiftSeveral && tiles >= 1250ll * n_obj) || (steps <= most && (many || steps <= 1.5 * quota));
   }
   if (views <= kOneKernelViews) return tiles >= kSiftOneObject || steps <= 2.0 + tiles / 800.0;
   if (tiles < kSiftOneObject) return false;
@@ -1757,7 +1763,7 @@ static hipError_t launch_tile(const FuseArgs& a, const TileWs& ws, const ObjTabl
   }
   const double steps = tile_steps(a, max_views, n_obj, tiles);
   const TimedLaunch timed(stream);
-  const bool sifted = !a.two_kernels && sift_tiles(a, n_obj, max_tiles, tiles);
+  const bool sifted = !a.two_kernels && sift_tiles(a, n_obj, tiles);
   bool both = false;
   if (tile_per_wave(a, max_views, S, n_obj, tiles, steps, ws.quota, sifted, &both)) {
     if (sifted) {

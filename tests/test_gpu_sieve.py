@@ -119,7 +119,7 @@ def test_unseen_tiles_of_an_object_whose_sample_is_all_seen(H, D, V, K, zero):
 # Table of 64 objects and one of six.  1: fewer points than a workgroup of the sieve has tiles for; 3: a list of three tiles; 4: of none
 @pytest.mark.parametrize("D,flags", [(256, 0), (256, 1), (512, 0), (512, 1)])   # 1: without the depth test
 def test_objects_of_two_launch_tables_without_views_points_or_seen_tiles(H, D, flags):
-    sizes = [0, 167, 44_000, 43_001, 43_001, 43_001] + [42_017] * 58 + [66_001] * 6
+    sizes = [0, 167, 44_000, 43_001, 43_001, 43_001] + [86_017] * 58 + [90_001] * 6
     views = [2, 2, 0, 3, 2, 3] + [2 + b % 2 for b in range(64)]
     s = _objects(sizes, views, D=D, K=9, P=2)
     _hide(s, range(5), 1)
@@ -127,13 +127,22 @@ def test_objects_of_two_launch_tables_without_views_points_or_seen_tiles(H, D, f
     _hide(s, range(1344), 4)
     _hide(s, range(0, 1344, 2), 5)
     for b in range(6, 70):
-        _hide(s, range(3 * b, 5 * b if b < 64 else 3 * b + 40), b)
-    _hide(s, range(250, 270), 67)
+        _hide(s, range(5 * b, 11 * b if b < 64 else 5 * b + 10), b)
+    _hide(s, range(_sample(2813)[0] - 10, _sample(2813)[0] + 10), 67)
     lists, unseen = _check(H, s, flags)
     assert lists[0] == lists[2] == lists[4] == 0 and lists[1] <= 1 and lists[3] <= 3
     assert min(unseen[2:]) > 0 and lists[67] > 0
     if flags:
         assert [-1 in part for part in (lists[:64], lists[64:])] == [True, True] and lists[33] > 0
+
+
+def test_a_list_of_four_hundred_thousand_tiles(H):
+    """No limit to a list's length: a cloud of 6250 tiles, 65 times over."""
+    s = _objects([200_000], [3], D=256, K=5, P=1)
+    s = replace(s, xyz=np.tile(s.xyz, (65, 1)), pt_offsets=np.array([0, 13_000_000], np.int64))
+    _hide(s, [*range(7), *range(300_000, 300_100), 406_249])
+    lists, unseen = _check(H, s)
+    assert lists[0] > 100_000 and lists[0] + unseen[0] == 406_250
 
 
 @pytest.mark.parametrize("K,P,shift,pitch", [(45, 3, 1, 3), (24, 1, 1, 4), (24, 2, 2, 8), (128, 8, 3, 5)])

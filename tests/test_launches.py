@@ -76,7 +76,9 @@ def test_every_instance_of_the_one_kernel_fusion_is_launched_by_some_call(record
     (dict(T=1e-39), False),                                            # exp(0 * inf)
     (dict(call="scores"), False), (dict(N=262_112), False), (dict(N=262_113), True),
     (dict(N=384_033, V=6, D=256, K=40), True), (dict(N=262_112, V=6, D=256, K=40), False),   # one producer, four
-    (dict(N=8 * 49_152 * 32), True), (dict(N=8 * 49_152 * 32 + 1), False),   # what a ticket of half a word counts
+    (dict(N=8 * 49_152 * 32), True), (dict(N=8 * 49_152 * 32 + 1), True), (dict(N=50_000_000), True),   # lists of any length
+    (dict(N=5 * 78_625, B=5, V=20, Hf=16), False), (dict(N=5 * 79_969, B=5, V=20, Hf=16), True),    # several objects: 12 288 tiles in all,
+    (dict(N=3 * 131_000, B=3, V=12, Hf=16), False), (dict(N=3 * 131_073, B=3, V=12, Hf=16), True),  # 2500 for each
 ])
 def test_the_sieve_is_left_out_where_unseen_tiles_are_not_zero_or_not_worth_it(recorder, kw, sieve):
     (status, log), = recorder([_call(**kw)])
