@@ -350,7 +350,8 @@ hipError_t launch_knn_densify(const float* fq, long long Nq, int D, const float*
   if (e != hipSuccess) return e;
   KnnArgs a{fq, Nq, D, Ns, K, P, k, static_cast<const sc_bf16x8*>(split), steps, ws,
             y, inverse_temperature(temperature), wq, prop, label, nn_idx, (Nq + 31) / 32, 1};
-  const bool aligned = (D & 31) == 0 && (reinterpret_cast<uintptr_t>(fq) & 15) == 0;
+  // (through LDS a row's place among a wave's 32 is 32 bits wide: score_products_staged)
+  const bool aligned = (D & 31) == 0 && D <= kStagedChannels && (reinterpret_cast<uintptr_t>(fq) & 15) == 0;
   switch (MT) {
     case 1: return launch_knn_mtk<1>(a, aligned, stream);
     case 2: return launch_knn_mtk<2>(a, aligned, stream);

@@ -44,6 +44,9 @@ __device__ __forceinline__ void copy_four(const void* base, const uint32_t (&off
 template <int N>
 __device__ __forceinline__ void wait_requests() { asm volatile("s_waitcnt vmcnt(%0)" :: "i"(N) : "memory"); }
 
+// Channels up to which the 32 rows of a wave end within 4 GiB.
+constexpr int kStagedChannels = 1 << 25;
+
 // The contraction of scores_core.hpp, rows and split source features (they are as many bytes as the rows of 160 queries, and every
 // wave needs all of them) on their way to the matrix cores through LDS, where copy_lanes puts them: whole 128-byte lines, no
 // registers while they are on their way, hence more waves per SIMD beside the accumulators.
@@ -55,7 +58,7 @@ __device__ __forceinline__ void wait_requests() { asm volatile("s_waitcnt vmcnt(
 // on its way.
 // Row n's piece c of a step (16 bytes) lies at place c ^ (n % 8) of the row's 128 bytes: eight neighbouring lanes, which read
 // the same piece of eight rows, meet in no bank.
-// Needs D to be a multiple of 32 and 16-byte aligned rows (no partial step); all threads of the workgroup must call
+// Needs D to be a multiple of 32, up to kStagedChannels, and 16-byte aligned rows (no partial step); all threads of the workgroup must call
 // this together; a wave without queries of its own (`work` false, uniform over the wave) only copies its share of the
 // sources and passes the barriers.  Nothing is on its way, and nobody reads LDS, when it returns.
 // rows: first of the wave's 32 queries; last_row: the last one that exists (from 0; the others read it again).

@@ -1,7 +1,7 @@
 // Runs library calls on a machine without a GPU and prints what they would launch.  The HIP entry points that libaura_fuse.so uses are
 // defined here, in the program, so the library finds these instead of the runtime's.  One call per line of standard input:
 //   call N B n_views H Hf D dtype K P flags norm_eps temperature fail
-// (call: single, scores, fuse, selected; B objects of equal shares; fail: the kernel whose launch shall fail, or -).  Per call one line:
+// (call: single, scores, fuse, selected, of B objects of equal shares, or densify, from B sources; fail: the kernel whose launch shall fail, or -).  Per call one line:
 //   status kernel(grid x, grid y, block) ... with S and E where the events of aura_time_next_fusion are recorded.
 #include <cstdint>
 #include <cstdio>
@@ -108,6 +108,8 @@ int main(int argc, char** argv) {
       s = aura_fuse_scores(&views, &par, f, N, po, vo, B, f, AURA_F32, K, f, P, f, i, m, V, f, f, i, at, ws, nullptr);
     else if (!strcmp(call, "fuse"))
       s = aura_fuse_features(&views, &par, f, N, po, vo, B, f, i, at, ws, nullptr);
+    else if (!strcmp(call, "densify"))   // (8 of B sources)
+      s = aura_knn_densify(f, N, D, f, B, f, K, 8, f, P, &par, f, f, i, i, at, ws, nullptr);
     else
       s = aura_fuse_selected(&views, &par, f, N, po, vo, B, m, V, f, i, at, ws, nullptr);
     printf("%d%s\n", s, g_log.c_str());

@@ -85,3 +85,11 @@ def test_the_sieve_is_left_out_where_unseen_tiles_are_not_zero_or_not_worth_it(r
     kernels = [x[0] for x in log if x not in ("S", "E")]
     fused, = [k for k in kernels if k.startswith("k_tile_fused<")]
     assert status == 0 and ("k_tile_sift" in kernels) == sieve and fused.endswith(",1>" if sieve else ",0>")
+
+
+@pytest.mark.parametrize("D,staged", [(512, True), (500, False), (1 << 25, True), ((1 << 25) + 32, False), (1 << 26, False)])
+def test_the_densification_stages_rows_whose_places_fit_32_bits(recorder, D, staged):
+    """A wave's 32 rows are reached by 32-bit offsets in bytes there: longer ones go through registers."""
+    (status, log), = recorder([_call("densify", N=64, B=64, D=D)])
+    kernel, = [x[0] for x in log if x[0].startswith("k_knn_densify<")]
+    assert status == 0 and kernel == f"k_knn_densify<2,1,{int(staged)}>"
