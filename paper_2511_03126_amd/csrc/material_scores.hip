@@ -375,7 +375,8 @@ void k_material_scores_wide(ScoreArgs a) {
 // materials 386 / 360, 1.68 M and 128 1890 / 1760, 200 000 of 768 channels and 64 materials 172 / 148.  One workgroup of twelve waves per
 // compute unit, which fetches the embeddings once instead of three times: 360 -> 371; two with sources four halves deep 366; operands
 // of the next pair of tiles read ahead: the same.  (Right behind the kernel that wrote the rows it gains as much, 473 -> 435 for 1 M rows, but
-// where such steps follow each other without a pause the fusion then takes 30 us longer: 1461 -> 1464 us a step, 1515 -> 1489 alone.)
+// where such steps follow each other without a pause the fusion then takes 30 us longer: 1461 -> 1464 and, in another session,
+// 1447 -> 1453 us a step; 1515 -> 1489 for a step alone.)
 constexpr int kStagedWaves = 4;
 constexpr long long kOneRound = 256 * kStagedWaves * kTileN;   // rows of one workgroup per compute unit
 template <int MT, typename T, int WAVES>

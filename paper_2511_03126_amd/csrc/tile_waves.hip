@@ -136,8 +136,10 @@ __device__ __forceinline__ void wave_scores(const TileStep* st, int from, int to
   }
 }
 
-// DT: 1 bf16, 2 fp16 feature maps.  MT: 1: up to 32 materials; 4: more (two or four tiles of them).  SIFTED: after k_tile_sift, only
-// the tiles on the objects' lists.
+// DT: 1 bf16, 2 fp16 feature maps.  MT: 1: up to 32 materials; 4: more (two or four tiles of them: 33 to 64 materials run with the
+// registers of four, `half_tiles`).  Three waves per SIMD leave 168 registers per lane, and up to eight views spill beyond them: 28 bytes of
+// scratch per lane with one tile of materials, 140 with four (144 with SIFTED); two waves per SIMD (MANY) spill nothing.  SIFTED: after
+// k_tile_sift, only the tiles on the objects' lists.
 template <int DT, bool MANY, int MT, bool SIFTED>
 __global__ __launch_bounds__(kTeam* kWave) __attribute__((amdgpu_waves_per_eu(waves_per_simd<MANY>(), waves_per_simd<MANY>())))
 void k_tile_fused(FuseArgs fa, TileWs ws, int n_obj, int lists_only, ObjTable tab) {

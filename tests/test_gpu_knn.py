@@ -103,7 +103,7 @@ def test_special_cases(orc):
     # k = 1 returns the nearest source's vector (phi w / phi in fp32: to rounding)
     g1 = _run_gpu(fq, fs, ws, y, 1)
     assert np.allclose(g1["wq"][rows], ws[g1["nn_idx"][rows, 0]], rtol=1e-6, atol=0)
-    # the zero query again where the sources' vectors are too many for the kernel's on-chip copy (eight-wave workgroups,
+    # the zero query again where the sources' vectors are too many for the kernel's on-chip copy (eight tiles of sources,
     # four tiles of materials)
     fq, fs, ws, y = _inputs(300, 256, 64, 128, 2, seed=3)
     fq[[0, 77, 299]] = 0.0
