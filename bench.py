@@ -35,8 +35,8 @@ def fuse_algorithmic_bytes(s):
 # HBM bytes per launch of the dominant kernel from the rocprofv3 counter runs summarised under profiles/ (FETCH_SIZE and
 # WRITE_SIZE, each scaled by the reading of the 256 MiB calibration copy in the same run), per workload.  Valid only for
 # the kernel source the counters were taken with: any change to that file makes the figure null until they are taken again.
-TRAFFIC_BYTES = {'c5': 13696974755}
-TRAFFIC_SOURCE_SHA256 = "5e4e6d3da2054e084613695e72be042059efba3ea19bbcf2483ef246829703a3"
+TRAFFIC_BYTES = {'c5': 13696201976}
+TRAFFIC_SOURCE_SHA256 = "568f1d556f31c38159b0d0b57e18629b42679db5b18fb68e98f0ce14bb3c74ff"
 
 
 def measured_traffic(workload):
